@@ -337,3 +337,125 @@ def tolerance(case):
         # a window whose two largest features are equal to rounding sends its gradient to either of them
         rel, limits = (1e-3 if case["dtype"] == "f32" else 3e-2), {"max": 0.99}
     return dict(limits, rel=rel)
+
+
+# ------------------------------------------------------------------------------------------------ the same in 64 bits
+def to64(tensors):
+    return {k: v.double().requires_grad_() for k, v in tensors.items()}
+
+
+def norm64(x, g, b):
+    return torch.nn.functional.layer_norm(x, x.shape[-1:], g, b, 1e-5)
+
+
+def block64(x, p, heads, kind):
+    """One pre-LayerNorm block, x [batch, seq, d]."""
+    B, S, d = x.shape
+    qkv = norm64(x, p["ln1_g"], p["ln1_b"]) @ p["w_qkv"].T + p["b_qkv"]
+    q, k, v = (t.view(B, S, heads, d // heads).transpose(1, 2) for t in qkv.split(d, -1))
+    if kind == "rotary_geglu":
+        half = d // heads // 2
+        angle = torch.outer(torch.arange(S, device="cuda", dtype=torch.float64),
+                            10000.0 ** (-torch.arange(half, device="cuda", dtype=torch.float64) / half))
+        cos, sin = angle.cos(), angle.sin()
+        q, k = (torch.stack((even * cos - odd * sin, even * sin + odd * cos), -1).flatten(-2)
+                for even, odd in ((t[..., ::2], t[..., 1::2]) for t in (q, k)))
+    later = torch.ones(S, S, dtype=torch.bool, device="cuda").triu(1)
+    scores = (q @ k.transpose(-1, -2) / math.sqrt(d // heads)).masked_fill(later, -math.inf)
+    o = (scores.softmax(-1) @ v).transpose(1, 2).reshape(B, S, d)
+    h = x + o @ p["w_o"].T + p["b_o"]
+    u = norm64(h, p["ln2_g"], p["ln2_b"]) @ p["w_1"].T + p["b_1"]
+    if kind == "rotary_geglu":
+        gate, up = u.chunk(2, -1)
+        u = torch.nn.functional.gelu(gate) * up
+    else:
+        u = torch.nn.functional.gelu(u)
+    return h + u @ p["w_2"].T + p["b_2"]
+
+
+def through_message64(x, scale_bits):
+    """What arrives of x as an int8 message: every 64 values share the scale max|x| / 127."""
+    blocks = x.detach().reshape(-1, 64)
+    scale = blocks.abs().amax(1, keepdim=True) / 127
+    if scale_bits == 16:
+        scale = scale.bfloat16().double()
+    return ((blocks / torch.where(scale > 0, scale, 1.0)).round().clamp(-127, 127) * scale).view(x.shape)
+
+
+def arrived64(msg, like):
+    codes, scales = msg
+    scales = (scales if scales.dtype == torch.float32 else scales.view(torch.bfloat16)).double()
+    return (codes.double().view(-1, 64) * scales[:, None]).view(like.shape).to(like.dtype).double()
+
+
+def exact_stage(s):
+    case = s["case"]
+    coded = case["coded"]
+    x = (arrived64(s["in_message"], s["x"]) if coded else s["x"].double()).requires_grad_(case["do"] != "forward")
+    params = [to64(p) for p in s["params"]]
+    y = x
+    with torch.set_grad_enabled(case["do"] != "forward"):
+        for p in params:
+            for _ in range(case["repeat"]):
+                y = block64(y, p, case["heads"], case["block"])
+    out = {}
+    if case["do"] != "backward":
+        out["y"] = through_message64(y, case["scale_bits"]) if coded else y.detach()
+    if case["do"] != "forward":
+        y.backward(arrived64(s["in_grad"], s["dy"]) if coded else s["dy"].double())
+        out["dx"] = through_message64(x.grad, case["scale_bits"]) if coded else x.grad
+        out["grads"] = [{k: v.grad for k, v in p.items()} for p in params]
+    return out
+
+
+def exact_boundary(s):
+    case, k = s["case"], s["case"]["d"] // s["case"]["d_comp"]
+    y, comp, dec = s["y"].double().requires_grad_(), to64(s["comp"]), to64(s["dec"])
+    a = norm64(y, comp["ln_g"], comp["ln_b"])
+    if case["kind"] == "bottleneck":
+        z = a @ comp["w_c"].T
+    else:
+        # the window's first maximum among the values as they are stored
+        stored = a.detach().to(s["y"].dtype).view(-1, case["d_comp"], k)
+        best = stored == stored.amax(-1, keepdim=True)
+        z = (a.view(stored.shape) * (best & (best.cumsum(-1) == 1))).sum(-1)
+    sent = z.detach().requires_grad_()
+    x = norm64(sent, dec["ln_g"], dec["ln_b"]) @ dec["w_d"].T
+    x.backward(s["dx"].double())
+    z.backward(sent.grad)
+    return {"z": z.detach(), "x": x.detach(), "dz": sent.grad, "dy": y.grad,
+            "dec_grads": {k: v.grad for k, v in dec.items()}, "comp_grads": {k: v.grad for k, v in comp.items()}}
+
+
+def exact_head(s):
+    V, tokens = s["case"]["vocab"], s["tokens"].long()
+    x, head, table = s["x"].double().requires_grad_(), to64(s["head"]), s["table"].double().requires_grad_()
+    embedded = table[tokens]
+    logits = norm64(x, head["ln_g"], head["ln_b"]) @ head["w_vocab"][:V].T
+    token_loss = torch.nn.functional.cross_entropy(logits, s["targets"].long(), reduction="none")
+    out = {"embedded": embedded.detach(), "loss": token_loss.mean().detach().view(1), "token_loss": token_loss.detach()}
+    if s["case"]["do"] == "loss":
+        return out
+    token_loss.mean().backward()
+    embedded.backward(s["d_embedded"].double())
+    return dict(out, dx=x.grad, head_grads={k: v.grad for k, v in head.items()}, table_grad=table.grad)
+
+
+def exact_lamb(s):
+    lr, b1, b2, eps, decay, step = 1e-3, 0.9, 0.95, 1e-6, 0.01, 100
+    out = []
+    for t in s["tensors"]:
+        w, g = t["master"].double(), t["grad"].double()
+        m, v = b1 * t["m"].double() + (1 - b1) * g, b2 * t["v"].double() + (1 - b2) * g * g
+        u = (m / (1 - b1 ** step)) / ((v / (1 - b2 ** step)).sqrt() + eps) + decay * w
+        w = w - lr * w.norm() / u.norm() * u
+        out.append({"master": w, "param": w, "m": m, "v": v})
+    return out
+
+
+def exact(case, seed):
+    if case["path"] == "codec":      # whole numbers and their products, compared bit for bit
+        return None
+    s = prepare(case, seed)
+    del s["workspace"]
+    return {"stage": exact_stage, "boundary": exact_boundary, "head": exact_head, "lamb": exact_lamb}[case["path"]](s)
