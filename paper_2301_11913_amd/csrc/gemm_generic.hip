@@ -1,4 +1,4 @@
-// Plain FMA GEMM for the fp32 parity configuration (and as an any-shape fallback).
+// Plain FMA GEMM, the any-shape fallback of both the fp32 and the bf16 kernels (odd widths, unaligned operands).
 // 64x64 output tile per workgroup, 16-deep K slices through LDS, 4x4 outputs per thread,
 // fp32 accumulation in ascending k: deterministic.  Not a performance path.
 #include "kernels.h"
@@ -107,7 +107,5 @@ swarm_status gemm_generic(const GemmArgs& g, bool bf16, hipStream_t st) {
     hipLaunchKernelGGL(gemm_generic_kernel<float>, grid, dim3(256), 0, st, g);
   return launch_status();
 }
-
-swarm_status gemm_f32(const GemmArgs& g, hipStream_t st) { return gemm_generic(g, false, st); }
 
 }  // namespace swarm

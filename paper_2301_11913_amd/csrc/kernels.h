@@ -51,10 +51,9 @@ struct GemmArgs {
 // Floats of split-K scratch that a bf16 product with an [M, N] output can make use of (0: it is never cut).
 size_t gemm_splitk_floats(int M, int N);
 
-// T = float: plain FMA tiles (parity configuration); T = bf16: MFMA kernel.
 swarm_status gemm_f32(const GemmArgs& g, hipStream_t st);
 swarm_status gemm_bf16(const GemmArgs& g, hipStream_t st);
-// Generic (slow, any dtype) kernel used by the fp32 path; `bf16` selects the element type.
+// Generic (slow, any shape, either dtype) kernel behind both; `bf16` selects the element type.
 swarm_status gemm_generic(const GemmArgs& g, bool bf16, hipStream_t st);
 
 // ------------------------------------------------------------------ LayerNorm / reductions

@@ -316,3 +316,45 @@ def _attention_case(shape, std):
         den = max(np.max(np.abs(rdqkv[..., sl])), 1e-3 * np.max(np.abs(rdqkv)))   # S = 1 has dq = dk = 0 exactly
         e = np.max(np.abs(got[..., sl] - rdqkv[..., sl])) / den
         assert e < 1.5e-2, (name, e)
+
+
+# fp32 GEMM on the matrix cores: every workgroup shape of its dispatch (32 x 32 blocks with K over 8 or 4 wavefronts,
+# 64 x 64, 128 x 128), ragged rows and columns, a K that leaves a partial slice and (transposed operands) a partial
+# 8-deep step, fewer 8-deep steps than wavefronts, every epilogue.
+@pytest.mark.parametrize("M,N,K,a_t,b_t,epi", [
+    (512, 256, 256, False, False, 2), (512, 1024, 256, False, False, 3), (33, 64, 64, False, False, 1),
+    (1, 68, 8, False, False, 0), (1030, 1028, 72, False, False, 2), (2049, 2052, 64, False, False, 3),
+    (512, 256, 768, False, True, 0), (77, 1024, 256, False, True, 4), (1665, 768, 104, False, True, 4),
+    (2085, 2048, 64, False, True, 0), (256, 1024, 511, True, True, 5), (768, 256, 37, True, True, 5),
+    (1024, 1024, 203, True, True, 5), (2048, 2304, 130, True, True, 5), (100, 36, 5, True, True, 5),
+    (64, 30, 64, False, False, 1), (64, 64, 60, False, False, 0)])
+def test_gemm_f32(M, N, K, a_t, b_t, epi):
+    lib = _lib()
+    g = torch.Generator().manual_seed(M + N + K)
+    rnd = lambda *s: torch.randn(s, generator=g)
+    A, B, bias, aux, C0 = rnd(*((K, M) if a_t else (M, K))), rnd(*((K, N) if b_t else (N, K))), rnd(N), rnd(M, N), rnd(M, N)
+    A64, B64 = (A.T if a_t else A).double(), (B if b_t else B.T).double()
+    ref, size = A64 @ B64, A64.abs() @ B64.abs()
+    Ad, Bd, bd, xd, Cd = (t.cuda() for t in (A, B, bias, aux, C0))
+    C2 = torch.full((M, N), 9.0, device="cuda")
+    s = lib.swarm_kernel_gemm(0, M, N, K, Ad.data_ptr(), A.shape[1], a_t, Bd.data_ptr(), B.shape[1], b_t, Cd.data_ptr(),
+                              N, epi, bd.data_ptr(), xd.data_ptr(), N, C2.data_ptr() if epi == 3 else None, N, None)
+    torch.cuda.synchronize()
+    assert s == 0
+    # K products and K additions, each off by half an ulp of at most the sum of magnitudes; two more for the epilogue
+    bound = (2 * K + 2) * 2.0 ** -24
+    if epi in (1, 2, 3):
+        ref, size = ref + bias.double(), size + bias.double().abs()
+    if epi == 2:
+        ref, size = ref + aux.double(), size + aux.double().abs()
+    if epi == 5:
+        ref, size = ref + C0.double(), size + C0.double().abs()
+    if epi == 3:
+        assert ((C2.cpu().double() - ref).abs() <= bound * size).all()
+        ref = torch.from_numpy(_gelu(ref.numpy()))
+        size = 1.13 * size + 8 / bound * 2.0 ** -24 * ref.abs().clamp(min=1)     # slope of GeLU; a few ulp of erf
+    if epi == 4:
+        d = torch.from_numpy(_gelu_grad(aux.double().numpy()))
+        size = size * d.abs() + 8 / bound * 2.0 ** -24 * ref.abs()
+        ref = ref * d
+    assert ((Cd.cpu().double() - ref).abs() <= bound * size).all()
