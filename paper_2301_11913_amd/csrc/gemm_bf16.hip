@@ -1,4 +1,5 @@
-// bf16 MFMA GEMM for gfx950 with fp32 accumulation:  C[M,N] (+)= sum_k A(m,k) B(n,k).
+// Dispatch of the bf16 products, and the register-staged kernel for those the direct-to-LDS kernels (gemm_bf16_dma.hip,
+// gemm_bf16_kw.hip) do not take: a k-contiguous operand whose K is a multiple of 8 but not of 32.
 //
 // Workgroup tile BM x BN x 64, WM x WN wavefronts, each owning a (BM/WM) x (BN/WN) sub-tile made
 // of 32x32 accumulators fed by v_mfma_f32_32x32x16_bf16.  Both operand tiles live in LDS as
@@ -255,19 +256,13 @@ swarm_status gemm_bf16_launch(const GemmArgs& g, hipStream_t st) {
   if (g.epilogue == EPI_BIAS_GEGLU)   // needs the gathered B tile of the direct-to-LDS kernel
     return gemm_bf16_dma(g, st);
   {
-    const swarm_status s = gemm_bf16_dma(g, st);   // tile-aligned shapes: pipelined direct-to-LDS kernel
+    const swarm_status s = gemm_bf16_dma(g, st);   // pipelined direct-to-LDS kernels
     if (s != SWARM_ERR_SHAPE) return s;
   }
-  KArgs k;
-  k.group_m = 8;   // measured best of {2,4,8,16,32} on the d=4096 shapes
-  k.A = (const bf16_raw*)g.A; k.B = (const bf16_raw*)g.B; k.M = g.M; k.N = g.N; k.K = g.K; k.lda = g.lda;
-  k.ldb = g.ldb; k.C = g.C; k.ldc = g.ldc; k.epilogue = g.epilogue; k.bias = (const bf16_raw*)g.bias;
-  k.aux = (const bf16_raw*)g.aux; k.ldaux = g.ldaux; k.C2 = (bf16_raw*)g.C2; k.ldc2 = g.ldc2; k.scales = g.scales; k.scales16 = g.scales16;
-  k.rope = g.rope; k.rope_S = g.rope_S; k.rope_dh = g.rope_dh; k.rope_cols = g.rope_cols; k.split = g.split;
-  k.ksplit = 1; k.part = nullptr; k.stream = 0; k.stamps = nullptr;
+  KArgs k = kargs_of(g);
+  k.stamps = nullptr;
   const long big_tiles = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
-  // What arrives here has a ragged M, N or K (whole tiles with K % 64 == 0 went to the direct-to-LDS kernels above):
-  // the bounds-checked instantiations only.
+  // What arrives here has a k-contiguous operand whose K is no multiple of 32 (the direct-to-LDS kernels took the rest).
   if (big_tiles >= 160) {
     k.tiles_m = (g.M + 255) / 256; k.tiles_n = (g.N + 255) / 256;
     return launch_layout<256, 256, 2, 4, true>(k, g.a_trans, g.b_trans, st);

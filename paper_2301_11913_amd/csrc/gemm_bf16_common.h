@@ -29,6 +29,18 @@ struct KArgs {
   long long* stamps;   // instrumented build only (nullptr otherwise): 16 words per workgroup, see gemm_bf16_k32_kernel
 };
 
+// The kernel arguments of a product, uncut, tiles still to be chosen.
+inline KArgs kargs_of(const GemmArgs& g) {
+  KArgs k{};
+  k.group_m = 8;   // measured best of {2,4,8,16,32} on the d=4096 shapes
+  k.A = (const bf16_raw*)g.A; k.B = (const bf16_raw*)g.B; k.M = g.M; k.N = g.N; k.K = g.K; k.lda = g.lda;
+  k.ldb = g.ldb; k.C = g.C; k.ldc = g.ldc; k.epilogue = g.epilogue; k.bias = (const bf16_raw*)g.bias;
+  k.aux = (const bf16_raw*)g.aux; k.ldaux = g.ldaux; k.C2 = (bf16_raw*)g.C2; k.ldc2 = g.ldc2; k.scales = g.scales;
+  k.scales16 = g.scales16; k.rope = g.rope; k.rope_S = g.rope_S; k.rope_dh = g.rope_dh; k.rope_cols = g.rope_cols;
+  k.split = g.split; k.ksplit = 1; k.stamps = g.stamps;
+  return k;
+}
+
 constexpr int EPI_PART_F32 = 100;   // kernel-internal: C (fp32, ldc = N) = acc, no read
 
 // Launch order maps consecutive workgroups to the 8 XCDs round-robin; give every XCD a contiguous band
@@ -132,6 +144,94 @@ __device__ __forceinline__ void stage_rows32(const Acc16<FM, FN>& acc, int i, fl
       for (int r = 0; r < 4; ++r) stage[(16 * h + 4 * q + r) * kEpiPitch + 16 * j + l16] = acc.blk[2 * i + h][j][r];
 }
 
+__device__ __forceinline__ bool epilogue_has_bias(int epi) {
+  return epi == EPI_BIAS || epi == EPI_BIAS_RESID || epi == EPI_BIAS_GELU || epi == EPI_BIAS_RESID_ENCODE ||
+         epi == EPI_BIAS_ROPE;
+}
+
+// The bf16 epilogues on eight consecutive columns (col .. col + 7, all inside N) of one row: x = the sums in, bias =
+// those of the columns (zero without one).  The fused encode needs the eight lanes of a 64-column block together.
+template <bool NT>
+__device__ __forceinline__ void finish_chunk(const KArgs& p, int epi, float (&x)[8], const float (&bias)[8], int row,
+                                             int col) {
+  bf16_raw* C = reinterpret_cast<bf16_raw*>(p.C);
+  if (epi == EPI_BIAS_RESID_ENCODE) {
+    // stage-exit codec fused: the 8 lanes of a row segment hold one 64-element block.  Values are
+    // rounded to bf16 first, so codes and scales equal the stand-alone encode of the stored tensor.
+    float a[8];
+    unpack8(load_stream<NT>(p.aux + (size_t)row * p.ldaux + col), a);
+    float amax = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      x[e] = bf16_bits_to_float(float_to_bf16_bits(x[e] + bias[e] + a[e]));
+      amax = fmaxf(amax, fabsf(x[e]));
+    }
+    amax = fmaxf(amax, __shfl_xor(amax, 1, 64));
+    amax = fmaxf(amax, __shfl_xor(amax, 2, 64));
+    amax = fmaxf(amax, __shfl_xor(amax, 4, 64));
+    const float sc = block_scale_rounded(amax / 127.0f, p.scales16);
+    uint32_t w[2] = {0u, 0u};
+    if (sc != 0.0f) {
+      const BlockDivisor div(sc);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float q = fminf(fmaxf(rintf(div.quotient(x[e])), -127.0f), 127.0f);
+        w[e >> 2] |= ((uint32_t)(int)q & 0xFFu) << (8 * (e & 3));
+      }
+    }
+    const size_t e0 = (size_t)row * p.ldc + col;
+    *reinterpret_cast<uint2*>(reinterpret_cast<int8_t*>(p.C) + e0) = make_uint2(w[0], w[1]);
+    if ((col & 63) == 0) block_scale_store(p.scales, e0 >> 6, sc, p.scales16);
+    return;
+  }
+  if (epi == EPI_BIAS) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] += bias[e];
+  } else if (epi == EPI_BIAS_RESID) {
+    float a[8];
+    unpack8(load_stream<NT>(p.aux + (size_t)row * p.ldaux + col), a);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = x[e] + bias[e] + a[e];
+  } else if (epi == EPI_BIAS_GELU) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] += bias[e];
+    if (p.C2) store_stream<NT>(p.C2 + (size_t)row * p.ldc2 + col, pack8_bf16(x));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = gelu_fast(x[e]);
+  } else if (epi == EPI_DGELU) {
+    float a[8];
+    unpack8(load_stream<NT>(p.aux + (size_t)row * p.ldaux + col), a);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] *= gelu_grad_fast(a[e]);
+  } else if (epi == EPI_BIAS_ROPE) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] += bias[e];
+    if (col < p.rope_cols) {   // pair (2i, 2i+1) of a head turns by pos * 10000^(-2i/d_head)
+      const int half = p.rope_dh >> 1;
+      const float* t = p.rope + 2 * ((size_t)(row % p.rope_S) * half + ((col % p.rope_dh) >> 1));
+      const float4 t0 = *reinterpret_cast<const float4*>(t), t1 = *reinterpret_cast<const float4*>(t + 4);
+      const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float a = x[2 * e], b = x[2 * e + 1];
+        x[2 * e] = a * cs[e] - b * sn[e];
+        x[2 * e + 1] = a * sn[e] + b * cs[e];
+      }
+    }
+  } else if (epi == EPI_DGEGLU) {
+    float gt[8], up[8], o2[8];
+    unpack8(load_stream<NT>(p.aux + (size_t)row * p.ldaux + col), gt);
+    unpack8(load_stream<NT>(p.aux + (size_t)row * p.ldaux + p.split + col), up);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      o2[e] = x[e] * gelu_fast(gt[e]);
+      x[e] = x[e] * up[e] * gelu_grad_fast(gt[e]);
+    }
+    store_stream<NT>(C + (size_t)row * p.ldc + p.split + col, pack8_bf16(o2));
+  }
+  store_stream<NT>(C + (size_t)row * p.ldc + col, pack8_bf16(x));
+}
+
 template <int FM, int FN, bool GUARD, bool NT, typename Acc>
 __device__ __forceinline__ void gemm_epilogue_nt(const KArgs& p, const Acc& acc, int row0, int col0, int l32,
                                               int lg, float* stage) {
@@ -225,10 +325,8 @@ __device__ __forceinline__ void gemm_epilogue_nt(const KArgs& p, const Acc& acc,
   float bias[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) bias[e] = 0.f;
-  if (col_ok && (epi == EPI_BIAS || epi == EPI_BIAS_RESID || epi == EPI_BIAS_GELU || epi == EPI_BIAS_RESID_ENCODE ||
-                 epi == EPI_BIAS_ROPE))
+  if (col_ok && epilogue_has_bias(epi))
     unpack8(*reinterpret_cast<const uint4*>(p.bias + col), bias);
-  bf16_raw* C = reinterpret_cast<bf16_raw*>(p.C);
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
     stage_rows32<FM, FN>(acc, i, stage, lane);
@@ -240,81 +338,7 @@ __device__ __forceinline__ void gemm_epilogue_nt(const KArgs& p, const Acc& acc,
       const float4 v1 = *reinterpret_cast<const float4*>(stage + rl * kEpiPitch + 8 * c8 + 4);
       if (!col_ok || (GUARD && row >= p.M)) continue;     // uniform over a lane octet (N % 64 == 0 when encoding)
       float x[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-      if (epi == EPI_BIAS_RESID_ENCODE) {
-        // stage-exit codec fused: the 8 lanes of a row segment hold one 64-element block.  Values are
-        // rounded to bf16 first, so codes and scales equal the stand-alone encode of the stored tensor.
-        float a[8];
-        unpack8(load_stream<NT>(p.aux + (size_t)row * p.ldaux + col), a);
-        float amax = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          x[e] = bf16_bits_to_float(float_to_bf16_bits(x[e] + bias[e] + a[e]));
-          amax = fmaxf(amax, fabsf(x[e]));
-        }
-        amax = fmaxf(amax, __shfl_xor(amax, 1, 64));
-        amax = fmaxf(amax, __shfl_xor(amax, 2, 64));
-        amax = fmaxf(amax, __shfl_xor(amax, 4, 64));
-        const float sc = block_scale_rounded(amax / 127.0f, p.scales16);
-        uint32_t w[2] = {0u, 0u};
-        if (sc != 0.0f) {
-          const BlockDivisor div(sc);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float q = fminf(fmaxf(rintf(div.quotient(x[e])), -127.0f), 127.0f);
-            w[e >> 2] |= ((uint32_t)(int)q & 0xFFu) << (8 * (e & 3));
-          }
-        }
-        const size_t e0 = (size_t)row * p.ldc + col;
-        *reinterpret_cast<uint2*>(reinterpret_cast<int8_t*>(p.C) + e0) = make_uint2(w[0], w[1]);
-        if (c8 == 0) block_scale_store(p.scales, e0 >> 6, sc, p.scales16);
-        continue;
-      }
-      if (epi == EPI_BIAS) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] += bias[e];
-      } else if (epi == EPI_BIAS_RESID) {
-        float a[8];
-        unpack8(load_stream<NT>(p.aux + (size_t)row * p.ldaux + col), a);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = x[e] + bias[e] + a[e];
-      } else if (epi == EPI_BIAS_GELU) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] += bias[e];
-        if (p.C2) store_stream<NT>(p.C2 + (size_t)row * p.ldc2 + col, pack8_bf16(x));
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = gelu_fast(x[e]);
-      } else if (epi == EPI_DGELU) {
-        float a[8];
-        unpack8(load_stream<NT>(p.aux + (size_t)row * p.ldaux + col), a);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] *= gelu_grad_fast(a[e]);
-      } else if (epi == EPI_BIAS_ROPE) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] += bias[e];
-        if (col < p.rope_cols) {   // pair (2i, 2i+1) of a head turns by pos * 10000^(-2i/d_head)
-          const int half = p.rope_dh >> 1;
-          const float* t = p.rope + 2 * ((size_t)(row % p.rope_S) * half + ((col % p.rope_dh) >> 1));
-          const float4 t0 = *reinterpret_cast<const float4*>(t), t1 = *reinterpret_cast<const float4*>(t + 4);
-          const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float a = x[2 * e], b = x[2 * e + 1];
-            x[2 * e] = a * cs[e] - b * sn[e];
-            x[2 * e + 1] = a * sn[e] + b * cs[e];
-          }
-        }
-      } else if (epi == EPI_DGEGLU) {
-        float gt[8], up[8], o2[8];
-        unpack8(load_stream<NT>(p.aux + (size_t)row * p.ldaux + col), gt);
-        unpack8(load_stream<NT>(p.aux + (size_t)row * p.ldaux + p.split + col), up);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          o2[e] = x[e] * gelu_fast(gt[e]);
-          x[e] = x[e] * up[e] * gelu_grad_fast(gt[e]);
-        }
-        store_stream<NT>(C + (size_t)row * p.ldc + p.split + col, pack8_bf16(o2));
-      }
-      store_stream<NT>(C + (size_t)row * p.ldc + col, pack8_bf16(x));
+      finish_chunk<NT>(p, epi, x, bias, row, col);
     }
   }
 }

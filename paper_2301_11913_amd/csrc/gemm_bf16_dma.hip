@@ -16,12 +16,11 @@
 //
 // One workgroup owns one output tile and walks K in order: deterministic.
 //
-// Three kernels share this file: gemm_bf16_dma_kernel (128 x 128 tiles, v_mfma_f32_32x32x16_bf16),
-// gemm_bf16_k32_kernel (256 x 256 and 256 x 128 tiles on eight wavefronts, v_mfma_f32_16x16x32_bf16: the dgrad and
-// wgrad layouts, the rotary and GeGLU epilogues) and gemm_bf16_w4_kernel (256 x 256 tiles on four wavefronts: the
-// forward layout with the store / bias / residual / int8-encoding / GeLU epilogues).  The two 16 x 16 x 32 kernels
-// accumulate a tile in the same order and give the same bits; the 32 x 32 x 16 kernel agrees with them to fp32
-// rounding of the sums.
+// Two kernels share this file, both on v_mfma_f32_16x16x32_bf16: gemm_bf16_k32_kernel (256 x 256 and 256 x 128 tiles on
+// eight wavefronts: the dgrad and wgrad layouts, the rotary and GeGLU epilogues) and gemm_bf16_w4_kernel (256 x 256 tiles
+// on four wavefronts: the forward layout with the store / bias / residual / int8-encoding / GeLU epilogues).  They
+// accumulate a tile in the same order and give the same bits.  Products with fewer tiles and ragged ones go to
+// gemm_bf16_kw.hip.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -37,17 +36,9 @@ constexpr int DBK = 64;        // K depth of a stage (32 or 64; 64 measured fast
 constexpr int NS = 2;          // LDS stages (NS x (BM+BN) x DBK x 2 bytes must fit 160 KiB)
 constexpr int KCH = DBK / 8;   // 16-byte chunks per row of a non-transposed tile
 
-// chunk swizzle of a non-transposed tile: makes the 16 rows that one LDS pass reads (64 banks x 4 B)
-// hit 16 distinct 16-byte bank groups
-__device__ __forceinline__ int swz_rows(int row) {
-  return DBK == 64 ? ((row & 7) ^ ((row >> 3) & 1)) : ((row >> 2) & 3);
-}
-// The same for the fragments of the 16 x 16 x 32 kernel, whose lanes read 16 rows x 4 k-quarters: measured with a
-// read-only loop, the swizzle above gives that lane order 151 B/clk per compute unit (two-way conflicts) and this
-// one 277 B/clk, the rate of a linear read.
+// Chunk swizzle of a non-transposed tile for lanes that read 16 rows x 4 k-quarters: 277 B/clk per compute unit in a
+// read-only loop, the rate of a linear read.
 __device__ __forceinline__ int swz_rows16(int row) { return row & 7; }
-template <bool K32>
-__device__ __forceinline__ int swz_rows_of(int row) { return K32 ? swz_rows16(row) : swz_rows(row); }
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>): a loop whose index is a constant expression
 template <typename F, int... I>
@@ -74,7 +65,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 // glu_split != 0 (GeGLU forward, B = W1 [2*split, K]): the tile's rows are gathered so that every 64-row group
 // (one wavefront column) holds 32 gate rows followed by the 32 up rows of the same features; r0 then counts
 // features: tile row 64*w + c -> W1 row r0 + 32*w + (c & 31) + (c >= 32 ? split : 0).
-template <int BR, int NW, bool TRANS, bool K32 = false>
+template <int BR, int NW, bool TRANS>
 __device__ __forceinline__ void issue_tile_one(const bf16_raw* __restrict__ g, int ld, int r0, int k0, bf16_raw* lds,
                                                int wave, int lane, int t, int glu_split = 0) {
   {
@@ -82,15 +73,15 @@ __device__ __forceinline__ void issue_tile_one(const bf16_raw* __restrict__ g, i
     const bf16_raw* src;
     if constexpr (!TRANS) {
       const int row = q * (64 / KCH) + lane / KCH;
-      const int chunk = (lane % KCH) ^ swz_rows_of<K32>(row);
+      const int chunk = (lane % KCH) ^ swz_rows16(row);
       const int grow = glu_split ? r0 + 32 * (row >> 6) + (row & 31) + ((row & 32) ? glu_split : 0) : r0 + row;
       src = g + (size_t)grow * ld + k0 + chunk * 8;
     } else {
       constexpr int CPR = BR / 8;           // 16-byte chunks per k-row
       const int krow = q * (64 / CPR) + lane / CPR;
-      // K32: the 16 x 16 x 32 kernel's transpose reads take k-rows 8 apart in one pass; one more swizzle bit keeps
+      // the transpose reads take k-rows 8 apart in one pass; one more swizzle bit keeps
       // them off each other's banks (148 -> 208 B/clk per compute unit in a read-only loop)
-      const int chunk = (lane % CPR) ^ (4 * (krow & 3)) ^ (K32 ? 2 * ((krow >> 3) & 1) : 0);
+      const int chunk = (lane % CPR) ^ (4 * (krow & 3)) ^ (2 * ((krow >> 3) & 1));
       src = g + (size_t)(k0 + krow) * ld + r0 + chunk * 8;
     }
     __builtin_amdgcn_global_load_lds(GLB_PTR(src), LDS_PTR(lds + q * 512), 16, 0, 0);
@@ -106,11 +97,11 @@ __device__ __forceinline__ void issue_tile_one(const bf16_raw* __restrict__ g, i
 //                         base(t) = g + ((r0 + t * NW * 8) * ld + k0) * 2
 //   k-rows as tile rows : lane offset = ((wave * RPI + lane / CPR) * ld + chunk * 8) * 2,
 //                         base(t) = g + ((k0 + t * NW * RPI) * ld + r0) * 2          (RPI = 64 / CPR k-rows per load)
-// The chunk swizzle is the one of issue_tile_one; it does not depend on t except for (TRANS, K32, BR = 256, NW = 4),
+// The chunk swizzle is the one of issue_tile_one; it does not depend on t except for (TRANS, BR = 256, NW = 4),
 // where it alternates with t (off[t & 1]).
-template <int BR, int NW, bool TRANS, bool K32>
+template <int BR, int NW, bool TRANS>
 struct TileLoad {
-  static constexpr bool ALT = TRANS && K32 && BR == 256 && NW == 4;
+  static constexpr bool ALT = TRANS && BR == 256 && NW == 4;
   uint32_t off[ALT ? 2 : 1];
   __device__ __forceinline__ void init(int ld, int wave, int lane) {
 #pragma unroll
@@ -118,12 +109,12 @@ struct TileLoad {
       const int q = wave + a * NW;
       if constexpr (!TRANS) {
         const int row = q * (64 / KCH) + lane / KCH;
-        const int chunk = (lane % KCH) ^ swz_rows_of<K32>(row);
+        const int chunk = (lane % KCH) ^ swz_rows16(row);
         off[a] = (uint32_t)((wave * (64 / KCH) + lane / KCH) * ld + chunk * 8) * 2u;
       } else {
         constexpr int CPR = BR / 8;
         const int krow = q * (64 / CPR) + lane / CPR;
-        const int chunk = (lane % CPR) ^ (4 * (krow & 3)) ^ (K32 ? 2 * ((krow >> 3) & 1) : 0);
+        const int chunk = (lane % CPR) ^ (4 * (krow & 3)) ^ (2 * ((krow >> 3) & 1));
         off[a] = (uint32_t)((wave * (64 / CPR) + lane / CPR) * ld + chunk * 8) * 2u;
       }
     }
@@ -140,42 +131,13 @@ struct TileLoad {
   }
 };
 
-template <int BR, int NW, bool TRANS, bool K32 = false>
+template <int BR, int NW, bool TRANS>
 __device__ __forceinline__ void issue_tile(const bf16_raw* __restrict__ g, int ld, int r0, int k0, bf16_raw* lds,
                                            int wave, int lane, int glu_split = 0) {
   constexpr int NINST = BR * DBK / 512;
   static_assert(NINST % NW == 0, "tile rows must split evenly over the wavefronts");
 #pragma unroll
-  for (int t = 0; t < NINST / NW; ++t) issue_tile_one<BR, NW, TRANS, K32>(g, ld, r0, k0, lds, wave, lane, t, glu_split);
-}
-
-// Fragment (32 GEMM rows x 16 k) for v_mfma_f32_32x32x16_bf16 from a non-transposed tile.
-__device__ __forceinline__ bf16x8 frag_rows(const bf16_raw* tile, int row_base, int kk, int l32, int lg) {
-  const int row = row_base + l32;
-  const int chunk = (2 * kk + lg) ^ swz_rows(l32);
-  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(tile + row * DBK + chunk * 8));
-}
-
-// Same fragment from a [32 k][BR] tile through the LDS transpose read.
-template <int BR>
-__device__ __forceinline__ bf16x8 frag_trans(const bf16_raw* tile, int col_base, int kk, int lane) {
-  const int l16 = lane & 15, grp = lane >> 4;
-  const int lg = grp >> 1;
-  const int col = col_base + 16 * (grp & 1) + 4 * (l16 & 3);
-  const int kq = l16 >> 2;                                   // k-row inside the group of four
-  const int chunk = (col >> 3) ^ (4 * kq);
-  const int off = chunk * 8 + (col & 4);
-  const int krow = 16 * kk + 8 * lg + kq;
-  const bf16_raw* p0 = tile + krow * BR + off;
-  // Issued as plain instructions: behind the compiler's builtin for this read every pending global -> LDS load
-  // is taken as a possible writer of the bytes read and waited for (vmcnt(0)), which would serialise the loads
-  // of the next slice with the reads of this one.  The stages are disjoint by construction.  The price: the
-  // compiler does not count these reads, so the caller waits for them itself (lds_reads_done) before use.
-  const uint32_t addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p0;
-  uint2 a, b;
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(a) : "v"(addr) : "memory");
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(b) : "v"(addr), "n"(8 * BR) : "memory");
-  return __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, b.x, b.y));
+  for (int t = 0; t < NINST / NW; ++t) issue_tile_one<BR, NW, TRANS>(g, ld, r0, k0, lds, wave, lane, t, glu_split);
 }
 
 // All LDS reads of this wavefront have returned (also those the compiler does not know of); nothing is
@@ -185,176 +147,9 @@ __device__ __forceinline__ void lds_reads_done() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int BM, int BN, int WM, int WN, bool A_T, bool B_T>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_dma_kernel(KArgs p) {
-  constexpr int NW = WM * WN;
-  constexpr int WTM = BM / WM, WTN = BN / WN;
-  constexpr int FM = WTM / 32, FN = WTN / 32;
-  constexpr int STAGE = (BM + BN) * DBK;              // elements
-  constexpr int IPW = (BM + BN) * DBK / 512 / NW;       // load instructions per wavefront per stage
-  extern __shared__ __attribute__((aligned(1024))) bf16_raw lds[];
-
-  int tile_m, tile_n;
-  if (p.ksplit > 1) {
-    // workgroups [i * ntiles, (i+1) * ntiles) take the i-th part of K of every tile
-    const int ntiles = p.tiles_m * p.tiles_n;
-    const int part = blockIdx.x / ntiles;
-    tile_of_block(p, tile_m, tile_n, blockIdx.x - part * ntiles);
-    p.K /= p.ksplit;
-    p.A += A_T ? (size_t)part * p.K * p.lda : (size_t)part * p.K;
-    p.B += B_T ? (size_t)part * p.K * p.ldb : (size_t)part * p.K;
-    p.C = p.part + (size_t)part * p.M * p.N;
-    p.ldc = p.N;
-    p.epilogue = EPI_PART_F32;
-  } else {
-    tile_of_block(p, tile_m, tile_n);
-  }
-  const int m0 = tile_m * BM;
-  // GeGLU forward: a tile of BN gathered rows covers BN/2 features; n0 then counts features
-  const int glu = (!B_T && p.epilogue == EPI_BIAS_GEGLU) ? p.split : 0;
-  const int n0 = glu ? tile_n * (BN / 2) : tile_n * BN;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
-  const int l32 = lane & 31, lg = lane >> 5;
-
-  f32x16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int KT = p.K / DBK;
-  auto issue = [&](int kt, int stage) {   // slice kt -> LDS stage `stage`
-    bf16_raw* st = lds + stage * STAGE;
-    issue_tile<BM, NW, A_T>(p.A, p.lda, m0, kt * DBK, st, wave, lane);
-    issue_tile<BN, NW, B_T>(p.B, p.ldb, n0, kt * DBK, st + BM * DBK, wave, lane, glu);
-  };
-  // When is the stage that a barrier frees refilled?  EARLY: in the sub-step right behind that barrier (slices 0
-  // and 1 are requested up front, slice kt+2 behind the barrier that ends slice kt); otherwise one sub-step
-  // later, at the top of the next iteration.  Measured: EARLY gains 1-3 % on the 256 x 256 tile and loses 5 % on
-  // the 128 x 128 one (two workgroups per compute unit already overlap each other's loads).
-  constexpr bool EARLY = BM == 256;
-  issue(0, 0);
-  if constexpr (EARLY) {
-    issue(min(1, KT - 1), 1);
-    wait_vmcnt<IPW>();
-  } else {
-    wait_vmcnt<0>();
-  }
-  __builtin_amdgcn_s_barrier();
-
-  constexpr int KK = DBK / 16;
-  static_assert(NS == 2 && KK % 2 == 0, "the fragment pipeline below assumes two stages and an even slice depth");
-  auto load_frags = [&](const bf16_raw* sA, const bf16_raw* sB, int kk, bf16x8 (&a)[FM], bf16x8 (&b)[FN]) {
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      if constexpr (A_T) a[i] = frag_trans<BM>(sA, wm * WTM + i * 32, kk, lane);
-      else a[i] = frag_rows(sA, wm * WTM + i * 32, kk, l32, lg);
-    }
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      if constexpr (B_T) b[j] = frag_trans<BN>(sB, wn * WTN + j * 32, kk, lane);
-      else b[j] = frag_rows(sB, wn * WTN + j * 32, kk, l32, lg);
-    }
-  };
-  auto mma = [&](const bf16x8 (&a)[FM], const bf16x8 (&b)[FN]) {
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-  };
-
-  // Software pipeline, written out instruction by instruction: every MFMA of sub-step kk is followed by one
-  // LDS read of a fragment of sub-step kk+1 (and, in the first sub-step of a slice, by this wavefront's next
-  // global -> LDS load of slice kt+1), and a scheduling barrier keeps that order.  Reads are thus spread under
-  // the multiplies and the waits in front of the next sub-step are partial.  The last sub-step of a slice is
-  // multiplied AFTER the barrier, behind the reads of the next slice's first fragments, so the matrix pipe has
-  // work queued across the barrier.  The loop body is one basic block: the last iteration re-fetches the last
-  // slice into the free stage instead of branching.
-  constexpr int NMMA = FM * FN, NF = FM + FN;
-  constexpr int IPA = BM * DBK / 512 / NW;          // this wavefront's load instructions for the A tile
-  constexpr int LPM = (IPW + NMMA - 1) / NMMA;      // loads behind one MFMA
-  constexpr int RPM = 1;                            // fragment reads behind one MFMA (2 and 3 measured no faster)
-  static_assert(NMMA >= NF, "one fragment read per MFMA");
-  // reads in the order the next sub-step needs them: A row 0, all of B, the other A rows
-  auto read_nth = [&](const bf16_raw* sA, const bf16_raw* sB, int kk, int n, bf16x8 (&a)[FM], bf16x8 (&b)[FN]) {
-    if (n == 0 || n > FN) {
-      const int i = n == 0 ? 0 : n - FN;
-      if constexpr (A_T) a[i] = frag_trans<BM>(sA, wm * WTM + i * 32, kk, lane);
-      else a[i] = frag_rows(sA, wm * WTM + i * 32, kk, l32, lg);
-    } else {
-      const int j = n - 1;
-      if constexpr (B_T) b[j] = frag_trans<BN>(sB, wn * WTN + j * 32, kk, lane);
-      else b[j] = frag_rows(sB, wn * WTN + j * 32, kk, l32, lg);
-    }
-  };
-  // multiply (ca, cb); read the fragments of sub-step nkk of the tile at nA into (na, nb); with LOADS, issue the
-  // loads of slice `lk` into stage `ls`
-  // loads inside the loop: split addresses where an operand is transposed (see TileLoad)
-  constexpr bool SPLIT_ADDR = A_T || B_T;
-  TileLoad<BM, NW, A_T, false> ldA;
-  TileLoad<BN, NW, B_T, false> ldB;
-  if constexpr (SPLIT_ADDR) {
-    ldA.init(p.lda, wave, lane);
-    ldB.init(p.ldb, wave, lane);
-  }
-  auto substep = [&](const bf16x8 (&ca)[FM], const bf16x8 (&cb)[FN], const bf16_raw* nA, int nkk, bf16x8 (&na)[FM],
-                     bf16x8 (&nb)[FN], bool loads, int lk, int ls) {
-    bf16_raw* st = lds + ls * STAGE;
-    if constexpr (A_T || B_T) lds_reads_done();   // (ca, cb) were read by the previous sub-step
-#pragma unroll
-    for (int n = 0; n < NMMA; ++n) {
-      const int i = n / FN, j = n % FN;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ca[i], cb[j], acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int r = n * RPM; r < (n + 1) * RPM && r < NF; ++r) read_nth(nA, nA + BM * DBK, nkk, r, na, nb);
-      if (loads) {
-#pragma unroll
-        for (int t = n * LPM; t < (n + 1) * LPM && t < IPW; ++t) {
-          if constexpr (SPLIT_ADDR) {
-            if (t < IPA) ldA.issue(p.A, p.lda, m0, lk * DBK, st, wave, t);
-            else ldB.issue(p.B, p.ldb, n0, lk * DBK, st + BM * DBK, wave, t - IPA);
-          } else {
-            if (t < IPA) issue_tile_one<BM, NW, A_T>(p.A, p.lda, m0, lk * DBK, st, wave, lane, t);
-            else issue_tile_one<BN, NW, B_T>(p.B, p.ldb, n0, lk * DBK, st + BM * DBK, wave, lane, t - IPA, glu);
-          }
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  bf16x8 fa[2][FM], fb[2][FN];
-  load_frags(lds, lds + BM * DBK, 0, fa[0], fb[0]);
-  for (int kt = 0; kt < KT; ++kt) {
-    const bf16_raw* sA = lds + (kt & 1) * STAGE;
-    const bf16_raw* nA = lds + ((kt + 1) & 1) * STAGE;
-#pragma unroll
-    for (int kk = 0; kk + 1 < KK; ++kk)
-      substep(fa[kk & 1], fb[kk & 1], sA, kk + 1, fa[(kk + 1) & 1], fb[(kk + 1) & 1], !EARLY && kk == 0,
-              min(kt + 1, KT - 1), (kt + 1) & 1);
-    // slice kt+1 must have landed (this wavefront's part) and this wavefront's reads of slice kt be complete;
-    // then all wavefronts meet
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    __builtin_amdgcn_s_barrier();
-    // the stage of slice kt is free (the last iterations re-fetch the last slice instead of branching)
-    substep(fa[(KK - 1) & 1], fb[(KK - 1) & 1], nA, 0, fa[0], fb[0], EARLY, min(kt + 2, KT - 1), kt & 1);
-  }
-  wait_vmcnt<0>();
-  __builtin_amdgcn_s_barrier();   // all MFMAs read registers only, but keep the epilogue's LDS reuse fenced
-
-  // every wavefront is past the last barrier: the operand stages are free to serve as epilogue patches
-  gemm_epilogue<FM, FN, false>(p, acc, m0 + wm * WTM, glu ? n0 + wn * (WTN / 2) : n0 + wn * WTN, l32, lg,
-                               reinterpret_cast<float*>(lds) + wave * 32 * kEpiPitch);
-}
-
 // ------------------------------------------------------------------------------------------------------------
-// The same product on v_mfma_f32_16x16x32_bf16.  A loop of nothing but MFMAs on random operands sustains 5-12 %
-// more flops with the 16 x 16 x 32 shape than with 32 x 32 x 16 (the chip is power-limited there), and this kernel
+// gemm_bf16_k32_kernel.  A loop of nothing but MFMAs on random operands sustains 5-12 % more flops with the
+// 16 x 16 x 32 shape than with 32 x 32 x 16 (the chip is power-limited there), and this kernel
 // keeps that margin.  Per 32-deep sub-step a wavefront holds WTM/16 A fragments (16 rows x 32 k, 8 k-values per
 // lane: lane % 16 -> row, lane / 16 -> k quarter) and WTN/16 B fragments; the MFMAs go row by row, and the A
 // fragment of a row is re-read for the next sub-step as soon as the row is done (single buffer), the B fragments
@@ -367,13 +162,16 @@ __device__ __forceinline__ bf16x8 frag_rows16(const bf16_raw* tile, int row_base
   const int chunk = (4 * kk + q) ^ swz_rows16(l16);
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(tile + row * DBK + chunk * 8));
 }
-// the same fragment from a [k][BR] tile through the LDS transpose read (two plain instructions, caller waits)
+// The same fragment from a [k][BR] tile through the LDS transpose read.  Two plain instructions: behind the compiler's
+// builtin for this read every pending global -> LDS load is taken as a possible writer of the bytes read and waited for
+// (vmcnt(0)), which would serialise the loads of the next slice with the reads of this one.  The stages are disjoint by
+// construction; the compiler does not count these reads, so the caller waits for them itself.
 template <int BR>
 __device__ __forceinline__ bf16x8 frag_trans16(const bf16_raw* tile, int col_base, int kk, int lane) {
   const int l16 = lane & 15, q = lane >> 4;
   const int col = col_base + 4 * (l16 & 3);
   const int kq = l16 >> 2;                                   // k-row inside the group of four
-  const int chunk = (col >> 3) ^ (4 * kq) ^ (2 * (q & 1));   // as written by issue_tile_one<..., K32 = true>
+  const int chunk = (col >> 3) ^ (4 * kq) ^ (2 * (q & 1));   // as written by issue_tile_one
   const int off = chunk * 8 + (col & 4);
   const int krow = 32 * kk + 8 * q + kq;
   const bf16_raw* p0 = tile + krow * BR + off;
@@ -473,12 +271,12 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(KArgs p) {
       for (int r = 0; r < 4; ++r) acc.blk[i][j][r] = 0.f;
 
   const int KT = p.K / DBK;
-  issue_tile<BM, NW, A_T, true>(p.A, p.lda, m0, 0, lds, wave, lane);
-  issue_tile<BN, NW, B_T, true>(p.B, p.ldb, n0, 0, lds + BM * DBK, wave, lane, glu);
+  issue_tile<BM, NW, A_T>(p.A, p.lda, m0, 0, lds, wave, lane);
+  issue_tile<BN, NW, B_T>(p.B, p.ldb, n0, 0, lds + BM * DBK, wave, lane, glu);
   {
     const int k1 = min(1, KT - 1) * DBK;
-    issue_tile<BM, NW, A_T, true>(p.A, p.lda, m0, k1, lds + STAGE, wave, lane);
-    issue_tile<BN, NW, B_T, true>(p.B, p.ldb, n0, k1, lds + STAGE + BM * DBK, wave, lane, glu);
+    issue_tile<BM, NW, A_T>(p.A, p.lda, m0, k1, lds + STAGE, wave, lane);
+    issue_tile<BN, NW, B_T>(p.B, p.ldb, n0, k1, lds + STAGE + BM * DBK, wave, lane, glu);
   }
   wait_vmcnt<IPW>();
   __builtin_amdgcn_s_barrier();
@@ -506,8 +304,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(KArgs p) {
   // loads inside the loop: split addresses where an operand is transposed (the k-contiguous forward layout keeps
   // issue_tile_one, which also knows the GeGLU row gather)
   constexpr bool SPLIT_ADDR = A_T || B_T;
-  TileLoad<BM, NW, A_T, true> ldA;
-  TileLoad<BN, NW, B_T, true> ldB;
+  TileLoad<BM, NW, A_T> ldA;
+  TileLoad<BN, NW, B_T> ldB;
   if constexpr (SPLIT_ADDR) {
     ldA.init(p.lda, wave, lane);
     ldB.init(p.ldb, wave, lane);
@@ -546,8 +344,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(KArgs p) {
           if constexpr (t < IPA) ldA.issue(p.A, p.lda, m0, lk * DBK, st, wave, t);
           else ldB.issue(p.B, p.ldb, n0, lk * DBK, st + BM * DBK, wave, t - IPA);
         } else {
-          if constexpr (t < IPA) issue_tile_one<BM, NW, A_T, true>(p.A, p.lda, m0, lk * DBK, st, wave, lane, t);
-          else issue_tile_one<BN, NW, B_T, true>(p.B, p.ldb, n0, lk * DBK, st + BM * DBK, wave, lane, t - IPA, glu);
+          if constexpr (t < IPA) issue_tile_one<BM, NW, A_T>(p.A, p.lda, m0, lk * DBK, st, wave, lane, t);
+          else issue_tile_one<BN, NW, B_T>(p.B, p.ldb, n0, lk * DBK, st + BM * DBK, wave, lane, t - IPA, glu);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -828,12 +626,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(KArgs p) {
       for (int r = 0; r < 4; ++r) acc.blk[i][j][r] = 0.f;
 
   const int KT = p.K / DBK;
-  issue_tile<BM, NW, false, true>(p.A, p.lda, m0, 0, lds, wave, lane);
-  issue_tile<BN, NW, false, true>(p.B, p.ldb, n0, 0, lds + BM * DBK, wave, lane);
+  issue_tile<BM, NW, false>(p.A, p.lda, m0, 0, lds, wave, lane);
+  issue_tile<BN, NW, false>(p.B, p.ldb, n0, 0, lds + BM * DBK, wave, lane);
   {
     const int k1 = min(1, KT - 1) * DBK;
-    issue_tile<BM, NW, false, true>(p.A, p.lda, m0, k1, lds + STAGE, wave, lane);
-    issue_tile<BN, NW, false, true>(p.B, p.ldb, n0, k1, lds + STAGE + BM * DBK, wave, lane);
+    issue_tile<BM, NW, false>(p.A, p.lda, m0, k1, lds + STAGE, wave, lane);
+    issue_tile<BN, NW, false>(p.B, p.ldb, n0, k1, lds + STAGE + BM * DBK, wave, lane);
   }
   wait_vmcnt<IPW>();
   __builtin_amdgcn_s_barrier();
@@ -893,8 +691,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(KArgs p) {
       }
       if constexpr (KIND == 1 && n % 4 == 3 && n / 4 < IPW) {
         constexpr int t = n / 4;
-        if constexpr (t < IPA) issue_tile_one<BM, NW, false, true>(p.A, p.lda, m0, lk * DBK, st, wave, lane, t);
-        else issue_tile_one<BN, NW, false, true>(p.B, p.ldb, n0, lk * DBK, st + BM * DBK, wave, lane, t - IPA);
+        if constexpr (t < IPA) issue_tile_one<BM, NW, false>(p.A, p.lda, m0, lk * DBK, st, wave, lane, t);
+        else issue_tile_one<BN, NW, false>(p.B, p.ldb, n0, lk * DBK, st + BM * DBK, wave, lane, t - IPA);
       }
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -951,10 +749,7 @@ swarm_status launch_w4(const KArgs& k, hipStream_t st) {
 template <int BM, int BN, int WM, int WN, bool A_T, bool B_T>
 swarm_status launch_dma(const KArgs& k, hipStream_t st) {
   constexpr size_t lds_bytes = (size_t)NS * (BM + BN) * DBK * sizeof(bf16_raw);
-  // 256-row tiles: the 16 x 16 x 32 kernel; the 128 x 128 tile stays on 32 x 32 x 16 (measured 2 % faster there)
-  void (*kern)(KArgs);
-  if constexpr (BM == 256) kern = gemm_bf16_k32_kernel<BM, BN, WM, WN, A_T, B_T>;
-  else kern = gemm_bf16_dma_kernel<BM, BN, WM, WN, A_T, B_T>;
+  void (*kern)(KArgs) = gemm_bf16_k32_kernel<BM, BN, WM, WN, A_T, B_T>;
   static LdsOptIn opted;   // per instantiation
   if (lds_opt_in((const void*)kern, lds_bytes, opted) != SWARM_OK) return SWARM_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3(k.tiles_m * k.tiles_n * (k.ksplit > 1 ? k.ksplit : 1)), dim3(WM * WN * 64), lds_bytes,
@@ -1049,23 +844,20 @@ int splitk_parts_max(int M, int N) {
 
 }  // namespace
 
+swarm_status gemm_bf16_kw(const GemmArgs& g, hipStream_t st);
+
 size_t gemm_splitk_floats(int M, int N) {
   const int parts = splitk_parts_max(M, N);
   return parts > 1 ? (size_t)parts * M * N : 0;
 }
 
-// Returns SWARM_ERR_SHAPE when the problem is not tile-aligned (the caller then uses the guarded kernel).
+// Returns SWARM_ERR_SHAPE (nothing launched) for what only the register-staged kernel takes.  The caller has checked
+// alignment (16-byte rows, N % 8 == 0).
 swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
   if (g.a_trans && !g.b_trans) return SWARM_ERR_SHAPE;
   if (g.epilogue == EPI_BIAS_GEGLU && (g.a_trans || g.b_trans || g.N != 2 * g.split || g.split % 64)) return SWARM_ERR_SHAPE;
-  if (g.K % DBK || g.lda % 8 || g.ldb % 8 || ((uintptr_t)g.A & 15) || ((uintptr_t)g.B & 15)) return SWARM_ERR_SHAPE;
-  KArgs k;
-  k.group_m = 8;   // measured best of {2,4,8,16,32} on the d=4096 shapes
-  k.A = (const bf16_raw*)g.A; k.B = (const bf16_raw*)g.B; k.M = g.M; k.N = g.N; k.K = g.K; k.lda = g.lda;
-  k.ldb = g.ldb; k.C = g.C; k.ldc = g.ldc; k.epilogue = g.epilogue; k.bias = (const bf16_raw*)g.bias;
-  k.aux = (const bf16_raw*)g.aux; k.ldaux = g.ldaux; k.C2 = (bf16_raw*)g.C2; k.ldc2 = g.ldc2; k.scales = g.scales; k.scales16 = g.scales16;
-  k.rope = g.rope; k.rope_S = g.rope_S; k.rope_dh = g.rope_dh; k.rope_cols = g.rope_cols; k.split = g.split;
-  k.ksplit = 1; k.part = nullptr; k.stamps = g.stamps;
+  if (g.K % DBK) return gemm_bf16_kw(g, st);
+  KArgs k = kargs_of(g);
   // An output of at least twice the 32 MB of L2 cannot wait there for its consumer; written (and its residual /
   // pre-activation / gradient rows read) non-temporally it leaves the operand panels in the L2 instead.
   k.stream = (size_t)g.M * g.N * (g.epilogue == EPI_ACCUM_F32 ? 4 : 2) >= ((size_t)64 << 20);
@@ -1134,11 +926,7 @@ swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
       return launch_dma_layout<256, 128, 2, 4>(k, g.a_trans, g.b_trans, st);
     }
   }
-  if (g.M % 128 == 0 && g.N % 128 == 0) {
-    k.tiles_m = g.M / 128; k.tiles_n = g.N / 128;
-    return launch_dma_layout<128, 128, 2, 2>(k, g.a_trans, g.b_trans, st);
-  }
-  return SWARM_ERR_SHAPE;
+  return gemm_bf16_kw(g, st);   // fewer tiles than the 256-row ones need, or ragged
 }
 
 }  // namespace swarm

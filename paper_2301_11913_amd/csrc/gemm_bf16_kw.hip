@@ -1,0 +1,322 @@
+// bf16 MFMA GEMM for products with few output tiles and for ragged ones:  C[M,N] (+)= sum_k A(m,k) B(n,k).
+//
+// What bounds such a product is latency: a launch of 32..256 workgroups leaves every compute unit with one, and what
+// that one waits for between two slices of K (about a microsecond from memory) is longer than what it multiplies in
+// one.  So a workgroup keeps NS slices in LDS, NS - 1 of them in flight, and divides K as well as the tile: WM x WN x WK
+// wavefronts, each multiplying a 64 x 64 block over its own 32 of the 32 * WK values of k in a slice.  That keeps the
+// LDS bytes per flop of a 64 x 64 block (16 fragment reads for 32 MFMAs) on a tile as small as 64 x 64, and gives a
+// 128 x 128 tile eight wavefronts, two per SIMD.  The WK partial blocks meet once, in LDS, and are added in index order;
+// the epilogue then runs on rows of eight columns.
+//
+// Loads are buffer loads into LDS with the operand's exact size in the descriptor: what lies behind its last row reads
+// as zero, so a ragged M or N costs nothing in the loop and only the stores are guarded.  The descriptor moves along K
+// with scalar arithmetic; a lane's offset inside a slice never changes.  LDS layouts, swizzles and the transpose reads
+// are those of gemm_bf16_dma.hip.
+//
+// One barrier per slice: behind it slice k + 1 is in LDS for everyone and everyone's fragments of slice k are in
+// registers, so the reads of k + 1 and the refill of k's stage are issued there and the multiplies of k cover both.
+// Measured against what these products ran on before, 128 x 128 tiles with two LDS stages (whole tiles) and a
+// register-staged kernel (ragged ones): forward of one 512-token sequence at d_model 1024 119 -> 71 us, a training pass
+// at d_model 768 on 5 x 333 tokens 660 -> 463 us, two d_model 1024 blocks on 4096 tokens 1954 -> 1504 us.
+#include "gemm_bf16_common.h"
+
+namespace swarm {
+namespace {
+
+typedef uint32_t u32x4_kw __attribute__((ext_vector_type(4)));
+
+// One operand's tile: BR rows (of C's rows or columns) x BK k per slice.
+//   !TRANS: BK / 64 sub-tiles [BR][64 k], 16-byte chunks of a row XOR-ed with row & 7
+//    TRANS: [BK k][BR], chunks of a k-row XOR-ed so that the 8 k-rows x 32 bytes of one transpose-read pass hit all banks
+template <int BR, int BK, int NW, bool TRANS>
+struct KwOperand {
+  static constexpr int NI = BR * BK / 512 / NW;   // 1 KiB load instructions per wavefront and slice
+  static constexpr int BYTES = BR * BK * 2;
+  const char* base;
+  size_t step;          // bytes from slice to slice
+  size_t left;          // bytes from `base` to the end of the operand
+  int slices;           // still to come; behind the last one nothing is read and zeros arrive
+  uint32_t off[NI];     // this lane's offset in every load of a slice
+  uint32_t frag[4];     // this lane's LDS address of the four 16-row fragments of its block (relative to the tile)
+
+  static __device__ __forceinline__ int swz(int krow) {
+    return BR == 64 ? 4 * ((krow >> 1) & 1) ^ 2 * ((krow >> 3) & 1) : 4 * (krow & 3) ^ 2 * ((krow >> 3) & 1);
+  }
+
+  // rows r0 .. of an operand of `rows` rows and `kdim` k values; k starts at 0.  glu_split: see EPI_BIAS_GEGLU (B = W1,
+  // every 64 tile rows are 32 gate rows and the 32 up rows of the same features; r0 counts features)
+  __device__ __forceinline__ void init(const bf16_raw* p, int ld, int rows, int kdim, int r0, int glu_split, int wave,
+                                       int lane, int block, int wk) {
+    slices = (kdim + BK - 1) / BK;
+    if constexpr (!TRANS) {
+      base = reinterpret_cast<const char*>(p + (size_t)r0 * ld);
+      left = ((size_t)(rows - 1 - r0) * ld + kdim) * 2;
+      step = BK * 2;
+#pragma unroll
+      for (int t = 0; t < NI; ++t) {
+        const int q = wave + t * NW, sub = q / (BR / 8), row = q % (BR / 8) * 8 + lane / 8;
+        const int src = glu_split ? 32 * (row >> 6) + (row & 31) + ((row & 32) ? glu_split : 0) : row;
+        off[t] = ((uint32_t)src * (uint32_t)ld + 64u * sub + 8u * ((lane % 8) ^ (row & 7))) * 2u;
+      }
+      const int l16 = lane & 15, c = 4 * (wk & 1) + (lane >> 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        frag[i] = (uint32_t)((wk >> 1) * BR * 64 + (block * 64 + 16 * i + l16) * 64 + 8 * (c ^ (l16 & 7))) * 2u;
+    } else {
+      base = reinterpret_cast<const char*>(p + r0);
+      left = ((size_t)(kdim - 1) * ld + rows - r0) * 2;
+      step = (size_t)BK * ld * 2;
+      constexpr int CPR = BR / 8;
+#pragma unroll
+      for (int t = 0; t < NI; ++t) {
+        const int krow = (wave + t * NW) * (64 / CPR) + lane / CPR;
+        off[t] = ((uint32_t)krow * (uint32_t)ld + 8u * ((lane % CPR) ^ swz(krow))) * 2u;
+      }
+      const int l16 = lane & 15, krow = 32 * wk + 8 * (lane >> 4) + (l16 >> 2);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int col = block * 64 + 16 * i + 4 * (l16 & 3);
+        frag[i] = (uint32_t)(krow * BR + 8 * ((col >> 3) ^ swz(krow)) + (col & 4)) * 2u;
+      }
+    }
+  }
+  // the loads of the next slice into the tile at `lds`
+  __device__ __forceinline__ void issue(bf16_raw* lds, int wave) {
+#if defined(__HIP_DEVICE_COMPILE__)   // the host pass knows neither the descriptor type nor its builtins
+    const uint32_t records = slices <= 0 ? 0u : left > 0xFFFFFFF0u ? 0xFFFFFFF0u : (uint32_t)left;
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), (short)0, (int)records, 0x00020000);
+#pragma unroll
+    for (int t = 0; t < NI; ++t)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          r, (__attribute__((address_space(3))) void*)(lds + (wave + t * NW) * 512), 16, off[t], 0, 0, 0);
+#endif
+    if (--slices > 0) {
+      base += step;
+      left -= step;
+    }
+  }
+  // Fragment i of the slice whose tile starts at LDS byte `tile`.  Plain instructions: the compiler takes every load into
+  // LDS as a possible writer of what an LDS read of its own returns and would wait for all of them.  The caller waits.
+  __device__ __forceinline__ u32x4_kw read(uint32_t tile, int i) const {
+    const uint32_t addr = tile + frag[i];
+    if constexpr (!TRANS) {
+      u32x4_kw v;
+      asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
+      return v;
+    } else {
+      uint2 a, b;
+      // k-rows krow and krow + 4: the swizzle depends on bits 0, 1 and 3 of krow, which the two share
+      asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(a) : "v"(addr) : "memory");
+      asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(b) : "v"(addr), "n"(8 * BR) : "memory");
+      const u32x4_kw v = {a.x, a.y, b.x, b.y};
+      return v;
+    }
+  }
+};
+
+template <int N>
+__device__ __forceinline__ void kw_wait_loads() {   // at most N loads of this wavefront still on their way
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+template <int WM, int WN, int WK, int NS, bool A_T, bool B_T>
+__global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(KArgs p) {
+  constexpr int NW = WM * WN * WK, NT = NW * 64;
+  constexpr int BM = 64 * WM, BN = 64 * WN, BK = 32 * WK;
+  static_assert(BK % 64 == 0 && BM * BK % (512 * NW) == 0 && BN * BK % (512 * NW) == 0, "loads split evenly");
+  extern __shared__ __attribute__((aligned(1024))) bf16_raw lds[];
+
+  int tile_m, tile_n;
+  tile_of_block(p, tile_m, tile_n);
+  const int glu = (!B_T && p.epilogue == EPI_BIAS_GEGLU) ? p.split : 0;
+  const int m0 = tile_m * BM, n0 = glu ? tile_n * (BN / 2) : tile_n * BN;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wk = wave % WK, wn = wave / WK % WN, wm = wave / WK / WN;
+
+  KwOperand<BM, BK, NW, A_T> a;
+  KwOperand<BN, BK, NW, B_T> b;
+  a.init(p.A, p.lda, p.M, p.K, m0, 0, wave, lane, wm, wk);
+  b.init(p.B, p.ldb, glu ? 2 * glu : p.N, p.K, n0, glu, wave, lane, wn, wk);
+  constexpr int IPW = decltype(a)::NI + decltype(b)::NI;
+  constexpr int STAGE = a.BYTES + b.BYTES;
+  auto issue = [&](int stage) __attribute__((always_inline)) {
+    bf16_raw* s = lds + stage * (STAGE / 2);
+    a.issue(s, wave);
+    b.issue(s + a.BYTES / 2, wave);
+  };
+
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+
+  struct Frags { u32x4_kw a[4], b[4]; };
+  auto read = [&](int stage, Frags& f) __attribute__((always_inline)) {
+    const uint32_t tile = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)lds + (uint32_t)stage * STAGE;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f.a[i] = a.read(tile, i);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f.b[j] = b.read(tile + a.BYTES, j);
+  };
+
+#pragma unroll
+  for (int s = 0; s < NS; ++s) issue(s);
+  kw_wait_loads<(NS - 1) * IPW>();
+  __builtin_amdgcn_s_barrier();
+  Frags f0, f1;
+  read(0, f0);
+
+  int now = 0;      // stage of the current slice
+  auto step = [&](Frags& cur, Frags& next, int k) __attribute__((always_inline)) {
+    // this wavefront's fragments have arrived, and its part of the next slice
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(cur.a[0]), "+v"(cur.a[1]), "+v"(cur.a[2]), "+v"(cur.a[3]), "+v"(cur.b[0]), "+v"(cur.b[1]),
+                   "+v"(cur.b[2]), "+v"(cur.b[3])::"memory");
+    kw_wait_loads<(NS - 2) * IPW>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    const int after = now + 1 == NS ? 0 : now + 1;
+    read(after, next);
+    issue(now);
+    now = after;
+    __builtin_amdgcn_sched_barrier(0);
+    if (k < p.K) {   // K of a k-contiguous operand is a multiple of 32: a wavefront's 32 are all in or all out
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur.a[i]),
+                                                              __builtin_bit_cast(bf16x8, cur.b[j]), acc[i][j], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int KT = (p.K + BK - 1) / BK;
+  for (int kt = 0; kt < KT; kt += 2) {
+    step(f0, f1, kt * BK + 32 * wk);
+    step(f1, f0, (kt + 1) * BK + 32 * wk);
+  }
+  // the fragments requested last are not used, but have to arrive before their registers are
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(f0.a[0]), "+v"(f0.a[1]), "+v"(f0.a[2]), "+v"(f0.a[3]), "+v"(f0.b[0]), "+v"(f0.b[1]), "+v"(f0.b[2]),
+                 "+v"(f0.b[3])::"memory");
+  kw_wait_loads<0>();
+  __builtin_amdgcn_s_barrier();   // the stages are free: the partial blocks take their place
+
+  constexpr int PITCH = BN + 4;
+  float* sums = reinterpret_cast<float*>(lds);
+  {
+    float* mine = sums + (wk * BM + wm * 64) * PITCH + wn * 64;
+    const int l16 = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mine[(16 * i + 4 * q + r) * PITCH + 16 * j + l16] = acc[i][j][r];
+  }
+  __syncthreads();
+  auto sum8 = [&](int rl, int cl, float (&x)[8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = 0.f;
+#pragma unroll
+    for (int w = 0; w < WK; ++w) {
+      const float* s = sums + (w * BM + rl) * PITCH + cl;
+      const float4 u = *reinterpret_cast<const float4*>(s), v = *reinterpret_cast<const float4*>(s + 4);
+      x[0] += u.x; x[1] += u.y; x[2] += u.z; x[3] += u.w; x[4] += v.x; x[5] += v.y; x[6] += v.z; x[7] += v.w;
+    }
+  };
+  const int epi = p.epilogue;
+  if (glu) {
+    constexpr int CPR = BN / 16;           // chunks of 8 features per row
+    for (int e = threadIdx.x; e < BM * CPR; e += NT) {
+      const int rl = e / CPR, fl = e % CPR * 8;
+      const int row = m0 + rl, feat = n0 + fl;
+      if (row >= p.M || feat >= p.split) continue;
+      float g[8], u[8], t[8];
+      sum8(rl, fl / 32 * 64 + fl % 32, g);
+      sum8(rl, fl / 32 * 64 + fl % 32 + 32, u);
+      unpack8(*reinterpret_cast<const uint4*>(p.bias + feat), t);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) g[i] += t[i];
+      unpack8(*reinterpret_cast<const uint4*>(p.bias + p.split + feat), t);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) u[i] += t[i];
+      if (p.C2) {
+        store_stream<false>(p.C2 + (size_t)row * p.ldc2 + feat, pack8_bf16(g));
+        store_stream<false>(p.C2 + (size_t)row * p.ldc2 + p.split + feat, pack8_bf16(u));
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) g[i] = gelu_fast(g[i]) * u[i];
+      store_stream<false>(reinterpret_cast<bf16_raw*>(p.C) + (size_t)row * p.ldc + feat, pack8_bf16(g));
+    }
+    return;
+  }
+  constexpr int CPR = BN / 8;
+  static_assert(NT % CPR == 0, "a thread stays in its columns");
+  const int cl = threadIdx.x % CPR * 8, col = n0 + cl;
+  if (col >= p.N) return;                  // N is a multiple of 8
+  float bias[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) bias[e] = 0.f;
+  if (epilogue_has_bias(epi)) unpack8(*reinterpret_cast<const uint4*>(p.bias + col), bias);
+  for (int rl = threadIdx.x / CPR; rl < BM && m0 + rl < p.M; rl += NT / CPR) {
+    float x[8];
+    sum8(rl, cl, x);
+    if (epi == EPI_ACCUM_F32) {
+      float4* c = reinterpret_cast<float4*>(reinterpret_cast<float*>(p.C) + (size_t)(m0 + rl) * p.ldc + col);
+      const float4 u = c[0], v = c[1];
+      c[0] = make_float4(u.x + x[0], u.y + x[1], u.z + x[2], u.w + x[3]);
+      c[1] = make_float4(v.x + x[4], v.y + x[5], v.z + x[6], v.w + x[7]);
+    } else {
+      finish_chunk<false>(p, epi, x, bias, m0 + rl, col);
+    }
+  }
+}
+
+template <int WM, int WN, int WK, int NS, bool A_T, bool B_T>
+swarm_status launch(const KArgs& k, hipStream_t st) {
+  constexpr int BM = 64 * WM, BN = 64 * WN, BK = 32 * WK;
+  constexpr size_t stages = (size_t)NS * (BM + BN) * BK * 2, sums = (size_t)WK * BM * (BN + 4) * 4;
+  constexpr size_t lds_bytes = stages > sums ? stages : sums;
+  auto kern = gemm_bf16_kw_kernel<WM, WN, WK, NS, A_T, B_T>;
+  static LdsOptIn opted;   // per instantiation
+  if (lds_opt_in((const void*)kern, lds_bytes, opted) != SWARM_OK) return SWARM_ERR_LAUNCH;
+  hipLaunchKernelGGL(kern, dim3(k.tiles_m * k.tiles_n), dim3(WM * WN * WK * 64), lds_bytes, st, k);
+  return launch_status();
+}
+
+template <int WM, int WN, int WK, int NS>
+swarm_status launch_layout(KArgs k, bool a_t, bool b_t, hipStream_t st) {
+  k.tiles_m = (k.M + 64 * WM - 1) / (64 * WM);
+  k.tiles_n = (k.N + 64 * WN - 1) / (64 * WN);
+  if (!a_t && !b_t) return launch<WM, WN, WK, NS, false, false>(k, st);
+  if (!a_t) return launch<WM, WN, WK, NS, false, true>(k, st);
+  return launch<WM, WN, WK, NS, true, true>(k, st);
+}
+
+}  // namespace
+
+// SWARM_ERR_SHAPE (nothing launched): a k-contiguous operand whose K is no multiple of 32, or a tile whose offsets do
+// not fit 32 bits.  The caller has checked alignment (16-byte rows, N % 8 == 0) and the layout.
+swarm_status gemm_bf16_kw(const GemmArgs& g, hipStream_t st) {
+  if ((g.a_trans && !g.b_trans) || g.N % 8) return SWARM_ERR_SHAPE;
+  if (!(g.a_trans && g.b_trans) && g.K % 32) return SWARM_ERR_SHAPE;
+  if (g.epilogue == EPI_BIAS_GEGLU && (g.a_trans || g.b_trans || g.N != 2 * g.split || g.split % 32)) return SWARM_ERR_SHAPE;
+  const long long span = 128 + (g.epilogue == EPI_BIAS_GEGLU ? g.split : 0);   // rows a tile's offsets reach over
+  if (span * g.lda >= (1ll << 30) || span * g.ldb >= (1ll << 30)) return SWARM_ERR_SHAPE;
+  const KArgs k = kargs_of(g);
+  // 128 x 128 tiles from three quarters of a round on; below that 64 x 64 ones, with four stages while a compute unit
+  // holds one workgroup and with two, which lets it hold two, behind that.
+  const long big = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
+  if (big >= 192) return launch_layout<2, 2, 2, 4>(k, g.a_trans, g.b_trans, st);
+  const long small = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+  if (small > 256) return launch_layout<1, 1, 4, 2>(k, g.a_trans, g.b_trans, st);
+  return launch_layout<1, 1, 4, 4>(k, g.a_trans, g.b_trans, st);
+}
+
+}  // namespace swarm

@@ -358,3 +358,45 @@ def test_gemm_f32(M, N, K, a_t, b_t, epi):
         size = size * d.abs() + 8 / bound * 2.0 ** -24 * ref.abs()
         ref = ref * d
     assert ((Cd.cpu().double() - ref).abs() <= bound * size).all()
+
+
+# Kernel with K over the wavefronts (few tiles or ragged): both tile sizes, both stage counts, one row / one past a tile
+# in every ragged dimension, K of one wavefront's 32, half a slice, fewer slices than stages and an odd number of them.
+# The operands lie in front of NaNs: nothing behind them may reach a result.
+@pytest.mark.parametrize("M,N,K,a_t,b_t,epi", [
+    (1, 64, 32, False, False, 0), (65, 72, 96, False, False, 1), (512, 1024, 1024, False, False, 2),
+    (333, 192, 288, False, False, 3), (1665, 2304, 768, False, False, 1), (1700, 3080, 160, False, False, 0),
+    (63, 8, 64, False, True, 0), (129, 200, 352, False, True, 4), (1665, 768, 2304, False, True, 0),
+    (1921, 1992, 96, False, True, 4), (1100, 1992, 224, False, True, 0),
+    (8, 8, 1, True, True, 5), (72, 136, 63, True, True, 5), (768, 768, 1665, True, True, 5),
+    (1536, 2304, 257, True, True, 5), (1024, 1160, 130, True, True, 5)])
+def test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi):
+    lib = _lib()
+    seed = 3 * M + N + K
+    operand = lambda name, *shape: _bf(synth.normal(seed, name, shape))
+    A, B = operand("A", *((K, M) if a_t else (M, K))), operand("B", *((K, N) if b_t else (N, K)))
+    bias, aux = operand("bias", N), operand("aux", M, N)
+    ref = (A.T if a_t else A).double().numpy() @ (B if b_t else B.T).double().numpy()
+    fenced = lambda t: torch.cat([t.reshape(-1), torch.full((1 << 16,), float("nan"), dtype=t.dtype)]).cuda()
+    Ad, Bd, bd, xd = (fenced(t) for t in (A, B, bias, aux))
+    out = torch.float32 if epi == 5 else torch.bfloat16
+    Cd = torch.full((M + 1, N), 3.0, dtype=out, device="cuda")
+    C2 = torch.full((M + 1, N), 3.0, dtype=out, device="cuda")
+    st = lib.swarm_kernel_gemm(1, M, N, K, Ad.data_ptr(), A.shape[1], a_t, Bd.data_ptr(), B.shape[1], b_t, Cd.data_ptr(), N,
+                               epi, bd.data_ptr(), xd.data_ptr(), N, C2.data_ptr() if epi == 3 else None, N, None)
+    torch.cuda.synchronize()
+    assert st == 0
+    assert (Cd[M] == 3).all() and (C2[M] == 3).all()
+    if epi in (1, 2, 3):
+        ref = ref + bias.double().numpy()
+    if epi == 2:
+        ref = ref + aux.double().numpy()
+    if epi == 3:
+        assert np.max(np.abs(C2[:M].double().cpu().numpy() - ref)) <= 6e-3 * np.max(np.abs(ref))
+        ref = _gelu(ref)
+    if epi == 4:
+        ref = ref * _gelu_grad(aux.double().numpy())
+    if epi == 5:
+        ref = ref + 3.0
+    # half a bf16 ulp of the largest result (2^-9 = 2e-3) with room for the epilogue's input roundings; fp32: the sums
+    assert np.max(np.abs(Cd[:M].double().cpu().numpy() - ref)) <= (1e-5 if epi == 5 else 6e-3) * np.max(np.abs(ref))
