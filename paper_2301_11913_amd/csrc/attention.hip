@@ -1,4 +1,4 @@
-// Attention dispatch: MFMA flash kernels for bf16, direct kernels otherwise.
+// Attention dispatch: matrix-core kernels for d_head 64 and 128 (bf16 and fp32), direct kernels for other widths.
 #include "kernels.h"
 
 namespace swarm {
@@ -8,19 +8,26 @@ swarm_status attention_bwd_naive(const void*, const void*, const void*, const fl
                                  int, bool, hipStream_t);
 
 swarm_status attention_fwd_mfma(const void*, void*, float*, int, int, int, int, hipStream_t);
+swarm_status attention_fwd_f32(const float*, float*, float*, int, int, int, int, hipStream_t);
 
 swarm_status attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int H, int dh, bool bf16,
                            hipStream_t st) {
   if (bf16 && (dh == 64 || dh == 128)) return attention_fwd_mfma(qkv, o, lse, B, S, H, dh, st);
+  if (!bf16 && (dh == 64 || dh == 128)) return attention_fwd_f32((const float*)qkv, (float*)o, lse, B, S, H, dh, st);
   return attention_fwd_naive(qkv, o, lse, B, S, H, dh, bf16, st);
 }
 
 swarm_status attention_bwd_mfma(const void*, const void*, const void*, const float*, float*, void*, int, int, int,
                                 int, hipStream_t);
+swarm_status attention_bwd_f32(const float*, const float*, const float*, const float*, float*, float*, int, int, int,
+                               int, hipStream_t);
 
 swarm_status attention_bwd(const void* qkv, const void* o, const void* dout, const float* lse, float* delta,
                            void* dqkv, int B, int S, int H, int dh, bool bf16, hipStream_t st) {
   if (bf16 && (dh == 64 || dh == 128)) return attention_bwd_mfma(qkv, o, dout, lse, delta, dqkv, B, S, H, dh, st);
+  if (!bf16 && (dh == 64 || dh == 128))
+    return attention_bwd_f32((const float*)qkv, (const float*)o, (const float*)dout, lse, delta, (float*)dqkv, B, S, H, dh,
+                             st);
   return attention_bwd_naive(qkv, o, dout, lse, delta, dqkv, B, S, H, dh, bf16, st);
 }
 

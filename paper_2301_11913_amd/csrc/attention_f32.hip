@@ -1,0 +1,277 @@
+// fp32 causal attention on the matrix cores (v_mfma_f32_32x32x2_f32), forward and backward, d_head 64 or 128.
+//
+// What bounds it: fp32 microbatches are small (tens of heads times a few hundred tokens), so a kernel has few blocks of
+// work and each is a chain of dependent loads and products.  Tiles are therefore 32 queries (32 keys for dK / dV) and a
+// workgroup's four wavefronts share one tile: each takes every fourth block of 32 keys (queries) with sums and softmax
+// statistics of its own, and they meet once, in LDS.  Operands go from global memory straight into registers.
+//
+// One layout serves everything.  A score block is formed with the streamed rows as the first MFMA operand and the
+// tile's rows as the second, so lane l holds column l % 32 (its own query, or key) and in register r row
+// 8 (r / 4) + 4 (l / 32) + r % 4 of the streamed block; softmax statistics are then per lane.  As second operand of
+// the product that follows (P V, dS K, P^T dO, dS^T Q), register r is exactly what MFMA number r wants from the lane
+// when the first operand brings the same row: no transpose, no LDS.
+//
+// Measured against one workgroup per row (attention_naive.hip: forward 20, dK / dV 37, dQ 25 us at 4 sequences of 128
+// tokens, 4 heads of 64, and growing with the square of the length): the training pass they are part of 302 -> 257 us.
+#include "kernels.h"
+
+namespace swarm {
+namespace {
+
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+constexpr int kWaves = 4, kNT = kWaves * 64;
+
+__device__ __forceinline__ float comp(const float4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
+__device__ __forceinline__ int row_of(int r, int lg) { return 8 * (r >> 2) + 4 * lg + (r & 3); }
+__device__ __forceinline__ f32x16_t zero16() {
+  f32x16_t z;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) z[r] = 0.f;
+  return z;
+}
+
+// this lane's row of a [rows, DH] operand: DH values in 8-deep steps, four per half of the wavefront
+template <int DH>
+__device__ __forceinline__ void load_row(float4 (&f)[DH / 8], const float* row, int lg) {
+#pragma unroll
+  for (int s = 0; s < DH / 8; ++s) f[s] = *reinterpret_cast<const float4*>(row + 8 * s + 4 * lg);
+}
+// streamed rows (lane's own: `row`) times the tile's rows (`f`): a 32 x 32 block of dot products over DH
+template <int DH>
+__device__ __forceinline__ f32x16_t dots(const float* row, const float4 (&f)[DH / 8], int lg) {
+  f32x16_t acc = zero16();
+  float4 x[DH / 8];
+  load_row<DH>(x, row, lg);
+#pragma unroll
+  for (int s = 0; s < DH / 8; ++s)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(x[s], c), comp(f[s], c), acc, 0, 0, 0);
+  return acc;
+}
+// out^T [DH][tile column] += sum over the block's 32 streamed rows of X[row][:] w[row][column].  `first` = first row of
+// the block, rows past `last` read row `last` (their weights are zero).
+template <int DH>
+__device__ __forceinline__ void accumulate(f32x16_t (&out)[DH / 32], const float* x, size_t ld, int first, int last,
+                                           const f32x16_t& w, int l32, int lg) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float* row = x + (size_t)min(first + row_of(r, lg), last) * ld + l32;
+#pragma unroll
+    for (int c = 0; c < DH / 32; ++c) out[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(row[32 * c], w[r], out[c], 0, 0, 0);
+  }
+}
+// The wavefronts' out^T meet 64 of its DH rows at a time: each writes its own to patch[wave] ([64][33]), and
+// emit(i, c, row) is called for every column i < columns of the tile and feature c, row = 33 (c % 64) + i.
+template <int DH, typename F>
+__device__ __forceinline__ void meet(const f32x16_t (&out)[DH / 32], float (*patch)[64 * 33], int wave, int l32, int lg,
+                                     int columns, F&& emit) {
+#pragma unroll
+  for (int c0 = 0; c0 < DH; c0 += 64) {
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) patch[wave][(32 * c + row_of(r, lg)) * 33 + l32] = out[c0 / 32 + c][r];
+    __syncthreads();
+    for (int e = threadIdx.x; e < 64 * columns; e += kNT) emit(e / 64, c0 + e % 64, e % 64 * 33 + e / 64);
+  }
+}
+
+// one workgroup per (32 queries, head, sequence), long rows first
+template <int DH>
+__global__ __launch_bounds__(kNT) void attn_f32_fwd_kernel(const float* __restrict__ qkv, float* __restrict__ o,
+                                                           float* __restrict__ lse, int S, int H) {
+  __shared__ float patch[kWaves][64 * 33];
+  __shared__ float stat[2][kWaves][32];
+  const int qt = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int d = H * DH;
+  const size_t ld = 3 * (size_t)d;
+  const float* base = qkv + (size_t)b * S * ld + h * DH;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, lg = lane >> 5;
+  const float scale = 1.0f / sqrtf((float)DH);
+  const int query = qt * 32 + l32;
+  float4 q[DH / 8];
+  load_row<DH>(q, base + (size_t)min(query, S - 1) * ld, lg);
+
+  float m = -INFINITY, l = 0.f;
+  f32x16_t out[DH / 32];
+#pragma unroll
+  for (int c = 0; c < DH / 32; ++c) out[c] = zero16();
+  for (int kb = wave; kb <= qt; kb += kWaves) {
+    f32x16_t s = dots<DH>(base + (size_t)min(kb * 32 + l32, S - 1) * ld + d, q, lg);
+    float top = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = kb * 32 + row_of(r, lg) <= query ? s[r] * scale : -INFINITY;
+      top = fmaxf(top, s[r]);
+    }
+    top = fmaxf(m, fmaxf(top, __shfl_xor(top, 32, 64)));   // finite: key 0 of the block, or the diagonal, is seen
+    const float old = expf(m - top);
+    m = top;
+    float sum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = expf(s[r] - m);
+      sum += s[r];
+    }
+    l = l * old + sum + __shfl_xor(sum, 32, 64);
+#pragma unroll
+    for (int c = 0; c < DH / 32; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) out[c][r] *= old;
+    accumulate<DH>(out, base + 2 * d, ld, kb * 32, S - 1, s, l32, lg);
+  }
+  if (lg == 0) {
+    stat[0][wave][l32] = m;
+    stat[1][wave][l32] = l;
+  }
+  meet<DH>(out, patch, wave, l32, lg, min(32, S - qt * 32), [&](int i, int c, int at) __attribute__((always_inline)) {
+    float top = stat[0][0][i];                             // wavefront 0 always has a block
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) top = fmaxf(top, stat[0][w][i]);
+    float sum = 0.f, acc = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float f = expf(stat[0][w][i] - top);
+      sum += f * stat[1][w][i];
+      acc += f * patch[w][at];
+    }
+    o[((size_t)b * S + qt * 32 + i) * d + h * DH + c] = acc / sum;
+    if (c == 0) lse[((size_t)b * H + h) * S + qt * 32 + i] = top + logf(sum);
+  });
+}
+
+// delta[b,h,i] = sum_c do[i,c] o[i,c]: a wavefront per (row, head)
+template <int DH>
+__global__ __launch_bounds__(kNT) void attn_f32_delta_kernel(const float* __restrict__ o, const float* __restrict__ dout,
+                                                             float* __restrict__ delta, int rows, int S, int H) {
+  const int item = blockIdx.x * kWaves + (threadIdx.x >> 6);
+  if (item >= rows * H) return;
+  const int row = item / H, h = item % H;
+  const size_t off = (size_t)item * DH + (threadIdx.x & 63);
+  float s = 0.f;
+#pragma unroll
+  for (int c = 0; c < DH; c += 64) s += o[off + c] * dout[off + c];
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) delta[((size_t)(row / S) * H + h) * S + row % S] = s;
+}
+
+// dQ of 32 queries
+template <int DH>
+__global__ __launch_bounds__(kNT) void attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ dout,
+                                                          const float* __restrict__ lse, const float* __restrict__ delta,
+                                                          float* __restrict__ dqkv, int S, int H) {
+  __shared__ float patch[kWaves][64 * 33];
+  const int qt = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int d = H * DH;
+  const size_t ld = 3 * (size_t)d;
+  const float* base = qkv + (size_t)b * S * ld + h * DH;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, lg = lane >> 5;
+  const float scale = 1.0f / sqrtf((float)DH);
+  const int query = qt * 32 + l32, qrow = min(query, S - 1);
+  float4 q[DH / 8], g[DH / 8];
+  load_row<DH>(q, base + (size_t)qrow * ld, lg);
+  load_row<DH>(g, dout + ((size_t)b * S + qrow) * d + h * DH, lg);
+  const float L = lse[((size_t)b * H + h) * S + qrow], D = delta[((size_t)b * H + h) * S + qrow];
+  f32x16_t out[DH / 32];
+#pragma unroll
+  for (int c = 0; c < DH / 32; ++c) out[c] = zero16();
+  for (int kb = wave; kb <= qt; kb += kWaves) {
+    const float* krow = base + (size_t)min(kb * 32 + l32, S - 1) * ld + d;
+    f32x16_t s = dots<DH>(krow, q, lg);
+    const f32x16_t dp = dots<DH>(krow + d, g, lg);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      s[r] = kb * 32 + row_of(r, lg) <= query ? expf(s[r] * scale - L) * (dp[r] - D) : 0.f;
+    accumulate<DH>(out, base + d, ld, kb * 32, S - 1, s, l32, lg);
+  }
+  meet<DH>(out, patch, wave, l32, lg, min(32, S - qt * 32), [&](int i, int c, int at) __attribute__((always_inline)) {
+    float acc = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) acc += patch[w][at];
+    dqkv[((size_t)b * S + qt * 32 + i) * ld + h * DH + c] = acc * scale;
+  });
+}
+
+// dK and dV of 32 keys
+template <int DH>
+__global__ __launch_bounds__(kNT) void attn_f32_dkdv_kernel(const float* __restrict__ qkv, const float* __restrict__ dout,
+                                                            const float* __restrict__ lse,
+                                                            const float* __restrict__ delta, float* __restrict__ dqkv,
+                                                            int S, int H) {
+  __shared__ float patch[kWaves][64 * 33];
+  const int kt = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int d = H * DH;
+  const size_t ld = 3 * (size_t)d;
+  const float* base = qkv + (size_t)b * S * ld + h * DH;
+  const float* gout = dout + (size_t)b * S * d + h * DH;
+  const float *L = lse + ((size_t)b * H + h) * S, *D = delta + ((size_t)b * H + h) * S;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, lg = lane >> 5;
+  const float scale = 1.0f / sqrtf((float)DH);
+  const int key = kt * 32 + l32, krow = min(key, S - 1);
+  float4 k[DH / 8], v[DH / 8];
+  load_row<DH>(k, base + (size_t)krow * ld + d, lg);
+  load_row<DH>(v, base + (size_t)krow * ld + 2 * d, lg);
+  f32x16_t dk[DH / 32], dv[DH / 32];
+#pragma unroll
+  for (int c = 0; c < DH / 32; ++c) dk[c] = dv[c] = zero16();
+  const int blocks = (S + 31) / 32;
+  for (int qb = kt + wave; qb < blocks; qb += kWaves) {
+    const int qrow = min(qb * 32 + l32, S - 1);
+    f32x16_t p = dots<DH>(base + (size_t)qrow * ld, k, lg);
+    f32x16_t ds = dots<DH>(gout + (size_t)qrow * d, v, lg);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int query = qb * 32 + row_of(r, lg), at = min(query, S - 1);
+      p[r] = query >= key && query < S ? expf(p[r] * scale - L[at]) : 0.f;
+      ds[r] = p[r] * (ds[r] - D[at]);
+    }
+    accumulate<DH>(dv, gout, d, qb * 32, S - 1, p, l32, lg);
+    accumulate<DH>(dk, base, ld, qb * 32, S - 1, ds, l32, lg);
+  }
+  auto emit = [&](int part, float factor) __attribute__((always_inline)) {
+    return [=](int i, int c, int at) __attribute__((always_inline)) {
+      float acc = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) acc += patch[w][at];
+      dqkv[((size_t)b * S + kt * 32 + i) * ld + part * d + h * DH + c] = acc * factor;
+    };
+  };
+  meet<DH>(dk, patch, wave, l32, lg, min(32, S - kt * 32), emit(1, scale));
+  meet<DH>(dv, patch, wave, l32, lg, min(32, S - kt * 32), emit(2, 1.0f));
+}
+
+template <int DH>
+swarm_status bwd(const float* qkv, const float* o, const float* dout, const float* lse, float* delta, float* dqkv, int B,
+                 int S, int H, hipStream_t st) {
+  const dim3 grid((S + 31) / 32, H, B);
+  const int items = B * S * H;
+  hipLaunchKernelGGL(attn_f32_delta_kernel<DH>, dim3((items + kWaves - 1) / kWaves), dim3(kNT), 0, st, o, dout, delta, B * S,
+                     S, H);
+  hipLaunchKernelGGL(attn_f32_dq_kernel<DH>, grid, dim3(kNT), 0, st, qkv, dout, lse, delta, dqkv, S, H);
+  hipLaunchKernelGGL(attn_f32_dkdv_kernel<DH>, grid, dim3(kNT), 0, st, qkv, dout, lse, delta, dqkv, S, H);
+  return launch_status();
+}
+
+}  // namespace
+
+// d_head 64 or 128
+swarm_status attention_fwd_f32(const float* qkv, float* o, float* lse, int B, int S, int H, int dh, hipStream_t st) {
+  const dim3 grid((S + 31) / 32, H, B);
+  if (dh == 64) hipLaunchKernelGGL(attn_f32_fwd_kernel<64>, grid, dim3(kNT), 0, st, qkv, o, lse, S, H);
+  else if (dh == 128) hipLaunchKernelGGL(attn_f32_fwd_kernel<128>, grid, dim3(kNT), 0, st, qkv, o, lse, S, H);
+  else return SWARM_ERR_SHAPE;
+  return launch_status();
+}
+
+swarm_status attention_bwd_f32(const float* qkv, const float* o, const float* dout, const float* lse, float* delta,
+                               float* dqkv, int B, int S, int H, int dh, hipStream_t st) {
+  if (dh == 64) return bwd<64>(qkv, o, dout, lse, delta, dqkv, B, S, H, st);
+  if (dh == 128) return bwd<128>(qkv, o, dout, lse, delta, dqkv, B, S, H, st);
+  return SWARM_ERR_SHAPE;
+}
+
+}  // namespace swarm

@@ -1,5 +1,5 @@
 // Direct (one query row or one key row per workgroup) causal attention in fp32 arithmetic.
-// Used by the fp32 parity configuration and for shapes the MFMA kernels do not cover.
+// For head sizes the matrix-core kernels do not cover (anything but 64 and 128).
 // Deterministic: every sum runs in a fixed order.
 #include "kernels.h"
 

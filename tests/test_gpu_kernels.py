@@ -318,6 +318,37 @@ def _attention_case(shape, std):
         assert e < 1.5e-2, (name, e)
 
 
+# fp32 attention: tiles of 32 over four wavefronts - one row, a tile short of or past a full one, fewer blocks than
+# wavefronts, many blocks, peaked scores, and a head size only the direct kernels take.
+@pytest.mark.parametrize("shape,std", [((2, 128, 3, 64), 1.5), ((1, 1, 2, 64), 1.5), ((3, 31, 2, 128), 1.5),
+                                       ((2, 33, 1, 64), 1.5), ((1, 161, 2, 128), 1.5), ((1, 1000, 2, 64), 1.5),
+                                       ((2, 300, 2, 128), 6.0), ((1, 1100, 1, 64), 6.0), ((2, 70, 3, 32), 1.5)])
+def test_attention_f32(shape, std):
+    B, S, H, dh = shape
+    lib, d = _attn_lib(), H * dh
+    qkv = torch.from_numpy(synth.normal(S + dh, "qkv", (B, S, 3 * d), std=std)).float()
+    dout = torch.from_numpy(synth.normal(S + dh, "dout", (B, S, d))).float()
+    ro, rlse, rdqkv = _attn_ref(qkv.double().numpy(), dout.double().numpy(), B, S, H, dh)
+    qd, dod = qkv.cuda(), dout.cuda()
+    o, lse, dqkv = torch.full_like(dod, 9.0), torch.full((B, H, S), 9.0, device="cuda"), torch.full_like(qd, 9.0)
+    delta = torch.empty_like(lse)
+    assert lib.swarm_kernel_attention_fwd(0, qd.data_ptr(), o.data_ptr(), lse.data_ptr(), B, S, H, dh, None) == 0
+    assert lib.swarm_kernel_attention_bwd(0, qd.data_ptr(), o.data_ptr(), dod.data_ptr(), lse.data_ptr(), delta.data_ptr(),
+                                          dqkv.data_ptr(), B, S, H, dh, None) == 0
+    torch.cuda.synchronize()
+    # a score is a sum of dh products of size std^2: off by up to about 2^-24 sqrt(dh) std^2 sqrt(dh) / sqrt(dh), and a
+    # probability is off by the same relatively
+    tol = 2.0 ** -24 * (16 + 4 * math.sqrt(dh) * std * std)
+    assert np.max(np.abs(o.double().cpu().numpy() - ro)) <= tol * np.max(np.abs(ro))
+    assert np.max(np.abs(lse.double().cpu().numpy() - rlse)) <= tol * max(1, np.max(np.abs(rlse)))
+    got = dqkv.double().cpu().numpy()
+    # dp - delta: two sums of dh products of size std that may cancel (S = 1: exactly), times a row of size std
+    floor = 2.0 ** -24 * 4 * math.sqrt(dh) * std * std
+    for i in range(3):
+        part = slice(i * d, (i + 1) * d)
+        assert np.max(np.abs(got[..., part] - rdqkv[..., part])) <= 4 * tol * np.max(np.abs(rdqkv[..., part])) + floor
+
+
 # fp32 GEMM on the matrix cores: every workgroup shape of its dispatch (32 x 32 blocks with K over 8 or 4 wavefronts,
 # 64 x 64, 128 x 128), ragged rows and columns, a K that leaves a partial slice and (transposed operands) a partial
 # 8-deep step, fewer 8-deep steps than wavefronts, every epilogue.
