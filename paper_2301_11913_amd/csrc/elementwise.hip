@@ -464,35 +464,49 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict
   }
 }
 
-// Stage 2: out[c] += sum_p partial[p*stride + c], p ascending.  Workgroup = 64 columns x 4 row groups.
+// Stage 2: out[c] += sum_p partial[p*stride + c].  Workgroup = 64 columns x RG row groups, each with eight running sums
+// (fixed assignment p mod 8, fixed combine order) that keep as many loads in flight.  Latency bound: with four row groups
+// the 512 partial rows of a LayerNorm backward are sixteen dependent rounds of loads, with sixteen groups four.
 // blockIdx.y = 1 (LayerNorm backward: dbeta next to dgamma in one launch) takes partial + C and out2.
-__global__ __launch_bounds__(256) void reduce_rows_accum_kernel(const float* __restrict__ partial, int P, int C,
-                                                                size_t stride, float* __restrict__ out,
-                                                                float* __restrict__ out2) {
-  __shared__ float red[4][64];
+template <int RG>
+__global__ __launch_bounds__(64 * RG) void reduce_rows_accum_kernel(const float* __restrict__ partial, int P, int C,
+                                                                    size_t stride, float* __restrict__ out,
+                                                                    float* __restrict__ out2) {
+  __shared__ float red[RG][64];
   if (blockIdx.y == 1) { partial += C; out = out2; }
   const int c = blockIdx.x * 64 + (threadIdx.x & 63);
   const int rg = threadIdx.x >> 6;
-  const int per = (P + 3) / 4;
+  const int per = (P + RG - 1) / RG;
   const int p0 = rg * per, p1 = min(P, p0 + per);
   float s = 0.f;
   if (c < C) {
-    // eight independent running sums (fixed assignment p mod 8, fixed combine order) keep loads in flight
     float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     int p = p0;
     for (; p + 8 <= p1; p += 8) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) a[u] += partial[(size_t)(p + u) * stride + c];
     }
-    for (int u = 0; p < p1; ++p, ++u) a[u] += partial[(size_t)p * stride + c];
+#pragma unroll
+    for (int u = 0; u < 7; ++u)
+      if (p + u < p1) a[u] += partial[(size_t)(p + u) * stride + c];
     s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
   }
   red[rg][threadIdx.x & 63] = s;
   __syncthreads();
   if (rg == 0 && c < C) {
     const int l = threadIdx.x & 63;
-    out[c] += ((red[0][l] + red[1][l]) + red[2][l]) + red[3][l];
+    float sum = red[0][l];
+#pragma unroll
+    for (int g = 1; g < RG; ++g) sum += red[g][l];
+    out[c] += sum;
   }
+}
+
+// out2 != nullptr: two neighbouring sums of C columns each
+void reduce_rows(const float* partial, int P, int C, size_t stride, float* out, float* out2, hipStream_t st) {
+  const dim3 grid((C + 63) / 64, out2 ? 2 : 1);
+  if (P > 32) hipLaunchKernelGGL(reduce_rows_accum_kernel<16>, grid, dim3(1024), 0, st, partial, P, C, stride, out, out2);
+  else hipLaunchKernelGGL(reduce_rows_accum_kernel<4>, grid, dim3(256), 0, st, partial, P, C, stride, out, out2);
 }
 
 template <typename T, bool DEC, int MAXK = 0>
@@ -573,9 +587,7 @@ swarm_status layernorm_bwd(const void* dy, const void* x, const float* mean, con
   }
   if (s != SWARM_OK) return s;
   const int P = (T + ln_rows_per_block(T) - 1) / ln_rows_per_block(T);
-  const int grid = (d + 63) / 64;
-  hipLaunchKernelGGL(reduce_rows_accum_kernel, dim3(grid, 2), dim3(256), 0, st, partial, P, d, (size_t)2 * d, dgamma,
-                     dbeta);
+  reduce_rows(partial, P, d, (size_t)2 * d, dgamma, dbeta, st);
   return launch_status();
 }
 
@@ -622,8 +634,7 @@ swarm_status layernorm_bwd_maxout(const void* dz, const void* x, const float* me
 #undef LN_MOB
   if (s != SWARM_OK) return s;
   const int P = (T + ln_rows_per_block(T) - 1) / ln_rows_per_block(T);
-  hipLaunchKernelGGL(reduce_rows_accum_kernel, dim3((d + 63) / 64, 2), dim3(256), 0, st, partial, P, d, (size_t)2 * d,
-                     dgamma, dbeta);
+  reduce_rows(partial, P, d, (size_t)2 * d, dgamma, dbeta, st);
   return launch_status();
 }
 
@@ -636,8 +647,7 @@ swarm_status colsum_accum(const void* X, int T, int N, float* out, float* partia
     hipLaunchKernelGGL(colsum_partial_kernel<bf16_raw>, grid, dim3(256), 0, st, (const bf16_raw*)X, T, N, partial);
   else
     hipLaunchKernelGGL(colsum_partial_kernel<float>, grid, dim3(256), 0, st, (const float*)X, T, N, partial);
-  hipLaunchKernelGGL(reduce_rows_accum_kernel, dim3((N + 63) / 64), dim3(256), 0, st, partial, P, N, (size_t)N,
-                     out, (float*)nullptr);
+  reduce_rows(partial, P, N, (size_t)N, out, nullptr, st);
   return launch_status();
 }
 

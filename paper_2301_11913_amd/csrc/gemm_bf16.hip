@@ -220,6 +220,8 @@ struct GemmTimer {
 
 swarm_status gemm_bf16_launch(const GemmArgs& g, hipStream_t st);
 swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st);
+bool gemm_bf16_sums_rows(const GemmArgs& g);
+bool gemm_f32_takes(const GemmArgs& g);
 
 swarm_status gemm_bf16(const GemmArgs& g, hipStream_t st) {
 #ifdef SWARM_KERNEL_HOOKS
@@ -237,15 +239,25 @@ swarm_status gemm_bf16(const GemmArgs& g, hipStream_t st) {
   return gemm_bf16_launch(g, st);
 }
 
-swarm_status gemm_bf16_launch(const GemmArgs& g, hipStream_t st) {
+static bool rows_of_eight(const GemmArgs& g) {
   // vector loads need 8-element alignment of every contiguous run
   auto al16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
-  bool vec_ok = (g.lda % 8 == 0) && (g.ldb % 8 == 0) && al16(g.A) && al16(g.B) &&
+  bool ok = (g.lda % 8 == 0) && (g.ldb % 8 == 0) && al16(g.A) && al16(g.B) &&
                 (g.a_trans ? g.M % 8 == 0 : g.K % 8 == 0) && (g.b_trans ? g.N % 8 == 0 : g.K % 8 == 0);
-  if (g.epilogue == EPI_ACCUM_F32) vec_ok = vec_ok && g.N % 4 == 0 && g.ldc % 4 == 0 && al16(g.C);
+  if (g.epilogue == EPI_ACCUM_F32) ok = ok && g.N % 4 == 0 && g.ldc % 4 == 0 && al16(g.C);
   if (g.epilogue != EPI_ACCUM_F32)   // the bf16 epilogue moves 8-element chunks
-    vec_ok = vec_ok && g.N % 8 == 0 && g.ldc % 8 == 0 && al16(g.C) && (!g.bias || al16(g.bias)) &&
+    ok = ok && g.N % 8 == 0 && g.ldc % 8 == 0 && al16(g.C) && (!g.bias || al16(g.bias)) &&
              (!g.aux || (al16(g.aux) && g.ldaux % 8 == 0)) && (!g.C2 || (al16(g.C2) && g.ldc2 % 8 == 0));
+  return ok;
+}
+
+bool gemm_sums_rows(const GemmArgs& g, bool bf16) {
+  if (!g.a_trans || g.epilogue != EPI_ACCUM_F32) return false;
+  return bf16 ? rows_of_eight(g) && gemm_bf16_sums_rows(g) : gemm_f32_takes(g);
+}
+
+swarm_status gemm_bf16_launch(const GemmArgs& g, hipStream_t st) {
+  const bool vec_ok = rows_of_eight(g);
   if (g.epilogue == EPI_BIAS_RESID_ENCODE && (!vec_ok || g.N % 64 || g.ldc != g.N || !g.scales)) return SWARM_ERR_SHAPE;
   // epilogues that only the MFMA kernels have: refuse (before any launch) what they cannot take
   const bool mfma_only = g.epilogue == EPI_BIAS_ROPE || g.epilogue == EPI_DGEGLU || g.epilogue == EPI_BIAS_GEGLU;

@@ -26,6 +26,7 @@ struct KArgs {
   int stream;    // != 0: the epilogue's global accesses are non-temporal (see store_stream)
   int ksplit;    // > 1: the grid holds ksplit workgroups per tile, each takes K / ksplit and stores its fp32 partial
   float* part;   //      tile sums to part + index * M * N (a second kernel adds them and applies the epilogue)
+  float* rowsum;   // see GemmArgs
   long long* stamps;   // instrumented build only (nullptr otherwise): 16 words per workgroup, see gemm_bf16_k32_kernel
 };
 
@@ -37,7 +38,7 @@ inline KArgs kargs_of(const GemmArgs& g) {
   k.ldb = g.ldb; k.C = g.C; k.ldc = g.ldc; k.epilogue = g.epilogue; k.bias = (const bf16_raw*)g.bias;
   k.aux = (const bf16_raw*)g.aux; k.ldaux = g.ldaux; k.C2 = (bf16_raw*)g.C2; k.ldc2 = g.ldc2; k.scales = g.scales;
   k.scales16 = g.scales16; k.rope = g.rope; k.rope_S = g.rope_S; k.rope_dh = g.rope_dh; k.rope_cols = g.rope_cols;
-  k.split = g.split; k.ksplit = 1; k.stamps = g.stamps;
+  k.split = g.split; k.ksplit = 1; k.rowsum = g.rowsum; k.stamps = g.stamps;
   return k;
 }
 

@@ -845,10 +845,20 @@ int splitk_parts_max(int M, int N) {
 }  // namespace
 
 swarm_status gemm_bf16_kw(const GemmArgs& g, hipStream_t st);
+bool gemm_bf16_kw_takes(const GemmArgs& g);
 
 size_t gemm_splitk_floats(int M, int N) {
   const int parts = splitk_parts_max(M, N);
   return parts > 1 ? (size_t)parts * M * N : 0;
+}
+
+static bool enough_256_tiles(const GemmArgs& g) {
+  return g.M % 256 == 0 && g.N % 256 == 0 && g.K % DBK == 0 && (long)(g.M / 256) * (g.N / 256) >= 160;
+}
+
+// A weight-gradient product that stays on the small tiles.
+bool gemm_bf16_sums_rows(const GemmArgs& g) {
+  return g.a_trans && g.b_trans && !enough_256_tiles(g) && gemm_bf16_kw_takes(g);
 }
 
 // Returns SWARM_ERR_SHAPE (nothing launched) for what only the register-staged kernel takes.  The caller has checked
@@ -911,7 +921,7 @@ swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
       return gemm_bf16_dma(r, st);
     }
   }
-  if (g.M % 256 == 0 && g.N % 256 == 0 && (long)(g.M / 256) * (g.N / 256) >= 160) {
+  if (enough_256_tiles(g)) {
     k.tiles_m = g.M / 256; k.tiles_n = g.N / 256;
     return launch_dma_layout<256, 256, 2, 4>(k, g.a_trans, g.b_trans, st);
   }

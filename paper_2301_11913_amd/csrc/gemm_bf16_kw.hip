@@ -155,6 +155,20 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(KArgs p) 
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
+  // Row sums of A (the bias gradient beside a weight gradient): one more MFMA against a column of ones per fragment row,
+  // each of the four in another column of tiles (tile_n modulo four), by the first column of wavefronts.
+  f32x4 rsum[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) rsum[i][r] = 0.f;
+  int sum_rows = 0;   // bit i: fragment row i is summed here
+  if constexpr (A_T) {
+    if (p.rowsum)
+      for (int i = 0; i < 4; ++i) sum_rows |= (i % p.tiles_n == tile_n) << i;
+  }
+  const u32x4_kw ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+
   struct Frags { u32x4_kw a[4], b[4]; };
   auto read = [&](int stage, Frags& f) __attribute__((always_inline)) {
     const uint32_t tile = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)lds + (uint32_t)stage * STAGE;
@@ -192,6 +206,15 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(KArgs p) 
         for (int j = 0; j < 4; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur.a[i]),
                                                               __builtin_bit_cast(bf16x8, cur.b[j]), acc[i][j], 0, 0, 0);
+      if constexpr (A_T) {
+        if (sum_rows && wn == 0) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (sum_rows & (1 << i))
+              rsum[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur.a[i]),
+                                                                __builtin_bit_cast(bf16x8, ones), rsum[i], 0, 0, 0);
+        }
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -218,8 +241,23 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(KArgs p) 
       for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) mine[(16 * i + 4 * q + r) * PITCH + 16 * j + l16] = acc[i][j][r];
+    if (A_T && sum_rows && wn == 0 && l16 == 0) {     // into the column behind the tile's
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mine[(16 * i + 4 * q + r) * PITCH + BN] = rsum[i][r];
+    }
   }
   __syncthreads();
+  if (A_T && sum_rows) {
+    const int rl = threadIdx.x;
+    if (rl < BM && m0 + rl < p.M && (sum_rows >> (rl % 64 / 16) & 1)) {
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < WK; ++w) s += sums[(w * BM + rl) * PITCH + BN];
+      p.rowsum[m0 + rl] += s;
+    }
+  }
   auto sum8 = [&](int rl, int cl, float (&x)[8]) __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] = 0.f;
@@ -301,14 +339,19 @@ swarm_status launch_layout(KArgs k, bool a_t, bool b_t, hipStream_t st) {
 
 }  // namespace
 
+// Whether gemm_bf16_kw takes the product.
+bool gemm_bf16_kw_takes(const GemmArgs& g) {
+  if ((g.a_trans && !g.b_trans) || g.N % 8) return false;
+  if (!(g.a_trans && g.b_trans) && g.K % 32) return false;
+  if (g.epilogue == EPI_BIAS_GEGLU && (g.a_trans || g.b_trans || g.N != 2 * g.split || g.split % 32)) return false;
+  const long long span = 128 + (g.epilogue == EPI_BIAS_GEGLU ? g.split : 0);   // rows a tile's offsets reach over
+  return span * g.lda < (1ll << 30) && span * g.ldb < (1ll << 30);
+}
+
 // SWARM_ERR_SHAPE (nothing launched): a k-contiguous operand whose K is no multiple of 32, or a tile whose offsets do
 // not fit 32 bits.  The caller has checked alignment (16-byte rows, N % 8 == 0) and the layout.
 swarm_status gemm_bf16_kw(const GemmArgs& g, hipStream_t st) {
-  if ((g.a_trans && !g.b_trans) || g.N % 8) return SWARM_ERR_SHAPE;
-  if (!(g.a_trans && g.b_trans) && g.K % 32) return SWARM_ERR_SHAPE;
-  if (g.epilogue == EPI_BIAS_GEGLU && (g.a_trans || g.b_trans || g.N != 2 * g.split || g.split % 32)) return SWARM_ERR_SHAPE;
-  const long long span = 128 + (g.epilogue == EPI_BIAS_GEGLU ? g.split : 0);   // rows a tile's offsets reach over
-  if (span * g.lda >= (1ll << 30) || span * g.ldb >= (1ll << 30)) return SWARM_ERR_SHAPE;
+  if (!gemm_bf16_kw_takes(g)) return SWARM_ERR_SHAPE;
   const KArgs k = kargs_of(g);
   // 128 x 128 tiles from three quarters of a round on; below that 64 x 64 ones, with four stages while a compute unit
   // holds one workgroup and with two, which lets it hold two, behind that.

@@ -87,9 +87,16 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
 #pragma unroll
   for (int j = 0; j < FN; ++j) b[j].init((const float*)g.B, g.ldb, min(n0 + (wn * FN + j) * 32 + l32, g.N - 1));
 
+  float rsum[FM];      // sum of this lane's values of A (a row's bias gradient beside its weight gradient)
+#pragma unroll
+  for (int i = 0; i < FM; ++i) rsum[i] = 0.f;
   const int part = ((g.K + 7) / 8 + WK - 1) / WK * 8;
   const int kbeg = wk * part, kend = min(g.K, kbeg + part);
   auto multiply = [&](const float4 (&fa)[FM], const float4 (&fb)[FN]) __attribute__((always_inline)) {
+    if constexpr (A_T) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i) rsum[i] += (fa[i].x + fa[i].y) + (fa[i].z + fa[i].w);
+    }
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -143,7 +150,21 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
     for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mine[(32 * i + 8 * (r >> 2) + 4 * lg + (r & 3)) * PITCH + 32 * j + l32] = acc[i][j][r];
+  const bool sum_rows = A_T && g.rowsum && n0 == 0;
+  if (sum_rows && wn == 0) {                               // into the column behind the tile's
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const float s = rsum[i] + __shfl_xor(rsum[i], 32, 64);
+      if (lg == 0) mine[(32 * i + l32) * PITCH + TN] = s;
+    }
+  }
   __syncthreads();
+  if (sum_rows && threadIdx.x < TM && m0 + (int)threadIdx.x < g.M) {
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < WK; ++w) s += lds[(w * TM + threadIdx.x) * PITCH + TN];
+    g.rowsum[m0 + threadIdx.x] += s;
+  }
   for (int e = threadIdx.x; e < TM * TN / 4; e += NT) {
     const int rl = e / (TN / 4), cl = e % (TN / 4) * 4;
     const int row = m0 + rl, col = n0 + cl;
@@ -211,15 +232,18 @@ swarm_status launch_layout(const GemmArgs& g, hipStream_t st) {
 
 }  // namespace
 
-swarm_status gemm_f32(const GemmArgs& g, hipStream_t st) {
+bool gemm_f32_takes(const GemmArgs& g) {
   auto al16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
   auto row_ok = [&](const void* q, int ld) { return !q || (al16(q) && ld % 4 == 0); };
   // rows of four in the epilogue, 16-byte fragment loads where k is contiguous
-  const bool ok = g.epilogue <= EPI_ACCUM_F32 && !(g.a_trans && !g.b_trans) && g.N % 4 == 0 && al16(g.bias) &&
-                  row_ok(g.C, g.ldc) && row_ok(g.aux, g.ldaux) && row_ok(g.C2, g.ldc2) &&
-                  (g.a_trans || (g.K % 8 == 0 && row_ok(g.A, g.lda))) &&
-                  (g.b_trans || (g.K % 8 == 0 && row_ok(g.B, g.ldb)));
-  if (!ok) return gemm_generic(g, false, st);
+  return g.epilogue <= EPI_ACCUM_F32 && !(g.a_trans && !g.b_trans) && g.N % 4 == 0 && al16(g.bias) &&
+         row_ok(g.C, g.ldc) && row_ok(g.aux, g.ldaux) && row_ok(g.C2, g.ldc2) &&
+         (g.a_trans || (g.K % 8 == 0 && row_ok(g.A, g.lda))) &&
+         (g.b_trans || (g.K % 8 == 0 && row_ok(g.B, g.ldb)));
+}
+
+swarm_status gemm_f32(const GemmArgs& g, hipStream_t st) {
+  if (!gemm_f32_takes(g)) return gemm_generic(g, false, st);
   auto tiles = [&](int t) { return (long)((g.M + t - 1) / t) * ((g.N + t - 1) / t); };
   // Large enough for a round of 128 x 128 tiles: 64 x 64 per wavefront, half the fragment loads per flop.  Otherwise
   // 64 x 64 tiles while they fill the chip, and below that one 32 x 32 block per workgroup, its K dealt to so many

@@ -15,6 +15,17 @@ extern "C" int swarm_kernel_gemm(int dtype, int M, int N, int K, const void* A, 
   return dtype ? gemm_bf16(g, (hipStream_t)stream) : gemm_f32(g, (hipStream_t)stream);
 }
 
+// dW [M, N] += A^T B and db [M] += column sums of A (A [K, M], B [K, N]) in one kernel; SWARM_ERR_SHAPE where the product's
+// kernel does not take the sums along.
+extern "C" int swarm_kernel_gemm_rowsum(int dtype, int M, int N, int K, const void* A, const void* B, float* dW, float* db,
+                                        void* stream) {
+  GemmArgs g{};
+  g.M = M; g.N = N; g.K = K; g.A = A; g.lda = M; g.a_trans = true; g.B = B; g.ldb = N; g.b_trans = true; g.C = dW; g.ldc = N;
+  g.epilogue = EPI_ACCUM_F32; g.rowsum = db;
+  if (!gemm_sums_rows(g, dtype != 0)) return SWARM_ERR_SHAPE;
+  return dtype ? gemm_bf16(g, (hipStream_t)stream) : gemm_f32(g, (hipStream_t)stream);
+}
+
 // The same with split-K scratch (floats) that the bf16 kernel may use; swarm_kernel_gemm_splitk_floats says how much.
 extern "C" size_t swarm_kernel_gemm_splitk_floats(int M, int N) { return gemm_splitk_floats(M, N); }
 extern "C" int swarm_kernel_gemm_ws(int M, int N, int K, const void* A, int lda, int a_trans, const void* B, int ldb,

@@ -45,11 +45,16 @@ struct GemmArgs {
   int split;               // EPI_DGEGLU / EPI_BIAS_GEGLU: f, the width of the gate (and of the up) half
   float* splitk_ws;        // optional scratch of splitk_floats floats (>= gemm_splitk_floats(M, N)): lets a product with
   size_t splitk_floats;    // few output tiles and a long K be cut along K (bf16 MFMA kernel only); nullptr: never cut
+  float* rowsum;           // EPI_ACCUM_F32 with both operands transposed: rowsum[m] += sum_k A(m,k) (the bias gradient next
+                           // to the weight gradient), where gemm_sums_rows says so; ignored elsewhere
   long long* stamps;       // instrumented build only: 16 int64 per workgroup of the 256 x 256 kernel (phase stamps)
 };
 
 // Floats of split-K scratch that a bf16 product with an [M, N] output can make use of (0: it is never cut).
 size_t gemm_splitk_floats(int M, int N);
+
+// Whether the kernel that this product goes to adds up the rows of A on the way (see GemmArgs::rowsum).
+bool gemm_sums_rows(const GemmArgs& g, bool bf16);
 
 swarm_status gemm_f32(const GemmArgs& g, hipStream_t st);
 swarm_status gemm_bf16(const GemmArgs& g, hipStream_t st);

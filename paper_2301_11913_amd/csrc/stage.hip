@@ -197,10 +197,11 @@ struct AppGrads {
 // dW[out,in] += dY^T X  and  db[out] += colsum(dY)  over `rows` token rows
 swarm_status weight_grads(const Dims& D, int rows, const void* dY, int n_out, const void* X, int n_in, float* dW,
                           float* db, float* partial, hipStream_t st) {
-  SWARM_TRY(colsum_accum(dY, rows, n_out, db, partial, D.bf16, st));
   GemmArgs w{};
   w.M = n_out; w.N = n_in; w.K = rows; w.A = dY; w.lda = n_out; w.a_trans = true; w.B = X; w.ldb = n_in;
   w.b_trans = true; w.C = dW; w.ldc = n_in; w.epilogue = EPI_ACCUM_F32;
+  if (gemm_sums_rows(w, D.bf16)) w.rowsum = db;
+  else SWARM_TRY(colsum_accum(dY, rows, n_out, db, partial, D.bf16, st));
   return gemm(D, w, st);
 }
 

@@ -431,3 +431,24 @@ def test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi):
         ref = ref + 3.0
     # half a bf16 ulp of the largest result (2^-9 = 2e-3) with room for the epilogue's input roundings; fp32: the sums
     assert np.max(np.abs(Cd[:M].double().cpu().numpy() - ref)) <= (1e-5 if epi == 5 else 6e-3) * np.max(np.abs(ref))
+
+
+# Row sums of the left operand beside a weight gradient (the bias gradient), where the product's kernel takes them along:
+# one tile, fewer and more columns of tiles than fragment rows, ragged rows and token counts, both dtypes.
+@pytest.mark.parametrize("bf16,M,N,K", [(1, 64, 64, 33), (1, 200, 128, 333), (1, 768, 192, 1665), (1, 768, 3072, 130),
+                                        (1, 1536, 2304, 257), (1, 2048, 1024, 4096), (0, 64, 64, 33), (0, 256, 1024, 511),
+                                        (0, 1000, 260, 77), (0, 1024, 1024, 203), (0, 2048, 2304, 130)])
+def test_weight_gradient_row_sums(bf16, M, N, K):
+    lib = _lib()
+    lib.swarm_kernel_gemm_rowsum.argtypes = [C.c_int] * 4 + [C.c_void_p] * 5
+    g = torch.Generator().manual_seed(M + N + K)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    A, B = (torch.randn((K, n), generator=g).to(dt) for n in (M, N))
+    db0, dW0 = torch.randn(M, generator=g), torch.randn((M, N), generator=g)
+    Ad, Bd, db, dW = A.cuda(), B.cuda(), db0.cuda(), dW0.cuda()
+    assert lib.swarm_kernel_gemm_rowsum(bf16, M, N, K, Ad.data_ptr(), Bd.data_ptr(), dW.data_ptr(), db.data_ptr(), None) == 0
+    torch.cuda.synchronize()
+    A, B = A.double(), B.double()
+    # K additions (and products), each off by half an ulp of at most the sum of magnitudes
+    assert ((db.cpu() - (db0 + A.sum(0))).abs() <= (K + 1) * 2.0 ** -24 * (A.abs().sum(0) + db0.abs())).all()
+    assert ((dW.cpu() - (dW0 + A.T @ B)).abs() <= (2 * K + 1) * 2.0 ** -24 * (A.abs().T @ B.abs() + dW0.abs())).all()
