@@ -207,28 +207,36 @@ __device__ __forceinline__ void tile_head_batch(int nt, int H, int& tile, int& h
 }
 
 // ---- forward ------------------------------------------------------------------------------------
-// grid (ceil(S/128), H, B); wavefront w owns query rows q0+32w .. q0+32w+31; KV tiles of 64.
-template <int DH>
-__global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const bf16_raw* __restrict__ qkv,
-                                                               bf16_raw* __restrict__ o, float* __restrict__ lse,
-                                                               int S, int H) {
+// 128 query rows per tile; wavefront w of each of the KG groups of four owns rows q0+32w .. q0+32w+31; KV tiles of 64, of
+// which group g takes every KG-th.  With KG = 2 the two partial softmax sums of a row meet in LDS at the end.
+//
+// A wavefront alone on its SIMD needs 1.1..1.5 us per KV tile, a chain of score product, softmax and value product; tiles
+// requested two or three ahead instead of one change nothing.  So where the launch leaves units idle the chain is cut
+// (layout_of): d_head 64, one sequence of 512 with 16 heads 16.4 -> 10.6 us, 5 sequences of 333 with 12 heads
+// 14.3 -> 9.2 us, the whole training pass of the latter with dQ (15.3 -> 9.7) and dK / dV (24.6 -> 19) 396 -> 374 us.
+template <int DH, int KG>
+__global__ __launch_bounds__(kThreads* KG, 2) void attn_fwd_kernel(const bf16_raw* __restrict__ qkv,
+                                                                   bf16_raw* __restrict__ o, float* __restrict__ lse,
+                                                                   int S, int H, int passes) {
   using T = Tile64<DH>;
   constexpr int KS = DH / 16, DB = DH / 32;
   constexpr int STAGE = 2 * T::ELEMS;
-  extern __shared__ __attribute__((aligned(1024))) bf16_raw lds[];
+  extern __shared__ __attribute__((aligned(1024))) bf16_raw lds_all[];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lg = lane >> 5;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // Causal rows get longer with the query index: a workgroup takes query tile nqt-1-pi and then tile pi, so every
-  // workgroup does the same amount of work and the launch has no tail of long rows.
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w = wave & 3, grp = KG > 1 ? wave >> 2 : 0;
+  bf16_raw* lds = lds_all + grp * 2 * STAGE;
+  // Causal rows get longer with the query index: with two passes a workgroup takes query tile nqt-1-pi and then tile
+  // pi, so every workgroup does the same amount of work and the launch has no tail of long rows.
   const int nqt = (S + 127) / 128;
   int pi, h, b;
-  tile_head_batch((nqt + 1) / 2, H, pi, h, b);
+  tile_head_batch(passes == 2 ? (nqt + 1) / 2 : nqt, H, pi, h, b);
   const int d = H * DH, ld = 3 * d;
   const bf16_raw* Q = qkv + (size_t)b * S * ld + h * DH;
   const bf16_raw* K = Q + d;
   const bf16_raw* V = Q + 2 * d;
   const float c = kLog2e / sqrtf((float)DH);
-  for (int pass = 0; pass < 2; ++pass) {
+  for (int pass = 0; pass < passes; ++pass) {
   const int qt = pass == 0 ? nqt - 1 - pi : pi;
   if (pass == 1 && qt == nqt - 1 - pi) break;     // odd tile count: the middle tile has no partner
   const int q0 = qt * 128;
@@ -240,15 +248,17 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const bf16_raw* _
 
   f32x16 oacc[DB];
   zero(oacc);
-  float m = -INFINITY, l = 0.f;
+  // a group's first tile may be masked as a whole for some of its queries: their reference has to be finite there
+  float m = KG > 1 ? -__FLT_MAX__ : -INFINITY, l = 0.f;
 
-  const int ntile = (min(S, q0 + 128) + 63) / 64;
-  auto issue = [&](int t) {
+  const int ntile = ((min(S, q0 + 128) + 63) / 64 + KG - 1) / KG;
+  auto issue = [&](int t) {          // t counts this group's tiles
     bf16_raw* st = lds + (t & 1) * STAGE;
-    T::issue(K, ld, t * 64, S, st, w, lane);
-    T::issue(V, ld, t * 64, S, st + T::ELEMS, w, lane);
+    const int row0 = (KG * t + grp) * 64;
+    T::issue(K, ld, row0, S, st, w, lane);
+    T::issue(V, ld, row0, S, st + T::ELEMS, w, lane);
   };
-  issue(0);
+  issue(0);                          // (rows past the end are taken from the last one)
   wait_vm0();
   __builtin_amdgcn_s_barrier();
 
@@ -261,7 +271,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const bf16_raw* _
   for (int t = 0; t < ntile; ++t) {
     const bf16_raw* sK = lds + (t & 1) * STAGE;
     const bf16_raw* sV = sK + T::ELEMS;
-    const int kv0 = t * 64;
+    const int kv0 = (KG * t + grp) * 64;
     if (t + 1 < ntile) issue(t + 1);
     if (kv0 <= wq_max) {
       // S^T = K Q^T: NQK MFMAs, fragment n = (ks = n / 2, key block n % 2); the read of fragment n+PF sits behind
@@ -357,6 +367,27 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const bf16_raw* _
     __builtin_amdgcn_s_barrier();
   }
 
+  if constexpr (KG > 1) {            // behind the last barrier the stages are free; one pass only
+    float* part = reinterpret_cast<float*>(lds_all) + w * (16 * DB + 2) * 64 + lane;
+    if (grp) {
+#pragma unroll
+      for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[(16 * i + r) * 64] = oacc[i][r];
+      part[16 * DB * 64] = m;
+      part[(16 * DB + 1) * 64] = l;
+    }
+    __syncthreads();
+    if (grp) return;
+    const float m1 = part[16 * DB * 64], l1 = part[(16 * DB + 1) * 64], top = fmaxf(m, m1);
+    const float f0 = __builtin_amdgcn_exp2f((m - top) * c), f1 = __builtin_amdgcn_exp2f((m1 - top) * c);
+    m = top;
+    l = l * f0 + l1 * f1;
+#pragma unroll
+    for (int i = 0; i < DB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[i][r] = oacc[i][r] * f0 + part[(16 * i + r) * 64] * f1;
+  }
   if (qrow < S) {
     store_rowT<DB>(o + ((size_t)b * S + qrow) * d + h * DH, oacc, 1.0f / l, lg);
     if (lg == 0) lse[((size_t)b * H + h) * S + qrow] = m * (c / kLog2e) + logf(l);
@@ -400,7 +431,7 @@ __global__ __launch_bounds__(kDkDvThreads) void attn_bwd_dkdv_kernel(const bf16_
                                                                      const bf16_raw* __restrict__ dout,
                                                                      const float* __restrict__ lse,
                                                                      const float* __restrict__ delta,
-                                                                     bf16_raw* __restrict__ dqkv, int S, int H) {
+                                                                     bf16_raw* __restrict__ dqkv, int S, int H, int passes) {
   using T = Tile64<DH>;
   constexpr int KS = DH / 16, DB = DH / 32;
   constexpr int STAGE = 2 * T::ELEMS + 256;     // Q, dO + (lse, delta) as 2 x 64 floats
@@ -409,11 +440,11 @@ __global__ __launch_bounds__(kDkDvThreads) void attn_bwd_dkdv_kernel(const bf16_
   const int w8 = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int w = w8 & 3;
   const bool is_dk = w8 >= 4;
-  // key block pi (the longest sweep over the query tiles), then its partner nkb-1-pi: equal work per workgroup
+  // key block pi (the longest sweep over the query tiles), with two passes then its partner nkb-1-pi: equal work
   const int nkb = (S + 127) / 128;
   int pi, h, b;
-  tile_head_batch((nkb + 1) / 2, H, pi, h, b);
-  for (int pass = 0; pass < 2; ++pass) {
+  tile_head_batch(passes == 2 ? (nkb + 1) / 2 : nkb, H, pi, h, b);
+  for (int pass = 0; pass < passes; ++pass) {
   const int kb = pass == 0 ? pi : nkb - 1 - pi;
   if (pass == 1 && kb == pi) break;
   const int d = H * DH, ld = 3 * d;
@@ -570,24 +601,26 @@ __global__ __launch_bounds__(kDkDvThreads) void attn_bwd_dkdv_kernel(const bf16_
   }   // pass
 }
 
-// dQ: grid (ceil(S/128), H, B); wavefront w owns query rows q0+32w..+31; KV tiles of 64.
-template <int DH>
-__global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(const bf16_raw* __restrict__ qkv,
+// dQ: tiles, wavefronts and groups as in the forward.
+template <int DH, int KG>
+__global__ __launch_bounds__(kThreads* KG, 2) void attn_bwd_dq_kernel(const bf16_raw* __restrict__ qkv,
                                                                   const bf16_raw* __restrict__ dout,
                                                                   const float* __restrict__ lse,
                                                                   const float* __restrict__ delta,
-                                                                  bf16_raw* __restrict__ dqkv, int S, int H) {
+                                                                  bf16_raw* __restrict__ dqkv, int S, int H, int passes) {
   using T = Tile64<DH>;
   constexpr int KS = DH / 16, DB = DH / 32;
   constexpr int STAGE = 2 * T::ELEMS;           // K, V
-  extern __shared__ __attribute__((aligned(1024))) bf16_raw lds[];
+  extern __shared__ __attribute__((aligned(1024))) bf16_raw lds_all[];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lg = lane >> 5;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w = wave & 3, grp = KG > 1 ? wave >> 2 : 0;
+  bf16_raw* lds = lds_all + grp * 2 * STAGE;
   const int nqt = (S + 127) / 128;
   int pi, h, b;
-  tile_head_batch((nqt + 1) / 2, H, pi, h, b);
+  tile_head_batch(passes == 2 ? (nqt + 1) / 2 : nqt, H, pi, h, b);
   const int d = H * DH, ld = 3 * d;
-  for (int pass = 0; pass < 2; ++pass) {          // query tile nqt-1-pi, then its partner pi (equal work per workgroup)
+  for (int pass = 0; pass < passes; ++pass) {     // query tile nqt-1-pi, with two passes then its partner pi
   const int qtile = pass == 0 ? nqt - 1 - pi : pi;
   if (pass == 1 && qtile == nqt - 1 - pi) break;
   const int q0 = qtile * 128;
@@ -613,13 +646,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(const bf16_raw
   f32x16 dqacc[DB];
   zero(dqacc);
 
-  const int ntile = (min(S, q0 + 128) + 63) / 64;
-  auto issue = [&](int t) {
+  const int ntile = ((min(S, q0 + 128) + 63) / 64 + KG - 1) / KG;
+  auto issue = [&](int t) {          // t counts this group's tiles
     bf16_raw* st = lds + (t & 1) * STAGE;
-    T::issue(K, ld, t * 64, S, st, w, lane);
-    T::issue(V, ld, t * 64, S, st + T::ELEMS, w, lane);
+    const int row0 = (KG * t + grp) * 64;
+    T::issue(K, ld, row0, S, st, w, lane);
+    T::issue(V, ld, row0, S, st + T::ELEMS, w, lane);
   };
-  issue(0);
+  issue(0);                          // (rows past the end are taken from the last one)
   wait_vm0();
   __builtin_amdgcn_s_barrier();
 
@@ -627,7 +661,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(const bf16_raw
   for (int t = 0; t < ntile; ++t) {
     const bf16_raw* sK = lds + (t & 1) * STAGE;
     const bf16_raw* sV = sK + T::ELEMS;
-    const int kv0 = t * 64;
+    const int kv0 = (KG * t + grp) * 64;
     if (t + 1 < ntile) issue(t + 1);
     if (kv0 <= wq_max) {
       const bool diag = kv0 + 63 > wq_min;
@@ -690,17 +724,56 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(const bf16_raw
     __builtin_amdgcn_s_barrier();
   }
 
+  if constexpr (KG > 1) {
+    float* part = reinterpret_cast<float*>(lds_all) + w * 16 * DB * 64 + lane;
+    if (grp) {
+#pragma unroll
+      for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[(16 * i + r) * 64] = dqacc[i][r];
+    }
+    __syncthreads();
+    if (grp) return;
+#pragma unroll
+    for (int i = 0; i < DB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dqacc[i][r] += part[(16 * i + r) * 64];
+  }
   if (qrow < S) store_rowT<DB>(dqkv + ((size_t)b * S + qrow) * ld + h * DH, dqacc, scale, lg);
   }   // pass
 }
 
-template <int DH>
-swarm_status launch_fwd(const bf16_raw* qkv, bf16_raw* o, float* lse, int B, int S, int H, hipStream_t st) {
-  constexpr size_t lds_bytes = (size_t)2 * 2 * 64 * DH * sizeof(bf16_raw);
+// How a launch is laid out, by the number of 128-row tiles over all heads.  Up to one tile per compute unit: single tiles,
+// the forward and dQ with two groups of wavefronts.  Beyond that tiles go in long-short pairs, which is what balances a
+// launch of many rounds and costs nothing at one (two d_model 1024 blocks, 512 tiles: 18.9 us in pairs or singly).
+struct Layout {
+  int passes;
+  unsigned grid;
+};
+Layout layout_of(int B, int S, int H) {
+  const int nt = (S + 127) / 128;
+  const int passes = (long long)nt * H * B <= 256 ? 1 : 2;
+  return {passes, (unsigned)((passes == 2 ? (nt + 1) / 2 : nt) * H * B)};
+}
+
+template <int DH, int KG>
+swarm_status launch_fwd(const bf16_raw* qkv, bf16_raw* o, float* lse, int S, int H, Layout L, hipStream_t st) {
+  constexpr size_t lds_bytes = (size_t)KG * 2 * 2 * 64 * DH * sizeof(bf16_raw);
   static LdsOptIn a0;
-  if (lds_opt_in((const void*)attn_fwd_kernel<DH>, lds_bytes, a0) != SWARM_OK) return SWARM_ERR_LAUNCH;
-  hipLaunchKernelGGL(attn_fwd_kernel<DH>, dim3((((S + 127) / 128 + 1) / 2) * H * B), dim3(kThreads), lds_bytes, st,
-                     qkv, o, lse, S, H);
+  if (lds_opt_in((const void*)attn_fwd_kernel<DH, KG>, lds_bytes, a0) != SWARM_OK) return SWARM_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_fwd_kernel<DH, KG>), dim3(L.grid), dim3(kThreads * KG), lds_bytes, st, qkv, o, lse, S, H,
+                     L.passes);
+  return launch_status();
+}
+
+template <int DH, int KG>
+swarm_status launch_dq(const bf16_raw* qkv, const bf16_raw* dout, const float* lse, const float* delta, bf16_raw* dqkv,
+                       int S, int H, Layout L, hipStream_t st) {
+  constexpr size_t lds_bytes = (size_t)KG * 2 * 2 * 64 * DH * sizeof(bf16_raw);
+  static LdsOptIn a0;
+  if (lds_opt_in((const void*)attn_bwd_dq_kernel<DH, KG>, lds_bytes, a0) != SWARM_OK) return SWARM_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, KG>), dim3(L.grid), dim3(kThreads * KG), lds_bytes, st, qkv, dout, lse, delta,
+                     dqkv, S, H, L.passes);
   return launch_status();
 }
 
@@ -708,23 +781,28 @@ template <int DH>
 swarm_status launch_bwd(const bf16_raw* qkv, const bf16_raw* o, const bf16_raw* dout, const float* lse, float* delta,
                         bf16_raw* dqkv, int B, int S, int H, hipStream_t st) {
   constexpr size_t lds_dkdv = (size_t)2 * (2 * 64 * DH + 256) * sizeof(bf16_raw);
-  constexpr size_t lds_dq = (size_t)2 * 2 * 64 * DH * sizeof(bf16_raw);
-  static LdsOptIn a1, a2;
+  static LdsOptIn a1;
   if (lds_opt_in((const void*)attn_bwd_dkdv_kernel<DH>, lds_dkdv, a1) != SWARM_OK) return SWARM_ERR_LAUNCH;
-  if (lds_opt_in((const void*)attn_bwd_dq_kernel<DH>, lds_dq, a2) != SWARM_OK) return SWARM_ERR_LAUNCH;
   hipLaunchKernelGGL(attn_delta_kernel<DH>, dim3(B * S), dim3(kThreads), 0, st, o, dout, delta, S, H);
-  dim3 grid((((S + 127) / 128 + 1) / 2) * H * B);   // workgroups take pairs of tiles
-  hipLaunchKernelGGL(attn_bwd_dkdv_kernel<DH>, grid, dim3(kDkDvThreads), lds_dkdv, st, qkv, dout, lse, delta, dqkv, S,
-                     H);
-  hipLaunchKernelGGL(attn_bwd_dq_kernel<DH>, grid, dim3(kThreads), lds_dq, st, qkv, dout, lse, delta, dqkv, S, H);
-  return launch_status();
+  const Layout L = layout_of(B, S, H);
+  hipLaunchKernelGGL(attn_bwd_dkdv_kernel<DH>, dim3(L.grid), dim3(kDkDvThreads), lds_dkdv, st, qkv, dout, lse, delta, dqkv,
+                     S, H, L.passes);
+  if (L.passes == 1) return launch_dq<DH, 2>(qkv, dout, lse, delta, dqkv, S, H, L, st);
+  return launch_dq<DH, 1>(qkv, dout, lse, delta, dqkv, S, H, L, st);
+}
+
+template <int DH>
+swarm_status launch_fwd_of(const bf16_raw* qkv, bf16_raw* o, float* lse, int B, int S, int H, hipStream_t st) {
+  const Layout L = layout_of(B, S, H);
+  if (L.passes == 1) return launch_fwd<DH, 2>(qkv, o, lse, S, H, L, st);
+  return launch_fwd<DH, 1>(qkv, o, lse, S, H, L, st);
 }
 
 }  // namespace
 
 swarm_status attention_fwd_mfma(const void* qkv, void* o, float* lse, int B, int S, int H, int dh, hipStream_t st) {
-  if (dh == 128) return launch_fwd<128>((const bf16_raw*)qkv, (bf16_raw*)o, lse, B, S, H, st);
-  if (dh == 64) return launch_fwd<64>((const bf16_raw*)qkv, (bf16_raw*)o, lse, B, S, H, st);
+  if (dh == 128) return launch_fwd_of<128>((const bf16_raw*)qkv, (bf16_raw*)o, lse, B, S, H, st);
+  if (dh == 64) return launch_fwd_of<64>((const bf16_raw*)qkv, (bf16_raw*)o, lse, B, S, H, st);
   return SWARM_ERR_SHAPE;
 }
 

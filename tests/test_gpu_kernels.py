@@ -283,6 +283,14 @@ def test_attention_bf16(shape):
     _attention_case(shape, 1.5)
 
 
+# either side of 256 tiles of 128 rows (single tiles on two groups of wavefronts, then pairs of tiles), odd tile counts, and
+# lengths where the second group has no tile or only a masked one
+@pytest.mark.parametrize("shape", [(2, 129, 64, 64), (3, 300, 29, 64), (2, 65, 128, 128), (17, 200, 8, 128),
+                                   (2, 64, 3, 64), (1, 65, 2, 128)])
+def test_attention_bf16_launch_layouts(shape):
+    _attention_case(shape, 1.5)
+
+
 @pytest.mark.parametrize("shape", [(1, 300, 2, 128), (2, 200, 2, 64), (1, 1100, 1, 128)])
 def test_attention_bf16_peaked_scores(shape):
     """Scores with a standard deviation of several tens: nearly one-hot softmax rows, the running reference of the
