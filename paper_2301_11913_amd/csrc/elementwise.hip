@@ -433,8 +433,10 @@ __global__ __launch_bounds__(kLnThreads) void ln_bwd_kernel(const T* __restrict_
   }
 }
 
-// Stage 1 of a column sum: workgroup = 64 column chunks (512 columns) x 4 row groups over kCsRows rows.
-constexpr int kCsRows = 128;
+// Stage 1 of a column sum: workgroup = 64 column chunks (512 columns) x 4 row groups over kCsRows rows.  The launches are
+// small (128 workgroups for 4096 x 2048) and bound by the latency of their loads, so a thread has kCsAhead rows on
+// their way; sums are taken in row order (4096 tokens, 2048 / 6144 / 8192 columns: 19.8 / 21.3 / 23.1 -> 7.4 / 11.2 / 17.9 us).
+constexpr int kCsRows = 128, kCsAhead = 8;
 template <typename T>
 __global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict__ X, int rows, int N,
                                                              float* __restrict__ partial) {
@@ -448,7 +450,17 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
   const bool active = cchunk * 8 < N;
   if (active) {
-    for (int r = r0 + rg; r < r1; r += 4) {
+    int r = r0 + rg;
+    for (; r + 4 * (kCsAhead - 1) < r1; r += 4 * kCsAhead) {
+      float v[kCsAhead][8];
+#pragma unroll
+      for (int u = 0; u < kCsAhead; ++u) V8<T>::load(X + (size_t)(r + 4 * u) * N + cchunk * 8, v[u]);
+#pragma unroll
+      for (int u = 0; u < kCsAhead; ++u)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] += v[u][i];
+    }
+    for (; r < r1; r += 4) {
       float v[8];
       V8<T>::load(X + (size_t)r * N + cchunk * 8, v);
 #pragma unroll
