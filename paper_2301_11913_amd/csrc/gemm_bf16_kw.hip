@@ -353,11 +353,12 @@ bool gemm_bf16_kw_takes(const GemmArgs& g) {
 swarm_status gemm_bf16_kw(const GemmArgs& g, hipStream_t st) {
   if (!gemm_bf16_kw_takes(g)) return SWARM_ERR_SHAPE;
   const KArgs k = kargs_of(g);
-  // 128 x 128 tiles from three quarters of a round on; below that 64 x 64 ones, with four stages while a compute unit
-  // holds one workgroup and with two, which lets it hold two, behind that.
-  const long big = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
-  if (big >= 192) return launch_layout<2, 2, 2, 4>(k, g.a_trans, g.b_trans, st);
+  // By rounds of workgroups.  A 64-deep slice takes 0.7 us on a 128 x 128 tile, of which a compute unit holds one, and
+  // 0.47 us on two 64 x 64 tiles with two stages.  So 64 x 64 tiles while one round (512) holds them, with four stages
+  // while a unit has one of them, and 128 x 128 tiles behind that: the last 1280 columns of a 50432-row vocabulary on
+  // 2048 tokens, K = 4096, 640 small or 160 large tiles: 74 -> 45 us.
   const long small = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+  if (small > 512) return launch_layout<2, 2, 2, 4>(k, g.a_trans, g.b_trans, st);
   if (small > 256) return launch_layout<1, 1, 4, 2>(k, g.a_trans, g.b_trans, st);
   return launch_layout<1, 1, 4, 4>(k, g.a_trans, g.b_trans, st);
 }

@@ -166,6 +166,13 @@ def test_gemm_256x128_tiles(shape, epi, b_t):
     gemm_case(M, N, K, False, b_t, epi, seed=60 + epi)
 
 
+# 64 x 64 tiles up to 512 of them (two per compute unit), 128 x 128 beyond
+@pytest.mark.parametrize("shape", [(2048, 1024, 192), (2048, 1088, 192), (1999, 1032, 96)])
+def test_gemm_round_of_small_tiles(shape):
+    M, N, K = shape
+    gemm_case(M, N, K, False, False, 2, seed=90 + N)
+
+
 @pytest.mark.parametrize("epi,b_t", [(0, False), (0, True), (1, False), (2, False), (3, False), (4, True)])
 def test_gemm_streaming_outputs(epi, b_t):
     """Outputs of 64 MB and more are written, and their residual / pre-activation rows read, with non-temporal
