@@ -126,19 +126,29 @@ __global__ __launch_bounds__(kNT) void attn_f32_fwd_kernel(const float* __restri
     stat[0][wave][l32] = m;
     stat[1][wave][l32] = l;
   }
-  meet<DH>(out, patch, wave, l32, lg, min(32, S - qt * 32), [&](int i, int c, int at) __attribute__((always_inline)) {
+  __syncthreads();
+  // each wavefront's weight in its columns' sums, once per column and not once per value (forward at 4 sequences of 128
+  // tokens, 4 heads of 64: 16.4 -> 15 us)
+  if (threadIdx.x < 32) {
+    const int i = threadIdx.x;
     float top = stat[0][0][i];                             // wavefront 0 always has a block
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) top = fmaxf(top, stat[0][w][i]);
-    float sum = 0.f, acc = 0.f;
+    float sum = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
       const float f = expf(stat[0][w][i] - top);
       sum += f * stat[1][w][i];
-      acc += f * patch[w][at];
+      stat[0][w][i] = f;
     }
-    o[((size_t)b * S + qt * 32 + i) * d + h * DH + c] = acc / sum;
-    if (c == 0) lse[((size_t)b * H + h) * S + qt * 32 + i] = top + logf(sum);
+    stat[1][0][i] = sum;
+    if (qt * 32 + i < S) lse[((size_t)b * H + h) * S + qt * 32 + i] = top + logf(sum);
+  }                                                        // (meet begins with a barrier)
+  meet<DH>(out, patch, wave, l32, lg, min(32, S - qt * 32), [&](int i, int c, int at) __attribute__((always_inline)) {
+    float acc = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) acc += stat[0][w][i] * patch[w][at];
+    o[((size_t)b * S + qt * 32 + i) * d + h * DH + c] = acc / stat[1][0][i];
   });
 }
 
