@@ -13,6 +13,7 @@
 //
 // Measured against one workgroup per row (attention_naive.hip: forward 20, dK / dV 37, dQ 25 us at 4 sequences of 128
 // tokens, 4 heads of 64, and growing with the square of the length): the training pass they are part of 302 -> 257 us.
+// With the second product's rows requested beside the first's the forward went from 15 to 8 us (pass 204 -> 189 us).
 #include "kernels.h"
 
 namespace swarm {
@@ -36,29 +37,41 @@ __device__ __forceinline__ void load_row(float4 (&f)[DH / 8], const float* row, 
 #pragma unroll
   for (int s = 0; s < DH / 8; ++s) f[s] = *reinterpret_cast<const float4*>(row + 8 * s + 4 * lg);
 }
-// streamed rows (lane's own: `row`) times the tile's rows (`f`): a 32 x 32 block of dot products over DH
+// streamed rows (lane's own: `x`) times the tile's rows (`f`): a 32 x 32 block of dot products over DH
 template <int DH>
-__device__ __forceinline__ f32x16_t dots(const float* row, const float4 (&f)[DH / 8], int lg) {
+__device__ __forceinline__ f32x16_t dots(const float4 (&x)[DH / 8], const float4 (&f)[DH / 8]) {
   f32x16_t acc = zero16();
-  float4 x[DH / 8];
-  load_row<DH>(x, row, lg);
 #pragma unroll
   for (int s = 0; s < DH / 8; ++s)
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(x[s], c), comp(f[s], c), acc, 0, 0, 0);
   return acc;
 }
-// out^T [DH][tile column] += sum over the block's 32 streamed rows of X[row][:] w[row][column].  `first` = first row of
-// the block, rows past `last` read row `last` (their weights are zero).
+// A block of 32 streamed rows as first operand of the second product: value (r, c) of a lane is X[first + row_of(r)][32 c +
+// l32].  Rows past `last` read row `last` (their weights are zero).  At d_head 64 a kernel requests these together with the
+// rows of the first product, whose multiplies and softmax then cover their latency; at 128 they do not fit beside them
+// (a pass at 2 x 512 tokens, 4 heads of 128: 652 us against 639).
 template <int DH>
-__device__ __forceinline__ void accumulate(f32x16_t (&out)[DH / 32], const float* x, size_t ld, int first, int last,
-                                           const f32x16_t& w, int l32, int lg) {
+constexpr bool kAhead = DH == 64;
+template <int DH>
+struct Streamed {
+  float v[16][DH / 32];
+  __device__ __forceinline__ void load(const float* x, size_t ld, int first, int last, int l32, int lg) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const float* row = x + (size_t)min(first + row_of(r, lg), last) * ld + l32;
+    for (int r = 0; r < 16; ++r) {
+      const float* row = x + (size_t)min(first + row_of(r, lg), last) * ld + l32;
 #pragma unroll
-    for (int c = 0; c < DH / 32; ++c) out[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(row[32 * c], w[r], out[c], 0, 0, 0);
+      for (int c = 0; c < DH / 32; ++c) v[r][c] = row[32 * c];
+    }
   }
+};
+// out^T [DH][tile column] += sum over the block's 32 streamed rows of X[row][:] w[row][column]
+template <int DH>
+__device__ __forceinline__ void accumulate(f32x16_t (&out)[DH / 32], const Streamed<DH>& x, const f32x16_t& w) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+#pragma unroll
+    for (int c = 0; c < DH / 32; ++c) out[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.v[r][c], w[r], out[c], 0, 0, 0);
 }
 // The wavefronts' out^T meet 64 of its DH rows at a time: each writes its own to patch[wave] ([64][33]), and
 // emit(i, c, row) is called for every column i < columns of the tile and feature c, row = 33 (c % 64) + i.
@@ -99,7 +112,14 @@ __global__ __launch_bounds__(kNT) void attn_f32_fwd_kernel(const float* __restri
 #pragma unroll
   for (int c = 0; c < DH / 32; ++c) out[c] = zero16();
   for (int kb = wave; kb <= qt; kb += kWaves) {
-    f32x16_t s = dots<DH>(base + (size_t)min(kb * 32 + l32, S - 1) * ld + d, q, lg);
+    float4 k[DH / 8];
+    Streamed<DH> v;
+    load_row<DH>(k, base + (size_t)min(kb * 32 + l32, S - 1) * ld + d, lg);
+    if constexpr (kAhead<DH>) {
+      v.load(base + 2 * d, ld, kb * 32, S - 1, l32, lg);
+      __builtin_amdgcn_sched_barrier(0);                   // requested here, not where they are used
+    }
+    f32x16_t s = dots<DH>(k, q);
     float top = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -120,7 +140,8 @@ __global__ __launch_bounds__(kNT) void attn_f32_fwd_kernel(const float* __restri
     for (int c = 0; c < DH / 32; ++c)
 #pragma unroll
       for (int r = 0; r < 16; ++r) out[c][r] *= old;
-    accumulate<DH>(out, base + 2 * d, ld, kb * 32, S - 1, s, l32, lg);
+    if constexpr (!kAhead<DH>) v.load(base + 2 * d, ld, kb * 32, S - 1, l32, lg);
+    accumulate<DH>(out, v, s);
   }
   if (lg == 0) {
     stat[0][wave][l32] = m;
@@ -190,12 +211,21 @@ __global__ __launch_bounds__(kNT) void attn_f32_dq_kernel(const float* __restric
   for (int c = 0; c < DH / 32; ++c) out[c] = zero16();
   for (int kb = wave; kb <= qt; kb += kWaves) {
     const float* krow = base + (size_t)min(kb * 32 + l32, S - 1) * ld + d;
-    f32x16_t s = dots<DH>(krow, q, lg);
-    const f32x16_t dp = dots<DH>(krow + d, g, lg);
+    float4 k[DH / 8], v[DH / 8];
+    Streamed<DH> kc;
+    load_row<DH>(k, krow, lg);
+    load_row<DH>(v, krow + d, lg);
+    if constexpr (kAhead<DH>) {
+      kc.load(base + d, ld, kb * 32, S - 1, l32, lg);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    f32x16_t s = dots<DH>(k, q);
+    const f32x16_t dp = dots<DH>(v, g);
 #pragma unroll
     for (int r = 0; r < 16; ++r)
       s[r] = kb * 32 + row_of(r, lg) <= query ? expf(s[r] * scale - L) * (dp[r] - D) : 0.f;
-    accumulate<DH>(out, base + d, ld, kb * 32, S - 1, s, l32, lg);
+    if constexpr (!kAhead<DH>) kc.load(base + d, ld, kb * 32, S - 1, l32, lg);
+    accumulate<DH>(out, kc, s);
   }
   meet<DH>(out, patch, wave, l32, lg, min(32, S - qt * 32), [&](int i, int c, int at) __attribute__((always_inline)) {
     float acc = 0.f;
@@ -231,16 +261,34 @@ __global__ __launch_bounds__(kNT) void attn_f32_dkdv_kernel(const float* __restr
   const int blocks = (S + 31) / 32;
   for (int qb = kt + wave; qb < blocks; qb += kWaves) {
     const int qrow = min(qb * 32 + l32, S - 1);
-    f32x16_t p = dots<DH>(base + (size_t)qrow * ld, k, lg);
-    f32x16_t ds = dots<DH>(gout + (size_t)qrow * d, v, lg);
+    float4 q[DH / 8], g[DH / 8];
+    Streamed<DH> gc, qc;
+    load_row<DH>(q, base + (size_t)qrow * ld, lg);
+    load_row<DH>(g, gout + (size_t)qrow * d, lg);
+    if constexpr (kAhead<DH>) {
+      gc.load(gout, d, qb * 32, S - 1, l32, lg);
+      qc.load(base, ld, qb * 32, S - 1, l32, lg);
+    }
+    float Lq[16], Dq[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int query = qb * 32 + row_of(r, lg), at = min(query, S - 1);
-      p[r] = query >= key && query < S ? expf(p[r] * scale - L[at]) : 0.f;
-      ds[r] = p[r] * (ds[r] - D[at]);
+      const int at = min(qb * 32 + row_of(r, lg), S - 1);
+      Lq[r] = L[at];
+      Dq[r] = D[at];
     }
-    accumulate<DH>(dv, gout, d, qb * 32, S - 1, p, l32, lg);
-    accumulate<DH>(dk, base, ld, qb * 32, S - 1, ds, l32, lg);
+    if constexpr (kAhead<DH>) __builtin_amdgcn_sched_barrier(0);
+    f32x16_t p = dots<DH>(q, k);
+    f32x16_t ds = dots<DH>(g, v);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int query = qb * 32 + row_of(r, lg);
+      p[r] = query >= key && query < S ? expf(p[r] * scale - Lq[r]) : 0.f;
+      ds[r] = p[r] * (ds[r] - Dq[r]);
+    }
+    if constexpr (!kAhead<DH>) gc.load(gout, d, qb * 32, S - 1, l32, lg);
+    accumulate<DH>(dv, gc, p);
+    if constexpr (!kAhead<DH>) qc.load(base, ld, qb * 32, S - 1, l32, lg);
+    accumulate<DH>(dk, qc, ds);
   }
   auto emit = [&](int part, float factor) __attribute__((always_inline)) {
     return [=](int i, int c, int at) __attribute__((always_inline)) {
