@@ -354,11 +354,14 @@ swarm_status gemm_bf16_kw(const GemmArgs& g, hipStream_t st) {
   if (!gemm_bf16_kw_takes(g)) return SWARM_ERR_SHAPE;
   const KArgs k = kargs_of(g);
   // By rounds of workgroups.  A 64-deep slice takes 0.7 us on a 128 x 128 tile, of which a compute unit holds one, and
-  // 0.47 us on two 64 x 64 tiles with two stages.  So 64 x 64 tiles while one round (512) holds them, with four stages
-  // while a unit has one of them, and 128 x 128 tiles behind that: the last 1280 columns of a 50432-row vocabulary on
-  // 2048 tokens, K = 4096, 640 small or 160 large tiles: 74 -> 45 us.
-  const long small = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+  // 0.47 us on two 64 x 64 tiles with two stages.  So 128 x 128 tiles where a round (512) of 64 x 64 ones does not hold the
+  // product: the last 1280 columns of a 50432-row vocabulary on 2048 tokens, K = 4096, 640 small or 160 large tiles: 74 ->
+  // 45 us.  Up to there one round of 128 x 64 tiles with eight wavefronts instead of two 64 x 64 ones per unit, unless half
+  // of those tiles' rows would be empty (a pass at d_model 768 on 5 x 333 tokens, 324 small tiles: 362 -> 356 us).  One
+  // 64 x 64 tile per unit has four stages; a fifth changes nothing (365 us).
+  const long small = (long)((g.M + 63) / 64) * ((g.N + 63) / 64), mid = (long)((g.M + 127) / 128) * ((g.N + 63) / 64);
   if (small > 512) return launch_layout<2, 2, 2, 4>(k, g.a_trans, g.b_trans, st);
+  if (small > 256 && mid <= 256) return launch_layout<2, 1, 4, 3>(k, g.a_trans, g.b_trans, st);
   if (small > 256) return launch_layout<1, 1, 4, 2>(k, g.a_trans, g.b_trans, st);
   return launch_layout<1, 1, 4, 4>(k, g.a_trans, g.b_trans, st);
 }

@@ -166,13 +166,6 @@ def test_gemm_256x128_tiles(shape, epi, b_t):
     gemm_case(M, N, K, False, b_t, epi, seed=60 + epi)
 
 
-# 64 x 64 tiles up to 512 of them (two per compute unit), 128 x 128 beyond
-@pytest.mark.parametrize("shape", [(2048, 1024, 192), (2048, 1088, 192), (1999, 1032, 96)])
-def test_gemm_round_of_small_tiles(shape):
-    M, N, K = shape
-    gemm_case(M, N, K, False, False, 2, seed=90 + N)
-
-
 @pytest.mark.parametrize("epi,b_t", [(0, False), (0, True), (1, False), (2, False), (3, False), (4, True)])
 def test_gemm_streaming_outputs(epi, b_t):
     """Outputs of 64 MB and more are written, and their residual / pre-activation rows read, with non-temporal
@@ -448,10 +441,21 @@ def test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi):
     assert np.max(np.abs(Cd[:M].double().cpu().numpy() - ref)) <= (1e-5 if epi == 5 else 6e-3) * np.max(np.abs(ref))
 
 
+# Either side of one round of 64 x 64 tiles (512), and what replaces those between 256 and 512: 128 x 64 tiles, or 64 x 64
+# where 128 rows would be half empty.  One slice and part of one, fewer than stages, an odd number, in every layout.
+@pytest.mark.parametrize("M,N,K,a_t,b_t,epi", [
+    (2048, 1024, 192, False, False, 2), (2048, 1088, 192, False, False, 2), (1999, 1032, 96, False, False, 1),
+    (1665, 768, 32, False, False, 1), (1700, 904, 288, False, False, 3), (1665, 768, 416, False, True, 0),
+    (1921, 776, 96, False, True, 4), (1544, 768, 333, True, True, 5), (1664, 712, 1, True, True, 5),
+    (64, 19264, 96, False, False, 0), (57, 20000, 160, False, True, 0)])
+def test_gemm_rounds_of_small_tiles(M, N, K, a_t, b_t, epi):
+    test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
+
+
 # Row sums of the left operand beside a weight gradient (the bias gradient), where the product's kernel takes them along:
 # one tile, fewer and more columns of tiles than fragment rows, ragged rows and token counts, both dtypes.
 @pytest.mark.parametrize("bf16,M,N,K", [(1, 64, 64, 33), (1, 200, 128, 333), (1, 768, 192, 1665), (1, 768, 3072, 130),
-                                        (1, 1536, 2304, 257), (1, 2048, 1024, 4096), (0, 64, 64, 33), (0, 256, 1024, 511),
+                                        (1, 1536, 2304, 257), (1, 1536, 768, 333), (1, 2048, 1024, 4096), (0, 64, 64, 33), (0, 256, 1024, 511),
                                         (0, 1000, 260, 77), (0, 1024, 1024, 203), (0, 2048, 2304, 130)])
 def test_weight_gradient_row_sums(bf16, M, N, K):
     lib = _lib()
