@@ -167,6 +167,14 @@ def test_gemm_256x128_tiles(shape, epi, b_t):
 
 
 @pytest.mark.parametrize("epi,b_t", [(0, False), (0, True), (1, False), (2, False), (3, False), (4, True)])
+@pytest.mark.parametrize("shape", [(7936, 768, 192), (2176, 2048, 64), (4224, 1920, 128)])
+def test_gemm_two_tiles_per_unit(shape, epi, b_t):
+    """257 .. 512 tiles of 128 x 128 in the forward and data-gradient layouts: one, two and three slices."""
+    M, N, K = shape
+    gemm_case(M, N, K, False, b_t, epi, seed=100 + epi)
+
+
+@pytest.mark.parametrize("epi,b_t", [(0, False), (0, True), (1, False), (2, False), (3, False), (4, True)])
 def test_gemm_streaming_outputs(epi, b_t):
     """Outputs of 64 MB and more are written, and their residual / pre-activation rows read, with non-temporal
     accesses (another copy of the epilogue code): 8192 x 4096 in bf16 is 64 MB."""
