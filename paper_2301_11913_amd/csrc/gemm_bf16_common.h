@@ -150,8 +150,27 @@ __device__ __forceinline__ bool epilogue_has_bias(int epi) {
          epi == EPI_BIAS_ROPE;
 }
 
+// Codes of eight values (rounded to bf16) of a 64-element block whose largest magnitude is amax, and, from the block's first
+// eight, its scale.
+__device__ __forceinline__ void encode_chunk(const KArgs& p, const float (&x)[8], float amax, int row, int col) {
+  const float sc = block_scale_rounded(amax / 127.0f, p.scales16);
+  uint32_t w[2] = {0u, 0u};
+  if (sc != 0.0f) {
+    const BlockDivisor div(sc);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float q = fminf(fmaxf(rintf(div.quotient(x[e])), -127.0f), 127.0f);
+      w[e >> 2] |= ((uint32_t)(int)q & 0xFFu) << (8 * (e & 3));
+    }
+  }
+  const size_t e0 = (size_t)row * p.ldc + col;
+  *reinterpret_cast<uint2*>(reinterpret_cast<int8_t*>(p.C) + e0) = make_uint2(w[0], w[1]);
+  if ((col & 63) == 0) block_scale_store(p.scales, e0 >> 6, sc, p.scales16);
+}
+
 // The bf16 epilogues on eight consecutive columns (col .. col + 7, all inside N) of one row: x = the sums in, bias =
-// those of the columns (zero without one).  The fused encode needs the eight lanes of a 64-column block together.
+// those of the columns (zero without one).  The fused encode needs the eight lanes of a 64-column block together (32-column
+// sub-tiles have a form of their own, in gemm_epilogue_nt).
 template <bool NT>
 __device__ __forceinline__ void finish_chunk(const KArgs& p, int epi, float (&x)[8], const float (&bias)[8], int row,
                                              int col) {
@@ -170,19 +189,7 @@ __device__ __forceinline__ void finish_chunk(const KArgs& p, int epi, float (&x)
     amax = fmaxf(amax, __shfl_xor(amax, 1, 64));
     amax = fmaxf(amax, __shfl_xor(amax, 2, 64));
     amax = fmaxf(amax, __shfl_xor(amax, 4, 64));
-    const float sc = block_scale_rounded(amax / 127.0f, p.scales16);
-    uint32_t w[2] = {0u, 0u};
-    if (sc != 0.0f) {
-      const BlockDivisor div(sc);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float q = fminf(fmaxf(rintf(div.quotient(x[e])), -127.0f), 127.0f);
-        w[e >> 2] |= ((uint32_t)(int)q & 0xFFu) << (8 * (e & 3));
-      }
-    }
-    const size_t e0 = (size_t)row * p.ldc + col;
-    *reinterpret_cast<uint2*>(reinterpret_cast<int8_t*>(p.C) + e0) = make_uint2(w[0], w[1]);
-    if ((col & 63) == 0) block_scale_store(p.scales, e0 >> 6, sc, p.scales16);
+    encode_chunk(p, x, amax, row, col);
     return;
   }
   if (epi == EPI_BIAS) {
@@ -314,6 +321,48 @@ __device__ __forceinline__ void gemm_epilogue_nt(const KArgs& p, const Acc& acc,
 #pragma unroll
         for (int e = 0; e < 8; ++e) g[e] = gelu_fast(g[e]) * u[e];
         store_stream<NT>(G + row * p.ldc + feat, pack8_bf16(g));
+      }
+    }
+    return;
+  }
+  if constexpr (FN == 1 && !GUARD) if (epi == EPI_BIAS_RESID_ENCODE) {
+    // A 64-element block is half this wavefront's and half its neighbour's in the row of wavefronts (whose patch is the next
+    // one): the two exchange the maxima of their halves through the columns that a 32-wide sub-tile leaves free in its patch,
+    // in two places by turns, so that one barrier per row group is enough.  Same values, in the same order, as in finish_chunk.
+    // (2048 x 4096, K = 4096 on 256 x 128 tiles: 66 us, the plain store 64; on the 64-column sub-tiles of other kernels 71..73.)
+    const int c4 = lane & 3, rsub4 = lane >> 2;
+    const int colq = col0 + 8 * c4;
+    const float* other = stage + ((col0 & 32) ? -32 : 32) * kEpiPitch;
+    float bias4[8];
+    unpack8(*reinterpret_cast<const uint4*>(p.bias + colq), bias4);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int at = COLS + (i & 1);
+      stage_rows32(acc, i, stage, lane);
+      float x[2][8], amax[2];
+#pragma unroll
+      for (int ps = 0; ps < 2; ++ps) {
+        const int rl = ps * 16 + rsub4;
+        const float* sp = stage + rl * kEpiPitch + 8 * c4;
+        const float4 v0 = *reinterpret_cast<const float4*>(sp), v1 = *reinterpret_cast<const float4*>(sp + 4);
+        const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        float a[8];
+        unpack8(load_stream<NT>(p.aux + (size_t)(row0 + i * 32 + rl) * p.ldaux + colq), a);
+        amax[ps] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          x[ps][e] = bf16_bits_to_float(float_to_bf16_bits(v[e] + bias4[e] + a[e]));
+          amax[ps] = fmaxf(amax[ps], fabsf(x[ps][e]));
+        }
+        amax[ps] = fmaxf(amax[ps], __shfl_xor(amax[ps], 1, 64));
+        amax[ps] = fmaxf(amax[ps], __shfl_xor(amax[ps], 2, 64));
+        if (c4 == 0) stage[rl * kEpiPitch + at] = amax[ps];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int ps = 0; ps < 2; ++ps) {
+        const int rl = ps * 16 + rsub4;
+        encode_chunk(p, x[ps], fmaxf(amax[ps], other[rl * kEpiPitch + at]), row0 + i * 32 + rl, colq);
       }
     }
     return;

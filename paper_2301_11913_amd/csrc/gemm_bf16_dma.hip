@@ -865,7 +865,9 @@ bool gemm_bf16_sums_rows(const GemmArgs& g) {
 }
 
 // Returns SWARM_ERR_SHAPE (nothing launched) for what only the register-staged kernel takes.  The caller has checked
-// alignment (16-byte rows, N % 8 == 0).
+// alignment (16-byte rows, N % 8 == 0).  EPI_BIAS_RESID_ENCODE takes the route of EPI_BIAS_RESID everywhere: a stage that
+// sends its output int8-encoded promises the bits of the stored output, encoded, and the kernels below differ in the order of
+// their sums.
 swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
   if (g.a_trans && !g.b_trans) return SWARM_ERR_SHAPE;
   if (g.epilogue == EPI_BIAS_GEGLU && (g.a_trans || g.b_trans || g.N != 2 * g.split || g.split % 64)) return SWARM_ERR_SHAPE;
@@ -901,7 +903,8 @@ swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
   // its own (smaller tiles or a cut along K fill the chip there).  Column-local epilogues only.
   if (!g.a_trans && g.M % 256 == 0 && g.N % 256 == 0 &&
       (g.epilogue == EPI_STORE || g.epilogue == EPI_BIAS || g.epilogue == EPI_BIAS_RESID ||
-       g.epilogue == EPI_BIAS_GELU || g.epilogue == EPI_DGELU || g.epilogue == EPI_BIAS_ROPE)) {
+       g.epilogue == EPI_BIAS_RESID_ENCODE || g.epilogue == EPI_BIAS_GELU || g.epilogue == EPI_DGELU ||
+       g.epilogue == EPI_BIAS_ROPE)) {
     const long tm = g.M / 256, tn = g.N / 256, tiles = tm * tn;
     const long whole = (tiles / 256) * 256;
     if (tiles > 256 && tiles - whole > 0 && tiles - whole <= 128 && whole % tm == 0) {
@@ -910,7 +913,12 @@ swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
       a.N = n1;
       r.N = g.N - n1;
       r.B = (const bf16_raw*)g.B + (g.b_trans ? (size_t)n1 : (size_t)n1 * g.ldb);
-      r.C = (bf16_raw*)g.C + n1;
+      if (g.epilogue == EPI_BIAS_RESID_ENCODE) {   // codes, and a scale per 64 of them (ldc is a multiple of 64)
+        r.C = (int8_t*)g.C + n1;
+        r.scales = (char*)g.scales + n1 / 64 * (g.scales16 ? 2 : 4);
+      } else {
+        r.C = (bf16_raw*)g.C + n1;
+      }
       if (g.bias) r.bias = (const bf16_raw*)g.bias + n1;
       if (g.aux) r.aux = (const bf16_raw*)g.aux + n1;
       if (g.C2) r.C2 = (bf16_raw*)g.C2 + n1;
@@ -930,9 +938,8 @@ swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
   }
   // Too few 256 x 256 tiles, but 256 x 128 tiles make one nearly full round (a 2048-row microbatch times a
   // 4096-wide weight: 256 tiles): one round of those beats two rounds of 128 x 128.  A wavefront's sub-tile is
-  // 32 columns wide there, so the epilogues that need 64 (fused encode, GeGLU) stay on the 128 x 128 tiles.
-  if (!g.a_trans && g.M % 256 == 0 && g.N % 128 == 0 && g.epilogue != EPI_BIAS_RESID_ENCODE &&
-      g.epilogue != EPI_BIAS_GEGLU) {
+  // 32 columns wide there, so GeGLU, whose gathered tile needs 64, goes on to the rules below.
+  if (!g.a_trans && g.M % 256 == 0 && g.N % 128 == 0 && g.epilogue != EPI_BIAS_GEGLU) {
     const long tiles = (long)(g.M / 256) * (g.N / 128);
     if (tiles >= 192 && tiles <= 256) {
       k.tiles_m = g.M / 256; k.tiles_n = g.N / 128;
@@ -942,8 +949,7 @@ swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
   // Between one and two 128 x 128 tiles per compute unit, forward and dgrad: two workgroups of four wavefronts share a
   // unit and hide each other's waits, where gemm_bf16_kw's eight run in two rounds, the second half empty (forward of
   // eight d_model 768 applications with 7936 tokens, 372 tiles: 2176 us there, 2034 here).
-  if (!g.a_trans && g.M % 128 == 0 && g.N % 128 == 0 && g.epilogue != EPI_BIAS_RESID_ENCODE &&
-      g.epilogue != EPI_BIAS_GEGLU) {
+  if (!g.a_trans && g.M % 128 == 0 && g.N % 128 == 0 && g.epilogue != EPI_BIAS_GEGLU) {
     const long tiles = (long)(g.M / 128) * (g.N / 128);
     if (tiles > 256 && tiles <= 512) {
       k.tiles_m = g.M / 128; k.tiles_n = g.N / 128;

@@ -249,6 +249,35 @@ def test_gemm_splitk_encode_equals_encode_of_stored():
     assert torch.equal(codes.reshape(-1), c2) and torch.equal(scales.view(torch.int32), s2.view(torch.int32))
 
 
+# The int8-encoding epilogue takes the route of bias + residual, whatever the number of tiles: codes and scales are those of
+# the stand-alone codec on what that epilogue stores, bit for bit.  256 x 256 tiles, whole and with the last columns as a
+# product of their own (cut along K, and not), 192 and 256 tiles of 256 x 128, 264 to 2080 of 128 x 128 with cached stores and
+# (8320 x 4096) streaming ones, few tiles, ragged rows.
+@pytest.mark.parametrize("shape", [(4096, 4096, 192), (8192, 2304, 320), (8192, 3072, 8192), (6144, 1024, 192),
+                                   (2048, 4096, 448), (4224, 1024, 320), (7936, 768, 192), (8192, 1024, 128),
+                                   (3840, 4096, 256), (1920, 8192, 192), (8064, 4160, 128), (8320, 4096, 128),
+                                   (640, 768, 256), (4001, 1024, 192), (2500, 4096, 96)])
+def test_gemm_encode_takes_the_route_of_the_store(shape):
+    import paper_2301_11913_amd as sw
+    M, N, K = shape
+    lib = _lib()
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+    A, B, bias, aux = rnd(M, K), rnd(N, K), rnd(N), rnd(M, N)
+    lib.swarm_kernel_gemm_splitk_floats.restype = C.c_size_t
+    ws = torch.empty(max(1, lib.swarm_kernel_gemm_splitk_floats(M, N), 2 * M * 1024), dtype=torch.float32, device="cuda")
+    stored = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    _splitk_call(lib, M, N, K, A, K, B, K, False, stored, 2, bias, aux, None, ws)
+    codes = torch.full((M * N,), 55, dtype=torch.int8, device="cuda")
+    scales = torch.full((M * N // 64,), -3.0, device="cuda")
+    _splitk_call(lib, M, N, K, A, K, B, K, False, codes, 6, bias, aux, scales, ws)
+    want_codes, want_scales = torch.empty_like(codes), torch.empty_like(scales)
+    sw.swarm_codec_encode(stored.reshape(-1), want_codes, want_scales)
+    torch.cuda.synchronize()
+    assert torch.equal(scales.view(torch.int32), want_scales.view(torch.int32))
+    assert torch.equal(codes, want_codes)
+
+
 # ------------------------------------------------------------------ attention
 def _attn_lib():
     lib = _lib()
