@@ -1,5 +1,6 @@
-// Dispatch of the bf16 products, and the register-staged kernel for those the direct-to-LDS kernels (gemm_bf16_dma.hip,
-// gemm_bf16_kw.hip) do not take: a k-contiguous operand whose K is a multiple of 8 but not of 32.
+// Entry of the bf16 products, and the register-staged kernel: any K that is a multiple of 8, ragged rows and columns.  It takes
+// what the direct-to-LDS kernels cannot (a k-contiguous operand whose K is no multiple of 32) and the ragged products that
+// it is faster at (register_staged_is_faster in gemm_bf16_dma.hip).
 //
 // Workgroup tile BM x BN x 64, WM x WN wavefronts, each owning a (BM/WM) x (BN/WN) sub-tile made
 // of 32x32 accumulators fed by v_mfma_f32_32x32x16_bf16.  Both operand tiles live in LDS as
@@ -274,7 +275,8 @@ swarm_status gemm_bf16_launch(const GemmArgs& g, hipStream_t st) {
   KArgs k = kargs_of(g);
   k.stamps = nullptr;
   const long big_tiles = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
-  // What arrives here has a k-contiguous operand whose K is no multiple of 32 (the direct-to-LDS kernels took the rest).
+  // What arrives here is ragged: a k-contiguous operand whose K is no multiple of 32, a weight gradient with N % 8 == 4, or
+  // what gemm_bf16_dma leaves because this kernel is faster at it.
   if (big_tiles >= 160) {
     k.tiles_m = (g.M + 255) / 256; k.tiles_n = (g.N + 255) / 256;
     return launch_layout<256, 256, 2, 4, true>(k, g.a_trans, g.b_trans, st);

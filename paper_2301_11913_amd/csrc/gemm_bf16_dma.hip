@@ -17,10 +17,11 @@
 // One workgroup owns one output tile and walks K in order: deterministic.
 //
 // Two kernels share this file, both on v_mfma_f32_16x16x32_bf16: gemm_bf16_k32_kernel (256 x 256 and 256 x 128 tiles on
-// eight wavefronts, 128 x 128 on four: the dgrad and wgrad layouts, the rotary and GeGLU epilogues) and gemm_bf16_w4_kernel (256 x 256 tiles
+// eight wavefronts: the dgrad and wgrad layouts, the rotary and GeGLU epilogues) and gemm_bf16_w4_kernel (256 x 256 tiles
 // on four wavefronts: the forward layout with the store / bias / residual / int8-encoding / GeLU epilogues).  They
-// accumulate a tile in the same order and give the same bits.  Products with fewer tiles and ragged ones go to
-// gemm_bf16_kw.hip.
+// accumulate a tile in the same order and give the same bits.  gemm_bf16_dma at the end decides which kernel a product
+// runs on: these, 128 x 128 tiles with two workgroups per unit (gemm_bf16_pair.hip), K over the wavefronts
+// (gemm_bf16_kw.hip) or, by refusing, the register-staged kernel (gemm_bf16.hip).
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -847,7 +848,8 @@ int splitk_parts_max(int M, int N) {
 
 }  // namespace
 
-swarm_status gemm_bf16_kw(const GemmArgs& g, hipStream_t st);
+swarm_status gemm_bf16_kw(const GemmArgs& g, int stream, hipStream_t st);
+swarm_status gemm_bf16_pair(const GemmArgs& g, int stream, hipStream_t st);
 bool gemm_bf16_kw_takes(const GemmArgs& g);
 
 size_t gemm_splitk_floats(int M, int N) {
@@ -859,23 +861,72 @@ static bool enough_256_tiles(const GemmArgs& g) {
   return g.M % 256 == 0 && g.N % 256 == 0 && g.K % DBK == 0 && (long)(g.M / 256) * (g.N / 256) >= 160;
 }
 
-// A weight-gradient product that stays on the small tiles.
-bool gemm_bf16_sums_rows(const GemmArgs& g) {
-  return g.a_trans && g.b_trans && !enough_256_tiles(g) && gemm_bf16_kw_takes(g);
+// Whole 128 x 128 tiles, those that get here (few 256-row ones): gemm_bf16_pair instead of gemm_bf16_kw?  Measured in turn:
+//   more than 256 of them    forward and data gradient 3..45 % faster there (1920 x 8192, K = 2048: 74.6 against 89.8 us; 3968 x
+//                            4096, K = 1024 with GeLU: 46.7 / 61.2), weight gradients 5..60 %; but where two rounds of it
+//                            replace three, long products with a transposed operand, whose epilogue or reads gemm_bf16_kw
+//                            hides better, are 3..7 % faster there (3968 x 3072, K = 2048 with GeLU' 67.3 / 63.0);
+//   129 to 256, short K      7..14 % at K = 256 (1920 x 2048: 7.1 / 8.0 us; weight gradients 20 %), 5 % at 512; not with an
+//                            epilogue that reads rows of its own (GeLU': 0.9 at 256);
+//   otherwise                gemm_bf16_kw by up to 2 x.
+// A weight gradient with row sums stays on gemm_bf16_kw, which spares the launches of a column sum (6..20 us).
+static bool two_tiles_per_unit(const GemmArgs& g) {
+  if (g.M % 128 || g.N % 128 || g.rowsum) return false;
+  const long tiles = (long)(g.M / 128) * (g.N / 128);
+  if (tiles > 256) return !(tiles > 512 && tiles <= 768 && g.b_trans && g.K >= (g.a_trans ? 2048 : 1536));
+  return tiles > 128 && g.K <= 512 && g.epilogue != EPI_DGELU && g.epilogue != EPI_DGEGLU;
 }
 
-// Returns SWARM_ERR_SHAPE (nothing launched) for what only the register-staged kernel takes.  The caller has checked
+// Ragged products that the register-staged kernel of gemm_bf16.hip takes faster than gemm_bf16_kw.  Its 256 x 256 tiles (128
+// x 128 below 160 of those) move half the operand bytes and pay prologue and epilogue less often, but waste more of a last
+// round that is not full.  So the measure is how many rounds of 256 small tiles replace one of large ones (4 at most), and
+// the line moves with K, measured in turn at 700..16000 tokens and d_model 256..8192:
+//   forward           2500 x 6144, K = 1536 (4 rounds for 1) 67 against 75 us; 7000 x 4608 (8 for 2) 112 / 151; K = 2048..4096
+//                     2..9 %, from 8192 on gemm_bf16_kw is ahead again unless the operands exceed the 256 MB memory-side
+//                     cache (10000 x 3072, K = 12288: 793 / 957); at 3 for 1 (6000 x 3072, K = 768 with GeLU) 75 / 62;
+//   data gradient     gemm_bf16_kw always, but for two rounds of it at K = 256 (5000 x 1024: 16.2 / 17.3);
+//   weight gradients  4 for 1 up to about 1400 tokens (4096 x 4096: 57 / 60 at 777, 87 / 85 at 1537), 3 for 1 up to 400 (3072 x
+//                     12288: 97 / 94 at 385); gradients of 240 MB and more with long rows up to 2560 (4096 x 16384: 347 / 397 at
+//                     1537; 8192 x 8192: 485 / 505 at 2500).  With the row sums inside gemm_bf16_kw (`sums`) the line lies where the launches of a column sum,
+//                     8 us, are made up for as well.
+static bool register_staged_is_faster(const GemmArgs& g, bool sums) {
+  if (g.M % 128 == 0 && g.N % 128 == 0 && g.K % DBK == 0) return false;
+  if (g.epilogue == EPI_BIAS_GEGLU) return false;           // needs the gathered tile
+  auto tiles = [&](int t) { return (long)((g.M + t - 1) / t) * ((g.N + t - 1) / t); };
+  const long small = tiles(128), large = tiles(256);
+  if (large < 160) {
+    if (small <= 256 || sums) return false;
+    const int one_round = g.a_trans ? 640 : g.b_trans ? 256 : 1024, more = g.a_trans ? 320 : g.b_trans ? 0 : 512;
+    return g.K <= (small <= 512 ? one_round : more);
+  }
+  const long rs = (small + 255) / 256, rl = (large + 255) / 256;
+  if (g.a_trans) {
+    if ((long long)g.M * g.N >= (60ll << 20) && g.N >= 8192) return g.K <= 2560;
+    return g.K * rl <= 1000 * rs - (sums ? 3600 : 2600) * rl;
+  }
+  if (g.b_trans) return false;
+  const bool beyond_cache = ((long long)g.M + g.N) * g.K * 2 > (256ll << 20);
+  return g.K <= 1536 ? 2 * rs >= 7 * rl : (g.K <= 4096 || beyond_cache) && rs >= 4 * rl;
+}
+
+// A weight-gradient product that stays on the small tiles.
+bool gemm_bf16_sums_rows(const GemmArgs& g) {
+  return g.a_trans && g.b_trans && !enough_256_tiles(g) && gemm_bf16_kw_takes(g) && !register_staged_is_faster(g, true);
+}
+
+// Returns SWARM_ERR_SHAPE (nothing launched) for what the register-staged kernel takes.  The caller has checked
 // alignment (16-byte rows, N % 8 == 0).  EPI_BIAS_RESID_ENCODE takes the route of EPI_BIAS_RESID everywhere: a stage that
 // sends its output int8-encoded promises the bits of the stored output, encoded, and the kernels below differ in the order of
 // their sums.
 swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
   if (g.a_trans && !g.b_trans) return SWARM_ERR_SHAPE;
   if (g.epilogue == EPI_BIAS_GEGLU && (g.a_trans || g.b_trans || g.N != 2 * g.split || g.split % 64)) return SWARM_ERR_SHAPE;
-  if (g.K % DBK) return gemm_bf16_kw(g, st);
+  if (!g.rowsum && register_staged_is_faster(g, false)) return SWARM_ERR_SHAPE;
   KArgs k = kargs_of(g);
   // An output of at least twice the 32 MB of L2 cannot wait there for its consumer; written (and its residual /
   // pre-activation / gradient rows read) non-temporally it leaves the operand panels in the L2 instead.
   k.stream = (size_t)g.M * g.N * (g.epilogue == EPI_ACCUM_F32 ? 4 : 2) >= ((size_t)64 << 20);
+  if (g.K % DBK) return gemm_bf16_kw(g, k.stream, st);
   // Few output tiles, long K, no transposed A (forward and dgrad products of short microbatches): the 256 x 256
   // tiles at ksplit workgroups per tile fill the chip where 128 x 128 tiles would run at their lower rate.
   // Every part keeps at least 4096 of K, which is where the second kernel's pass over the partial sums pays.
@@ -946,17 +997,8 @@ swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
       return launch_dma_layout<256, 128, 2, 4>(k, g.a_trans, g.b_trans, st);
     }
   }
-  // Between one and two 128 x 128 tiles per compute unit, forward and dgrad: two workgroups of four wavefronts share a
-  // unit and hide each other's waits, where gemm_bf16_kw's eight run in two rounds, the second half empty (forward of
-  // eight d_model 768 applications with 7936 tokens, 372 tiles: 2176 us there, 2034 here).
-  if (!g.a_trans && g.M % 128 == 0 && g.N % 128 == 0 && g.epilogue != EPI_BIAS_GEGLU) {
-    const long tiles = (long)(g.M / 128) * (g.N / 128);
-    if (tiles > 256 && tiles <= 512) {
-      k.tiles_m = g.M / 128; k.tiles_n = g.N / 128;
-      return launch_dma_layout<128, 128, 1, 4>(k, g.a_trans, g.b_trans, st);
-    }
-  }
-  return gemm_bf16_kw(g, st);   // fewer tiles than the 256-row ones need, or ragged
+  if (two_tiles_per_unit(g)) return gemm_bf16_pair(g, k.stream, st);
+  return gemm_bf16_kw(g, k.stream, st);
 }
 
 }  // namespace swarm

@@ -1,7 +1,8 @@
 // bf16 MFMA GEMM for products with few output tiles and for ragged ones:  C[M,N] (+)= sum_k A(m,k) B(n,k).
 //
-// What bounds such a product is latency: a launch of 32..256 workgroups leaves every compute unit with one, and what
-// that one waits for between two slices of K (about a microsecond from memory) is longer than what it multiplies in
+// What bounds such a product is latency: a launch of 32..256 workgroups (or a ragged one of more, whose 135 KB workgroups
+// still run one to a unit) leaves every compute unit with one, and what that one waits for between two slices of K (about a
+// microsecond from memory) is longer than what it multiplies in
 // one.  So a workgroup keeps NS slices in LDS, NS - 1 of them in flight, and divides K as well as the tile: WM x WN x WK
 // wavefronts, each multiplying a 64 x 64 block over its own 32 of the 32 * WK values of k in a slice.  That keeps the
 // LDS bytes per flop of a 64 x 64 block (16 fragment reads for 32 MFMAs) on a tile as small as 64 x 64, and gives a
@@ -120,9 +121,11 @@ __device__ __forceinline__ void kw_wait_loads() {   // at most N loads of this w
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-template <int WM, int WN, int WK, int NS, bool A_T, bool B_T>
+// NT: the bf16 epilogues' global accesses are non-temporal (see KArgs::stream; a kernel of its own, since two copies of the
+// epilogue in one cost the small launches 0.2..0.5 us of instruction fetch).
+template <int WM, int WN, int WK, int NS, bool A_T, bool B_T, bool NT>
 __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(KArgs p) {
-  constexpr int NW = WM * WN * WK, NT = NW * 64;
+  constexpr int NW = WM * WN * WK, NTHR = NW * 64;
   constexpr int BM = 64 * WM, BN = 64 * WN, BK = 32 * WK;
   static_assert(BK % 64 == 0 && BM * BK % (512 * NW) == 0 && BN * BK % (512 * NW) == 0, "loads split evenly");
   extern __shared__ __attribute__((aligned(1024))) bf16_raw lds[];
@@ -270,8 +273,8 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(KArgs p) 
   };
   const int epi = p.epilogue;
   if (glu) {
-    constexpr int CPR = BN / 16;           // chunks of 8 features per row
-    for (int e = threadIdx.x; e < BM * CPR; e += NT) {
+    constexpr int CPR = BN / 16;         // chunks of 8 features per row
+    for (int e = threadIdx.x; e < BM * CPR; e += NTHR) {
       const int rl = e / CPR, fl = e % CPR * 8;
       const int row = m0 + rl, feat = n0 + fl;
       if (row >= p.M || feat >= p.split) continue;
@@ -285,43 +288,45 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(KArgs p) 
 #pragma unroll
       for (int i = 0; i < 8; ++i) u[i] += t[i];
       if (p.C2) {
-        store_stream<false>(p.C2 + (size_t)row * p.ldc2 + feat, pack8_bf16(g));
-        store_stream<false>(p.C2 + (size_t)row * p.ldc2 + p.split + feat, pack8_bf16(u));
+        store_stream<NT>(p.C2 + (size_t)row * p.ldc2 + feat, pack8_bf16(g));
+        store_stream<NT>(p.C2 + (size_t)row * p.ldc2 + p.split + feat, pack8_bf16(u));
       }
 #pragma unroll
       for (int i = 0; i < 8; ++i) g[i] = gelu_fast(g[i]) * u[i];
-      store_stream<false>(reinterpret_cast<bf16_raw*>(p.C) + (size_t)row * p.ldc + feat, pack8_bf16(g));
+      store_stream<NT>(reinterpret_cast<bf16_raw*>(p.C) + (size_t)row * p.ldc + feat, pack8_bf16(g));
     }
     return;
   }
   constexpr int CPR = BN / 8;
-  static_assert(NT % CPR == 0, "a thread stays in its columns");
+  static_assert(NTHR % CPR == 0, "a thread stays in its columns");
   const int cl = threadIdx.x % CPR * 8, col = n0 + cl;
-  if (col >= p.N) return;                  // N is a multiple of 8
+  if (col >= p.N) return;                // N is a multiple of 8
   float bias[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) bias[e] = 0.f;
   if (epilogue_has_bias(epi)) unpack8(*reinterpret_cast<const uint4*>(p.bias + col), bias);
-  for (int rl = threadIdx.x / CPR; rl < BM && m0 + rl < p.M; rl += NT / CPR) {
+  for (int rl = threadIdx.x / CPR; rl < BM && m0 + rl < p.M; rl += NTHR / CPR) {
     float x[8];
     sum8(rl, cl, x);
     if (epi == EPI_ACCUM_F32) {
+      // (never streamed: a 64 MB gradient partly stays in the memory-side cache between microbatches; 4096 x 4096 over 513
+      // tokens 50 -> 63 us with non-temporal accesses)
       float4* c = reinterpret_cast<float4*>(reinterpret_cast<float*>(p.C) + (size_t)(m0 + rl) * p.ldc + col);
       const float4 u = c[0], v = c[1];
       c[0] = make_float4(u.x + x[0], u.y + x[1], u.z + x[2], u.w + x[3]);
       c[1] = make_float4(v.x + x[4], v.y + x[5], v.z + x[6], v.w + x[7]);
     } else {
-      finish_chunk<false>(p, epi, x, bias, m0 + rl, col);
+      finish_chunk<NT>(p, epi, x, bias, m0 + rl, col);
     }
   }
 }
 
-template <int WM, int WN, int WK, int NS, bool A_T, bool B_T>
+template <int WM, int WN, int WK, int NS, bool A_T, bool B_T, bool NT = false>
 swarm_status launch(const KArgs& k, hipStream_t st) {
   constexpr int BM = 64 * WM, BN = 64 * WN, BK = 32 * WK;
   constexpr size_t stages = (size_t)NS * (BM + BN) * BK * 2, sums = (size_t)WK * BM * (BN + 4) * 4;
   constexpr size_t lds_bytes = stages > sums ? stages : sums;
-  auto kern = gemm_bf16_kw_kernel<WM, WN, WK, NS, A_T, B_T>;
+  auto kern = gemm_bf16_kw_kernel<WM, WN, WK, NS, A_T, B_T, NT>;
   static LdsOptIn opted;   // per instantiation
   if (lds_opt_in((const void*)kern, lds_bytes, opted) != SWARM_OK) return SWARM_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3(k.tiles_m * k.tiles_n), dim3(WM * WN * WK * 64), lds_bytes, st, k);
@@ -332,6 +337,10 @@ template <int WM, int WN, int WK, int NS>
 swarm_status launch_layout(KArgs k, bool a_t, bool b_t, hipStream_t st) {
   k.tiles_m = (k.M + 64 * WM - 1) / (64 * WM);
   k.tiles_n = (k.N + 64 * WN - 1) / (64 * WN);
+  if constexpr (WM == 2 && WN == 2) {      // an output of 64 MB has many tiles
+    if (k.stream && !a_t && !b_t) return launch<WM, WN, WK, NS, false, false, true>(k, st);
+    if (k.stream && !a_t) return launch<WM, WN, WK, NS, false, true, true>(k, st);
+  }
   if (!a_t && !b_t) return launch<WM, WN, WK, NS, false, false>(k, st);
   if (!a_t) return launch<WM, WN, WK, NS, false, true>(k, st);
   return launch<WM, WN, WK, NS, true, true>(k, st);
@@ -349,10 +358,12 @@ bool gemm_bf16_kw_takes(const GemmArgs& g) {
 }
 
 // SWARM_ERR_SHAPE (nothing launched): a k-contiguous operand whose K is no multiple of 32, or a tile whose offsets do
-// not fit 32 bits.  The caller has checked alignment (16-byte rows, N % 8 == 0) and the layout.
-swarm_status gemm_bf16_kw(const GemmArgs& g, hipStream_t st) {
+// not fit 32 bits.  The caller has checked alignment (16-byte rows, N % 8 == 0) and the layout.  stream: see KArgs (8100 x
+// 16384, K = 4096 with GeLU 1224 -> 1180 us, its gradient 1284 -> 1208).
+swarm_status gemm_bf16_kw(const GemmArgs& g, int stream, hipStream_t st) {
   if (!gemm_bf16_kw_takes(g)) return SWARM_ERR_SHAPE;
-  const KArgs k = kargs_of(g);
+  KArgs k = kargs_of(g);
+  k.stream = stream;
   // By rounds of workgroups.  A 64-deep slice takes 0.7 us on a 128 x 128 tile, of which a compute unit holds one, and
   // 0.47 us on two 64 x 64 tiles with two stages.  So 128 x 128 tiles where a round (512) of 64 x 64 ones does not hold the
   // product: the last 1280 columns of a 50432-row vocabulary on 2048 tokens, K = 4096, 640 small or 160 large tiles: 74 ->

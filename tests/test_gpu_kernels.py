@@ -489,6 +489,34 @@ def test_gemm_rounds_of_small_tiles(M, N, K, a_t, b_t, epi):
     test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
 
 
+# Whole 128 x 128 tiles, two workgroups per unit: either side of 128, 256, 512 and 768 of them, one slice, an odd number and
+# the longest K of its rules, every layout and epilogue (rotary, GeGLU and the encoding one through the stage tests).
+@pytest.mark.parametrize("M,N,K,a_t,b_t,epi", [
+    (1408, 1536, 64, False, False, 0), (1408, 1536, 512, False, False, 1), (1024, 2048, 192, False, False, 3),
+    (640, 6656, 192, False, False, 2), (2176, 2176, 128, False, False, 1), (1664, 5120, 192, False, False, 3),
+    (8064, 4224, 64, False, False, 0), (1408, 1536, 320, False, True, 0), (2176, 2176, 64, False, True, 4),
+    (2944, 3456, 192, False, True, 0), (4480, 2944, 128, False, True, 4), (2944, 2944, 2048, False, True, 4),
+    (1152, 2304, 64, True, True, 5), (1152, 4608, 448, True, True, 5), (3200, 3200, 192, True, True, 5),
+    (3200, 3200, 2048, True, True, 5), (3200, 4480, 64, True, True, 5)])
+def test_gemm_two_workgroups_per_unit(M, N, K, a_t, b_t, epi):
+    test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
+
+
+# Ragged products either side of the line between the register-staged kernel and the one with K over the wavefronts: rows that
+# fill most of a round of 256-row tiles and rows that do not, K at and past the limits, outputs large enough for streaming
+# stores.
+@pytest.mark.parametrize("M,N,K,a_t,b_t,epi", [
+    (2500, 2048, 512, False, False, 3), (1500, 3072, 1024, False, False, 1), (1500, 3072, 1056, False, False, 1),
+    (6001, 1536, 512, False, False, 2), (4001, 4096, 96, False, False, 3), (5000, 3072, 160, False, False, 2),
+    (2600, 4096, 96, False, False, 1), (3900, 4096, 4128, False, False, 0), (5000, 1024, 256, False, True, 4),
+    (4001, 4096, 96, False, True, 0), (1536, 4608, 65, True, True, 5), (1536, 4608, 641, True, True, 5),
+    (3072, 3072, 321, True, True, 5), (4096, 4096, 130, True, True, 5), (4104, 4000, 1, True, True, 5),
+    (3072, 4096, 700, True, True, 5), (8200, 4096, 64, False, False, 2), (8200, 4096, 96, False, False, 3),
+    (8200, 4104, 64, False, True, 4)])
+def test_gemm_ragged_routes(M, N, K, a_t, b_t, epi):
+    test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
+
+
 # Row sums of the left operand beside a weight gradient (the bias gradient), where the product's kernel takes them along:
 # one tile, fewer and more columns of tiles than fragment rows, ragged rows and token counts, both dtypes.
 @pytest.mark.parametrize("bf16,M,N,K", [(1, 64, 64, 33), (1, 200, 128, 333), (1, 768, 192, 1665), (1, 768, 3072, 130),

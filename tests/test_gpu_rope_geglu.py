@@ -58,6 +58,16 @@ def test_mfma_shapes_bf16(shape):
     _check(_wl("bf16", shape))
 
 
+@pytest.mark.parametrize("shape", [
+    # token counts that are an odd multiple of 128, where the rotary, GeGLU and GeGLU-gradient epilogues run on 128 x 128 tiles
+    # with two workgroups per unit (132 .. 272 of them)
+    (512, 4, 1024, 704, 2, 1, 1),
+    (256, 2, 2048, 1088, 2, 1, 1),
+])
+def test_odd_multiples_of_128_tokens_bf16(shape):
+    _check(_wl("bf16", shape), dt=np.float32)
+
+
 def test_positions_restart_per_sequence():
     """Rotary positions count from 0 in every sequence of the microbatch: a microbatch of two sequences gives,
     bit for bit, what the two single-sequence calls give."""
