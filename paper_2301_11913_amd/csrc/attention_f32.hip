@@ -64,6 +64,14 @@ struct Streamed {
       for (int c = 0; c < DH / 32; ++c) v[r][c] = row[32 * c];
     }
   }
+  // zeros in the place of rows past `last`: row `last`, which they repeat, may hold a value that is not finite
+  __device__ __forceinline__ void drop_past(int first, int last, int lg) {
+    if (first + 31 <= last) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int c = 0; c < DH / 32; ++c) v[r][c] = first + row_of(r, lg) <= last ? v[r][c] : 0.f;
+  }
 };
 // out^T [DH][tile column] += sum over the block's 32 streamed rows of X[row][:] w[row][column]
 template <int DH>
@@ -73,6 +81,40 @@ __device__ __forceinline__ void accumulate(f32x16_t (&out)[DH / 32], const Strea
 #pragma unroll
     for (int c = 0; c < DH / 32; ++c) out[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.v[r][c], w[r], out[c], 0, 0, 0);
 }
+// On the diagonal some columns must not see some rows.  Their weight is zero, but zero times a value that is not finite is
+// not, and a bad token would reach rows that do not depend on it.  The diagonal block is therefore a wavefront's first: if
+// its sums are not all finite, they are formed again from the rows that a column sees, one by one.  `rows`: what the block
+// streams; scratch: 32 x 33 floats of this wavefront's.  (Fifty to a hundred vector instructions on a finite block.)
+template <int DH, typename Seen>
+__device__ __forceinline__ void keep_unseen_apart(f32x16_t (&out)[DH / 32], const f32x16_t& w, const float* rows, size_t ld,
+                                                  int first, int last, float* scratch, int l32, int lg, Seen&& seen) {
+  float z = 0.f;
+#pragma unroll
+  for (int c = 0; c < DH / 32; ++c)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z = fmaf(out[c][r], 0.f, z);
+  if (__builtin_amdgcn_ballot_w64(!(z == 0.f)) == 0) return;
+#pragma unroll
+  for (int c = 0; c < DH / 32; ++c) out[c] = zero16();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) scratch[row_of(r, lg) * 33 + l32] = w[r];
+#pragma unroll 1
+  for (int j = 0; j < 32 && first + j <= last; ++j) {
+    if (!seen(first + j)) continue;
+    const float wj = scratch[j * 33 + l32];
+    const float* row = rows + (size_t)(first + j) * ld;
+#pragma unroll
+    for (int c = 0; c < DH / 32; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) out[c][r] = fmaf(wj, row[32 * c + row_of(r, lg)], out[c][r]);
+  }
+}
+// The block of 32 keys that wavefront `wave` takes i-th for query tile qt: every fourth, the diagonal first; and how many.
+__device__ __forceinline__ int key_block(int i, int qt, int wave) {
+  const bool diagonal = wave == qt % kWaves;
+  return diagonal ? (i == 0 ? qt : wave + kWaves * (i - 1)) : wave + kWaves * i;
+}
+__device__ __forceinline__ int key_blocks(int qt, int wave) { return wave <= qt ? (qt - wave) / kWaves + 1 : 0; }
 // The wavefronts' out^T meet 64 of its DH rows at a time: each writes its own to patch[wave] ([64][33]), and
 // emit(i, c, row) is called for every column i < columns of the tile and feature c, row = 33 (c % 64) + i.
 template <int DH, typename F>
@@ -92,7 +134,7 @@ __device__ __forceinline__ void meet(const f32x16_t (&out)[DH / 32], float (*pat
 
 // one workgroup per (32 queries, head, sequence), long rows first
 template <int DH>
-__global__ __launch_bounds__(kNT) void attn_f32_fwd_kernel(const float* __restrict__ qkv, float* __restrict__ o,
+__global__ __launch_bounds__(kNT, 2) void attn_f32_fwd_kernel(const float* __restrict__ qkv, float* __restrict__ o,
                                                            float* __restrict__ lse, int S, int H) {
   __shared__ float patch[kWaves][64 * 33];
   __shared__ float stat[2][kWaves][32];
@@ -107,11 +149,12 @@ __global__ __launch_bounds__(kNT) void attn_f32_fwd_kernel(const float* __restri
   float4 q[DH / 8];
   load_row<DH>(q, base + (size_t)min(query, S - 1) * ld, lg);
 
-  float m = -INFINITY, l = 0.f;
+  float m = -__FLT_MAX__, l = 0.f;     // finite: the scores of a block may all be -inf
   f32x16_t out[DH / 32];
 #pragma unroll
   for (int c = 0; c < DH / 32; ++c) out[c] = zero16();
-  for (int kb = wave; kb <= qt; kb += kWaves) {
+  for (int i = 0; i < key_blocks(qt, wave); ++i) {
+    const int kb = key_block(i, qt, wave);
     float4 k[DH / 8];
     Streamed<DH> v;
     load_row<DH>(k, base + (size_t)min(kb * 32 + l32, S - 1) * ld + d, lg);
@@ -126,7 +169,7 @@ __global__ __launch_bounds__(kNT) void attn_f32_fwd_kernel(const float* __restri
       s[r] = kb * 32 + row_of(r, lg) <= query ? s[r] * scale : -INFINITY;
       top = fmaxf(top, s[r]);
     }
-    top = fmaxf(m, fmaxf(top, __shfl_xor(top, 32, 64)));   // finite: key 0 of the block, or the diagonal, is seen
+    top = fmaxf(m, fmaxf(top, __shfl_xor(top, 32, 64)));
     const float old = expf(m - top);
     m = top;
     float sum = 0.f;
@@ -142,6 +185,9 @@ __global__ __launch_bounds__(kNT) void attn_f32_fwd_kernel(const float* __restri
       for (int r = 0; r < 16; ++r) out[c][r] *= old;
     if constexpr (!kAhead<DH>) v.load(base + 2 * d, ld, kb * 32, S - 1, l32, lg);
     accumulate<DH>(out, v, s);
+    if (kb == qt)
+      keep_unseen_apart<DH>(out, s, base + 2 * d, ld, kb * 32, S - 1, patch[wave], l32, lg,
+                            [&](int key) __attribute__((always_inline)) { return key <= query; });
   }
   if (lg == 0) {
     stat[0][wave][l32] = m;
@@ -152,7 +198,7 @@ __global__ __launch_bounds__(kNT) void attn_f32_fwd_kernel(const float* __restri
   // tokens, 4 heads of 64: 16.4 -> 15 us)
   if (threadIdx.x < 32) {
     const int i = threadIdx.x;
-    float top = stat[0][0][i];                             // wavefront 0 always has a block
+    float top = stat[0][0][i];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) top = fmaxf(top, stat[0][w][i]);
     float sum = 0.f;
@@ -163,7 +209,8 @@ __global__ __launch_bounds__(kNT) void attn_f32_fwd_kernel(const float* __restri
       stat[0][w][i] = f;
     }
     stat[1][0][i] = sum;
-    if (qt * 32 + i < S) lse[((size_t)b * H + h) * S + qt * 32 + i] = top + logf(sum);
+    // (a row in which every score is -inf has no weights: 0 / 0, and its lse is NaN)
+    if (qt * 32 + i < S) lse[((size_t)b * H + h) * S + qt * 32 + i] = sum > 0.f ? top + logf(sum) : NAN;
   }                                                        // (meet begins with a barrier)
   meet<DH>(out, patch, wave, l32, lg, min(32, S - qt * 32), [&](int i, int c, int at) __attribute__((always_inline)) {
     float acc = 0.f;
@@ -190,7 +237,7 @@ __global__ __launch_bounds__(kNT) void attn_f32_delta_kernel(const float* __rest
 
 // dQ of 32 queries
 template <int DH>
-__global__ __launch_bounds__(kNT) void attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ dout,
+__global__ __launch_bounds__(kNT, DH == 64 ? 2 : 1) void attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ dout,
                                                           const float* __restrict__ lse, const float* __restrict__ delta,
                                                           float* __restrict__ dqkv, int S, int H) {
   __shared__ float patch[kWaves][64 * 33];
@@ -209,7 +256,8 @@ __global__ __launch_bounds__(kNT) void attn_f32_dq_kernel(const float* __restric
   f32x16_t out[DH / 32];
 #pragma unroll
   for (int c = 0; c < DH / 32; ++c) out[c] = zero16();
-  for (int kb = wave; kb <= qt; kb += kWaves) {
+  for (int i = 0; i < key_blocks(qt, wave); ++i) {
+    const int kb = key_block(i, qt, wave);
     const float* krow = base + (size_t)min(kb * 32 + l32, S - 1) * ld + d;
     float4 k[DH / 8], v[DH / 8];
     Streamed<DH> kc;
@@ -226,6 +274,9 @@ __global__ __launch_bounds__(kNT) void attn_f32_dq_kernel(const float* __restric
       s[r] = kb * 32 + row_of(r, lg) <= query ? expf(s[r] * scale - L) * (dp[r] - D) : 0.f;
     if constexpr (!kAhead<DH>) kc.load(base + d, ld, kb * 32, S - 1, l32, lg);
     accumulate<DH>(out, kc, s);
+    if (kb == qt)
+      keep_unseen_apart<DH>(out, s, base + d, ld, kb * 32, S - 1, patch[wave], l32, lg,
+                            [&](int key) __attribute__((always_inline)) { return key <= query; });
   }
   meet<DH>(out, patch, wave, l32, lg, min(32, S - qt * 32), [&](int i, int c, int at) __attribute__((always_inline)) {
     float acc = 0.f;
@@ -282,13 +333,21 @@ __global__ __launch_bounds__(kNT) void attn_f32_dkdv_kernel(const float* __restr
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int query = qb * 32 + row_of(r, lg);
-      p[r] = query >= key && query < S ? expf(p[r] * scale - Lq[r]) : 0.f;
-      ds[r] = p[r] * (ds[r] - Dq[r]);
+      const bool seen = query >= key && query < S;
+      p[r] = seen ? expf(p[r] * scale - Lq[r]) : 0.f;
+      ds[r] = seen ? p[r] * (ds[r] - Dq[r]) : 0.f;
     }
     if constexpr (!kAhead<DH>) gc.load(gout, d, qb * 32, S - 1, l32, lg);
+    gc.drop_past(qb * 32, S - 1, lg);
     accumulate<DH>(dv, gc, p);
     if constexpr (!kAhead<DH>) qc.load(base, ld, qb * 32, S - 1, l32, lg);
+    qc.drop_past(qb * 32, S - 1, lg);
     accumulate<DH>(dk, qc, ds);
+    if (qb == kt) {
+      auto seen = [&](int query) __attribute__((always_inline)) { return query >= key; };
+      keep_unseen_apart<DH>(dv, p, gout, d, qb * 32, S - 1, patch[wave], l32, lg, seen);
+      keep_unseen_apart<DH>(dk, ds, base, ld, qb * 32, S - 1, patch[wave], l32, lg, seen);
+    }
   }
   auto emit = [&](int part, float factor) __attribute__((always_inline)) {
     return [=](int i, int c, int at) __attribute__((always_inline)) {

@@ -394,6 +394,82 @@ def test_attention_f32(shape, std):
         assert np.max(np.abs(got[..., part] - rdqkv[..., part])) <= 4 * tol * np.max(np.abs(rdqkv[..., part])) + floor
 
 
+def _attention_f32_run(qkv, dout, B, S, H, dh):
+    lib = _attn_lib()
+    qd, dod = qkv.cuda(), dout.cuda()
+    o, lse, dqkv = torch.full_like(dod, 9.0), torch.full((B, H, S), 9.0, device="cuda"), torch.full_like(qd, 9.0)
+    delta = torch.empty_like(lse)
+    assert lib.swarm_kernel_attention_fwd(0, qd.data_ptr(), o.data_ptr(), lse.data_ptr(), B, S, H, dh, None) == 0
+    assert lib.swarm_kernel_attention_bwd(0, qd.data_ptr(), o.data_ptr(), dod.data_ptr(), lse.data_ptr(), delta.data_ptr(),
+                                          dqkv.data_ptr(), B, S, H, dh, None) == 0
+    torch.cuda.synchronize()
+    return o.cpu(), lse.cpu(), dqkv.cpu()
+
+
+# A value that is not finite reaches only what depends on it: everything else is what it is without it, to the rounding of
+# another order of at most S additions in the rows of the same block, bit for bit elsewhere.  Row `bad` of one of q, k, v
+# (parts 0..2) or of dout (3), inside a block of 32 rows, first and last of one, in a last block that is short.
+@pytest.mark.parametrize("value", [math.inf, -math.inf, math.nan])
+@pytest.mark.parametrize("part", [0, 1, 2, 3])
+@pytest.mark.parametrize("S,bad,dh", [(150, 45, 64), (150, 64, 64), (150, 149, 128), (200, 95, 128), (300, 17, 128)])
+def test_attention_f32_keeps_masked_positions_apart(S, bad, dh, part, value):
+    B, H, h = 2, 4, 1
+    d = H * dh
+    g = torch.Generator().manual_seed(S + dh)
+    qkv, dout = torch.randn((B, S, 3 * d), generator=g), torch.randn((B, S, d), generator=g)
+    clean = _attention_f32_run(qkv, dout, B, S, H, dh)
+    if part < 3:
+        qkv[0, bad, part * d + h * dh + 5] = value
+    else:
+        dout[0, bad, h * dh + 5] = value
+    got = _attention_f32_run(qkv, dout, B, S, H, dh)
+    views = lambda x: (x[0].view(B, S, H, dh), x[1], x[2].view(B, S, 3, H, dh))
+    (o, lse, grads), (co, clse, cgrads) = views(got), views(clean)
+    bound = S * 2.0 ** -24
+    same = lambda a, b: bool((a == b).all())
+    close = lambda a, b: bool(((a - b).abs() <= bound * b.abs().max()).all())
+    other = [x for x in range(H) if x != h]
+    assert same(o[1], co[1]) and same(lse[1], clse[1]) and same(grads[1], cgrads[1])             # the other sequence
+    assert same(o[0][:, other], co[0][:, other]) and same(grads[0][:, :, other], cgrads[0][:, :, other])   # the other heads
+    first = bad // 32 * 32                                                                       # earlier queries
+    assert same(o[0, :first, h], co[0, :first, h]) and same(lse[0, h, :bad], clse[0, h, :bad])
+    assert same(grads[0, :first, 0, h], cgrads[0, :first, 0, h])
+    if bad > first:
+        assert close(o[0, first:bad, h], co[0, first:bad, h]) and close(grads[0, first:bad, 0, h], cgrads[0, first:bad, 0, h])
+    if part in (0, 3) and bad + 1 < S:      # a query (or its gradient) touches its own row and earlier keys only
+        assert close(o[0, bad + 1:, h], co[0, bad + 1:, h]) and same(lse[0, h, bad + 1:], clse[0, h, bad + 1:])
+        assert close(grads[0, bad + 1:, :, h], cgrads[0, bad + 1:, :, h])
+    assert not torch.isfinite(torch.cat([got[0][0, bad], got[2][0, bad]])).all()                 # and its own row shows it
+
+
+def test_attention_f32_scores_of_minus_infinity():
+    """Keys whose scores overflow to -inf have no weight, also where they are all the keys that one wavefront takes; a row in
+    which every score does gives NaN."""
+    B, S, H, dh = 2, 260, 4, 64
+    d = H * dh
+    g = torch.Generator().manual_seed(5)
+    qkv, dout = torch.randn((B, S, 3 * d), generator=g), torch.randn((B, S, d), generator=g)
+    qkv[0, 200:, 7] = 3e38                     # queries 200 .. of head 0
+    keys = torch.arange(S)
+    hidden = (keys // 32 % 4 == 2) & (keys < 200)
+    qkv[0, hidden, d + 7] = -4.0               # q k = -1.2e39 there, and 0 for this column elsewhere
+    qkv[0, ~hidden, d + 7] = 0.0
+    o, lse, dqkv = _attention_f32_run(qkv, dout, B, S, H, dh)
+    x = qkv.double().view(B, S, 3, H, dh).permute(2, 0, 3, 1, 4)
+    x[0][0, 0, 200:, 7] = 0.0                  # the same scores without the overflow: masked where it happens
+    s = x[0] @ x[1].transpose(-1, -2) / math.sqrt(dh)
+    mask = torch.tril(torch.ones(S, S, dtype=torch.bool)).expand(B, H, S, S).clone()
+    mask[0, 0, 200:, hidden] = False
+    s = s.masked_fill(~mask, -math.inf)
+    want = (torch.softmax(s, -1) @ x[2]).permute(0, 2, 1, 3).reshape(B, S, d)
+    assert torch.isfinite(o).all() and torch.isfinite(lse).all()
+    assert (o.double() - want).abs().max() <= 1e-5 * want.abs().max()
+    assert (lse.double() - torch.logsumexp(s, -1)).abs().max() <= 1e-5 * 6
+    qkv[1, :, d + 7], qkv[1, 100, 7] = -4.0, 3e38     # every score of this row
+    o, lse, dqkv = _attention_f32_run(qkv, dout, B, S, H, dh)
+    assert torch.isnan(o[1, 100, :dh]).all() and torch.isfinite(o[1, :100]).all() and torch.isfinite(o[1, 101:]).all()
+
+
 # fp32 GEMM on the matrix cores: every workgroup shape of its dispatch (32 x 32 blocks with K over 8 or 4 wavefronts,
 # 64 x 64, 128 x 128), ragged rows and columns, a K that leaves a partial slice and (transposed operands) a partial
 # 8-deep step, fewer 8-deep steps than wavefronts, every epilogue.
