@@ -744,16 +744,20 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_bwd_dq_kernel(const bf16
 }
 
 // How a launch is laid out, by the number of 128-row tiles over all heads.  Up to one tile per compute unit: single tiles,
-// the forward and dQ with two groups of wavefronts.  Beyond that tiles go in long-short pairs, which is what balances a
-// launch of many rounds and costs nothing at one (two d_model 1024 blocks, 512 tiles: 18.9 us in pairs or singly).
+// the forward and dQ with two groups of wavefronts where a row is long enough to be worth the merge: from four 64-key tiles at
+// d_head 64 (one sequence of 256, 4 heads: forward 7.9 -> 7.5 us; of 128 6.7 -> 7.1, and one of 64 8 % slower, its second group
+// having nothing to do), from six at d_head 128 (384 tokens 12.8 -> 12.3; 192 8.4 -> 9.1).  Beyond that tiles go in
+// long-short pairs, which is what balances a launch of many rounds and costs nothing at one (two d_model 1024 blocks, 512
+// tiles: 18.9 us in pairs or singly).
 struct Layout {
-  int passes;
+  int passes, groups;
   unsigned grid;
 };
-Layout layout_of(int B, int S, int H) {
+Layout layout_of(int B, int S, int H, int dh) {
   const int nt = (S + 127) / 128;
   const int passes = (long long)nt * H * B <= 256 ? 1 : 2;
-  return {passes, (unsigned)((passes == 2 ? (nt + 1) / 2 : nt) * H * B)};
+  const int groups = passes == 1 && (S + 63) / 64 >= (dh == 64 ? 4 : 6) ? 2 : 1;
+  return {passes, groups, (unsigned)((passes == 2 ? (nt + 1) / 2 : nt) * H * B)};
 }
 
 template <int DH, int KG>
@@ -784,17 +788,17 @@ swarm_status launch_bwd(const bf16_raw* qkv, const bf16_raw* o, const bf16_raw* 
   static LdsOptIn a1;
   if (lds_opt_in((const void*)attn_bwd_dkdv_kernel<DH>, lds_dkdv, a1) != SWARM_OK) return SWARM_ERR_LAUNCH;
   hipLaunchKernelGGL(attn_delta_kernel<DH>, dim3(B * S), dim3(kThreads), 0, st, o, dout, delta, S, H);
-  const Layout L = layout_of(B, S, H);
+  const Layout L = layout_of(B, S, H, DH);
   hipLaunchKernelGGL(attn_bwd_dkdv_kernel<DH>, dim3(L.grid), dim3(kDkDvThreads), lds_dkdv, st, qkv, dout, lse, delta, dqkv,
                      S, H, L.passes);
-  if (L.passes == 1) return launch_dq<DH, 2>(qkv, dout, lse, delta, dqkv, S, H, L, st);
+  if (L.groups == 2) return launch_dq<DH, 2>(qkv, dout, lse, delta, dqkv, S, H, L, st);
   return launch_dq<DH, 1>(qkv, dout, lse, delta, dqkv, S, H, L, st);
 }
 
 template <int DH>
 swarm_status launch_fwd_of(const bf16_raw* qkv, bf16_raw* o, float* lse, int B, int S, int H, hipStream_t st) {
-  const Layout L = layout_of(B, S, H);
-  if (L.passes == 1) return launch_fwd<DH, 2>(qkv, o, lse, S, H, L, st);
+  const Layout L = layout_of(B, S, H, DH);
+  if (L.groups == 2) return launch_fwd<DH, 2>(qkv, o, lse, S, H, L, st);
   return launch_fwd<DH, 1>(qkv, o, lse, S, H, L, st);
 }
 

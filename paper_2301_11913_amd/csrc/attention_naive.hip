@@ -1,5 +1,6 @@
 // Direct (one query row or one key row per workgroup) causal attention in fp32 arithmetic.
-// For head sizes the matrix-core kernels do not cover (anything but 64 and 128).
+// For head sizes the matrix-core kernels do not cover (anything but 64 and 128; the stage accepts no others) and for fp32 calls
+// of few short rows (direct_is_faster in attention.hip).
 // Deterministic: every sum runs in a fixed order.
 #include "kernels.h"
 

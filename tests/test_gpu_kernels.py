@@ -328,6 +328,12 @@ def test_attention_bf16_launch_layouts(shape):
     _attention_case(shape, 1.5)
 
 
+# up to 256 tiles: one group of wavefronts while a row has fewer than four (d_head 64) or six (128) tiles of 64 keys, then two
+@pytest.mark.parametrize("shape", [(3, 192, 4, 64), (3, 193, 4, 64), (2, 256, 4, 64), (1, 257, 3, 64), (2, 320, 3, 128),
+                                   (2, 321, 3, 128), (1, 384, 3, 128), (40, 64, 6, 64), (40, 33, 6, 128)])
+def test_attention_bf16_wavefront_groups(shape):
+    _attention_case(shape, 1.5)
+
 @pytest.mark.parametrize("shape", [(1, 300, 2, 128), (2, 200, 2, 64), (1, 1100, 1, 128)])
 def test_attention_bf16_peaked_scores(shape):
     """Scores with a standard deviation of several tens: nearly one-hot softmax rows, the running reference of the
@@ -393,6 +399,12 @@ def test_attention_f32(shape, std):
         part = slice(i * d, (i + 1) * d)
         assert np.max(np.abs(got[..., part] - rdqkv[..., part])) <= 4 * tol * np.max(np.abs(rdqkv[..., part])) + floor
 
+
+# fp32 calls either side of the line between the direct kernels and the matrix cores: B H S^2 = 512 d_head, S = d_head
+@pytest.mark.parametrize("shape", [(1, 64, 8, 64), (1, 64, 9, 64), (2, 65, 1, 64), (8, 32, 4, 64), (8, 33, 4, 64), (1, 1, 3, 128),
+                                   (1, 128, 4, 128), (1, 128, 5, 128), (1, 129, 2, 128), (64, 32, 1, 128)])
+def test_attention_f32_few_short_rows(shape):
+    test_attention_f32(shape, 1.5)
 
 def _attention_f32_run(qkv, dout, B, S, H, dh):
     lib = _attn_lib()
