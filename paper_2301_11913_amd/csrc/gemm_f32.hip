@@ -87,15 +87,17 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
 #pragma unroll
   for (int j = 0; j < FN; ++j) b[j].init((const float*)g.B, g.ldb, min(n0 + (wn * FN + j) * 32 + l32, g.N - 1));
 
-  float rsum[FM];      // sum of this lane's values of A (a row's bias gradient beside its weight gradient)
+  // Sum of this lane's values of A (a row's bias gradient beside its weight gradient).  In doubles, one addition per 8-deep
+  // step: the rows of shared layers make one K of up to 2^22, where a running fp32 sum loses (32768 rows of mean 1 5.9e-7).
+  double rsum[FM];
 #pragma unroll
-  for (int i = 0; i < FM; ++i) rsum[i] = 0.f;
+  for (int i = 0; i < FM; ++i) rsum[i] = 0.0;
   const int part = ((g.K + 7) / 8 + WK - 1) / WK * 8;
   const int kbeg = wk * part, kend = min(g.K, kbeg + part);
   auto multiply = [&](const float4 (&fa)[FM], const float4 (&fb)[FN]) __attribute__((always_inline)) {
     if constexpr (A_T) {
 #pragma unroll
-      for (int i = 0; i < FM; ++i) rsum[i] += (fa[i].x + fa[i].y) + (fa[i].z + fa[i].w);
+      for (int i = 0; i < FM; ++i) rsum[i] += (double)((fa[i].x + fa[i].y) + (fa[i].z + fa[i].w));
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c)
@@ -154,8 +156,8 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
   if (sum_rows && wn == 0) {                               // into the column behind the tile's
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      const float s = rsum[i] + __shfl_xor(rsum[i], 32, 64);
-      if (lg == 0) mine[(32 * i + l32) * PITCH + TN] = s;
+      const double s = rsum[i] + __shfl_xor(rsum[i], 32, 64);
+      if (lg == 0) mine[(32 * i + l32) * PITCH + TN] = (float)s;
     }
   }
   __syncthreads();

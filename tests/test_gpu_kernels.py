@@ -624,3 +624,26 @@ def test_weight_gradient_row_sums(bf16, M, N, K):
     # K additions (and products), each off by half an ulp of at most the sum of magnitudes
     assert ((db.cpu() - (db0 + A.sum(0))).abs() <= (K + 1) * 2.0 ** -24 * (A.abs().sum(0) + db0.abs())).all()
     assert ((dW.cpu() - (dW0 + A.T @ B)).abs() <= (2 * K + 1) * 2.0 ** -24 * (A.abs().T @ B.abs() + dW0.abs())).all()
+
+
+# The same over very many rows (the applications of shared layers are one K).  The blocked column sum that these replace adds
+# at most 32 + 4 + ceil(K / 16384) + 24 values in a row, and every addition is off by half an ulp of at most the running sum of
+# magnitudes: with rows of one sign the errors are independent and few standard deviations (half the square root of the chain,
+# in ulps) cover 2048 rows.  A running sum over all K misses this by 2 to 6 times.
+@pytest.mark.parametrize("bf16,M,N,K", [(1, 256, 128, 131105), (1, 2048, 1024, 131072), (0, 256, 128, 131105),
+                                        (0, 2048, 1024, 40000), (1, 64, 64, 1000003)])
+def test_row_sums_over_many_rows(bf16, M, N, K):
+    lib = _lib()
+    lib.swarm_kernel_gemm_rowsum.argtypes = [C.c_int] * 4 + [C.c_void_p] * 5
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    A = (torch.randn((K, M), generator=g, device="cuda") + 1.0).to(dt)
+    B = torch.randn((K, N), generator=g, device="cuda").to(dt)
+    db, dW = torch.zeros(M, device="cuda"), torch.zeros((M, N), device="cuda")
+    assert lib.swarm_kernel_gemm_rowsum(bf16, M, N, K, A.data_ptr(), B.data_ptr(), dW.data_ptr(), db.data_ptr(), None) == 0
+    torch.cuda.synchronize()
+    rows = range(0, K, 1 << 16)
+    want = sum(A[r:r + (1 << 16)].double().sum(0) for r in rows)
+    size = sum(A[r:r + (1 << 16)].double().abs().sum(0) for r in rows)
+    chain = 32 + 4 + -(-K // 16384) + 24
+    assert ((db.double() - want).abs() <= 0.5 * math.sqrt(chain) * 2.0 ** -24 * size).all()
