@@ -31,9 +31,8 @@ __device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 1
 // element offset of 16-byte chunk `chunk` (0..7) of row `row` in a [rows][64] bf16 tile
 __device__ __forceinline__ int tile_off(int row, int chunk) { return row * BK + ((chunk ^ swz(row)) << 3); }
 
-
 // Global -> registers for one operand tile (BR rows of the GEMM x 64 k).
-template <int BR, int NT, bool TRANS, bool GUARD>
+template <int BR, int NT, bool TRANS>
 struct TileLoader {
   // non-transposed: BR*8 16-byte chunks; transposed: (BR/4)*8 patches of 8(k) x 4
   static constexpr int NI = TRANS ? ((BR / 4) * 8 + NT - 1) / NT : (BR * 8) / NT;
@@ -49,7 +48,7 @@ struct TileLoader {
         const int row = it >> 3, chunk = it & 7;
         const int gr = r0 + row, gk = k0 + chunk * 8;
         uint4 v = make_uint4(0, 0, 0, 0);
-        if (!GUARD || (gr < rows && gk < kdim)) v = *reinterpret_cast<const uint4*>(p + (size_t)gr * ld + gk);
+        if (gr < rows && gk < kdim) v = *reinterpret_cast<const uint4*>(p + (size_t)gr * ld + gk);
         r[2 * i] = make_uint2(v.x, v.y);
         r[2 * i + 1] = make_uint2(v.z, v.w);
       }
@@ -64,7 +63,7 @@ struct TileLoader {
         for (int j = 0; j < 8; ++j) {
           const int gk = k0 + kg * 8 + j;
           uint2 v = make_uint2(0, 0);
-          if (in && (!GUARD || (gk < kdim && col < rows)))
+          if (in && gk < kdim && col < rows)
             v = *reinterpret_cast<const uint2*>(p + (size_t)gk * ld + col);
           r[i * 8 + j] = v;
         }
@@ -108,7 +107,7 @@ struct TileLoader {
   }
 };
 
-template <int BM, int BN, int WM, int WN, bool A_T, bool B_T, bool GUARD>
+template <int BM, int BN, int WM, int WN, bool A_T, bool B_T>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(KArgs p) {
   constexpr int NT = WM * WN * 64;
   constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -133,8 +132,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(KArgs p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  TileLoader<BM, NT, A_T, GUARD> la;
-  TileLoader<BN, NT, B_T, GUARD> lb;
+  TileLoader<BM, NT, A_T> la;
+  TileLoader<BN, NT, B_T> lb;
 
   const int KT = (p.K + BK - 1) / BK;
   la.load(p.A, p.lda, p.M, p.K, m0, 0, tid);
@@ -182,25 +181,25 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(KArgs p) {
   }
 
   // every wavefront is past the last barrier: the operand stages are free to serve as epilogue patches
-  gemm_epilogue<FM, FN, GUARD>(p, acc, m0 + wm * WTM, n0 + wn * WTN, l32, lg,
+  gemm_epilogue<FM, FN, true>(p, acc, m0 + wm * WTM, n0 + wn * WTN, l32, lg,
                                reinterpret_cast<float*>(lds) + wave * 32 * kEpiPitch);
 }
 
-template <int BM, int BN, int WM, int WN, bool A_T, bool B_T, bool GUARD>
+template <int BM, int BN, int WM, int WN, bool A_T, bool B_T>
 swarm_status launch(const KArgs& k, hipStream_t st) {
   constexpr size_t lds_bytes = (size_t)2 * (BM + BN) * BK * sizeof(bf16_raw);
-  auto kern = gemm_bf16_kernel<BM, BN, WM, WN, A_T, B_T, GUARD>;
+  auto kern = gemm_bf16_kernel<BM, BN, WM, WN, A_T, B_T>;
   static LdsOptIn opted;   // per instantiation
   if (lds_opt_in((const void*)kern, lds_bytes, opted) != SWARM_OK) return SWARM_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3(k.tiles_m * k.tiles_n), dim3(WM * WN * 64), lds_bytes, st, k);
   return launch_status();
 }
 
-template <int BM, int BN, int WM, int WN, bool GUARD>
+template <int BM, int BN, int WM, int WN>
 swarm_status launch_layout(const KArgs& k, bool a_t, bool b_t, hipStream_t st) {
-  if (!a_t && !b_t) return launch<BM, BN, WM, WN, false, false, GUARD>(k, st);
-  if (!a_t && b_t) return launch<BM, BN, WM, WN, false, true, GUARD>(k, st);
-  if (a_t && b_t) return launch<BM, BN, WM, WN, true, true, GUARD>(k, st);
+  if (!a_t && !b_t) return launch<BM, BN, WM, WN, false, false>(k, st);
+  if (!a_t && b_t) return launch<BM, BN, WM, WN, false, true>(k, st);
+  if (a_t && b_t) return launch<BM, BN, WM, WN, true, true>(k, st);
   return SWARM_ERR_SHAPE;
 }
 
@@ -279,10 +278,10 @@ swarm_status gemm_bf16_launch(const GemmArgs& g, hipStream_t st) {
   // what gemm_bf16_dma leaves because this kernel is faster at it.
   if (big_tiles >= 160) {
     k.tiles_m = (g.M + 255) / 256; k.tiles_n = (g.N + 255) / 256;
-    return launch_layout<256, 256, 2, 4, true>(k, g.a_trans, g.b_trans, st);
+    return launch_layout<256, 256, 2, 4>(k, g.a_trans, g.b_trans, st);
   }
   k.tiles_m = (g.M + 127) / 128; k.tiles_n = (g.N + 127) / 128;
-  return launch_layout<128, 128, 2, 2, true>(k, g.a_trans, g.b_trans, st);
+  return launch_layout<128, 128, 2, 2>(k, g.a_trans, g.b_trans, st);
 }
 
 }  // namespace swarm
