@@ -13,7 +13,8 @@
 //
 // Measured against one workgroup per row (attention_naive.hip: forward 20, dK / dV 37, dQ 25 us at 4 sequences of 128
 // tokens, 4 heads of 64, and growing with the square of the length): the training pass they are part of 302 -> 257 us.
-// With the second product's rows requested beside the first's the forward went from 15 to 8 us (pass 204 -> 189 us).
+// With the second product's rows requested beside the first's the forward went from 15 to 8 us (pass 204 -> 189 us).  The
+// smallest calls stay with those kernels (attention.hip).
 #include "kernels.h"
 
 namespace swarm {
@@ -135,7 +136,7 @@ __device__ __forceinline__ void meet(const f32x16_t (&out)[DH / 32], float (*pat
 // one workgroup per (32 queries, head, sequence), long rows first
 template <int DH>
 __global__ __launch_bounds__(kNT, 2) void attn_f32_fwd_kernel(const float* __restrict__ qkv, float* __restrict__ o,
-                                                           float* __restrict__ lse, int S, int H) {
+                                                              float* __restrict__ lse, int S, int H) {
   __shared__ float patch[kWaves][64 * 33];
   __shared__ float stat[2][kWaves][32];
   const int qt = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -237,9 +238,11 @@ __global__ __launch_bounds__(kNT) void attn_f32_delta_kernel(const float* __rest
 
 // dQ of 32 queries
 template <int DH>
-__global__ __launch_bounds__(kNT, DH == 64 ? 2 : 1) void attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ dout,
-                                                          const float* __restrict__ lse, const float* __restrict__ delta,
-                                                          float* __restrict__ dqkv, int S, int H) {
+__global__ __launch_bounds__(kNT, DH == 64 ? 2 : 1) void attn_f32_dq_kernel(const float* __restrict__ qkv,
+                                                                            const float* __restrict__ dout,
+                                                                            const float* __restrict__ lse,
+                                                                            const float* __restrict__ delta,
+                                                                            float* __restrict__ dqkv, int S, int H) {
   __shared__ float patch[kWaves][64 * 33];
   const int qt = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int d = H * DH;

@@ -478,7 +478,8 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict
 
 // Stage 2: out[c] += sum_p partial[p*stride + c].  Workgroup = 64 columns x RG row groups, each with eight running sums
 // (fixed assignment p mod 8, fixed combine order) that keep as many loads in flight.  Latency bound: with four row groups
-// the 512 partial rows of a LayerNorm backward are sixteen dependent rounds of loads, with sixteen groups four.
+// the 512 partial rows of a LayerNorm backward are sixteen dependent rounds of loads, with sixteen groups four (training
+// passes at d_model 768 on 5 x 333 tokens 364 -> 356 us, two blocks of 1024 on 4096 tokens 1400 -> 1385, 2048 1793 -> 1778).
 // blockIdx.y = 1 (LayerNorm backward: dbeta next to dgamma in one launch) takes partial + C and out2.
 template <int RG>
 __global__ __launch_bounds__(64 * RG) void reduce_rows_accum_kernel(const float* __restrict__ partial, int P, int C,

@@ -863,9 +863,10 @@ static bool enough_256_tiles(const GemmArgs& g) {
 
 // Whole 128 x 128 tiles, those that get here (few 256-row ones): gemm_bf16_pair instead of gemm_bf16_kw?  Measured in turn:
 //   more than 256 of them    forward and data gradient 3..45 % faster there (1920 x 8192, K = 2048: 74.6 against 89.8 us; 3968 x
-//                            4096, K = 1024 with GeLU: 46.7 / 61.2), weight gradients 5..60 %; but where two rounds of it
-//                            replace three, long products with a transposed operand, whose epilogue or reads gemm_bf16_kw
-//                            hides better, are 3..7 % faster there (3968 x 3072, K = 2048 with GeLU' 67.3 / 63.0);
+//                            4096, K = 1024 with GeLU: 46.7 / 61.2), weight gradients 5..60 % (2048 x 4096 over 8192 tokens
+//                            169 / 184); but where two rounds of it replace three, long products with a transposed operand,
+//                            whose epilogue or reads gemm_bf16_kw hides better, are 3..7 % faster there (3968 x 3072, K = 2048
+//                            with GeLU' 67.3 / 63.0);
 //   129 to 256, short K      7..14 % at K = 256 (1920 x 2048: 7.1 / 8.0 us; weight gradients 20 %), 5 % at 512; not with an
 //                            epilogue that reads rows of its own (GeLU': 0.9 at 256);
 //   otherwise                gemm_bf16_kw by up to 2 x.
