@@ -80,8 +80,7 @@ LAYOUTS = [(False, False), (False, True), (True, True)]
 @pytest.mark.parametrize("a_t,b_t", LAYOUTS)
 @pytest.mark.parametrize("shape", [(256, 256, 64), (128, 128, 128), (512, 768, 256), (300, 192, 320),
                                    (37, 64, 64), (1000, 1088, 200), (4096, 4096, 512), (2048, 4096 + 64, 256 + 64),
-                                   # whole tiles but K no multiple of 64: the register-staged kernels (128 x 128
-                                   # and, from 160 big tiles on, 256 x 256), and a ragged M there
+                                   # whole tiles but K no multiple of 64, few and many of them, and a ragged M there
                                    (256, 384, 96), (4096, 2560, 96), (4104, 2560, 96),
                                    (40, 24, 20)])         # K no multiple of 8: the scalar kernel
 def test_gemm_layouts(a_t, b_t, shape):
@@ -600,7 +599,10 @@ def test_gemm_two_workgroups_per_unit(M, N, K, a_t, b_t, epi):
     (4001, 4096, 96, False, True, 0), (1536, 4608, 65, True, True, 5), (1536, 4608, 641, True, True, 5),
     (3072, 3072, 321, True, True, 5), (4096, 4096, 130, True, True, 5), (4104, 4000, 1, True, True, 5),
     (3072, 4096, 700, True, True, 5), (8200, 4096, 64, False, False, 2), (8200, 4096, 96, False, False, 3),
-    (8200, 4104, 64, False, True, 4)])
+    (8200, 4104, 64, False, True, 4),
+    # K no multiple of 32: the register-staged kernel only, on both of its tiles
+    (4096, 2560, 72, False, True, 0), (4104, 2560, 40, False, False, 1), (300, 256, 136, False, True, 4),
+    (130, 264, 24, False, False, 3), (64, 19200, 65, True, True, 5)])
 def test_gemm_ragged_routes(M, N, K, a_t, b_t, epi):
     test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
 

@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import swarm_synth as synth
-from stage_util import run_gpu, run_oracle, compare
+from stage_util import run_gpu, run_oracle, compare, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -44,6 +44,35 @@ def test_small_ragged(dtype, shape):
                         n_repeat=R, grad_sigma=1.0 if dtype == "f32" else 1e-2, seed=4242 + d + S)
     _check(wl)
 
+
+@pytest.mark.parametrize("dtype,block", [("f32", "gelu"), ("f32", "rotary_geglu"), ("bf16", "gelu"), ("bf16", "rotary_geglu")])
+def test_matrices_at_odd_addresses(dtype, block):
+    """Weights, biases and their gradients one element past a 16-byte boundary: no kernel with vector accesses may take them,
+    and the sums and activations that others fuse run as kernels of their own."""
+    import paper_2301_11913_amd as sw
+    wl = synth.Workload(name="odd", dtype=dtype, d_model=128, n_heads=2, d_ffn=192, seq=37, batch=3, n_layers=1, n_repeat=2,
+                        grad_sigma=1.0 if dtype == "f32" else 1e-2, seed=31, block=block)
+    params, x, G = synth.make_params(wl), synth.make_x_in(wl), synth.make_grad_out(wl)
+
+    def shifted(t):
+        flat = torch.zeros(t.numel() + 1, dtype=t.dtype, device="cuda")
+        flat[1:] = t.reshape(-1)
+        return flat[1:].view(t.shape)
+
+    cfg = sw.StageConfig(wl.d_model, wl.n_heads, wl.d_ffn, 1, wl.n_repeat, wl.batch, wl.seq, dtype, wl.ln_eps, block)
+    place = lambda k, t: t if k.startswith("ln") else shifted(t)
+    dp = [{k: place(k, to_dev(params[0][k], wl)) for k in sw.PARAM_FIELDS}]
+    gp = [{k: place(k, torch.zeros(params[0][k].shape, device="cuda")) for k in sw.PARAM_FIELDS}]
+    xd, Gd = to_dev(x, wl), to_dev(G, wl)
+    y, gin = torch.full_like(xd, 7.0), torch.full_like(xd, 7.0)
+    ws = torch.empty(sw.swarm_stage_workspace_bytes(cfg, True), dtype=torch.uint8, device="cuda")
+    sw.swarm_stage_forward(cfg, dp, xd, y, ws)
+    sw.swarm_stage_backward(cfg, dp, xd, Gd, gin, gp, ws)
+    torch.cuda.synchronize()
+    f64 = lambda t: t.float().cpu().numpy().astype(np.float64)
+    gpu = {"x_out": f64(y), "grad_in": f64(gin), "grads": [{k: f64(g) for k, g in gp[0].items()}]}
+    errs, bad = compare(gpu, run_oracle(wl, params, x, G), TOL[dtype])
+    assert not bad, bad
 
 @pytest.mark.parametrize("case", [
     # dtype, d_model, heads: widths whose 8-element chunks do not fill the last pass of the LayerNorm kernels' lanes
