@@ -222,21 +222,34 @@ swarm_status gemm_bf16_launch(const GemmArgs& g, hipStream_t st);
 swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st);
 bool gemm_bf16_sums_rows(const GemmArgs& g);
 bool gemm_f32_takes(const GemmArgs& g);
+swarm_status gemm_bf16_wgrads(const GemmArgs* g, int n, hipStream_t st);
+swarm_status gemm_f32_wgrads(const GemmArgs* g, int n, hipStream_t st);
+
+#ifdef SWARM_KERNEL_HOOKS
+// fn() between an event pair, filed as a product [M, N] over K
+template <typename F>
+static swarm_status timed(double flops, int M, int N, int K, bool a_t, bool b_t, int epilogue, hipStream_t st, F&& fn) {
+  if (!g_timer.enabled || g_timer.used >= GemmTimer::kMax) return fn();
+  const int i = g_timer.used;
+  (void)hipEventRecord(g_timer.ev[2 * i], st);
+  const swarm_status s = fn();
+  if (s == SWARM_ERR_SHAPE) return s;      // nothing launched: the caller goes another way
+  (void)hipEventRecord(g_timer.ev[2 * i + 1], st);
+  g_timer.used++;
+  g_timer.flops[i] = flops;
+  int* sh = &g_timer.shape[6 * i];
+  sh[0] = M; sh[1] = N; sh[2] = K; sh[3] = a_t; sh[4] = b_t; sh[5] = epilogue;
+  return s;
+}
+#endif
 
 swarm_status gemm_bf16(const GemmArgs& g, hipStream_t st) {
 #ifdef SWARM_KERNEL_HOOKS
-  if (g_timer.enabled && g_timer.used < GemmTimer::kMax) {
-    const int i = g_timer.used++;
-    g_timer.flops[i] = 2.0 * g.M * g.N * g.K;
-    int* sh = &g_timer.shape[6 * i];
-    sh[0] = g.M; sh[1] = g.N; sh[2] = g.K; sh[3] = g.a_trans; sh[4] = g.b_trans; sh[5] = g.epilogue;
-    (void)hipEventRecord(g_timer.ev[2 * i], st);
-    swarm_status s = gemm_bf16_launch(g, st);
-    (void)hipEventRecord(g_timer.ev[2 * i + 1], st);
-    return s;
-  }
-#endif
+  return timed(2.0 * g.M * g.N * g.K, g.M, g.N, g.K, g.a_trans, g.b_trans, g.epilogue, st,
+               [&] { return gemm_bf16_launch(g, st); });
+#else
   return gemm_bf16_launch(g, st);
+#endif
 }
 
 static bool rows_of_eight(const GemmArgs& g) {
@@ -254,6 +267,39 @@ static bool rows_of_eight(const GemmArgs& g) {
 bool gemm_sums_rows(const GemmArgs& g, bool bf16) {
   if (!g.a_trans || g.epilogue != EPI_ACCUM_F32) return false;
   return bf16 ? rows_of_eight(g) && gemm_bf16_sums_rows(g) : gemm_f32_takes(g);
+}
+
+// One after the other, products may add to the same memory (a caller that ties two gradients, or gives all that it does not
+// want one buffer); at the same time they may not.
+static bool outputs_apart(const GemmArgs* g, int n) {
+  struct Range { uintptr_t lo, hi; } r[2 * kMaxWgrads];
+  int m = 0;
+  for (int i = 0; i < n; ++i) {
+    const uintptr_t c = (uintptr_t)g[i].C, s = (uintptr_t)g[i].rowsum;
+    r[m++] = {c, c + ((size_t)(g[i].M - 1) * g[i].ldc + g[i].N) * 4};
+    if (s) r[m++] = {s, s + (size_t)g[i].M * 4};
+  }
+  for (int i = 0; i < m; ++i)
+    for (int j = 0; j < i; ++j)
+      if (r[i].lo < r[j].hi && r[j].lo < r[i].hi) return false;
+  return true;
+}
+
+swarm_status gemm_wgrads(const GemmArgs* g, int n, bool bf16, hipStream_t st) {
+  if (n < 1 || n > kMaxWgrads || !outputs_apart(g, n)) return SWARM_ERR_SHAPE;
+  for (int i = 0; i < n; ++i)
+    if (!g[i].a_trans || !g[i].b_trans || g[i].epilogue != EPI_ACCUM_F32 || g[i].K != g[0].K || (bf16 && !rows_of_eight(g[i])))
+      return SWARM_ERR_SHAPE;
+  if (!bf16) return gemm_f32_wgrads(g, n, st);
+#ifdef SWARM_KERNEL_HOOKS
+  long long outputs = 0;
+  for (int i = 0; i < n; ++i) outputs += (long long)g[i].M * g[i].N;
+  const int N = g[n - 1].N;                // filed as one product of that many columns
+  return timed(2.0 * outputs * g[0].K, (int)(outputs / N), N, g[0].K, true, true, EPI_ACCUM_F32, st,
+               [&] { return gemm_bf16_wgrads(g, n, st); });
+#else
+  return gemm_bf16_wgrads(g, n, st);
+#endif
 }
 
 swarm_status gemm_bf16_launch(const GemmArgs& g, hipStream_t st) {

@@ -30,10 +30,12 @@ struct KArgs {
   long long* stamps;   // instrumented build only (nullptr otherwise): 16 words per workgroup, see gemm_bf16_k32_kernel
 };
 
+constexpr int kGroupM = 8;   // measured best of {2,4,8,16,32} on the d=4096 shapes
+
 // The kernel arguments of a product, uncut, tiles still to be chosen.
 inline KArgs kargs_of(const GemmArgs& g) {
   KArgs k{};
-  k.group_m = 8;   // measured best of {2,4,8,16,32} on the d=4096 shapes
+  k.group_m = kGroupM;
   k.A = (const bf16_raw*)g.A; k.B = (const bf16_raw*)g.B; k.M = g.M; k.N = g.N; k.K = g.K; k.lda = g.lda;
   k.ldb = g.ldb; k.C = g.C; k.ldc = g.ldc; k.epilogue = g.epilogue; k.bias = (const bf16_raw*)g.bias;
   k.aux = (const bf16_raw*)g.aux; k.ldaux = g.ldaux; k.C2 = (bf16_raw*)g.C2; k.ldc2 = g.ldc2; k.scales = g.scales;
@@ -57,6 +59,26 @@ __device__ __forceinline__ void tile_of_block(const KArgs& p, int& tile_m, int& 
   tile_m = first_m + (pid % per_group) % gsz;
   tile_n = (pid % per_group) / gsz;
 }
+
+// The same for weight gradients, whose kernels take several products in one launch (see WgradGroup): this workgroup's product
+// and its tile; false: nothing to do.
+__device__ __forceinline__ bool tile_of_block(const WgradGroup& g, KArgs& p, int& tile_m, int& tile_n) {
+  int tile;
+  const WgradProduct& q = g.q[wgrad_of_block(g, blockIdx.x, tile)];
+  p = KArgs{};
+  p.A = (const bf16_raw*)q.A; p.B = (const bf16_raw*)q.B; p.M = q.M; p.N = q.N; p.K = g.K; p.lda = q.lda; p.ldb = q.ldb;
+  p.C = q.C; p.ldc = q.ldc; p.epilogue = EPI_ACCUM_F32; p.rowsum = q.rowsum; p.tiles_m = q.tiles_m; p.tiles_n = q.tiles_n;
+  p.stream = g.stream; p.stamps = g.stamps;
+  const int per_group = kGroupM * q.tiles_n;
+  const int first_m = tile / per_group * kGroupM, gsz = min(q.tiles_m - first_m, kGroupM);
+  if (gsz <= 0) return false;
+  tile_m = first_m + tile % per_group % gsz;
+  tile_n = tile % per_group / gsz;
+  return tile_n < q.tiles_n;
+}
+// What a kernel for this layout is launched with.
+template <bool A_T> struct LaunchArgs { typedef KArgs type; };
+template <> struct LaunchArgs<true> { typedef WgradGroup type; };
 
 // acc[i][j][r] is C(row, col) with row = row0 + i*32 + 8*(r/4) + 4*lg + (r%4), col = col0 + j*32 + l32
 // (row0/col0 = first row/column of this wavefront's sub-tile).

@@ -17,7 +17,7 @@
 // One workgroup owns one output tile and walks K in order: deterministic.
 //
 // Two kernels share this file, both on v_mfma_f32_16x16x32_bf16: gemm_bf16_k32_kernel (256 x 256 and 256 x 128 tiles on
-// eight wavefronts: the dgrad and wgrad layouts, the rotary and GeGLU epilogues) and gemm_bf16_w4_kernel (256 x 256 tiles
+// eight wavefronts: the dgrad layout, weight gradients of any size and several in a launch, the rotary and GeGLU epilogues) and gemm_bf16_w4_kernel (256 x 256 tiles
 // on four wavefronts: the forward layout with the store / bias / residual / int8-encoding / GeLU epilogues).  They
 // accumulate a tile in the same order and give the same bits.  gemm_bf16_dma at the end decides which kernel a product
 // runs on: these, 128 x 128 tiles with two workgroups per unit (gemm_bf16_pair.hip), K over the wavefronts
@@ -132,6 +132,44 @@ struct TileLoad {
   }
 };
 
+// Both operands of a weight gradient: rows are k, so what lies behind the last token, or the last feature of the last row, has
+// to read as zero for any K, M and N to do.  Buffer loads whose descriptor ends with the operand do that; it moves along K with
+// scalar arithmetic, and a lane keeps one offset.
+template <int BR, int NW>
+struct BufferTile {
+  static constexpr int RPI = 64 / (BR / 8);   // k-rows per load instruction
+  const char* base;
+  size_t step, left;      // bytes from slice to slice, and to the operand's end
+  int slices;             // still to come; behind the last one zeros arrive and nothing is read
+  uint32_t off, hop;
+  __device__ __forceinline__ void init(const bf16_raw* p, int ld, int rows, int kdim, int r0, int wave, int lane) {
+    base = reinterpret_cast<const char*>(p + r0);
+    left = ((size_t)(kdim - 1) * ld + rows - r0) * 2;
+    step = (size_t)DBK * ld * 2;
+    slices = (kdim + DBK - 1) / DBK;
+    const int krow = wave * RPI + lane / (BR / 8);
+    const int chunk = (lane % (BR / 8)) ^ (4 * (krow & 3)) ^ (2 * ((krow >> 3) & 1));
+    off = (uint32_t)(krow * ld + chunk * 8) * 2u;
+    hop = (uint32_t)(NW * RPI * ld) * 2u;
+    static_assert(NW * RPI % 16 == 0, "the swizzle is the same in all loads of a lane");
+  }
+  // the t-th of this wavefront's loads of the current slice into the stage at `lds`
+  __device__ __forceinline__ void issue(bf16_raw* lds, int wave, int t) const {
+#if defined(__HIP_DEVICE_COMPILE__)   // the host pass knows neither the descriptor type nor its builtins
+    const uint32_t records = slices <= 0 ? 0u : left > 0xFFFFFFF0u ? 0xFFFFFFF0u : (uint32_t)left;
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), (short)0, (int)records, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, LDS_PTR(lds + (wave + t * NW) * 512), 16, off + t * hop, 0, 0, 0);
+#endif
+  }
+  __device__ __forceinline__ void next() {
+    if (--slices > 0) {
+      base += step;
+      left -= step;
+    }
+  }
+};
+
 template <int BR, int NW, bool TRANS>
 __device__ __forceinline__ void issue_tile(const bf16_raw* __restrict__ g, int ld, int r0, int k0, bf16_raw* lds,
                                            int wave, int lane, int glu_split = 0) {
@@ -223,7 +261,8 @@ constexpr int k32_younger(int prev, int cur, int i, int ia, int ib) {
 }
 
 template <int BM, int BN, int WM, int WN, bool A_T, bool B_T>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(KArgs p) {
+__global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(typename LaunchArgs<A_T>::type args) {
+  static_assert(!A_T || (B_T && BM == 256 && BN == 256), "a transposed A comes with weight gradients");
   constexpr int NW = WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN;
   constexpr int FM = WTM / 16, FN = WTN / 16;
@@ -242,12 +281,15 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(KArgs p) {
 #endif
 
   int tile_m, tile_n;
-  if (p.ksplit > 1) {
+  KArgs p;
+  if constexpr (A_T) {
+    if (!tile_of_block(args, p, tile_m, tile_n)) return;
+  } else if (p = args; p.ksplit > 1) {
     const int ntiles = p.tiles_m * p.tiles_n;
     const int part = blockIdx.x / ntiles;
     tile_of_block(p, tile_m, tile_n, blockIdx.x - part * ntiles);
     p.K /= p.ksplit;
-    p.A += A_T ? (size_t)part * p.K * p.lda : (size_t)part * p.K;
+    p.A += (size_t)part * p.K;
     p.B += B_T ? (size_t)part * p.K * p.ldb : (size_t)part * p.K;
     p.C = p.part + (size_t)part * p.M * p.N;
     p.ldc = p.N;
@@ -272,10 +314,40 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(KArgs p) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc.blk[i][j][r] = 0.f;
 
-  const int KT = p.K / DBK;
-  issue_tile<BM, NW, A_T>(p.A, p.lda, m0, 0, lds, wave, lane);
-  issue_tile<BN, NW, B_T>(p.B, p.ldb, n0, 0, lds + BM * DBK, wave, lane, glu);
-  {
+  // Row sums of A (the bias gradient beside a weight gradient).  The first two columns of tiles share a tile's rows, and in them
+  // every wavefront sums one of its eight fragment rows, the columns of wavefronts one apart: per slice two more fragment
+  // reads and two more MFMAs, against a column of ones, instead of a second read of A (a column sum of its own takes 13..23 us
+  // for 4096 tokens x 2048..8192).  They sit between the sub-steps, behind one branch: a test in every row of multiplies
+  // instead costs 9 % of the product, a second copy of the loop its registers.  Every 32 slices the sums move on to doubles, kept in LDS behind the stages: over shared
+  // layers K is up to 2^22, where one running fp32 sum loses.
+  f32x4 rsum = {0.f, 0.f, 0.f, 0.f};
+  const int sum_row = A_T && p.rowsum && tile_n < 2 ? 4 * tile_n + wn : -1;
+  double* total = reinterpret_cast<double*>(lds + NS * STAGE) + wm * WTM + 16 * max(sum_row, 0) + 4 * q;
+  const bool holds_sum = sum_row >= 0 && l16 == 0;
+  if (A_T && holds_sum) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) total[r] = 0.0;
+  }
+  static_assert(!A_T || (FM == 8 && WN == 4), "eight fragment rows over two columns of tiles and four of wavefronts");
+
+  const int KT = (p.K + DBK - 1) / DBK;
+  BufferTile<BM, NW> bufA;
+  BufferTile<BN, NW> bufB;
+  if constexpr (A_T) {
+    bufA.init(p.A, p.lda, p.M, p.K, m0, wave, lane);
+    bufB.init(p.B, p.ldb, p.N, p.K, n0, wave, lane);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int t = 0; t < IPA; ++t) bufA.issue(lds + s * STAGE, wave, t);
+#pragma unroll
+      for (int t = 0; t < IPW - IPA; ++t) bufB.issue(lds + s * STAGE + BM * DBK, wave, t);
+      bufA.next();
+      bufB.next();
+    }
+  } else {
+    issue_tile<BM, NW, A_T>(p.A, p.lda, m0, 0, lds, wave, lane);
+    issue_tile<BN, NW, B_T>(p.B, p.ldb, n0, 0, lds + BM * DBK, wave, lane, glu);
     const int k1 = min(1, KT - 1) * DBK;
     issue_tile<BM, NW, A_T>(p.A, p.lda, m0, k1, lds + STAGE, wave, lane);
     issue_tile<BN, NW, B_T>(p.B, p.ldb, n0, k1, lds + STAGE + BM * DBK, wave, lane, glu);
@@ -305,7 +377,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(KArgs p) {
 
   // loads inside the loop: split addresses where an operand is transposed (the k-contiguous forward layout keeps
   // issue_tile_one, which also knows the GeGLU row gather)
-  constexpr bool SPLIT_ADDR = A_T || B_T;
+  constexpr bool SPLIT_ADDR = !A_T && B_T;
   TileLoad<BM, NW, A_T> ldA;
   TileLoad<BN, NW, B_T> ldB;
   if constexpr (SPLIT_ADDR) {
@@ -342,7 +414,10 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(KArgs p) {
       if constexpr (f >= FM) nb[f - FM] = read_b(nA, f - FM, nkk);
       if constexpr (KIND == 1 && n >= FN + 2 && (n - FN) % GAP == 0 && (n - FN - 2) / GAP < IPW) {
         constexpr int t = (n - FN - 2) / GAP;
-        if constexpr (SPLIT_ADDR) {
+        if constexpr (A_T) {
+          if constexpr (t < IPA) bufA.issue(st, wave, t);
+          else bufB.issue(st + BM * DBK, wave, t - IPA);
+        } else if constexpr (SPLIT_ADDR) {
           if constexpr (t < IPA) ldA.issue(p.A, p.lda, m0, lk * DBK, st, wave, t);
           else ldB.issue(p.B, p.ldb, n0, lk * DBK, st + BM * DBK, wave, t - IPA);
         } else {
@@ -357,21 +432,49 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(KArgs p) {
     const bf16_raw* sA = lds + (kt & 1) * STAGE;
     const bf16_raw* nA = lds + ((kt + 1) & 1) * STAGE;
     substep(std::integral_constant<int, 0>{}, fb[0], fb[1], sA, 1, 0, 0);
+    if constexpr (A_T) {
+      if (sum_row >= 0) {
+        bf16x8 f0 = read_a(sA, sum_row, 0), f1 = read_a(sA, sum_row, 1);
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f0), "+v"(f1)::"memory");
+        const uint4 ones = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
+        rsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0, __builtin_bit_cast(bf16x8, ones), rsum, 0, 0, 0);
+        rsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1, __builtin_bit_cast(bf16x8, ones), rsum, 0, 0, 0);
+        if ((kt & 31) == 31) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (holds_sum) total[r] += (double)rsum[r];
+            rsum[r] = 0.f;
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
     // the stage of slice kt is free behind the barrier (the last iterations re-fetch the last slice instead of
     // branching)
     substep(std::integral_constant<int, 1>{}, fb[1], fb[0], nA, 0, min(kt + 2, KT - 1), kt & 1);
+    if constexpr (A_T) {
+      bufA.next();
+      bufB.next();
+    }
   }
   wait_vmcnt<0>();
   __builtin_amdgcn_s_waitcnt(0xC07F);
   __builtin_amdgcn_s_barrier();   // every wavefront is past its last LDS read: the stages become epilogue patches
+  if (A_T && holds_sum) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = m0 + wm * WTM + 16 * sum_row + 4 * q + r;
+      if (row < p.M) p.rowsum[row] += (float)(total[r] + (double)rsum[r]);
+    }
+  }
 #ifdef SWARM_KERNEL_HOOKS
   stamp[2] = wall_clock64();
   cyc[1] = clock64();
 #endif
 
-  gemm_epilogue<WTM / 32, WTN / 32, false>(p, acc, m0 + wm * WTM, glu ? n0 + wn * (WTN / 2) : n0 + wn * WTN,
-                                          lane & 31, lane >> 5,
-                                          reinterpret_cast<float*>(lds) + wave * 32 * kEpiPitch);
+  const int col0 = glu ? n0 + wn * (WTN / 2) : n0 + wn * WTN;
+  float* patch = reinterpret_cast<float*>(lds) + wave * 32 * kEpiPitch;
+  gemm_epilogue<WTM / 32, WTN / 32, A_T>(p, acc, m0 + wm * WTM, col0, lane & 31, lane >> 5, patch);
 #ifdef SWARM_KERNEL_HOOKS
   if (p.stamps) {
     wait_vmcnt<0>();   // the stores have left
@@ -738,6 +841,17 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(KArgs p) {
 int g_gemm_four_waves = 1;   // measurement switch of the instrumented build (swarm_kernel_gemm_four_waves)
 #endif
 
+// An output of at least twice the 32 MB of L2 cannot wait there for its consumer; written (and its residual /
+// pre-activation rows read) non-temporally it leaves the operand panels in the L2 instead.  A gradient that is added to is read
+// again by the next microbatch: it stays in the 256 MB memory-side cache, unless together with the operands it does not fit (8192
+// x 4096 over 1024 tokens 115 us streamed, 100 cached; 20480 x 4096 222, 237; four gradients of one set count together).
+bool streams_output(const GemmArgs& g) { return (size_t)g.M * g.N * 2 >= ((size_t)64 << 20); }
+bool streams_gradients(const GemmArgs* g, int n) {
+  size_t bytes = 0;
+  for (int i = 0; i < n; ++i) bytes += (size_t)g[i].M * g[i].N * 4 + ((size_t)g[i].M + g[i].N) * g[i].K * 2;
+  return bytes >= ((size_t)272 << 20);
+}
+
 swarm_status launch_w4(const KArgs& k, hipStream_t st) {
   constexpr size_t stage_bytes = (size_t)NS * 512 * DBK * sizeof(bf16_raw);
   constexpr size_t lds_bytes = stage_bytes > 4 * (size_t)kW4PatchBytes ? stage_bytes : 4 * (size_t)kW4PatchBytes;
@@ -749,33 +863,36 @@ swarm_status launch_w4(const KArgs& k, hipStream_t st) {
 }
 
 template <int BM, int BN, int WM, int WN, bool A_T, bool B_T>
-swarm_status launch_dma(const KArgs& k, hipStream_t st) {
-  constexpr size_t lds_bytes = (size_t)NS * (BM + BN) * DBK * sizeof(bf16_raw);
-  void (*kern)(KArgs) = gemm_bf16_k32_kernel<BM, BN, WM, WN, A_T, B_T>;
+swarm_status launch_dma(const typename LaunchArgs<A_T>::type& k, int workgroups, hipStream_t st) {
+  // weight gradients: the row sums' doubles behind the stages
+  constexpr size_t lds_bytes = (size_t)NS * (BM + BN) * DBK * sizeof(bf16_raw) + (A_T ? BM * sizeof(double) : 0);
+  auto kern = gemm_bf16_k32_kernel<BM, BN, WM, WN, A_T, B_T>;
   static LdsOptIn opted;   // per instantiation
   if (lds_opt_in((const void*)kern, lds_bytes, opted) != SWARM_OK) return SWARM_ERR_LAUNCH;
-  hipLaunchKernelGGL(kern, dim3(k.tiles_m * k.tiles_n * (k.ksplit > 1 ? k.ksplit : 1)), dim3(WM * WN * 64), lds_bytes,
-                     st, k);
+  hipLaunchKernelGGL(kern, dim3(workgroups), dim3(WM * WN * 64), lds_bytes, st, k);
   return launch_status();
 }
 
 template <int BM, int BN, int WM, int WN>
-swarm_status launch_dma_layout(const KArgs& k, bool a_t, bool b_t, hipStream_t st) {
+swarm_status launch_dma_layout(const KArgs& k, bool b_t, hipStream_t st) {
   if constexpr (BM == 256 && BN == 256) {
     // both operands k-contiguous and a short epilogue: four wavefronts of 128 x 128.  The epilogues with much
     // vector arithmetic (GeLU, rotary, GeGLU) stay on eight wavefronts: two per SIMD issue it twice as fast.
-    bool w4 = !a_t && !b_t && w4_epilogue_ok(k.epilogue);
+    bool w4 = !b_t && w4_epilogue_ok(k.epilogue);
 #ifdef SWARM_KERNEL_HOOKS
     w4 = w4 && g_gemm_four_waves;
 #endif
     if (w4) return launch_w4(k, st);
   }
-  if (!a_t && !b_t) return launch_dma<BM, BN, WM, WN, false, false>(k, st);
-  if (!a_t && b_t) return launch_dma<BM, BN, WM, WN, false, true>(k, st);
-  if constexpr (BM == 256 && BN == 256) {
-    if (a_t && b_t) return launch_dma<BM, BN, WM, WN, true, true>(k, st);
-  }
-  return SWARM_ERR_SHAPE;
+  const int workgroups = k.tiles_m * k.tiles_n * (k.ksplit > 1 ? k.ksplit : 1);
+  if (!b_t) return launch_dma<BM, BN, WM, WN, false, false>(k, workgroups, st);
+  return launch_dma<BM, BN, WM, WN, false, true>(k, workgroups, st);
+}
+
+swarm_status launch_wgrads_256(const GemmArgs* g, int n, hipStream_t st) {
+  WgradGroup w = wgrad_group_of(g, n, 256, 256);
+  w.stream = streams_gradients(g, n);
+  return launch_dma<256, 256, 2, 4, true, true>(w, w.tiles, st);
 }
 
 // ---- split-K: second kernel.  C = epilogue(part_0 + part_1 + ...), summed in index order; a lane owns 8 columns.
@@ -849,6 +966,7 @@ int splitk_parts_max(int M, int N) {
 }  // namespace
 
 swarm_status gemm_bf16_kw(const GemmArgs& g, int stream, hipStream_t st);
+swarm_status gemm_bf16_kw_wgrads(const GemmArgs* g, int n, hipStream_t st);
 swarm_status gemm_bf16_pair(const GemmArgs& g, int stream, hipStream_t st);
 bool gemm_bf16_kw_takes(const GemmArgs& g);
 
@@ -861,6 +979,8 @@ static bool enough_256_tiles(const GemmArgs& g) {
   return g.M % 256 == 0 && g.N % 256 == 0 && g.K % DBK == 0 && (long)(g.M / 256) * (g.N / 256) >= 160;
 }
 
+static long tiles_of(const GemmArgs& g, int t) { return (long)((g.M + t - 1) / t) * ((g.N + t - 1) / t); }
+
 // Whole 128 x 128 tiles, those that get here (few 256-row ones): gemm_bf16_pair instead of gemm_bf16_kw?  Measured in turn:
 //   more than 256 of them    forward and data gradient 3..45 % faster there (1920 x 8192, K = 2048: 74.6 against 89.8 us; 3968 x
 //                            4096, K = 1024 with GeLU: 46.7 / 61.2), weight gradients 5..60 % (2048 x 4096 over 8192 tokens
@@ -870,10 +990,9 @@ static bool enough_256_tiles(const GemmArgs& g) {
 //   129 to 256, short K      7..14 % at K = 256 (1920 x 2048: 7.1 / 8.0 us; weight gradients 20 %), 5 % at 512; not with an
 //                            epilogue that reads rows of its own (GeLU': 0.9 at 256);
 //   otherwise                gemm_bf16_kw by up to 2 x.
-// A weight gradient with row sums stays on gemm_bf16_kw, which spares the launches of a column sum (6..20 us).
 static bool two_tiles_per_unit(const GemmArgs& g) {
-  if (g.M % 128 || g.N % 128 || g.rowsum) return false;
-  const long tiles = (long)(g.M / 128) * (g.N / 128);
+  if (g.M % 128 || g.N % 128) return false;
+  const long tiles = tiles_of(g, 128);
   if (tiles > 256) return !(tiles > 512 && tiles <= 768 && g.b_trans && g.K >= (g.a_trans ? 2048 : 1536));
   return tiles > 128 && g.K <= 512 && g.epilogue != EPI_DGELU && g.epilogue != EPI_DGEGLU;
 }
@@ -886,33 +1005,60 @@ static bool two_tiles_per_unit(const GemmArgs& g) {
 //                     2..9 %, from 8192 on gemm_bf16_kw is ahead again unless the operands exceed the 256 MB memory-side
 //                     cache (10000 x 3072, K = 12288: 793 / 957); at 3 for 1 (6000 x 3072, K = 768 with GeLU) 75 / 62;
 //   data gradient     gemm_bf16_kw always, but for two rounds of it at K = 256 (5000 x 1024: 16.2 / 17.3);
-//   weight gradients  4 for 1 up to about 1400 tokens (4096 x 4096: 57 / 60 at 777, 87 / 85 at 1537), 3 for 1 up to 400 (3072 x
-//                     12288: 97 / 94 at 385); gradients of 240 MB and more with long rows up to 2560 (4096 x 16384: 347 / 397 at
-//                     1537; 8192 x 8192: 485 / 505 at 2500).  With the row sums inside gemm_bf16_kw (`sums`) the line lies where the launches of a column sum,
-//                     8 us, are made up for as well.
-static bool register_staged_is_faster(const GemmArgs& g, bool sums) {
+//   weight gradients  those that wgrad_alone leaves, two rounds for one and few tokens.
+static bool register_staged_is_faster(const GemmArgs& g) {
   if (g.M % 128 == 0 && g.N % 128 == 0 && g.K % DBK == 0) return false;
   if (g.epilogue == EPI_BIAS_GEGLU) return false;           // needs the gathered tile
-  auto tiles = [&](int t) { return (long)((g.M + t - 1) / t) * ((g.N + t - 1) / t); };
-  const long small = tiles(128), large = tiles(256);
+  const long small = tiles_of(g, 128), large = tiles_of(g, 256);
   if (large < 160) {
-    if (small <= 256 || sums) return false;
-    const int one_round = g.a_trans ? 640 : g.b_trans ? 256 : 1024, more = g.a_trans ? 320 : g.b_trans ? 0 : 512;
+    if (small <= 256) return false;
+    const int one_round = g.a_trans ? 640 : g.b_trans ? 256 : 1024, more = g.a_trans || g.b_trans ? 0 : 512;
     return g.K <= (small <= 512 ? one_round : more);
   }
   const long rs = (small + 255) / 256, rl = (large + 255) / 256;
-  if (g.a_trans) {
-    if ((long long)g.M * g.N >= (60ll << 20) && g.N >= 8192) return g.K <= 2560;
-    return g.K * rl <= 1000 * rs - (sums ? 3600 : 2600) * rl;
-  }
+  if (g.a_trans) return g.K * rl <= 1000 * rs - 2600 * rl;
   if (g.b_trans) return false;
   const bool beyond_cache = ((long long)g.M + g.N) * g.K * 2 > (256ll << 20);
   return g.K <= 1536 ? 2 * rs >= 7 * rl : (g.K <= 4096 || beyond_cache) && rs >= 4 * rl;
 }
 
-// A weight-gradient product that stays on the small tiles.
-bool gemm_bf16_sums_rows(const GemmArgs& g) {
-  return g.a_trans && g.b_trans && !enough_256_tiles(g) && gemm_bf16_kw_takes(g) && !register_staged_is_faster(g, true);
+// Weight gradients, n in one launch: 256 x 256 tiles instead of gemm_bf16_kw?  Any sizes (BufferTile); a round of large tiles
+// takes 2.2..2.7 times as long as one of 128 x 128, less for few tokens, where the epilogue is most of it.  Measured over d_model
+// 256..4096, 64..16000 tokens: at three rounds of small tiles for one 8..34 % faster (the four gradients of d_model 1024 over 4096
+// tokens 104 against 124 us), at 2.5 within 4 % either way at 1536 tokens, at two 2..20 % up to 512 tokens and 2..25 % slower
+// from 700.  The row sums need two columns of tiles.
+static bool wgrads_on_256_tiles(const GemmArgs* g, int n) {
+  long large = 0, small = 0;
+  for (int i = 0; i < n; ++i) {
+    if (g[i].rowsum && g[i].N <= 256) return false;
+    large += tiles_of(g[i], 256);
+    small += tiles_of(g[i], 128);
+  }
+  const long rl = (large + 255) / 256, rs = (small + 255) / 256;
+  return 10 * rs >= 29 * rl || (5 * rs >= 12 * rl && g[0].K <= 1536) || (rs >= 2 * rl && g[0].K <= 512);
+}
+
+// In one launch, each product's bias gradient with it: 42 us instead of 73 one by one at d_model 768 on 1665 tokens, 104
+// instead of 147 at 1024 on 4096, 8 instead of 29 at 256 on 512, 1200 instead of 1540 at 3072 on 5800.
+swarm_status gemm_bf16_wgrads(const GemmArgs* g, int n, hipStream_t st) {
+  for (int i = 0; i < n; ++i)
+    if (!gemm_bf16_kw_takes(g[i])) return SWARM_ERR_SHAPE;
+  if (wgrads_on_256_tiles(g, n)) return launch_wgrads_256(g, n, st);
+  return gemm_bf16_kw_wgrads(g, n, st);
+}
+
+// Whether a weight gradient can take the row sums along.
+bool gemm_bf16_sums_rows(const GemmArgs& g) { return g.a_trans && g.b_trans && gemm_bf16_kw_takes(g); }
+
+// One weight gradient without row sums has more kernels to choose from; SWARM_ERR_SHAPE: the register-staged one.  Ragged ones
+// where 256 x 256 tiles pay: 17152 x 3072 over 250 tokens 88 us against 97, 30464 x 768 38 against 48.
+static swarm_status wgrad_alone(const GemmArgs& g, hipStream_t st) {
+  const bool whole = g.M % 128 == 0 && g.N % 128 == 0 && g.K % DBK == 0, takes = gemm_bf16_kw_takes(g);
+  const long rl = (tiles_of(g, 256) + 255) / 256, rs = (tiles_of(g, 128) + 255) / 256;
+  if (takes && (whole ? enough_256_tiles(g) : 10 * rs >= 29 * rl)) return launch_wgrads_256(&g, 1, st);
+  if (register_staged_is_faster(g)) return SWARM_ERR_SHAPE;
+  if (whole && two_tiles_per_unit(g)) return gemm_bf16_pair(g, streams_gradients(&g, 1), st);
+  return gemm_bf16_kw(g, 0, st);
 }
 
 // Returns SWARM_ERR_SHAPE (nothing launched) for what the register-staged kernel takes.  The caller has checked
@@ -922,24 +1068,24 @@ bool gemm_bf16_sums_rows(const GemmArgs& g) {
 swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
   if (g.a_trans && !g.b_trans) return SWARM_ERR_SHAPE;
   if (g.epilogue == EPI_BIAS_GEGLU && (g.a_trans || g.b_trans || g.N != 2 * g.split || g.split % 64)) return SWARM_ERR_SHAPE;
-  if (!g.rowsum && register_staged_is_faster(g, false)) return SWARM_ERR_SHAPE;
+  if (g.a_trans && g.epilogue != EPI_ACCUM_F32) return SWARM_ERR_SHAPE;
+  if (g.a_trans) return g.rowsum ? gemm_bf16_wgrads(&g, 1, st) : wgrad_alone(g, st);
+  if (register_staged_is_faster(g)) return SWARM_ERR_SHAPE;
   KArgs k = kargs_of(g);
-  // An output of at least twice the 32 MB of L2 cannot wait there for its consumer; written (and its residual /
-  // pre-activation / gradient rows read) non-temporally it leaves the operand panels in the L2 instead.
-  k.stream = (size_t)g.M * g.N * (g.epilogue == EPI_ACCUM_F32 ? 4 : 2) >= ((size_t)64 << 20);
+  k.stream = streams_output(g);
   if (g.K % DBK) return gemm_bf16_kw(g, k.stream, st);
-  // Few output tiles, long K, no transposed A (forward and dgrad products of short microbatches): the 256 x 256
+  // Few output tiles, long K (forward and dgrad products of short microbatches): the 256 x 256
   // tiles at ksplit workgroups per tile fill the chip where 128 x 128 tiles would run at their lower rate.
   // Every part keeps at least 4096 of K, which is where the second kernel's pass over the partial sums pays.
   const bool epi_ok = g.epilogue == EPI_STORE || g.epilogue == EPI_BIAS || g.epilogue == EPI_BIAS_RESID ||
                       g.epilogue == EPI_BIAS_RESID_ENCODE;
-  if (g.splitk_ws && !g.a_trans && epi_ok && g.N % 64 == 0 && ((uintptr_t)g.splitk_ws & 15) == 0) {
+  if (g.splitk_ws && epi_ok && g.N % 64 == 0 && ((uintptr_t)g.splitk_ws & 15) == 0) {
     int parts = splitk_parts_max(g.M, g.N);
     while (parts > 1 && (g.K / parts < 4096 || g.K % (parts * DBK))) parts >>= 1;
     if (parts > 1 && g.splitk_floats >= (size_t)parts * g.M * g.N) {
       k.ksplit = parts; k.part = g.splitk_ws;
       k.tiles_m = g.M / 256; k.tiles_n = g.N / 256;
-      const swarm_status s = launch_dma_layout<256, 256, 2, 4>(k, g.a_trans, g.b_trans, st);
+      const swarm_status s = launch_dma_layout<256, 256, 2, 4>(k, g.b_trans, st);
       if (s != SWARM_OK) return s;
       const unsigned blocks = (unsigned)(((size_t)g.M * (g.N / 8) + 255) / 256);
       if (g.epilogue == EPI_STORE) hipLaunchKernelGGL(splitk_reduce_kernel<EPI_STORE>, dim3(blocks), dim3(256), 0, st, k);
@@ -953,7 +1099,7 @@ swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
   // A tile count that leaves the last round of 256 workgroups at most half full (384 tiles = 1.5 rounds for the
   // QKV product of a 2048-row microbatch): the columns that make whole rounds go first, the rest is a product of
   // its own (smaller tiles or a cut along K fill the chip there).  Column-local epilogues only.
-  if (!g.a_trans && g.M % 256 == 0 && g.N % 256 == 0 &&
+  if (g.M % 256 == 0 && g.N % 256 == 0 &&
       (g.epilogue == EPI_STORE || g.epilogue == EPI_BIAS || g.epilogue == EPI_BIAS_RESID ||
        g.epilogue == EPI_BIAS_RESID_ENCODE || g.epilogue == EPI_BIAS_GELU || g.epilogue == EPI_DGELU ||
        g.epilogue == EPI_BIAS_ROPE)) {
@@ -986,16 +1132,16 @@ swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st) {
   }
   if (enough_256_tiles(g)) {
     k.tiles_m = g.M / 256; k.tiles_n = g.N / 256;
-    return launch_dma_layout<256, 256, 2, 4>(k, g.a_trans, g.b_trans, st);
+    return launch_dma_layout<256, 256, 2, 4>(k, g.b_trans, st);
   }
   // Too few 256 x 256 tiles, but 256 x 128 tiles make one nearly full round (a 2048-row microbatch times a
   // 4096-wide weight: 256 tiles): one round of those beats two rounds of 128 x 128.  A wavefront's sub-tile is
   // 32 columns wide there, so GeGLU, whose gathered tile needs 64, goes on to the rules below.
-  if (!g.a_trans && g.M % 256 == 0 && g.N % 128 == 0 && g.epilogue != EPI_BIAS_GEGLU) {
+  if (g.M % 256 == 0 && g.N % 128 == 0 && g.epilogue != EPI_BIAS_GEGLU) {
     const long tiles = (long)(g.M / 256) * (g.N / 128);
     if (tiles >= 192 && tiles <= 256) {
       k.tiles_m = g.M / 256; k.tiles_n = g.N / 128;
-      return launch_dma_layout<256, 128, 2, 4>(k, g.a_trans, g.b_trans, st);
+      return launch_dma_layout<256, 128, 2, 4>(k, g.b_trans, st);
     }
   }
   if (two_tiles_per_unit(g)) return gemm_bf16_pair(g, k.stream, st);

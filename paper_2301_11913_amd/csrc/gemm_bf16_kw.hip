@@ -124,14 +124,20 @@ __device__ __forceinline__ void kw_wait_loads() {   // at most N loads of this w
 // NT: the bf16 epilogues' global accesses are non-temporal (see KArgs::stream; a kernel of its own, since two copies of the
 // epilogue in one cost the small launches 0.2..0.5 us of instruction fetch).
 template <int WM, int WN, int WK, int NS, bool A_T, bool B_T, bool NT>
-__global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(KArgs p) {
+__global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename LaunchArgs<A_T>::type args) {
   constexpr int NW = WM * WN * WK, NTHR = NW * 64;
   constexpr int BM = 64 * WM, BN = 64 * WN, BK = 32 * WK;
   static_assert(BK % 64 == 0 && BM * BK % (512 * NW) == 0 && BN * BK % (512 * NW) == 0, "loads split evenly");
   extern __shared__ __attribute__((aligned(1024))) bf16_raw lds[];
 
   int tile_m, tile_n;
-  tile_of_block(p, tile_m, tile_n);
+  KArgs p;
+  if constexpr (A_T) {
+    if (!tile_of_block(args, p, tile_m, tile_n)) return;
+  } else {
+    p = args;
+    tile_of_block(p, tile_m, tile_n);
+  }
   const int glu = (!B_T && p.epilogue == EPI_BIAS_GEGLU) ? p.split : 0;
   const int m0 = tile_m * BM, n0 = glu ? tile_n * (BN / 2) : tile_n * BN;
   const int lane = threadIdx.x & 63;
@@ -321,8 +327,8 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(KArgs p) 
     float x[8];
     sum8(rl, cl, x);
     if (epi == EPI_ACCUM_F32) {
-      // (never streamed: a 64 MB gradient partly stays in the memory-side cache between microbatches; 4096 x 4096 over 513
-      // tokens 50 -> 63 us with non-temporal accesses)
+      // (never streamed: what comes here mostly stays in the memory-side cache between microbatches; 4096 x 4096 over 513 tokens
+      // 50 -> 63 us with non-temporal accesses)
       float4* c = reinterpret_cast<float4*>(reinterpret_cast<float*>(p.C) + (size_t)(m0 + rl) * p.ldc + col);
       const float4 u = c[0], v = c[1];
       c[0] = make_float4(u.x + x[0], u.y + x[1], u.z + x[2], u.w + x[3]);
@@ -334,28 +340,36 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(KArgs p) 
 }
 
 template <int WM, int WN, int WK, int NS, bool A_T, bool B_T, bool NT = false>
-swarm_status launch(const KArgs& k, hipStream_t st) {
+swarm_status launch(const typename LaunchArgs<A_T>::type& k, int tiles, hipStream_t st) {
   constexpr int BM = 64 * WM, BN = 64 * WN, BK = 32 * WK;
   constexpr size_t stages = (size_t)NS * (BM + BN) * BK * 2, sums = (size_t)WK * BM * (BN + 4) * 4;
   constexpr size_t lds_bytes = stages > sums ? stages : sums;
   auto kern = gemm_bf16_kw_kernel<WM, WN, WK, NS, A_T, B_T, NT>;
   static LdsOptIn opted;   // per instantiation
   if (lds_opt_in((const void*)kern, lds_bytes, opted) != SWARM_OK) return SWARM_ERR_LAUNCH;
-  hipLaunchKernelGGL(kern, dim3(k.tiles_m * k.tiles_n), dim3(WM * WN * WK * 64), lds_bytes, st, k);
+  hipLaunchKernelGGL(kern, dim3(tiles), dim3(WM * WN * WK * 64), lds_bytes, st, k);
   return launch_status();
 }
 
 template <int WM, int WN, int WK, int NS>
-swarm_status launch_layout(KArgs k, bool a_t, bool b_t, hipStream_t st) {
+swarm_status launch_layout(const GemmArgs& g, int stream, hipStream_t st) {
+  KArgs k = kargs_of(g);
+  k.stream = stream;
   k.tiles_m = (k.M + 64 * WM - 1) / (64 * WM);
   k.tiles_n = (k.N + 64 * WN - 1) / (64 * WN);
+  const int tiles = k.tiles_m * k.tiles_n;
   if constexpr (WM == 2 && WN == 2) {      // an output of 64 MB has many tiles
-    if (k.stream && !a_t && !b_t) return launch<WM, WN, WK, NS, false, false, true>(k, st);
-    if (k.stream && !a_t) return launch<WM, WN, WK, NS, false, true, true>(k, st);
+    if (k.stream && !g.b_trans) return launch<WM, WN, WK, NS, false, false, true>(k, tiles, st);
+    if (k.stream) return launch<WM, WN, WK, NS, false, true, true>(k, tiles, st);
   }
-  if (!a_t && !b_t) return launch<WM, WN, WK, NS, false, false>(k, st);
-  if (!a_t) return launch<WM, WN, WK, NS, false, true>(k, st);
-  return launch<WM, WN, WK, NS, true, true>(k, st);
+  if (!g.b_trans) return launch<WM, WN, WK, NS, false, false>(k, tiles, st);
+  return launch<WM, WN, WK, NS, false, true>(k, tiles, st);
+}
+
+template <int WM, int WN, int WK, int NS>
+swarm_status launch_wgrads(const GemmArgs* g, int n, hipStream_t st) {
+  const WgradGroup w = wgrad_group_of(g, n, 64 * WM, 64 * WN);
+  return launch<WM, WN, WK, NS, true, true>(w, w.tiles, st);
 }
 
 }  // namespace
@@ -369,24 +383,37 @@ bool gemm_bf16_kw_takes(const GemmArgs& g) {
   return span * g.lda < (1ll << 30) && span * g.ldb < (1ll << 30);
 }
 
+// n weight gradients over the same rows, all of which gemm_bf16_kw_takes, in one launch; the rule of gemm_bf16_kw over the tiles
+// of all of them.
+swarm_status gemm_bf16_kw_wgrads(const GemmArgs* g, int n, hipStream_t st) {
+  long small = 0, mid = 0;
+  for (int i = 0; i < n; ++i) {
+    small += (long)((g[i].M + 63) / 64) * ((g[i].N + 63) / 64);
+    mid += (long)((g[i].M + 127) / 128) * ((g[i].N + 63) / 64);
+  }
+  if (small > 512) return launch_wgrads<2, 2, 2, 4>(g, n, st);
+  if (small > 256 && mid <= 256) return launch_wgrads<2, 1, 4, 3>(g, n, st);
+  if (small > 256) return launch_wgrads<1, 1, 4, 2>(g, n, st);
+  return launch_wgrads<1, 1, 4, 4>(g, n, st);
+}
+
 // SWARM_ERR_SHAPE (nothing launched): a k-contiguous operand whose K is no multiple of 32, or a tile whose offsets do
 // not fit 32 bits.  The caller has checked alignment (16-byte rows, N % 8 == 0) and the layout.  stream: see KArgs (8100 x
 // 16384, K = 4096 with GeLU 1224 -> 1180 us, its gradient 1284 -> 1208).
 swarm_status gemm_bf16_kw(const GemmArgs& g, int stream, hipStream_t st) {
   if (!gemm_bf16_kw_takes(g)) return SWARM_ERR_SHAPE;
-  KArgs k = kargs_of(g);
-  k.stream = stream;
   // By rounds of workgroups.  A 64-deep slice takes 0.7 us on a 128 x 128 tile, of which a compute unit holds one, and
   // 0.47 us on two 64 x 64 tiles with two stages.  So 128 x 128 tiles where a round (512) of 64 x 64 ones does not hold the
   // product: the last 1280 columns of a 50432-row vocabulary on 2048 tokens, K = 4096, 640 small or 160 large tiles: 74 ->
   // 45 us.  Up to there one round of 128 x 64 tiles with eight wavefronts instead of two 64 x 64 ones per unit, unless half
   // of those tiles' rows would be empty (a pass at d_model 768 on 5 x 333 tokens, 324 small tiles: 362 -> 356 us).  One
   // 64 x 64 tile per unit has four stages; a fifth changes nothing (365 us).
+  if (g.a_trans) return gemm_bf16_kw_wgrads(&g, 1, st);
   const long small = (long)((g.M + 63) / 64) * ((g.N + 63) / 64), mid = (long)((g.M + 127) / 128) * ((g.N + 63) / 64);
-  if (small > 512) return launch_layout<2, 2, 2, 4>(k, g.a_trans, g.b_trans, st);
-  if (small > 256 && mid <= 256) return launch_layout<2, 1, 4, 3>(k, g.a_trans, g.b_trans, st);
-  if (small > 256) return launch_layout<1, 1, 4, 2>(k, g.a_trans, g.b_trans, st);
-  return launch_layout<1, 1, 4, 4>(k, g.a_trans, g.b_trans, st);
+  if (small > 512) return launch_layout<2, 2, 2, 4>(g, stream, st);
+  if (small > 256 && mid <= 256) return launch_layout<2, 1, 4, 3>(g, stream, st);
+  if (small > 256) return launch_layout<1, 1, 4, 2>(g, stream, st);
+  return launch_layout<1, 1, 4, 4>(g, stream, st);
 }
 
 }  // namespace swarm

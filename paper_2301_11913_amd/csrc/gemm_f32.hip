@@ -51,19 +51,35 @@ struct Operand {
 
 __device__ __forceinline__ float comp(const float4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
+// What a kernel for this layout is launched with: weight gradients come several in a launch.
+template <bool A_T> struct F32Args { typedef GemmArgs type; };
+template <> struct F32Args<true> { typedef WgradGroup type; };
+
 // A workgroup: WM x WN x WK wavefronts; wavefront (wm, wn, wk) multiplies block (wm, wn) of 32 FM x 32 FN over the
 // wk-th part of K.
 template <int FM, int FN, int WM, int WN, int WK, bool A_T, bool B_T>
-__global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32Args<A_T>::type args, int tiles_m, int tiles_n) {
   constexpr int TM = 32 * FM * WM, TN = 32 * FN * WN, NT = WM * WN * WK * 64;
   constexpr int U = FM * FN == 1 ? 4 : 2;      // 8-deep steps per slice: 32 registers of fragments in flight
   constexpr int PITCH = TN + 4;
   extern __shared__ __attribute__((aligned(16))) float lds[];
 
   // contiguous bands of tiles per XCD, walked in groups of 8 tile rows
-  int pid = blockIdx.x;
-  const int ntiles = tiles_m * tiles_n;
-  if ((ntiles & 7) == 0) pid = (pid & 7) * (ntiles >> 3) + (pid >> 3);
+  int pid;
+  GemmArgs g;
+  if constexpr (A_T) {
+    const WgradProduct& q = args.q[wgrad_of_block(args, blockIdx.x, pid)];
+    g = GemmArgs{};
+    g.M = q.M; g.N = q.N; g.K = args.K; g.A = q.A; g.lda = q.lda; g.B = q.B; g.ldb = q.ldb; g.C = q.C; g.ldc = q.ldc;
+    g.epilogue = EPI_ACCUM_F32; g.rowsum = q.rowsum;
+    tiles_m = q.tiles_m; tiles_n = q.tiles_n;
+    if (pid >= tiles_m * tiles_n) return;
+  } else {
+    g = args;
+    pid = blockIdx.x;
+    const int ntiles = tiles_m * tiles_n;
+    if ((ntiles & 7) == 0) pid = (pid & 7) * (ntiles >> 3) + (pid >> 3);
+  }
   const int per_group = 8 * tiles_n, first = pid / per_group * 8, gsz = min(tiles_m - first, 8);
   const int m0 = (first + pid % per_group % gsz) * TM, n0 = pid % per_group / gsz * TN;
 
@@ -71,13 +87,19 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
   const int wk = wave % WK, wn = wave / WK % WN, wm = wave / WK / WN;
   const int l32 = lane & 31, lg = lane >> 5;
 
-  f32x16_t acc[FM][FN];
+  // Weight gradients of 32 x 32 blocks have four sets of sums, one per MFMA of an 8-deep step, and so a quarter as long chains of
+  // additions: several of them in a launch have enough tiles without dealing K to eight wavefronts, and lose nothing for it (d_model
+  // 256, 512 tokens, distance from 64 bits 2.1e-7 -> 1.2e-7).
+  constexpr int NS = A_T && FM * FN == 1 ? 4 : 1;
+  f32x16_t acc[FM][FN], more[NS];      // more[0] is not used
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+#pragma unroll
+  for (int c = 0; c < NS; ++c) more[c] = acc[0][0];
 
   // rows and columns past the end read the last one; what they produce is not stored
   Operand<A_T> a[FM];
@@ -105,7 +127,10 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(fa[i], c), comp(fb[j], c), acc[i][j], 0, 0, 0);
+        {
+          f32x16_t& sum = c > 0 && NS > 1 ? more[c < NS ? c : 0] : acc[i][j];
+          sum = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(fa[i], c), comp(fb[j], c), sum, 0, 0, 0);
+        }
   };
   const int nfull = max(kend - kbeg, 0) / (8 * U);
   if (nfull > 0) {
@@ -144,6 +169,7 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
     multiply(fa, fb);
   }
 
+  if constexpr (NS > 1) acc[0][0] = (acc[0][0] + more[1 % NS]) + (more[2 % NS] + more[3 % NS]);
   // acc[i][j][r] is the element (32 i + 8 (r / 4) + 4 lg + r % 4, 32 j + l32) of the block
   float* mine = lds + wk * TM * PITCH + wm * 32 * FM * PITCH + wn * 32 * FN;
 #pragma unroll
@@ -212,7 +238,7 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
 }
 
 template <int FM, int FN, int WM, int WN, int WK, bool A_T, bool B_T>
-swarm_status launch(const GemmArgs& g, hipStream_t st) {
+swarm_status launch(const typename F32Args<A_T>::type& g, int tm, int tn, int tiles, hipStream_t st) {
   constexpr int TM = 32 * FM * WM, TN = 32 * FN * WN;
   constexpr size_t lds_bytes = (size_t)WK * TM * (TN + 4) * sizeof(float);
   auto kern = gemm_f32_kernel<FM, FN, WM, WN, WK, A_T, B_T>;
@@ -220,16 +246,26 @@ swarm_status launch(const GemmArgs& g, hipStream_t st) {
     static LdsOptIn opted;   // per instantiation
     if (lds_opt_in((const void*)kern, lds_bytes, opted) != SWARM_OK) return SWARM_ERR_LAUNCH;
   }
-  const int tm = (g.M + TM - 1) / TM, tn = (g.N + TN - 1) / TN;
-  hipLaunchKernelGGL(kern, dim3((unsigned)tm * tn), dim3(WM * WN * WK * 64), lds_bytes, st, g, tm, tn);
+  hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(WM * WN * WK * 64), lds_bytes, st, g, tm, tn);
   return launch_status();
 }
 
+// n > 1: weight gradients
 template <int FM, int FN, int WM, int WN, int WK>
-swarm_status launch_layout(const GemmArgs& g, hipStream_t st) {
-  if (!g.a_trans && !g.b_trans) return launch<FM, FN, WM, WN, WK, false, false>(g, st);
-  if (!g.a_trans) return launch<FM, FN, WM, WN, WK, false, true>(g, st);
-  return launch<FM, FN, WM, WN, WK, true, true>(g, st);
+swarm_status launch_layout(const GemmArgs* g, int n, hipStream_t st) {
+  constexpr int TM = 32 * FM * WM, TN = 32 * FN * WN;
+  if constexpr (!(FM == 1 && WM == 2)) {
+    if (g->a_trans) {
+      const WgradGroup w = wgrad_group_of(g, n, TM, TN);
+      return launch<FM, FN, WM, WN, WK, true, true>(w, 0, 0, w.tiles, st);
+    }
+  }
+  const int tm = (g->M + TM - 1) / TM, tn = (g->N + TN - 1) / TN;
+  if constexpr (!(FM == 2 && WM == 1)) {
+    if (!g->b_trans) return launch<FM, FN, WM, WN, WK, false, false>(*g, tm, tn, tm * tn, st);
+    return launch<FM, FN, WM, WN, WK, false, true>(*g, tm, tn, tm * tn, st);
+  }
+  return SWARM_ERR_SHAPE;
 }
 
 }  // namespace
@@ -238,22 +274,46 @@ bool gemm_f32_takes(const GemmArgs& g) {
   auto al16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
   auto row_ok = [&](const void* q, int ld) { return !q || (al16(q) && ld % 4 == 0); };
   // rows of four in the epilogue, 16-byte fragment loads where k is contiguous
-  return g.epilogue <= EPI_ACCUM_F32 && !(g.a_trans && !g.b_trans) && g.N % 4 == 0 && al16(g.bias) &&
+  if (g.a_trans && (!g.b_trans || g.epilogue != EPI_ACCUM_F32)) return false;
+  return g.epilogue <= EPI_ACCUM_F32 && g.N % 4 == 0 && al16(g.bias) &&
          row_ok(g.C, g.ldc) && row_ok(g.aux, g.ldaux) && row_ok(g.C2, g.ldc2) &&
          (g.a_trans || (g.K % 8 == 0 && row_ok(g.A, g.lda))) &&
          (g.b_trans || (g.K % 8 == 0 && row_ok(g.B, g.ldb)));
 }
 
-swarm_status gemm_f32(const GemmArgs& g, hipStream_t st) {
-  if (!gemm_f32_takes(g)) return gemm_generic(g, false, st);
-  auto tiles = [&](int t) { return (long)((g.M + t - 1) / t) * ((g.N + t - 1) / t); };
+static swarm_status launch_by_size(const GemmArgs* g, int n, hipStream_t st) {
+  auto tiles = [&](int t) {
+    long sum = 0;
+    for (int i = 0; i < n; ++i) sum += (long)((g[i].M + t - 1) / t) * ((g[i].N + t - 1) / t);
+    return sum;
+  };
+  // Weight gradients: 64 x 64 per wavefront (half the fragment loads per flop of 32 x 32), K dealt to four, from 400 of those tiles
+  // on: the four gradients of d_model 768 over 1292 tokens 182 us (32 x 32 blocks: 207, 64 x 64 tiles of four with K whole: 212),
+  // 1024 over 2048 635 (753, 743); at 192 tiles (d_model 256, 512 tokens) 15.9 against 13.5.
+  if (g->a_trans) {
+    if (tiles(128) >= 1024) return launch_layout<2, 2, 2, 2, 1>(g, n, st);
+    if (tiles(64) >= 400) return launch_layout<2, 2, 1, 1, 4>(g, n, st);
+    if (tiles(32) >= 256) return launch_layout<1, 1, 1, 1, 4>(g, n, st);
+    return launch_layout<1, 1, 1, 1, 8>(g, n, st);
+  }
   // Large enough for a round of 128 x 128 tiles: 64 x 64 per wavefront, half the fragment loads per flop.  Otherwise
   // 64 x 64 tiles while they fill the chip, and below that one 32 x 32 block per workgroup, its K dealt to so many
   // wavefronts that every SIMD has one.
-  if (tiles(128) >= 256) return launch_layout<2, 2, 2, 2, 1>(g, st);
-  if (tiles(64) >= 256) return launch_layout<1, 1, 2, 2, 1>(g, st);
-  if (tiles(32) >= 256) return launch_layout<1, 1, 1, 1, 4>(g, st);
-  return launch_layout<1, 1, 1, 1, 8>(g, st);
+  if (tiles(128) >= 256) return launch_layout<2, 2, 2, 2, 1>(g, n, st);
+  if (tiles(64) >= 256) return launch_layout<1, 1, 2, 2, 1>(g, n, st);
+  if (tiles(32) >= 256) return launch_layout<1, 1, 1, 1, 4>(g, n, st);
+  return launch_layout<1, 1, 1, 1, 8>(g, n, st);
+}
+
+swarm_status gemm_f32(const GemmArgs& g, hipStream_t st) {
+  if (!gemm_f32_takes(g)) return gemm_generic(g, false, st);
+  return launch_by_size(&g, 1, st);
+}
+
+swarm_status gemm_f32_wgrads(const GemmArgs* g, int n, hipStream_t st) {
+  for (int i = 0; i < n; ++i)
+    if (!gemm_f32_takes(g[i])) return SWARM_ERR_SHAPE;
+  return launch_by_size(g, n, st);
 }
 
 }  // namespace swarm

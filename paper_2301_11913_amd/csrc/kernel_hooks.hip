@@ -26,6 +26,18 @@ extern "C" int swarm_kernel_gemm_rowsum(int dtype, int M, int N, int K, const vo
   return dtype ? gemm_bf16(g, (hipStream_t)stream) : gemm_f32(g, (hipStream_t)stream);
 }
 
+// n weight-gradient products over the same K rows in one launch: mn = M, N of each, pointers per product: A, B, dW, db (or NULL).
+extern "C" int swarm_kernel_wgrads(int dtype, int n, const int* mn, int K, void* const* ptrs, void* stream) {
+  GemmArgs g[kMaxWgrads] = {};
+  if (n < 1 || n > kMaxWgrads) return SWARM_ERR_SHAPE;
+  for (int i = 0; i < n; ++i) {
+    g[i].M = g[i].lda = mn[2 * i]; g[i].N = g[i].ldb = g[i].ldc = mn[2 * i + 1]; g[i].K = K; g[i].a_trans = g[i].b_trans = true;
+    g[i].A = ptrs[4 * i]; g[i].B = ptrs[4 * i + 1]; g[i].C = ptrs[4 * i + 2]; g[i].rowsum = (float*)ptrs[4 * i + 3];
+    g[i].epilogue = EPI_ACCUM_F32;
+  }
+  return gemm_wgrads(g, n, dtype != 0, (hipStream_t)stream);
+}
+
 // The same with split-K scratch (floats) that the bf16 kernel may use; swarm_kernel_gemm_splitk_floats says how much.
 extern "C" size_t swarm_kernel_gemm_splitk_floats(int M, int N) { return gemm_splitk_floats(M, N); }
 extern "C" int swarm_kernel_gemm_ws(int M, int N, int K, const void* A, int lda, int a_trans, const void* B, int ldb,

@@ -50,6 +50,48 @@ struct GemmArgs {
   long long* stamps;       // instrumented build only: 16 int64 per workgroup of the 256 x 256 kernel (phase stamps)
 };
 
+// Weight-gradient products over the same token rows (one parameter set's four), as ONE launch of their kernel takes them: the
+// workgroups of product i start at `first`, `tiles` in all.
+constexpr int kMaxWgrads = 4;
+struct WgradProduct {
+  const void* A; const void* B;   // [K, M], [K, N]
+  float* C;                       // [M, N] += A^T B
+  float* rowsum;                  // [M] += column sums of A, or nullptr
+  int M, N, lda, ldb, ldc;
+  int tiles_m, tiles_n, first;
+};
+struct WgradGroup {
+  WgradProduct q[kMaxWgrads];
+  int n, K, tiles;
+  int stream;                     // bf16: see KArgs
+  long long* stamps;              // bf16, instrumented build: see GemmArgs
+};
+inline WgradGroup wgrad_group_of(const GemmArgs* g, int n, int tile_m, int tile_n) {
+  WgradGroup w{};
+  w.n = n; w.K = g[0].K; w.stamps = g[0].stamps;
+  for (int i = 0; i < n; ++i) {
+    WgradProduct& q = w.q[i];
+    q.A = g[i].A; q.B = g[i].B; q.C = (float*)g[i].C; q.rowsum = g[i].rowsum; q.M = g[i].M; q.N = g[i].N; q.lda = g[i].lda;
+    q.ldb = g[i].ldb; q.ldc = g[i].ldc;
+    q.tiles_m = (q.M + tile_m - 1) / tile_m; q.tiles_n = (q.N + tile_n - 1) / tile_n;
+    q.first = w.tiles;
+    w.tiles += (q.tiles_m * q.tiles_n + 7) / 8 * 8;
+  }
+  return w;
+}
+// Which product workgroup `pid` works on, and which of its tiles.  Workgroups go to the 8 XCDs in turn; every XCD gets a contiguous
+// band of every product's tiles, one product after the other, so that all XCDs read the same operands at a time (bands of the
+// whole list instead: four gradients of a d_model 4096 block over 8192 tokens 2610 -> 3000 us).  A product's share of the list is
+// padded to a multiple of 8: tile >= its number means nothing to do.
+__device__ __forceinline__ int wgrad_of_block(const WgradGroup& g, int pid, int& tile) {
+  int i = 0;
+  while (i + 1 < g.n && pid >= g.q[i + 1].first) ++i;
+  const int tiles = g.q[i].tiles_m * g.q[i].tiles_n;
+  pid -= g.q[i].first;
+  tile = (pid & 7) * ((tiles + 7) >> 3) + (pid >> 3);
+  return i;
+}
+
 // Floats of split-K scratch that a bf16 product with an [M, N] output can make use of (0: it is never cut).
 size_t gemm_splitk_floats(int M, int N);
 
@@ -57,6 +99,9 @@ size_t gemm_splitk_floats(int M, int N);
 bool gemm_sums_rows(const GemmArgs& g, bool bf16);
 
 swarm_status gemm_f32(const GemmArgs& g, hipStream_t st);
+// n <= kMaxWgrads weight-gradient products (both operands transposed, EPI_ACCUM_F32, the same K, row sums wherever rowsum is
+// set) in one launch; SWARM_ERR_SHAPE (nothing launched) where they are better off, or only possible, one by one.
+swarm_status gemm_wgrads(const GemmArgs* g, int n, bool bf16, hipStream_t st);
 swarm_status gemm_bf16(const GemmArgs& g, hipStream_t st);
 // Generic (slow, any shape, either dtype) kernel behind both; `bf16` selects the element type.
 swarm_status gemm_generic(const GemmArgs& g, bool bf16, hipStream_t st);

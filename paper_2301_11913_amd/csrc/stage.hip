@@ -192,16 +192,12 @@ struct AppGrads {
   void *du, *dh, *dqkv;
 };
 
-// dW[out,in] += dY^T X  and  db[out] += colsum(dY)  over `rows` token rows: in one kernel where the product's takes the sums
-// along (training passes at d_model 256 in fp32 221 -> 189 us, 768 on 5 x 333 tokens 384 -> 356, two blocks of 1024 1432 -> 1379)
-swarm_status weight_grads(const Dims& D, int rows, const void* dY, int n_out, const void* X, int n_in, float* dW,
-                          float* db, float* partial, hipStream_t st) {
+// The product dW[out,in] += dY^T X over `rows` token rows, db[out] += colsum(dY) beside it.
+GemmArgs weight_grad(int rows, const void* dY, int n_out, const void* X, int n_in, float* dW, float* db) {
   GemmArgs w{};
   w.M = n_out; w.N = n_in; w.K = rows; w.A = dY; w.lda = n_out; w.a_trans = true; w.B = X; w.ldb = n_in;
-  w.b_trans = true; w.C = dW; w.ldc = n_in; w.epilogue = EPI_ACCUM_F32;
-  if (gemm_sums_rows(w, D.bf16)) w.rowsum = db;
-  else SWARM_TRY(colsum_accum(dY, rows, n_out, db, partial, D.bf16, st));
-  return gemm(D, w, st);
+  w.b_trans = true; w.C = dW; w.ldc = n_in; w.epilogue = EPI_ACCUM_F32; w.rowsum = db;
+  return w;
 }
 
 // dX[T,in] = dY[T,out] W[out,in]
@@ -263,10 +259,18 @@ swarm_status block_backward(const Dims& D, const swarm_block_params& p, const sw
 swarm_status set_weight_grads(const Dims& D, const swarm_block_grads& gp, int n, const void* dy, const AppGrads& ag,
                               const Saved& s, float* partial, hipStream_t st) {
   const int rows = n * D.T, d = D.d;
-  SWARM_TRY(weight_grads(D, rows, dy, d, s.g, D.f, gp.w_2, gp.b_2, partial, st));
-  SWARM_TRY(weight_grads(D, rows, ag.du, D.f1, s.c, d, gp.w_1, gp.b_1, partial, st));
-  SWARM_TRY(weight_grads(D, rows, ag.dh, d, s.o, d, gp.w_o, gp.b_o, partial, st));
-  SWARM_TRY(weight_grads(D, rows, ag.dqkv, 3 * d, s.a, d, gp.w_qkv, gp.b_qkv, partial, st));
+  GemmArgs w[4] = {weight_grad(rows, dy, d, s.g, D.f, gp.w_2, gp.b_2), weight_grad(rows, ag.du, D.f1, s.c, d, gp.w_1, gp.b_1),
+                   weight_grad(rows, ag.dh, d, s.o, d, gp.w_o, gp.b_o),
+                   weight_grad(rows, ag.dqkv, 3 * d, s.a, d, gp.w_qkv, gp.b_qkv)};
+  const swarm_status together = gemm_wgrads(w, 4, D.bf16, st);
+  if (together != SWARM_ERR_SHAPE) return together;
+  for (GemmArgs& g : w) {
+    if (!gemm_sums_rows(g, D.bf16)) {
+      SWARM_TRY(colsum_accum(g.A, rows, g.M, g.rowsum, partial, D.bf16, st));
+      g.rowsum = nullptr;
+    }
+    SWARM_TRY(gemm(D, g, st));
+  }
   return SWARM_OK;
 }
 

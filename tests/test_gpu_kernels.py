@@ -598,7 +598,7 @@ def test_gemm_two_workgroups_per_unit(M, N, K, a_t, b_t, epi):
     (2600, 4096, 96, False, False, 1), (3900, 4096, 4128, False, False, 0), (5000, 1024, 256, False, True, 4),
     (4001, 4096, 96, False, True, 0), (1536, 4608, 65, True, True, 5), (1536, 4608, 641, True, True, 5),
     (3072, 3072, 321, True, True, 5), (4096, 4096, 130, True, True, 5), (4104, 4000, 1, True, True, 5),
-    (3072, 4096, 700, True, True, 5), (8200, 4096, 64, False, False, 2), (8200, 4096, 96, False, False, 3),
+    (3072, 4096, 700, True, True, 5), (4104, 4104, 65, True, True, 5), (16392, 1544, 200, True, True, 5), (8200, 4096, 64, False, False, 2), (8200, 4096, 96, False, False, 3),
     (8200, 4104, 64, False, True, 4),
     # K no multiple of 32: the register-staged kernel only, on both of its tiles
     (4096, 2560, 72, False, True, 0), (4104, 2560, 40, False, False, 1), (300, 256, 136, False, True, 4),
@@ -628,11 +628,50 @@ def test_weight_gradient_row_sums(bf16, M, N, K):
     assert ((dW.cpu() - (dW0 + A.T @ B)).abs() <= (2 * K + 1) * 2.0 ** -24 * (A.abs().T @ B.abs() + dW0.abs())).all()
 
 
+# Several weight gradients over the same rows in one launch, bias gradients with them: every tile shape (64 x 64 with four and two
+# stages, 128 x 64, 128 x 128, 256 x 256; fp32 32, 64 and 128), each with one k value, a whole slice and parts of one, ragged M
+# and N, products smaller than a tile beside larger ones, and shares of the launch that are no multiple of 8 tiles.
+@pytest.mark.parametrize("bf16,K,shapes", [
+    (1, 1, [(64, 64), (192, 64)]), (1, 333, [(264, 520), (8, 264), (200, 72)]), (1, 130, [(136, 1032), (520, 2056), (264, 1032)]),
+    (1, 65, [(640, 640), (640, 640), (320, 704)]), (1, 513, [(1000, 1096), (512, 512), (768, 264), (24, 2048)]),
+    (1, 513, [(768, 1536), (1536, 768), (768, 768), (2304, 768)]), (1, 1, [(1032, 4104), (4104, 1032), (264, 1032), (520, 1032)]),
+    (1, 63, [(1032, 4104), (4104, 1032), (264, 1032), (3096, 1032)]), (1, 64, [(1024, 4096), (4096, 1024), (1024, 1024), (3072, 1024)]),
+    (1, 2113, [(1032, 4104), (4104, 1032), (1032, 1032), (3096, 1032)]), (1, 129, [(3080, 4104), (8, 264)]),
+    (0, 1, [(64, 64), (33, 36)]), (0, 77, [(256, 1024), (1024, 256), (256, 256), (768, 256)]),
+    (0, 130, [(1000, 1028), (777, 516), (64, 64)]), (0, 203, [(1024, 4096), (2052, 1024), (300, 68)])])
+def test_weight_gradients_in_one_launch(bf16, K, shapes):
+    lib = _lib()
+    g = torch.Generator(device="cuda").manual_seed(K + sum(map(sum, shapes)))
+    dt = torch.bfloat16 if bf16 else torch.float32
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    t = [(rn(K, M).to(dt), rn(K, N).to(dt), rn(M, N), rn(M)) for M, N in shapes]
+    want = [(A.double().T @ B.double() + W.double(), A.double().sum(0) + b.double(),
+             A.double().abs().T @ B.double().abs() + W.double().abs(), A.double().abs().sum(0) + b.double().abs())
+            for A, B, W, b in t]
+    for q in t[1::3]:                 # a bias gradient may be left out
+        q[3].fill_(7.0)
+    ptrs = [v.data_ptr() if j < 3 or i % 3 != 1 else None for i, q in enumerate(t) for j, v in enumerate(q)]
+    flat = [v for s in shapes for v in s]
+    call = lambda p: lib.swarm_kernel_wgrads(bf16, len(shapes), (C.c_int * len(flat))(*flat), K, (C.c_void_p * len(p))(*p), None)
+    assert call(ptrs) == 0
+    torch.cuda.synchronize()
+    # K additions (and products), each off by half an ulp of at most the sum of magnitudes
+    for i, ((A, B, W, b), (w64, b64, wsize, bsize)) in enumerate(zip(t, want)):
+        assert ((W.double() - w64).abs() <= (2 * K + 1) * 2.0 ** -24 * wsize).all()
+        if i % 3 == 1:
+            assert (b == 7.0).all()
+        else:
+            assert ((b.double() - b64).abs() <= (K + 1) * 2.0 ** -24 * bsize).all()
+    # two products that add to the same memory are not for one launch
+    ptrs[6] = ptrs[2]
+    assert call(ptrs) == -2
+
+
 # The same over very many rows (the applications of shared layers are one K).  The blocked column sum that these replace adds
 # at most 32 + 4 + ceil(K / 16384) + 24 values in a row, and every addition is off by half an ulp of at most the running sum of
 # magnitudes: with rows of one sign the errors are independent and few standard deviations (half the square root of the chain,
 # in ulps) cover 2048 rows.  A running sum over all K misses this by 2 to 6 times.
-@pytest.mark.parametrize("bf16,M,N,K", [(1, 256, 128, 131105), (1, 2048, 1024, 131072), (0, 256, 128, 131105),
+@pytest.mark.parametrize("bf16,M,N,K", [(1, 256, 128, 131105), (1, 2048, 1024, 131072), (1, 2048, 4096, 131105), (0, 256, 128, 131105),
                                         (0, 2048, 1024, 40000), (1, 64, 64, 1000003)])
 def test_row_sums_over_many_rows(bf16, M, N, K):
     lib = _lib()
