@@ -254,18 +254,13 @@ swarm_status launch(const typename F32Args<A_T>::type& g, int tm, int tn, int ti
 template <int FM, int FN, int WM, int WN, int WK>
 swarm_status launch_layout(const GemmArgs* g, int n, hipStream_t st) {
   constexpr int TM = 32 * FM * WM, TN = 32 * FN * WN;
-  if constexpr (!(FM == 1 && WM == 2)) {
-    if (g->a_trans) {
-      const WgradGroup w = wgrad_group_of(g, n, TM, TN);
-      return launch<FM, FN, WM, WN, WK, true, true>(w, 0, 0, w.tiles, st);
-    }
+  if (g->a_trans) {
+    const WgradGroup w = wgrad_group_of(g, n, TM, TN);
+    return launch<FM, FN, WM, WN, WK, true, true>(w, 0, 0, w.tiles, st);
   }
   const int tm = (g->M + TM - 1) / TM, tn = (g->N + TN - 1) / TN;
-  if constexpr (!(FM == 2 && WM == 1)) {
-    if (!g->b_trans) return launch<FM, FN, WM, WN, WK, false, false>(*g, tm, tn, tm * tn, st);
-    return launch<FM, FN, WM, WN, WK, false, true>(*g, tm, tn, tm * tn, st);
-  }
-  return SWARM_ERR_SHAPE;
+  if (!g->b_trans) return launch<FM, FN, WM, WN, WK, false, false>(*g, tm, tn, tm * tn, st);
+  return launch<FM, FN, WM, WN, WK, false, true>(*g, tm, tn, tm * tn, st);
 }
 
 }  // namespace
@@ -287,20 +282,18 @@ static swarm_status launch_by_size(const GemmArgs* g, int n, hipStream_t st) {
     for (int i = 0; i < n; ++i) sum += (long)((g[i].M + t - 1) / t) * ((g[i].N + t - 1) / t);
     return sum;
   };
-  // Weight gradients: 64 x 64 per wavefront (half the fragment loads per flop of 32 x 32), K dealt to four, from 400 of those tiles
-  // on: the four gradients of d_model 768 over 1292 tokens 182 us (32 x 32 blocks: 207, 64 x 64 tiles of four with K whole: 212),
-  // 1024 over 2048 635 (753, 743); at 192 tiles (d_model 256, 512 tokens) 15.9 against 13.5.
-  if (g->a_trans) {
-    if (tiles(128) >= 1024) return launch_layout<2, 2, 2, 2, 1>(g, n, st);
-    if (tiles(64) >= 400) return launch_layout<2, 2, 1, 1, 4>(g, n, st);
-    if (tiles(32) >= 256) return launch_layout<1, 1, 1, 1, 4>(g, n, st);
-    return launch_layout<1, 1, 1, 1, 8>(g, n, st);
-  }
-  // Large enough for a round of 128 x 128 tiles: 64 x 64 per wavefront, half the fragment loads per flop.  Otherwise
-  // 64 x 64 tiles while they fill the chip, and below that one 32 x 32 block per workgroup, its K dealt to so many
-  // wavefronts that every SIMD has one.
-  if (tiles(128) >= 256) return launch_layout<2, 2, 2, 2, 1>(g, n, st);
-  if (tiles(64) >= 256) return launch_layout<1, 1, 2, 2, 1>(g, n, st);
+  // 64 x 64 per wavefront loads half the fragments per flop of 32 x 32, and K dealt to the four wavefronts of a workgroup makes a
+  // 64 x 64 tile of it: four times as many workgroups as 128 x 128 tiles with K whole.  Measured in turn, us, on 64 x 64 tiles with K
+  // dealt | 32 x 32 with K dealt | 64 x 64 of four 32 x 32 with K whole | 128 x 128 with K whole:
+  //   forward         1292 x 3072, K = 768 (1008 tiles of 64)  62 | 105 | 95 | 108      2048 x 1024, K = 4096  143 | 242 | 231 | 325
+  //                   1292 x 768, K = 3072 (252)  65 | 99 | 92 | 251                    381 x 2048, K = 512 (192)  14.1 | 16.5 | 18 | 44
+  //                   512 x 1024, K = 256 (128)  9.3 | 8.1 | 11 | 25                    2048 x 4096, K = 1024 (2048)  152 | - | - | 143
+  //   data gradient   the lanes of a load share rows already, so 32 x 32 holds out longer: (252) 66 | 75 | 90, (192) 13.9 | 12.3 | 16
+  //   weight gradient the four of d_model 768 over 1292 tokens  182 | 207 | 212; 1024 over 2048  635 | 753 | 743 | 638;
+  //                   256 over 512 (192)  15.9 | 13.5 | 18.7
+  if (tiles(128) >= (g->a_trans ? 1024 : 448)) return launch_layout<2, 2, 2, 2, 1>(g, n, st);
+  if (tiles(64) >= (g->a_trans ? 400 : g->b_trans ? 240 : 160)) return launch_layout<2, 2, 1, 1, 4>(g, n, st);
+  // One 32 x 32 block per workgroup, its K dealt to so many wavefronts that every SIMD has one.
   if (tiles(32) >= 256) return launch_layout<1, 1, 1, 1, 4>(g, n, st);
   return launch_layout<1, 1, 1, 1, 8>(g, n, st);
 }

@@ -490,7 +490,12 @@ def test_attention_f32_scores_of_minus_infinity():
     (512, 256, 768, False, True, 0), (77, 1024, 256, False, True, 4), (1665, 768, 104, False, True, 4),
     (2085, 2048, 64, False, True, 0), (256, 1024, 511, True, True, 5), (768, 256, 37, True, True, 5),
     (1024, 1024, 203, True, True, 5), (2048, 2304, 130, True, True, 5), (100, 36, 5, True, True, 5),
-    (64, 30, 64, False, False, 1), (64, 64, 60, False, False, 0)])
+    (64, 30, 64, False, False, 1), (64, 64, 60, False, False, 0),
+    # either side of the tile counts that the dispatch changes at
+    (3390, 188, 72, False, False, 2), (1021, 640, 72, False, False, 3), (3390, 188, 8, False, False, 0),
+    (15290, 60, 40, False, True, 0), (953, 1024, 104, False, True, 4), (960, 1024, 8, False, True, 0),
+    (19070, 380, 64, False, False, 1), (3581, 2048, 64, False, False, 3), (3581, 2044, 40, False, True, 4),
+    (1344, 1212, 65, True, True, 5), (1280, 1276, 37, True, True, 5), (4096, 4092, 33, True, True, 5)])
 def test_gemm_f32(M, N, K, a_t, b_t, epi):
     lib = _lib()
     g = torch.Generator().manual_seed(M + N + K)
