@@ -4,9 +4,9 @@
 // still run one to a unit) leaves every compute unit with one, and what that one waits for between two slices of K (about a
 // microsecond from memory) is longer than what it multiplies in
 // one.  So a workgroup keeps NS slices in LDS, NS - 1 of them in flight, and divides K as well as the tile: WM x WN x WK
-// wavefronts, each multiplying a 64 x 64 block over its own 32 of the 32 * WK values of k in a slice.  That keeps the
-// LDS bytes per flop of a 64 x 64 block (16 fragment reads for 32 MFMAs) on a tile as small as 64 x 64, and gives a
-// 128 x 128 tile eight wavefronts, two per SIMD.  The WK partial blocks meet once, in LDS, and are added in index order;
+// wavefronts, each multiplying a 64 x 64 block (or, for the fewest tiles, 16 or 32 rows of one) over its own 32 of the 32 * WK
+// values of k in a slice.  That keeps the LDS bytes per flop of a 64 x 64 block (16 fragment reads for 32 MFMAs) on a tile as small
+// as 64 x 64, and gives a 128 x 128 tile eight wavefronts, two per SIMD.  The WK partial blocks meet once, in LDS, and are added in index order;
 // the epilogue then runs on rows of eight columns.
 //
 // Loads are buffer loads into LDS with the operand's exact size in the descriptor: what lies behind its last row reads
@@ -47,7 +47,7 @@ struct KwOperand {
   // rows r0 .. of an operand of `rows` rows and `kdim` k values; k starts at 0.  glu_split: see EPI_BIAS_GEGLU (B = W1,
   // every 64 tile rows are 32 gate rows and the 32 up rows of the same features; r0 counts features)
   __device__ __forceinline__ void init(const bf16_raw* p, int ld, int rows, int kdim, int r0, int glu_split, int wave,
-                                       int lane, int block, int wk) {
+                                       int lane, int block_row, int wk) {
     slices = (kdim + BK - 1) / BK;
     if constexpr (!TRANS) {
       base = reinterpret_cast<const char*>(p + (size_t)r0 * ld);
@@ -62,7 +62,7 @@ struct KwOperand {
       const int l16 = lane & 15, c = 4 * (wk & 1) + (lane >> 4);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        frag[i] = (uint32_t)((wk >> 1) * BR * 64 + (block * 64 + 16 * i + l16) * 64 + 8 * (c ^ (l16 & 7))) * 2u;
+        frag[i] = (uint32_t)((wk >> 1) * BR * 64 + (block_row + 16 * i + l16) * 64 + 8 * (c ^ (l16 & 7))) * 2u;
     } else {
       base = reinterpret_cast<const char*>(p + r0);
       left = ((size_t)(kdim - 1) * ld + rows - r0) * 2;
@@ -76,7 +76,7 @@ struct KwOperand {
       const int l16 = lane & 15, krow = 32 * wk + 8 * (lane >> 4) + (l16 >> 2);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int col = block * 64 + 16 * i + 4 * (l16 & 3);
+        const int col = block_row + 16 * i + 4 * (l16 & 3);
         frag[i] = (uint32_t)(krow * BR + 8 * ((col >> 3) ^ swz(krow)) + (col & 4)) * 2u;
       }
     }
@@ -124,10 +124,11 @@ __device__ __forceinline__ void kw_wait_loads() {   // at most N loads of this w
 
 // NT: the bf16 epilogues' global accesses are non-temporal (see KArgs::stream; a kernel of its own, since two copies of the
 // epilogue in one cost the small launches 0.2..0.5 us of instruction fetch).
-template <int WM, int WN, int WK, int NS, bool A_T, bool B_T, bool NT>
+template <int FM, int WM, int WN, int WK, int NS, bool A_T, bool B_T, bool NT>
 __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename LaunchArgs<A_T>::type args) {
   constexpr int NW = WM * WN * WK, NTHR = NW * 64;
-  constexpr int BM = 64 * WM, BN = 64 * WN, BK = 32 * WK;
+  constexpr int BM = 16 * FM * WM, BN = 64 * WN, BK = 32 * WK;
+  static_assert(FM == 4 || !A_T, "weight gradients have enough tiles");
   static_assert(BK % 64 == 0 && BM * BK % (512 * NW) == 0 && BN * BK % (512 * NW) == 0, "loads split evenly");
   extern __shared__ __attribute__((aligned(1024))) bf16_raw lds[];
 
@@ -147,8 +148,8 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename 
 
   KwOperand<BM, BK, NW, A_T> a;
   KwOperand<BN, BK, NW, B_T> b;
-  a.init(p.A, p.lda, p.M, p.K, m0, 0, wave, lane, wm, wk);
-  b.init(p.B, p.ldb, glu ? 2 * glu : p.N, p.K, n0, glu, wave, lane, wn, wk);
+  a.init(p.A, p.lda, p.M, p.K, m0, 0, wave, lane, wm * 16 * FM, wk);
+  b.init(p.B, p.ldb, glu ? 2 * glu : p.N, p.K, n0, glu, wave, lane, wn * 64, wk);
   constexpr int IPW = decltype(a)::NI + decltype(b)::NI;
   constexpr int STAGE = a.BYTES + b.BYTES;
   auto issue_one = [&](int stage, int t) __attribute__((always_inline)) {      // A's, then B's
@@ -161,9 +162,9 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename 
     b.next_slice();
   };
 
-  f32x4 acc[4][4];
+  f32x4 acc[FM][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -187,11 +188,20 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename 
   }
   const u32x4_kw ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
 
-  struct Frags { u32x4_kw a[4], b[4]; };
+  constexpr int NM = 4 * FM, NR = FM + 4;      // multiplies and fragment reads of a wavefront and slice
+  struct Frags { u32x4_kw a[FM], b[4]; };
   auto read_one = [&](int stage, Frags& f, int n) __attribute__((always_inline)) {
     const uint32_t tile = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)lds + (uint32_t)stage * STAGE;
-    if (n < 4) f.a[n & 3] = a.read(tile, n & 3);
-    else f.b[n & 3] = b.read(tile + a.BYTES, n & 3);
+    if (n < FM) f.a[n % FM] = a.read(tile, n % FM);
+    else f.b[(n - FM) & 3] = b.read(tile + a.BYTES, (n - FM) & 3);
+  };
+  // every fragment read so far has returned; nothing that uses one moves in front of this
+  auto arrived = [&](Frags& f) __attribute__((always_inline)) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < FM; ++i) asm volatile("" : "+v"(f.a[i])::"memory");
+#pragma unroll
+    for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(f.b[j])::"memory");
   };
 
 #pragma unroll
@@ -204,38 +214,38 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename 
   __builtin_amdgcn_s_barrier();
   Frags f0, f1;
 #pragma unroll
-  for (int n = 0; n < 8; ++n) read_one(0, f0, n);
+  for (int n = 0; n < NR; ++n) read_one(0, f0, n);
 
   // A unit takes in 64 bytes per clock, 512 clocks for a slice of 32 KB, as long as the multiplies and the fragment reads of a
-  // slice together: so a load goes out behind every GAP-th multiply and a read behind each of the first eight.  Requested in front
-  // of the multiplies, a wavefront waits for its loads to be taken before it multiplies (K = 4096 on one 64 x 64 tile 16.7 us, of
-  // which 11.9 without the multiplies and reads).
-  constexpr int GAP = 16 / IPW;
-  static_assert(IPW <= 16, "a load per multiply at most");
+  // slice together: so the loads are spread over the multiplies, the reads over the first half of them.  Requested in front of
+  // them, a wavefront waits for its loads to be taken before it multiplies (K = 4096 on one 64 x 64 tile 16.7 us, of which 11.9
+  // without the multiplies and reads; spread 13.2).
   int now = 0;      // stage of the current slice
   auto step = [&](Frags& cur, Frags& next, int k) __attribute__((always_inline)) {
     // this wavefront's fragments have arrived, and its part of the next slice
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(cur.a[0]), "+v"(cur.a[1]), "+v"(cur.a[2]), "+v"(cur.a[3]), "+v"(cur.b[0]), "+v"(cur.b[1]),
-                   "+v"(cur.b[2]), "+v"(cur.b[3])::"memory");
+    arrived(cur);
     kw_wait_loads<(NS - 2) * IPW>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     const int after = now + 1 == NS ? 0 : now + 1;
     if (k < p.K) {   // K of a k-contiguous operand is a multiple of 32: a wavefront's 32 are all in or all out
 #pragma unroll
-      for (int n = 0; n < 16; ++n) {
+      for (int n = 0; n < NM; ++n) {
         const int i = n >> 2, j = n & 3;
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur.a[i]),
                                                             __builtin_bit_cast(bf16x8, cur.b[j]), acc[i][j], 0, 0, 0);
-        if (n < 8) read_one(after, next, n);
-        if (n % GAP == GAP - 1 && n / GAP < IPW) issue_one(now, n / GAP);
+        if (n < NM / 2) {
+#pragma unroll
+          for (int r = n * NR / (NM / 2); r < (n + 1) * NR / (NM / 2); ++r) read_one(after, next, r);
+        }
+#pragma unroll
+        for (int t = n * IPW / NM; t < (n + 1) * IPW / NM; ++t) issue_one(now, t);
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (A_T) {
         if (sum_rows && wn == 0) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+          for (int i = 0; i < FM; ++i)
             if (sum_rows & (1 << i))
               rsum[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur.a[i]),
                                                                 __builtin_bit_cast(bf16x8, ones), rsum[i], 0, 0, 0);
@@ -243,7 +253,7 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename 
       }
     } else {
 #pragma unroll
-      for (int n = 0; n < 8; ++n) read_one(after, next, n);
+      for (int n = 0; n < NR; ++n) read_one(after, next, n);
 #pragma unroll
       for (int t = 0; t < IPW; ++t) issue_one(now, t);
     }
@@ -265,19 +275,17 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename 
     }
   }
   // the fragments requested last are not used, but have to arrive before their registers are
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(f0.a[0]), "+v"(f0.a[1]), "+v"(f0.a[2]), "+v"(f0.a[3]), "+v"(f0.b[0]), "+v"(f0.b[1]), "+v"(f0.b[2]),
-                 "+v"(f0.b[3])::"memory");
+  arrived(f0);
   kw_wait_loads<0>();
   __builtin_amdgcn_s_barrier();   // the stages are free: the partial blocks take their place
 
   constexpr int PITCH = BN + 4;
   float* sums = reinterpret_cast<float*>(lds);
   {
-    float* mine = sums + (wk * BM + wm * 64) * PITCH + wn * 64;
+    float* mine = sums + (wk * BM + wm * 16 * FM) * PITCH + wn * 64;
     const int l16 = lane & 15, q = lane >> 4;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -359,37 +367,37 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename 
   }
 }
 
-template <int WM, int WN, int WK, int NS, bool A_T, bool B_T, bool NT = false>
+template <int FM, int WM, int WN, int WK, int NS, bool A_T, bool B_T, bool NT = false>
 swarm_status launch(const typename LaunchArgs<A_T>::type& k, int tiles, hipStream_t st) {
-  constexpr int BM = 64 * WM, BN = 64 * WN, BK = 32 * WK;
+  constexpr int BM = 16 * FM * WM, BN = 64 * WN, BK = 32 * WK;
   constexpr size_t stages = (size_t)NS * (BM + BN) * BK * 2, sums = (size_t)WK * BM * (BN + 4) * 4;
   constexpr size_t lds_bytes = stages > sums ? stages : sums;
-  auto kern = gemm_bf16_kw_kernel<WM, WN, WK, NS, A_T, B_T, NT>;
+  auto kern = gemm_bf16_kw_kernel<FM, WM, WN, WK, NS, A_T, B_T, NT>;
   static LdsOptIn opted;   // per instantiation
   if (lds_opt_in((const void*)kern, lds_bytes, opted) != SWARM_OK) return SWARM_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(WM * WN * WK * 64), lds_bytes, st, k);
   return launch_status();
 }
 
-template <int WM, int WN, int WK, int NS>
+template <int WM, int WN, int WK, int NS, int FM = 4>
 swarm_status launch_layout(const GemmArgs& g, int stream, hipStream_t st) {
   KArgs k = kargs_of(g);
   k.stream = stream;
-  k.tiles_m = (k.M + 64 * WM - 1) / (64 * WM);
+  k.tiles_m = (k.M + 16 * FM * WM - 1) / (16 * FM * WM);
   k.tiles_n = (k.N + 64 * WN - 1) / (64 * WN);
   const int tiles = k.tiles_m * k.tiles_n;
   if constexpr (WM == 2 && WN == 2) {      // an output of 64 MB has many tiles
-    if (k.stream && !g.b_trans) return launch<WM, WN, WK, NS, false, false, true>(k, tiles, st);
-    if (k.stream) return launch<WM, WN, WK, NS, false, true, true>(k, tiles, st);
+    if (k.stream && !g.b_trans) return launch<FM, WM, WN, WK, NS, false, false, true>(k, tiles, st);
+    if (k.stream) return launch<FM, WM, WN, WK, NS, false, true, true>(k, tiles, st);
   }
-  if (!g.b_trans) return launch<WM, WN, WK, NS, false, false>(k, tiles, st);
-  return launch<WM, WN, WK, NS, false, true>(k, tiles, st);
+  if (!g.b_trans) return launch<FM, WM, WN, WK, NS, false, false>(k, tiles, st);
+  return launch<FM, WM, WN, WK, NS, false, true>(k, tiles, st);
 }
 
 template <int WM, int WN, int WK, int NS>
 swarm_status launch_wgrads(const GemmArgs* g, int n, hipStream_t st) {
   const WgradGroup w = wgrad_group_of(g, n, 64 * WM, 64 * WN);
-  return launch<WM, WN, WK, NS, true, true>(w, w.tiles, st);
+  return launch<4, WM, WN, WK, NS, true, true>(w, w.tiles, st);
 }
 
 }  // namespace
@@ -429,7 +437,15 @@ swarm_status gemm_bf16_kw(const GemmArgs& g, int stream, hipStream_t st) {
   // of those tiles' rows would be empty (a pass at d_model 768 on 5 x 333 tokens, 324 small tiles: 362 -> 356 us).  One
   // 64 x 64 tile per unit has four stages; a fifth changes nothing (365 us).
   if (g.a_trans) return gemm_bf16_kw_wgrads(&g, 1, st);
-  const long small = (long)((g.M + 63) / 64) * ((g.N + 63) / 64), mid = (long)((g.M + 127) / 128) * ((g.N + 63) / 64);
+  //
+  // Fewer 64 x 64 tiles than a quarter or half of the units: what bounds the workgroup is the bytes that its unit takes in, so it
+  // gets 16 or 32 rows, and the 16 rows K over eight wavefronts, unless K is shorter than four slices of that.  On 64 | 32 | 16 rows:
+  // 200 x 1024, K = 4096 14.3 | 10.7 | 9.4 us, K = 1024 7.0 | 5.4 | 5.1; 64 x 64, K = 256 4.9 | 4.0 | 4.2; 512 x 1024, K = 4096 15.1 |
+  // 10.9 | 19.4 (two rounds).  (32 rows on eight wavefronts lie between: 10.2, 5.6, 4.6, 11.0.)
+  const long cols = (g.N + 63) / 64;
+  if ((g.M + 15) / 16 * cols <= 256 && g.K >= 1024) return launch_layout<1, 1, 8, 3, 1>(g, stream, st);
+  if ((g.M + 31) / 32 * cols <= 256) return launch_layout<1, 1, 4, 4, 2>(g, stream, st);
+  const long small = (g.M + 63) / 64 * cols, mid = (g.M + 127) / 128 * cols;
   if (small > 512) return launch_layout<2, 2, 2, 4>(g, stream, st);
   if (small > 256 && mid <= 256) return launch_layout<2, 1, 4, 3>(g, stream, st);
   if (small > 256) return launch_layout<1, 1, 4, 2>(g, stream, st);

@@ -581,6 +581,18 @@ def test_gemm_rounds_of_small_tiles(M, N, K, a_t, b_t, epi):
     test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
 
 
+# Tiles of 16 and 32 rows for the fewest: one row, one more than a tile, either side of a round of each (256 workgroups) and of the
+# K that the 16 rows start at, a K that leaves wavefronts without a part, fewer slices than stages and an odd number of them.
+@pytest.mark.parametrize("M,N,K,a_t,b_t,epi", [
+    (1, 64, 1024, False, False, 0), (17, 72, 1056, False, False, 1), (256, 1024, 1120, False, False, 2),
+    (257, 1024, 1024, False, False, 3), (250, 1024, 992, False, False, 1), (33, 200, 4096, False, True, 4),
+    (4096, 64, 1312, False, True, 0), (64, 4096, 2080, False, True, 0), (33, 64, 32, False, False, 0),
+    (512, 1024, 96, False, False, 2), (513, 1024, 96, False, False, 3), (8192, 64, 352, False, False, 1),
+    (31, 16384, 64, False, True, 4), (500, 1000, 256, False, True, 0), (8190, 56, 992, False, True, 4)])
+def test_gemm_few_rows(M, N, K, a_t, b_t, epi):
+    test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
+
+
 # Whole 128 x 128 tiles, two workgroups per unit: either side of 128, 256, 512 and 768 of them, one slice, an odd number and
 # the longest K of its rules, every layout and epilogue (rotary, GeGLU and the encoding one through the stage tests).
 @pytest.mark.parametrize("M,N,K,a_t,b_t,epi", [
