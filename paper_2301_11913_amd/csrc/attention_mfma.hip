@@ -367,7 +367,7 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_fwd_kernel(const bf16_ra
     __builtin_amdgcn_s_barrier();
   }
 
-  if constexpr (KG > 1) {            // behind the last barrier the stages are free; one pass only
+  if constexpr (KG > 1) {            // behind the last barrier the stages are free
     float* part = reinterpret_cast<float*>(lds_all) + w * (16 * DB + 2) * 64 + lane;
     if (grp) {
 #pragma unroll
@@ -378,17 +378,19 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_fwd_kernel(const bf16_ra
       part[(16 * DB + 1) * 64] = l;
     }
     __syncthreads();
-    if (grp) return;
-    const float m1 = part[16 * DB * 64], l1 = part[(16 * DB + 1) * 64], top = fmaxf(m, m1);
-    const float f0 = __builtin_amdgcn_exp2f((m - top) * c), f1 = __builtin_amdgcn_exp2f((m1 - top) * c);
-    m = top;
-    l = l * f0 + l1 * f1;
+    if (!grp) {
+      const float m1 = part[16 * DB * 64], l1 = part[(16 * DB + 1) * 64], top = fmaxf(m, m1);
+      const float f0 = __builtin_amdgcn_exp2f((m - top) * c), f1 = __builtin_amdgcn_exp2f((m1 - top) * c);
+      m = top;
+      l = l * f0 + l1 * f1;
 #pragma unroll
-    for (int i = 0; i < DB; ++i)
+      for (int i = 0; i < DB; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[i][r] = oacc[i][r] * f0 + part[(16 * i + r) * 64] * f1;
+        for (int r = 0; r < 16; ++r) oacc[i][r] = oacc[i][r] * f0 + part[(16 * i + r) * 64] * f1;
+    }
+    __syncthreads();                 // the next pass loads into the stages again
   }
-  if (qrow < S) {
+  if (grp == 0 && qrow < S) {
     store_rowT<DB>(o + ((size_t)b * S + qrow) * d + h * DH, oacc, 1.0f / l, lg);
     if (lg == 0) lse[((size_t)b * H + h) * S + qrow] = m * (c / kLog2e) + logf(l);
   }
@@ -396,32 +398,6 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_fwd_kernel(const bf16_ra
 }
 
 // ---- backward -----------------------------------------------------------------------------------
-// delta[b,h,s] = sum_c dO[s, h, c] * O[s, h, c].  One workgroup per token; a head's dh/8 chunks sit in
-// adjacent lanes.
-template <int DH>
-__global__ __launch_bounds__(kThreads) void attn_delta_kernel(const bf16_raw* __restrict__ o,
-                                                              const bf16_raw* __restrict__ dout,
-                                                              float* __restrict__ delta, int S, int H) {
-  constexpr int LPH = DH / 8;   // lanes per head
-  const int token = blockIdx.x;
-  const int b = token / S, sidx = token % S;
-  const int d = H * DH;
-  for (int ch = threadIdx.x; ch < d / 8; ch += kThreads) {   // d/8 is a multiple of LPH, so whole heads stay together
-    const uint4 a = *reinterpret_cast<const uint4*>(o + (size_t)token * d + ch * 8);
-    const uint4 g = *reinterpret_cast<const uint4*>(dout + (size_t)token * d + ch * 8);
-    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, gw[4] = {g.x, g.y, g.z, g.w};
-    float acc = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      acc = fmaf(__uint_as_float(aw[i] << 16), __uint_as_float(gw[i] << 16), acc);
-      acc = fmaf(__uint_as_float(aw[i] & 0xFFFF0000u), __uint_as_float(gw[i] & 0xFFFF0000u), acc);
-    }
-#pragma unroll
-    for (int msk = LPH / 2; msk >= 1; msk >>= 1) acc += __shfl_xor(acc, msk, 64);
-    if ((ch % LPH) == 0) delta[((size_t)b * H + ch / LPH) * S + sidx] = acc;
-  }
-}
-
 // dK, dV: grid (ceil(S/128), H, B), 8 wavefronts.  Wavefronts w and w+4 both own key rows kv0+32w..+31;
 // the first computes dV (S -> P, dV^T += dO^T P), the second dK (S, dP -> dS, dK^T += Q^T dS), so each holds
 // one 32 x d_head accumulator and two wavefronts fit a SIMD.  Both read the same Q / dO tiles of 64 queries.
@@ -601,12 +577,27 @@ __global__ __launch_bounds__(kDkDvThreads) void attn_bwd_dkdv_kernel(const bf16_
   }   // pass
 }
 
-// dQ: tiles, wavefronts and groups as in the forward.
+// products of eight values each, summed in order
+__device__ __forceinline__ float dot8(const bf16x8& x, const bf16x8& y, float acc) {
+  const uint4 a = __builtin_bit_cast(uint4, x), g = __builtin_bit_cast(uint4, y);
+  const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, gw[4] = {g.x, g.y, g.z, g.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    acc = fmaf(__uint_as_float(aw[i] << 16), __uint_as_float(gw[i] << 16), acc);
+    acc = fmaf(__uint_as_float(aw[i] & 0xFFFF0000u), __uint_as_float(gw[i] & 0xFFFF0000u), acc);
+  }
+  return acc;
+}
+
+// dQ: tiles, wavefronts and groups as in the forward.  It runs before dK / dV and leaves delta[b,h,s] = sum_c dO[s,h,c] O[s,h,c]
+// for it: a row of dO is in its registers anyway, and a kernel of its own for this is another 1.5..3 us of a backward pass (one
+// sequence of 64, 4 heads 12.2 -> 10.6 us; 8 of 512, 16 heads 53.4 -> 50.1).
 template <int DH, int KG>
 __global__ __launch_bounds__(kThreads* KG, 2) void attn_bwd_dq_kernel(const bf16_raw* __restrict__ qkv,
                                                                   const bf16_raw* __restrict__ dout,
+                                                                  const bf16_raw* __restrict__ o,
                                                                   const float* __restrict__ lse,
-                                                                  const float* __restrict__ delta,
+                                                                  float* __restrict__ delta,
                                                                   bf16_raw* __restrict__ dqkv, int S, int H, int passes) {
   using T = Tile64<DH>;
   constexpr int KS = DH / 16, DB = DH / 32;
@@ -639,9 +630,13 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_bwd_dq_kernel(const bf16
     dof[ks] = global_frag(dO, d, qrow, S, 16 * ks + 8 * lg);
   }
   float L2 = 0.f, dl = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+    dl = dot8(global_frag(o + (size_t)b * S * d + h * DH, d, qrow, S, 16 * ks + 8 * lg), dof[ks], dl);
+  dl += __shfl_xor(dl, 32, 64);
   if (qrow < S) {
     L2 = lse[((size_t)b * H + h) * S + qrow] * kLog2e;
-    dl = delta[((size_t)b * H + h) * S + qrow];
+    if (grp == 0 && lg == 0) delta[((size_t)b * H + h) * S + qrow] = dl;
   }
   f32x16 dqacc[DB];
   zero(dqacc);
@@ -733,13 +728,15 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_bwd_dq_kernel(const bf16
         for (int r = 0; r < 16; ++r) part[(16 * i + r) * 64] = dqacc[i][r];
     }
     __syncthreads();
-    if (grp) return;
+    if (!grp) {
 #pragma unroll
-    for (int i = 0; i < DB; ++i)
+      for (int i = 0; i < DB; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) dqacc[i][r] += part[(16 * i + r) * 64];
+        for (int r = 0; r < 16; ++r) dqacc[i][r] += part[(16 * i + r) * 64];
+    }
+    __syncthreads();                 // the next pass loads into the stages again
   }
-  if (qrow < S) store_rowT<DB>(dqkv + ((size_t)b * S + qrow) * ld + h * DH, dqacc, scale, lg);
+  if (grp == 0 && qrow < S) store_rowT<DB>(dqkv + ((size_t)b * S + qrow) * ld + h * DH, dqacc, scale, lg);
   }   // pass
 }
 
@@ -748,16 +745,19 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_bwd_dq_kernel(const bf16
 // d_head 64 (one sequence of 256, 4 heads: forward 7.9 -> 7.5 us; of 128 6.7 -> 7.1, and one of 64 8 % slower, its second group
 // having nothing to do), from six at d_head 128 (384 tokens 12.8 -> 12.3; 192 8.4 -> 9.1).  Beyond that tiles go in
 // long-short pairs, which is what balances a launch of many rounds and costs nothing at one (two d_model 1024 blocks, 512
-// tiles: 18.9 us in pairs or singly).
+// tiles: 18.9 us in pairs or singly).  A pair per unit at most has two groups as well, where its merges are few: forward at d_head
+// 64, 16 heads, 8 x 512 tokens 16.3 -> 15.1 us, 3 x 1000 22.7 -> 19.4 (256 13.0 -> 13.1); at 128, 2048 tokens 52.3 -> 47.8 (512 24.3
+// -> 25.4).
 struct Layout {
   int passes, groups;
   unsigned grid;
 };
 Layout layout_of(int B, int S, int H, int dh) {
-  const int nt = (S + 127) / 128;
+  const int nt = (S + 127) / 128, keys = (S + 63) / 64;
   const int passes = (long long)nt * H * B <= 256 ? 1 : 2;
-  const int groups = passes == 1 && (S + 63) / 64 >= (dh == 64 ? 4 : 6) ? 2 : 1;
-  return {passes, groups, (unsigned)((passes == 2 ? (nt + 1) / 2 : nt) * H * B)};
+  const unsigned grid = (unsigned)((passes == 2 ? (nt + 1) / 2 : nt) * H * B);
+  const int enough = passes == 1 ? (dh == 64 ? 4 : 6) : (dh == 64 ? 8 : 16);
+  return {passes, grid <= 256 && keys >= enough ? 2 : 1, grid};
 }
 
 template <int DH, int KG>
@@ -771,13 +771,13 @@ swarm_status launch_fwd(const bf16_raw* qkv, bf16_raw* o, float* lse, int S, int
 }
 
 template <int DH, int KG>
-swarm_status launch_dq(const bf16_raw* qkv, const bf16_raw* dout, const float* lse, const float* delta, bf16_raw* dqkv,
-                       int S, int H, Layout L, hipStream_t st) {
+swarm_status launch_dq(const bf16_raw* qkv, const bf16_raw* dout, const bf16_raw* o, const float* lse, float* delta,
+                       bf16_raw* dqkv, int S, int H, Layout L, hipStream_t st) {
   constexpr size_t lds_bytes = (size_t)KG * 2 * 2 * 64 * DH * sizeof(bf16_raw);
   static LdsOptIn a0;
   if (lds_opt_in((const void*)attn_bwd_dq_kernel<DH, KG>, lds_bytes, a0) != SWARM_OK) return SWARM_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, KG>), dim3(L.grid), dim3(kThreads * KG), lds_bytes, st, qkv, dout, lse, delta,
-                     dqkv, S, H, L.passes);
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, KG>), dim3(L.grid), dim3(kThreads * KG), lds_bytes, st, qkv, dout, o, lse,
+                     delta, dqkv, S, H, L.passes);
   return launch_status();
 }
 
@@ -787,12 +787,13 @@ swarm_status launch_bwd(const bf16_raw* qkv, const bf16_raw* o, const bf16_raw* 
   constexpr size_t lds_dkdv = (size_t)2 * (2 * 64 * DH + 256) * sizeof(bf16_raw);
   static LdsOptIn a1;
   if (lds_opt_in((const void*)attn_bwd_dkdv_kernel<DH>, lds_dkdv, a1) != SWARM_OK) return SWARM_ERR_LAUNCH;
-  hipLaunchKernelGGL(attn_delta_kernel<DH>, dim3(B * S), dim3(kThreads), 0, st, o, dout, delta, S, H);
   const Layout L = layout_of(B, S, H, DH);
+  const swarm_status dq = L.groups == 2 ? launch_dq<DH, 2>(qkv, dout, o, lse, delta, dqkv, S, H, L, st)
+                                        : launch_dq<DH, 1>(qkv, dout, o, lse, delta, dqkv, S, H, L, st);
+  if (dq != SWARM_OK) return dq;
   hipLaunchKernelGGL(attn_bwd_dkdv_kernel<DH>, dim3(L.grid), dim3(kDkDvThreads), lds_dkdv, st, qkv, dout, lse, delta, dqkv,
                      S, H, L.passes);
-  if (L.groups == 2) return launch_dq<DH, 2>(qkv, dout, lse, delta, dqkv, S, H, L, st);
-  return launch_dq<DH, 1>(qkv, dout, lse, delta, dqkv, S, H, L, st);
+  return launch_status();
 }
 
 template <int DH>

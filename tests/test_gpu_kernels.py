@@ -329,7 +329,9 @@ def test_attention_bf16_launch_layouts(shape):
 
 # up to 256 tiles: one group of wavefronts while a row has fewer than four (d_head 64) or six (128) tiles of 64 keys, then two
 @pytest.mark.parametrize("shape", [(3, 192, 4, 64), (3, 193, 4, 64), (2, 256, 4, 64), (1, 257, 3, 64), (2, 320, 3, 128),
-                                   (2, 321, 3, 128), (1, 384, 3, 128), (40, 64, 6, 64), (40, 33, 6, 128)])
+                                   (2, 321, 3, 128), (1, 384, 3, 128), (40, 64, 6, 64), (40, 33, 6, 128),
+                                   # pairs of tiles, one pair per unit: either side of 8 (16) tiles of 64 keys, odd counts
+                                   (10, 448, 7, 64), (9, 450, 8, 64), (5, 600, 11, 64), (2, 1000, 17, 128), (2, 960, 17, 128)])
 def test_attention_bf16_wavefront_groups(shape):
     _attention_case(shape, 1.5)
 
