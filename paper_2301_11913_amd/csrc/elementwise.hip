@@ -476,50 +476,12 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict
   }
 }
 
-// Stage 2: out[c] += sum_p partial[p*stride + c].  Workgroup = 64 columns x RG row groups, each with eight running sums
-// (fixed assignment p mod 8, fixed combine order) that keep as many loads in flight.  Latency bound: with four row groups
-// the 512 partial rows of a LayerNorm backward are sixteen dependent rounds of loads, with sixteen groups four (training
-// passes at d_model 768 on 5 x 333 tokens 364 -> 356 us, two blocks of 1024 on 4096 tokens 1400 -> 1385, 2048 1793 -> 1778).
-// blockIdx.y = 1 (LayerNorm backward: dbeta next to dgamma in one launch) takes partial + C and out2.
-template <int RG>
-__global__ __launch_bounds__(64 * RG) void reduce_rows_accum_kernel(const float* __restrict__ partial, int P, int C,
-                                                                    size_t stride, float* __restrict__ out,
-                                                                    float* __restrict__ out2) {
-  __shared__ float red[RG][64];
-  if (blockIdx.y == 1) { partial += C; out = out2; }
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int rg = threadIdx.x >> 6;
-  const int per = (P + RG - 1) / RG;
-  const int p0 = rg * per, p1 = min(P, p0 + per);
-  float s = 0.f;
-  if (c < C) {
-    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int p = p0;
-    for (; p + 8 <= p1; p += 8) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) a[u] += partial[(size_t)(p + u) * stride + c];
-    }
-#pragma unroll
-    for (int u = 0; u < 7; ++u)
-      if (p + u < p1) a[u] += partial[(size_t)(p + u) * stride + c];
-    s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-  }
-  red[rg][threadIdx.x & 63] = s;
-  __syncthreads();
-  if (rg == 0 && c < C) {
-    const int l = threadIdx.x & 63;
-    float sum = red[0][l];
-#pragma unroll
-    for (int g = 1; g < RG; ++g) sum += red[g][l];
-    out[c] += sum;
-  }
-}
-
-// out2 != nullptr: two neighbouring sums of C columns each
-void reduce_rows(const float* partial, int P, int C, size_t stride, float* out, float* out2, hipStream_t st) {
-  const dim3 grid((C + 63) / 64, out2 ? 2 : 1);
-  if (P > 32) hipLaunchKernelGGL(reduce_rows_accum_kernel<16>, grid, dim3(1024), 0, st, partial, P, C, stride, out, out2);
-  else hipLaunchKernelGGL(reduce_rows_accum_kernel<4>, grid, dim3(256), 0, st, partial, P, C, stride, out, out2);
+// Stage 2, where it does not ride in the launch of the weight gradients (training passes at d_model 768 on 5 x 333 tokens with
+// sixteen row groups instead of four 364 -> 356 us, two blocks of 1024 on 4096 tokens 1400 -> 1385, 2048 1793 -> 1778).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void column_sums_kernel(ColumnSums s) {
+  __shared__ float red[THREADS / 64][64];
+  column_sums_block<THREADS>(s, blockIdx.x, red);
 }
 
 template <typename T, bool DEC, int MAXK = 0>
@@ -559,6 +521,14 @@ swarm_status ln_bwd_dispatch(const T* dy, const T* x, const float* mean, const f
 
 }  // namespace
 
+swarm_status column_sums(const ColumnSums& s, hipStream_t st) {
+  if (s.rows > 32) hipLaunchKernelGGL(column_sums_kernel<1024>, dim3(s.blocks), dim3(1024), 0, st, s);
+  else hipLaunchKernelGGL(column_sums_kernel<256>, dim3(s.blocks), dim3(256), 0, st, s);
+  return launch_status();
+}
+
+int layernorm_bwd_partial_rows(int T) { return (T + ln_rows_per_block(T) - 1) / ln_rows_per_block(T); }
+
 swarm_status layernorm_fwd(const void* x, const void* gamma, const void* beta, void* y, float* mean, float* rstd,
                            int T, int d, float eps, bool bf16, hipStream_t st) {
   if (bf16)
@@ -577,8 +547,7 @@ swarm_status layernorm_fwd_decode(const int8_t* codes, const void* scales, void*
 }
 
 size_t layernorm_bwd_scratch_floats(int T, int d) {
-  const int rpb = ln_rows_per_block(T);
-  return (size_t)((T + rpb - 1) / rpb) * 2 * d;
+  return (size_t)layernorm_bwd_partial_rows(T) * 2 * d;
 }
 
 // codes != nullptr: dx is not written; its int8 encoding goes to codes / scales (needs d % 256 == 0)
@@ -599,9 +568,8 @@ swarm_status layernorm_bwd(const void* dy, const void* x, const float* mean, con
     s = ln_bwd_dispatch<float, false>(a, b, mean, rstd, g, r, (float*)dx, partial, T, d, nullptr, nullptr, st);
   }
   if (s != SWARM_OK) return s;
-  const int P = (T + ln_rows_per_block(T) - 1) / ln_rows_per_block(T);
-  reduce_rows(partial, P, d, (size_t)2 * d, dgamma, dbeta, st);
-  return launch_status();
+  if (!dgamma) return SWARM_OK;
+  return column_sums(column_sums_of(partial, layernorm_bwd_partial_rows(T), d, (size_t)2 * d, 0, dgamma, dbeta, nullptr, nullptr), st);
 }
 
 // Fused LayerNorm + maxout_k (k in {2, 4, 8}, d % 8 == 0; anything else: SWARM_ERR_SHAPE, nothing launched).
@@ -646,9 +614,8 @@ swarm_status layernorm_bwd_maxout(const void* dz, const void* x, const float* me
   }
 #undef LN_MOB
   if (s != SWARM_OK) return s;
-  const int P = (T + ln_rows_per_block(T) - 1) / ln_rows_per_block(T);
-  reduce_rows(partial, P, d, (size_t)2 * d, dgamma, dbeta, st);
-  return launch_status();
+  if (!dgamma) return SWARM_OK;
+  return column_sums(column_sums_of(partial, layernorm_bwd_partial_rows(T), d, (size_t)2 * d, 0, dgamma, dbeta, nullptr, nullptr), st);
 }
 
 size_t colsum_scratch_floats(int T, int N) { return (size_t)((T + kCsRows - 1) / kCsRows) * N; }
@@ -660,8 +627,7 @@ swarm_status colsum_accum(const void* X, int T, int N, float* out, float* partia
     hipLaunchKernelGGL(colsum_partial_kernel<bf16_raw>, grid, dim3(256), 0, st, (const bf16_raw*)X, T, N, partial);
   else
     hipLaunchKernelGGL(colsum_partial_kernel<float>, grid, dim3(256), 0, st, (const float*)X, T, N, partial);
-  reduce_rows(partial, P, N, (size_t)N, out, nullptr, st);
-  return launch_status();
+  return column_sums(column_sums_of(partial, P, N, (size_t)N, 0, out, nullptr, nullptr, nullptr), st);
 }
 
 }  // namespace swarm

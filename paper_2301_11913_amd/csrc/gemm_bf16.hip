@@ -222,8 +222,8 @@ swarm_status gemm_bf16_launch(const GemmArgs& g, hipStream_t st);
 swarm_status gemm_bf16_dma(const GemmArgs& g, hipStream_t st);
 bool gemm_bf16_sums_rows(const GemmArgs& g);
 bool gemm_f32_takes(const GemmArgs& g);
-swarm_status gemm_bf16_wgrads(const GemmArgs* g, int n, hipStream_t st);
-swarm_status gemm_f32_wgrads(const GemmArgs* g, int n, hipStream_t st);
+swarm_status gemm_bf16_wgrads(const GemmArgs* g, int n, const ColumnSums* sums, hipStream_t st);
+swarm_status gemm_f32_wgrads(const GemmArgs* g, int n, const ColumnSums* sums, hipStream_t st);
 
 #ifdef SWARM_KERNEL_HOOKS
 // fn() between an event pair, filed as a product [M, N] over K
@@ -271,34 +271,35 @@ bool gemm_sums_rows(const GemmArgs& g, bool bf16) {
 
 // One after the other, products may add to the same memory (a caller that ties two gradients, or gives all that it does not
 // want one buffer); at the same time they may not.
-static bool outputs_apart(const GemmArgs* g, int n) {
-  struct Range { uintptr_t lo, hi; } r[2 * kMaxWgrads];
+static bool outputs_apart(const GemmArgs* g, int n, const ColumnSums* sums) {
+  struct Range { uintptr_t lo, hi; } r[2 * kMaxWgrads + 4];
   int m = 0;
   for (int i = 0; i < n; ++i) {
     const uintptr_t c = (uintptr_t)g[i].C, s = (uintptr_t)g[i].rowsum;
     r[m++] = {c, c + ((size_t)(g[i].M - 1) * g[i].ldc + g[i].N) * 4};
     if (s) r[m++] = {s, s + (size_t)g[i].M * 4};
   }
+  for (int i = 0; sums && i < sums->n_out; ++i) r[m++] = {(uintptr_t)sums->out[i], (uintptr_t)(sums->out[i] + sums->cols)};
   for (int i = 0; i < m; ++i)
     for (int j = 0; j < i; ++j)
       if (r[i].lo < r[j].hi && r[j].lo < r[i].hi) return false;
   return true;
 }
 
-swarm_status gemm_wgrads(const GemmArgs* g, int n, bool bf16, hipStream_t st) {
-  if (n < 1 || n > kMaxWgrads || !outputs_apart(g, n)) return SWARM_ERR_SHAPE;
+swarm_status gemm_wgrads(const GemmArgs* g, int n, const ColumnSums* sums, bool bf16, hipStream_t st) {
+  if (n < 1 || n > kMaxWgrads || !outputs_apart(g, n, sums)) return SWARM_ERR_SHAPE;
   for (int i = 0; i < n; ++i)
     if (!g[i].a_trans || !g[i].b_trans || g[i].epilogue != EPI_ACCUM_F32 || g[i].K != g[0].K || (bf16 && !rows_of_eight(g[i])))
       return SWARM_ERR_SHAPE;
-  if (!bf16) return gemm_f32_wgrads(g, n, st);
+  if (!bf16) return gemm_f32_wgrads(g, n, sums, st);
 #ifdef SWARM_KERNEL_HOOKS
   long long outputs = 0;
   for (int i = 0; i < n; ++i) outputs += (long long)g[i].M * g[i].N;
   const int N = g[n - 1].N;                // filed as one product of that many columns
   return timed(2.0 * outputs * g[0].K, (int)(outputs / N), N, g[0].K, true, true, EPI_ACCUM_F32, st,
-               [&] { return gemm_bf16_wgrads(g, n, st); });
+               [&] { return gemm_bf16_wgrads(g, n, sums, st); });
 #else
-  return gemm_bf16_wgrads(g, n, st);
+  return gemm_bf16_wgrads(g, n, sums, st);
 #endif
 }
 

@@ -135,6 +135,10 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename 
   int tile_m, tile_n;
   KArgs p;
   if constexpr (A_T) {
+    if ((int)blockIdx.x < args.sums.blocks) {
+      column_sums_block<NTHR>(args.sums, blockIdx.x, reinterpret_cast<float (*)[64]>(lds));
+      return;
+    }
     if (!tile_of_block(args, p, tile_m, tile_n)) return;
   } else {
     p = args;
@@ -395,9 +399,9 @@ swarm_status launch_layout(const GemmArgs& g, int stream, hipStream_t st) {
 }
 
 template <int WM, int WN, int WK, int NS>
-swarm_status launch_wgrads(const GemmArgs* g, int n, hipStream_t st) {
-  const WgradGroup w = wgrad_group_of(g, n, 64 * WM, 64 * WN);
-  return launch<4, WM, WN, WK, NS, true, true>(w, w.tiles, st);
+swarm_status launch_wgrads(const GemmArgs* g, int n, const ColumnSums* sums, hipStream_t st) {
+  const WgradGroup w = wgrad_group_of(g, n, sums, 64 * WM, 64 * WN);
+  return launch<4, WM, WN, WK, NS, true, true>(w, w.sums.blocks + w.tiles, st);
 }
 
 }  // namespace
@@ -413,16 +417,16 @@ bool gemm_bf16_kw_takes(const GemmArgs& g) {
 
 // n weight gradients over the same rows, all of which gemm_bf16_kw_takes, in one launch; the rule of gemm_bf16_kw over the tiles
 // of all of them.
-swarm_status gemm_bf16_kw_wgrads(const GemmArgs* g, int n, hipStream_t st) {
+swarm_status gemm_bf16_kw_wgrads(const GemmArgs* g, int n, const ColumnSums* sums, hipStream_t st) {
   long small = 0, mid = 0;
   for (int i = 0; i < n; ++i) {
     small += (long)((g[i].M + 63) / 64) * ((g[i].N + 63) / 64);
     mid += (long)((g[i].M + 127) / 128) * ((g[i].N + 63) / 64);
   }
-  if (small > 512) return launch_wgrads<2, 2, 2, 4>(g, n, st);
-  if (small > 256 && mid <= 256) return launch_wgrads<2, 1, 4, 3>(g, n, st);
-  if (small > 256) return launch_wgrads<1, 1, 4, 2>(g, n, st);
-  return launch_wgrads<1, 1, 4, 4>(g, n, st);
+  if (small > 512) return launch_wgrads<2, 2, 2, 4>(g, n, sums, st);
+  if (small > 256 && mid <= 256) return launch_wgrads<2, 1, 4, 3>(g, n, sums, st);
+  if (small > 256) return launch_wgrads<1, 1, 4, 2>(g, n, sums, st);
+  return launch_wgrads<1, 1, 4, 4>(g, n, sums, st);
 }
 
 // SWARM_ERR_SHAPE (nothing launched): a k-contiguous operand whose K is no multiple of 32, or a tile whose offsets do
@@ -436,7 +440,7 @@ swarm_status gemm_bf16_kw(const GemmArgs& g, int stream, hipStream_t st) {
   // 45 us.  Up to there one round of 128 x 64 tiles with eight wavefronts instead of two 64 x 64 ones per unit, unless half
   // of those tiles' rows would be empty (a pass at d_model 768 on 5 x 333 tokens, 324 small tiles: 362 -> 356 us).  One
   // 64 x 64 tile per unit has four stages; a fifth changes nothing (365 us).
-  if (g.a_trans) return gemm_bf16_kw_wgrads(&g, 1, st);
+  if (g.a_trans) return gemm_bf16_kw_wgrads(&g, 1, nullptr, st);
   //
   // Fewer 64 x 64 tiles than a quarter or half of the units: what bounds the workgroup is the bytes that its unit takes in, so it
   // gets 16 or 32 rows, and the 16 rows K over eight wavefronts, unless K is shorter than four slices of that.  On 64 | 32 | 16 rows:

@@ -68,7 +68,11 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32A
   int pid;
   GemmArgs g;
   if constexpr (A_T) {
-    const WgradProduct& q = args.q[wgrad_of_block(args, blockIdx.x, pid)];
+    if ((int)blockIdx.x < args.sums.blocks) {
+      column_sums_block<NT>(args.sums, blockIdx.x, reinterpret_cast<float (*)[64]>(lds));
+      return;
+    }
+    const WgradProduct& q = args.q[wgrad_of_block(args, blockIdx.x - args.sums.blocks, pid)];
     g = GemmArgs{};
     g.M = q.M; g.N = q.N; g.K = args.K; g.A = q.A; g.lda = q.lda; g.B = q.B; g.ldb = q.ldb; g.C = q.C; g.ldc = q.ldc;
     g.epilogue = EPI_ACCUM_F32; g.rowsum = q.rowsum;
@@ -252,11 +256,11 @@ swarm_status launch(const typename F32Args<A_T>::type& g, int tm, int tn, int ti
 
 // n > 1: weight gradients
 template <int FM, int FN, int WM, int WN, int WK>
-swarm_status launch_layout(const GemmArgs* g, int n, hipStream_t st) {
+swarm_status launch_layout(const GemmArgs* g, int n, const ColumnSums* sums, hipStream_t st) {
   constexpr int TM = 32 * FM * WM, TN = 32 * FN * WN;
   if (g->a_trans) {
-    const WgradGroup w = wgrad_group_of(g, n, TM, TN);
-    return launch<FM, FN, WM, WN, WK, true, true>(w, 0, 0, w.tiles, st);
+    const WgradGroup w = wgrad_group_of(g, n, sums, TM, TN);
+    return launch<FM, FN, WM, WN, WK, true, true>(w, 0, 0, w.sums.blocks + w.tiles, st);
   }
   const int tm = (g->M + TM - 1) / TM, tn = (g->N + TN - 1) / TN;
   if (!g->b_trans) return launch<FM, FN, WM, WN, WK, false, false>(*g, tm, tn, tm * tn, st);
@@ -276,7 +280,7 @@ bool gemm_f32_takes(const GemmArgs& g) {
          (g.b_trans || (g.K % 8 == 0 && row_ok(g.B, g.ldb)));
 }
 
-static swarm_status launch_by_size(const GemmArgs* g, int n, hipStream_t st) {
+static swarm_status launch_by_size(const GemmArgs* g, int n, const ColumnSums* sums, hipStream_t st) {
   auto tiles = [&](int t) {
     long sum = 0;
     for (int i = 0; i < n; ++i) sum += (long)((g[i].M + t - 1) / t) * ((g[i].N + t - 1) / t);
@@ -291,22 +295,22 @@ static swarm_status launch_by_size(const GemmArgs* g, int n, hipStream_t st) {
   //   data gradient   the lanes of a load share rows already, so 32 x 32 holds out longer: (252) 66 | 75 | 90, (192) 13.9 | 12.3 | 16
   //   weight gradient the four of d_model 768 over 1292 tokens  182 | 207 | 212; 1024 over 2048  635 | 753 | 743 | 638;
   //                   256 over 512 (192)  15.9 | 13.5 | 18.7
-  if (tiles(128) >= (g->a_trans ? 1024 : 448)) return launch_layout<2, 2, 2, 2, 1>(g, n, st);
-  if (tiles(64) >= (g->a_trans ? 400 : g->b_trans ? 240 : 160)) return launch_layout<2, 2, 1, 1, 4>(g, n, st);
+  if (tiles(128) >= (g->a_trans ? 1024 : 448)) return launch_layout<2, 2, 2, 2, 1>(g, n, sums, st);
+  if (tiles(64) >= (g->a_trans ? 400 : g->b_trans ? 240 : 160)) return launch_layout<2, 2, 1, 1, 4>(g, n, sums, st);
   // One 32 x 32 block per workgroup, its K dealt to so many wavefronts that every SIMD has one.
-  if (tiles(32) >= 256) return launch_layout<1, 1, 1, 1, 4>(g, n, st);
-  return launch_layout<1, 1, 1, 1, 8>(g, n, st);
+  if (tiles(32) >= 256) return launch_layout<1, 1, 1, 1, 4>(g, n, sums, st);
+  return launch_layout<1, 1, 1, 1, 8>(g, n, sums, st);
 }
 
 swarm_status gemm_f32(const GemmArgs& g, hipStream_t st) {
   if (!gemm_f32_takes(g)) return gemm_generic(g, false, st);
-  return launch_by_size(&g, 1, st);
+  return launch_by_size(&g, 1, nullptr, st);
 }
 
-swarm_status gemm_f32_wgrads(const GemmArgs* g, int n, hipStream_t st) {
+swarm_status gemm_f32_wgrads(const GemmArgs* g, int n, const ColumnSums* sums, hipStream_t st) {
   for (int i = 0; i < n; ++i)
     if (!gemm_f32_takes(g[i])) return SWARM_ERR_SHAPE;
-  return launch_by_size(g, n, st);
+  return launch_by_size(g, n, sums, st);
 }
 
 }  // namespace swarm

@@ -35,7 +35,7 @@ extern "C" int swarm_kernel_wgrads(int dtype, int n, const int* mn, int K, void*
     g[i].A = ptrs[4 * i]; g[i].B = ptrs[4 * i + 1]; g[i].C = ptrs[4 * i + 2]; g[i].rowsum = (float*)ptrs[4 * i + 3];
     g[i].epilogue = EPI_ACCUM_F32;
   }
-  return gemm_wgrads(g, n, dtype != 0, (hipStream_t)stream);
+  return gemm_wgrads(g, n, nullptr, dtype != 0, (hipStream_t)stream);
 }
 
 // The same with split-K scratch (floats) that the bf16 kernel may use; swarm_kernel_gemm_splitk_floats says how much.

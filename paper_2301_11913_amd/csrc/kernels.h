@@ -50,6 +50,55 @@ struct GemmArgs {
   long long* stamps;       // instrumented build only: 16 int64 per workgroup of the 256 x 256 kernel (phase stamps)
 };
 
+// Sums over the rows of a [rows, stride] matrix of partial sums, added to up to four vectors: out[2 i + j][c] += sum_p
+// partial[i * set + p * stride + j * cols + c] (LayerNorm backward: dgamma, dbeta, of one or two norms).
+struct ColumnSums {
+  const float* partial;
+  int rows, cols, n_out;
+  size_t stride, set;
+  float* out[4];
+  int blocks;         // workgroups that do it: 64 columns of one vector each
+};
+inline ColumnSums column_sums_of(const float* partial, int rows, int cols, size_t stride, size_t set, float* o0, float* o1,
+                                 float* o2, float* o3) {
+  ColumnSums c{partial, rows, cols, o2 ? 4 : o1 ? 2 : 1, stride, set, {o0, o1, o2, o3}, 0};
+  c.blocks = (cols + 63) / 64 * c.n_out;
+  return c;
+}
+// One of those workgroups, of THREADS: 64 columns x THREADS / 64 row groups, each with eight running sums (fixed assignment p mod
+// 8, fixed combine order) that keep as many loads in flight.  Latency bound: with four row groups the 512 partial rows of a
+// LayerNorm backward are sixteen dependent rounds of loads, with sixteen groups four.
+template <int THREADS>
+__device__ __forceinline__ void column_sums_block(const ColumnSums& s, int block, float (*red)[64]) {
+  constexpr int RG = THREADS / 64;
+  const int per_out = (s.cols + 63) / 64, o = block / per_out, l = threadIdx.x & 63, rg = threadIdx.x >> 6;
+  const int c = block % per_out * 64 + l;
+  const float* partial = s.partial + (o >> 1) * s.set + (size_t)(o & 1) * s.cols;
+  const int per = (s.rows + RG - 1) / RG, p0 = rg * per, p1 = min(s.rows, p0 + per);
+  float sum = 0.f;
+  if (c < s.cols) {
+    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    int p = p0;
+    for (; p + 8 <= p1; p += 8) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a[u] += partial[(size_t)(p + u) * s.stride + c];
+    }
+#pragma unroll
+    for (int u = 0; u < 7; ++u)
+      if (p + u < p1) a[u] += partial[(size_t)(p + u) * s.stride + c];
+    sum = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+  }
+  red[rg][l] = sum;
+  __syncthreads();
+  if (rg == 0 && c < s.cols) {
+    sum = red[0][l];
+#pragma unroll
+    for (int g = 1; g < RG; ++g) sum += red[g][l];
+    float* out = o == 0 ? s.out[0] : o == 1 ? s.out[1] : o == 2 ? s.out[2] : s.out[3];
+    out[c] += sum;
+  }
+}
+
 // Weight-gradient products over the same token rows (one parameter set's four), as ONE launch of their kernel takes them: the
 // workgroups of product i start at `first`, `tiles` in all.
 constexpr int kMaxWgrads = 4;
@@ -63,11 +112,13 @@ struct WgradProduct {
 struct WgradGroup {
   WgradProduct q[kMaxWgrads];
   int n, K, tiles;
+  ColumnSums sums;                // done by the first workgroups of the launch, sums.blocks of them
   int stream;                     // bf16: see KArgs
   long long* stamps;              // bf16, instrumented build: see GemmArgs
 };
-inline WgradGroup wgrad_group_of(const GemmArgs* g, int n, int tile_m, int tile_n) {
+inline WgradGroup wgrad_group_of(const GemmArgs* g, int n, const ColumnSums* sums, int tile_m, int tile_n) {
   WgradGroup w{};
+  if (sums) w.sums = *sums;
   w.n = n; w.K = g[0].K; w.stamps = g[0].stamps;
   for (int i = 0; i < n; ++i) {
     WgradProduct& q = w.q[i];
@@ -100,8 +151,9 @@ bool gemm_sums_rows(const GemmArgs& g, bool bf16);
 
 swarm_status gemm_f32(const GemmArgs& g, hipStream_t st);
 // n <= kMaxWgrads weight-gradient products (both operands transposed, EPI_ACCUM_F32, the same K, row sums wherever rowsum is
-// set) in one launch; SWARM_ERR_SHAPE (nothing launched) where they are better off, or only possible, one by one.
-swarm_status gemm_wgrads(const GemmArgs* g, int n, bool bf16, hipStream_t st);
+// set) in one launch, column sums with them (sums != nullptr); SWARM_ERR_SHAPE (nothing launched) where they are only possible
+// one by one.
+swarm_status gemm_wgrads(const GemmArgs* g, int n, const ColumnSums* sums, bool bf16, hipStream_t st);
 swarm_status gemm_bf16(const GemmArgs& g, hipStream_t st);
 // Generic (slow, any shape, either dtype) kernel behind both; `bf16` selects the element type.
 swarm_status gemm_generic(const GemmArgs& g, bool bf16, hipStream_t st);
@@ -113,6 +165,9 @@ swarm_status layernorm_fwd(const void* x, const void* gamma, const void* beta, v
 // dx = dres + LN-backward(dy) (dres == nullptr: no residual), dgamma += sum_t dy*xhat, dbeta += sum_t dy.
 // `partial` is scratch of layernorm_bwd_scratch_floats(T, d) floats.
 size_t layernorm_bwd_scratch_floats(int T, int d);
+// dgamma == nullptr: the sums stay in `partial`, [layernorm_bwd_partial_rows(T)][2 d] (dgamma | dbeta), for column_sums.
+int layernorm_bwd_partial_rows(int T);
+swarm_status column_sums(const ColumnSums& s, hipStream_t st);
 // With codes != nullptr dx is not stored: its int8 blockwise encoding is (fused stage-exit encode, bf16 and
 // d % 256 == 0 only).
 swarm_status layernorm_bwd(const void* dy, const void* x, const float* mean, const float* rstd, const void* gamma,

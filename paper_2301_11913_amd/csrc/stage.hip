@@ -182,6 +182,7 @@ struct BwdTemps {
   void *dc, *dout, *da;
   void* dg;   // GeGLU block only: gradient of g [T,f]
   float *delta, *partial;
+  float *ln1, *ln2;   // this application's partial sums of the LayerNorm parameter gradients
 };
 
 // Gradients that feed the weight-gradient GEMMs of one application: the gradient of the block output (dy, given),
@@ -209,11 +210,11 @@ swarm_status data_grad(const Dims& D, const void* dY, int n_out, const void* W, 
   return gemm(D, g, st);
 }
 
-// Data gradients and LayerNorm parameter gradients of one application; the matrix weight / bias gradients are
-// left to set_weight_grads, which reads dy and the tensors stored in `ag`.
-swarm_status block_backward(const Dims& D, const swarm_block_params& p, const swarm_block_grads& gp, const Saved& s,
-                            const BwdTemps& t, const AppGrads& ag, const void* dy, void* dx, hipStream_t st,
-                            int8_t* dx_codes = nullptr, void* dx_scales = nullptr, bool scales16 = false) {
+// Data gradients of one application and the partial sums of its LayerNorm parameter gradients; the parameter gradients are left
+// to set_weight_grads, which reads dy and the tensors stored in `ag`.
+swarm_status block_backward(const Dims& D, const swarm_block_params& p, const Saved& s, const BwdTemps& t,
+                            const AppGrads& ag, const void* dy, void* dx, hipStream_t st, int8_t* dx_codes = nullptr,
+                            void* dx_scales = nullptr, bool scales16 = false) {
   const int d = D.d, f = D.f;
   // y = h + g W2^T + b2,  g = gelu(u)  or  gelu(u_gate) * u_up
   if (D.rope_geglu) {
@@ -237,7 +238,7 @@ swarm_status block_backward(const Dims& D, const swarm_block_params& p, const sw
   // u = c W1^T + b1
   SWARM_TRY(data_grad(D, ag.du, D.f1, p.w_1, d, t.dc, EPI_STORE, nullptr, st));
   // c = LN2(h);  dh = dy + LN2'(dc)
-  SWARM_TRY(layernorm_bwd(t.dc, s.h, s.mean2, s.rstd2, p.ln2_g, dy, ag.dh, gp.ln2_g, gp.ln2_b, t.partial, D.T, d,
+  SWARM_TRY(layernorm_bwd(t.dc, s.h, s.mean2, s.rstd2, p.ln2_g, dy, ag.dh, nullptr, nullptr, t.ln2, D.T, d,
                           D.bf16, st));
   // h = x + o Wo^T + bo
   SWARM_TRY(data_grad(D, ag.dh, d, p.w_o, d, t.dout, EPI_STORE, nullptr, st));
@@ -247,8 +248,30 @@ swarm_status block_backward(const Dims& D, const swarm_block_params& p, const sw
   // qkv = a Wqkv^T + bqkv
   SWARM_TRY(data_grad(D, ag.dqkv, 3 * d, p.w_qkv, d, t.da, EPI_STORE, nullptr, st));
   // a = LN1(x);  dx = dh + LN1'(da)
-  SWARM_TRY(layernorm_bwd(t.da, s.x, s.mean1, s.rstd1, p.ln1_g, ag.dh, dx, gp.ln1_g, gp.ln1_b, t.partial, D.T, d,
+  SWARM_TRY(layernorm_bwd(t.da, s.x, s.mean1, s.rstd1, p.ln1_g, ag.dh, dx, nullptr, nullptr, t.ln1, D.T, d,
                           D.bf16, st, dx_codes, dx_scales, scales16));
+  return SWARM_OK;
+}
+
+// The LayerNorm parameter gradients of a set from the partial sums of `n` applications: with the weight gradients (`sums`), or
+// in a launch of their own where a set has more applications than there is room for.
+struct LnPartials {
+  float* base;        // [2 norms][slots][floats]
+  size_t floats;      // of one norm of one application: [layernorm_bwd_partial_rows][2 d]
+  int slots;
+};
+ColumnSums ln_column_sums(const Dims& D, const swarm_block_grads& gp, const LnPartials& L, int n) {
+  return column_sums_of(L.base, n * layernorm_bwd_partial_rows(D.T), D.d, (size_t)2 * D.d, L.slots * L.floats, gp.ln1_g,
+                        gp.ln1_b, gp.ln2_g, gp.ln2_b);
+}
+swarm_status add_ln_grads(const ColumnSums& c, hipStream_t st) {
+  bool apart = true;      // the two norms' gradients, that is: tied ones are added one after the other
+  for (int i = 0; i < 2; ++i)
+    for (int j = 2; j < 4; ++j) apart = apart && (c.out[i] + c.cols <= c.out[j] || c.out[j] + c.cols <= c.out[i]);
+  if (apart) return column_sums(c, st);
+  for (int i = 0; i < 2; ++i)
+    SWARM_TRY(column_sums(column_sums_of(c.partial + i * c.set, c.rows, c.cols, c.stride, 0, c.out[2 * i], c.out[2 * i + 1], nullptr,
+                                         nullptr), st));
   return SWARM_OK;
 }
 
@@ -257,13 +280,14 @@ swarm_status block_backward(const Dims& D, const swarm_block_params& p, const sw
 // the applications is the K dimension of a single product, dW += [dY_0; ...; dY_{n-1}]^T [X_0; ...; X_{n-1}],
 // so the fp32 gradient matrix is read and written once per set instead of once per application.
 swarm_status set_weight_grads(const Dims& D, const swarm_block_grads& gp, int n, const void* dy, const AppGrads& ag,
-                              const Saved& s, float* partial, hipStream_t st) {
+                              const Saved& s, const ColumnSums* ln, float* partial, hipStream_t st) {
   const int rows = n * D.T, d = D.d;
   GemmArgs w[4] = {weight_grad(rows, dy, d, s.g, D.f, gp.w_2, gp.b_2), weight_grad(rows, ag.du, D.f1, s.c, d, gp.w_1, gp.b_1),
                    weight_grad(rows, ag.dh, d, s.o, d, gp.w_o, gp.b_o),
                    weight_grad(rows, ag.dqkv, 3 * d, s.a, d, gp.w_qkv, gp.b_qkv)};
-  const swarm_status together = gemm_wgrads(w, 4, D.bf16, st);
+  const swarm_status together = gemm_wgrads(w, 4, ln, D.bf16, st);
   if (together != SWARM_ERR_SHAPE) return together;
+  if (ln) SWARM_TRY(add_ln_grads(*ln, st));
   for (GemmArgs& g : w) {
     if (!gemm_sums_rows(g, D.bf16)) {
       SWARM_TRY(colsum_accum(g.A, rows, g.M, g.rowsum, partial, D.bf16, st));
@@ -297,6 +321,10 @@ size_t plan_forward(const Dims& D, void* ws, FwdPlan& P) {
 // Token rows per weight-gradient product (a longer run of shared applications is cut into several products).
 constexpr long long kMaxWgradRows = 1ll << 22;
 
+// Applications of a set whose LayerNorm partial sums are kept (a launch for every norm of every application instead: four
+// applications of a d_model 256 block on 171 tokens, training, eight launches of 4..5 us).
+constexpr int kLnSlots = 8;
+
 int wgrad_chunk(const Dims& D, int R) {
   return (int)std::max<long long>(1, std::min<long long>(R, kMaxWgradRows / D.T));
 }
@@ -308,6 +336,7 @@ struct BwdPlan {
   char* app_slots;                        // [apps] slots of app_pitch bytes: qkv, h, u, row statistics, lse, input
   size_t app_pitch, off_h, off_u, off_stats, off_lse, off_x;
   BwdTemps t;
+  LnPartials ln;
   char *du_slots, *dh_slots, *dqkv_slots;   // [R] slots of [T,f1], [T,d], [T,3d]: one per application of a set
   char* dys[2];              // [R] slots of [T,d] (gradient of each application's output), by parameter-set parity
   float* rope;
@@ -341,9 +370,10 @@ size_t plan_backward(const Dims& D, int L, int R, void* ws, BwdPlan& P) {
   P.t.dg = D.rope_geglu ? cv.take(Tf) : nullptr;
   P.t.dc = cv.take(Td); P.t.dout = cv.take(Td); P.t.da = cv.take(Td);
   P.t.delta = (float*)cv.take((size_t)D.B * D.H * D.S * 4);
-  size_t pf = layernorm_bwd_scratch_floats(D.T, D.d);
-  pf = std::max(pf, colsum_scratch_floats(wgrad_chunk(D, R) * D.T, std::max(3 * D.d, D.f1)));
-  P.t.partial = (float*)cv.take(pf * 4);
+  P.t.partial = (float*)cv.take(colsum_scratch_floats(wgrad_chunk(D, R) * D.T, std::max(3 * D.d, D.f1)) * 4);
+  P.ln.floats = layernorm_bwd_scratch_floats(D.T, D.d);
+  P.ln.slots = std::min(R, kLnSlots);
+  P.ln.base = (float*)cv.take(2 * P.ln.slots * P.ln.floats * 4);
   P.splitk = splitk_floats_of(D) ? (float*)cv.take(splitk_floats_of(D) * 4) : nullptr;
   return cv.total();
 }
@@ -395,25 +425,36 @@ swarm_status run_backward(const Dims& D, const swarm_stage_config* cfg, const sw
   for (int l = L - 1; l >= 0; --l) {
     char* base = P.dys[l & 1];
     const bool from_caller = direct && l == L - 1;
+    int kept = 0;                // applications whose LayerNorm partial sums wait
     for (int r = R - 1; r >= 0; --r) {
       app = l * R + r;
+      if (kept == P.ln.slots) {
+        SWARM_TRY(add_ln_grads(ln_column_sums(D, grad_params[l], P.ln, kept), st));
+        kept = 0;
+      }
+      BwdTemps t = P.t;
+      t.ln1 = P.ln.base + kept * P.ln.floats;
+      t.ln2 = t.ln1 + P.ln.slots * P.ln.floats;
+      ++kept;
       const void* dy = from_caller ? grad_out : base + (size_t)r * Td;
       const AppGrads ag{P.du_slots + (size_t)r * Tf1, P.dh_slots + (size_t)r * Td, P.dqkv_slots + (size_t)r * 3 * Td};
       const Saved sv = saved_at(P, D, app, app == 0 ? x_in : input_buffer_at(P, app));
       if (app == 0) {
-        SWARM_TRY(block_backward(D, params[l], grad_params[l], sv, P.t, ag, dy, grad_in, st,
-                                 grad_in ? nullptr : gin_codes, grad_in ? nullptr : gin_scales, scales16));
+        SWARM_TRY(block_backward(D, params[l], sv, t, ag, dy, grad_in, st, grad_in ? nullptr : gin_codes,
+                                 grad_in ? nullptr : gin_scales, scales16));
       } else {
         void* dx = r > 0 ? base + (size_t)(r - 1) * Td : P.dys[(l - 1) & 1] + (size_t)(R - 1) * Td;
-        SWARM_TRY(block_backward(D, params[l], grad_params[l], sv, P.t, ag, dy, dx, st));
+        SWARM_TRY(block_backward(D, params[l], sv, t, ag, dy, dx, st));
       }
     }
+    const ColumnSums ln = ln_column_sums(D, grad_params[l], P.ln, kept);
     for (int r0 = 0; r0 < R; r0 += chunk) {
       const int n = std::min(chunk, R - r0);
       const void* dy = from_caller ? grad_out : base + (size_t)r0 * Td;
       const AppGrads ag{P.du_slots + (size_t)r0 * Tf1, P.dh_slots + (size_t)r0 * Td,
                         P.dqkv_slots + (size_t)r0 * 3 * Td};
-      SWARM_TRY(set_weight_grads(D, grad_params[l], n, dy, ag, saved_at(P, D, l * R + r0, nullptr), P.t.partial, st));
+      SWARM_TRY(set_weight_grads(D, grad_params[l], n, dy, ag, saved_at(P, D, l * R + r0, nullptr),
+                                 r0 == 0 ? &ln : nullptr, P.t.partial, st));
     }
   }
   return SWARM_OK;

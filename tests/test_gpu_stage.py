@@ -168,18 +168,47 @@ def test_forward_and_backward_replay_from_a_hip_graph():
                 assert torch.allclose(g[k].double(), n * one, rtol=1e-6, atol=1e-6 * float(one.abs().max())), (n, k)
 
 
-def test_shared_equals_unrolled_on_gpu():
-    wl = synth.Workload(name="shared", dtype="bf16", d_model=256, n_heads=2, d_ffn=512, seq=96, batch=2,
-                        n_layers=1, n_repeat=3, grad_sigma=1e-2, seed=77)
+# (8 applications' LayerNorm partial sums are kept before they are added up)
+@pytest.mark.parametrize("dtype,R,d,seq", [("bf16", 3, 256, 96), ("bf16", 8, 128, 40), ("bf16", 9, 128, 40), ("f32", 17, 128, 37)])
+def test_shared_equals_unrolled_on_gpu(dtype, R, d, seq):
+    wl = synth.Workload(name="shared", dtype=dtype, d_model=d, n_heads=2, d_ffn=512, seq=seq, batch=2,
+                        n_layers=1, n_repeat=R, grad_sigma=1e-2, seed=77)
     params, x, G = synth.make_params(wl), synth.make_x_in(wl), synth.make_grad_out(wl)
     shared = run_gpu(wl, params, x, G)
-    unrolled = run_gpu(wl.replace(n_layers=3, n_repeat=1), [params[0]] * 3, x, G)
+    unrolled = run_gpu(wl.replace(n_layers=R, n_repeat=1), [params[0]] * R, x, G)
     assert np.array_equal(shared["x_out"], unrolled["x_out"])
     assert np.array_equal(shared["grad_in"], unrolled["grad_in"])
     for k in shared["grads"][0]:
-        tot = sum(unrolled["grads"][l][k] for l in range(3))
+        tot = sum(unrolled["grads"][l][k] for l in range(R))
         den = np.max(np.abs(tot)) or 1.0
         assert np.max(np.abs(shared["grads"][0][k] - tot)) / den < 1e-5, k
+
+
+@pytest.mark.parametrize("dtype,tied", [
+    ("bf16", [("ln1_g", "ln2_g")]), ("bf16", [("b_o", "b_2")]), ("f32", [("ln1_b", "ln2_g"), ("b_o", "ln1_g")]),
+    ("f32", [("w_qkv", "w_1")]), ("bf16", [("w_1", "w_2"), ("b_2", "ln2_b")])])
+def test_tied_gradients(dtype, tied):
+    """Two parameters whose gradients are one buffer: what a launch adds up for both may not be added at the same time."""
+    import paper_2301_11913_amd as sw
+    wl = synth.Workload(name="tied", dtype=dtype, d_model=128, n_heads=2, d_ffn=384, seq=50, batch=2, n_layers=1, n_repeat=2,
+                        grad_sigma=1.0 if dtype == "f32" else 1e-2, seed=12)
+    params, x, G = synth.make_params(wl), synth.make_x_in(wl), synth.make_grad_out(wl)
+    apart = run_gpu(wl, params, x, G, forward=False)["grads"][0]
+    cfg = sw.StageConfig(wl.d_model, wl.n_heads, wl.d_ffn, 1, 2, wl.batch, wl.seq, dtype, wl.ln_eps, wl.block)
+    dp = [{k: to_dev(params[0][k], wl) for k in sw.PARAM_FIELDS}]
+    gp = [{k: torch.zeros(params[0][k].shape, device="cuda") for k in sw.PARAM_FIELDS}]
+    for a, b in tied:
+        gp[0][b] = gp[0][a].view(-1)[:gp[0][b].numel()].view(gp[0][b].shape)
+    xd, Gd = to_dev(x, wl), to_dev(G, wl)
+    gin = torch.empty_like(xd)
+    ws = torch.empty(sw.swarm_stage_workspace_bytes(cfg, True), dtype=torch.uint8, device="cuda")
+    sw.swarm_stage_backward(cfg, dp, xd, Gd, gin, gp, ws)
+    torch.cuda.synchronize()
+    for a, b in tied:
+        want, n = apart[a].reshape(-1).copy(), apart[b].size
+        want[:n] += apart[b].reshape(-1)
+        got = gp[0][a].double().cpu().numpy().reshape(-1)
+        assert np.max(np.abs(got - want)) <= 1e-5 * np.max(np.abs(want)), (a, b)
 
 
 def test_argument_validation_on_device():
