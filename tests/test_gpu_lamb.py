@@ -35,7 +35,9 @@ def _run(n, steps, seed, param_dtype=torch.bfloat16, **hyper):
     return wd
 
 
-@pytest.mark.parametrize("n", [1, 7, 4096, 4099, 1 << 20, (1 << 20) + 13])
+# one workgroup for the whole tensor (up to 12288 elements, 4 to 12 per thread), partial sums added up by every workgroup (up to
+# 4194304) or by one of their own
+@pytest.mark.parametrize("n", [1, 7, 3071, 4096, 4099, 8192, 8195, 12288, 12289, 1 << 20, (1 << 20) + 13, 1 << 22, (1 << 22) + 1])
 def test_lamb_steps(n):
     _run(n, 3, seed=n % 97)
 
