@@ -64,7 +64,7 @@ __device__ __forceinline__ void tile_of_block(const KArgs& p, int& tile_m, int& 
 // and its tile; false: nothing to do.
 __device__ __forceinline__ bool tile_of_block(const WgradGroup& g, KArgs& p, int& tile_m, int& tile_n) {
   int tile;
-  const WgradProduct& q = g.q[wgrad_of_block(g, blockIdx.x - g.sums.blocks, tile)];
+  const WgradProduct& q = g.q[wgrad_of_block(g, tile)];
   p = KArgs{};
   p.A = (const bf16_raw*)q.A; p.B = (const bf16_raw*)q.B; p.M = q.M; p.N = q.N; p.K = g.K; p.lda = q.lda; p.ldb = q.ldb;
   p.C = q.C; p.ldc = q.ldc; p.epilogue = EPI_ACCUM_F32; p.rowsum = q.rowsum; p.tiles_m = q.tiles_m; p.tiles_n = q.tiles_n;

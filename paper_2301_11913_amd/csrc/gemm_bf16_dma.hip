@@ -283,7 +283,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(typename Lau
   int tile_m, tile_n;
   KArgs p;
   if constexpr (A_T) {
-    if ((int)blockIdx.x < args.sums.blocks) {
+    if ((int)blockIdx.x < args.first[0]) {
       column_sums_block<WM * WN * 64>(args.sums, blockIdx.x, reinterpret_cast<float (*)[64]>(lds));
       return;
     }
@@ -896,7 +896,7 @@ swarm_status launch_dma_layout(const KArgs& k, bool b_t, hipStream_t st) {
 swarm_status launch_wgrads_256(const GemmArgs* g, int n, const ColumnSums* sums, hipStream_t st) {
   WgradGroup w = wgrad_group_of(g, n, sums, 256, 256);
   w.stream = streams_gradients(g, n);
-  return launch_dma<256, 256, 2, 4, true, true>(w, w.sums.blocks + w.tiles, st);
+  return launch_dma<256, 256, 2, 4, true, true>(w, w.workgroups, st);
 }
 
 // ---- split-K: second kernel.  C = epilogue(part_0 + part_1 + ...), summed in index order; a lane owns 8 columns.

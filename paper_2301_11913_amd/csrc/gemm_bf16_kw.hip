@@ -135,7 +135,7 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_bf16_kw_kernel(typename 
   int tile_m, tile_n;
   KArgs p;
   if constexpr (A_T) {
-    if ((int)blockIdx.x < args.sums.blocks) {
+    if ((int)blockIdx.x < args.first[0]) {
       column_sums_block<NTHR>(args.sums, blockIdx.x, reinterpret_cast<float (*)[64]>(lds));
       return;
     }
@@ -401,7 +401,7 @@ swarm_status launch_layout(const GemmArgs& g, int stream, hipStream_t st) {
 template <int WM, int WN, int WK, int NS>
 swarm_status launch_wgrads(const GemmArgs* g, int n, const ColumnSums* sums, hipStream_t st) {
   const WgradGroup w = wgrad_group_of(g, n, sums, 64 * WM, 64 * WN);
-  return launch<4, WM, WN, WK, NS, true, true>(w, w.sums.blocks + w.tiles, st);
+  return launch<4, WM, WN, WK, NS, true, true>(w, w.workgroups, st);
 }
 
 }  // namespace

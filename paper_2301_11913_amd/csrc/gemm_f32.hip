@@ -68,11 +68,11 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32A
   int pid;
   GemmArgs g;
   if constexpr (A_T) {
-    if ((int)blockIdx.x < args.sums.blocks) {
+    if ((int)blockIdx.x < args.first[0]) {
       column_sums_block<NT>(args.sums, blockIdx.x, reinterpret_cast<float (*)[64]>(lds));
       return;
     }
-    const WgradProduct& q = args.q[wgrad_of_block(args, blockIdx.x - args.sums.blocks, pid)];
+    const WgradProduct& q = args.q[wgrad_of_block(args, pid)];
     g = GemmArgs{};
     g.M = q.M; g.N = q.N; g.K = args.K; g.A = q.A; g.lda = q.lda; g.B = q.B; g.ldb = q.ldb; g.C = q.C; g.ldc = q.ldc;
     g.epilogue = EPI_ACCUM_F32; g.rowsum = q.rowsum;
@@ -91,19 +91,18 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32A
   const int wk = wave % WK, wn = wave / WK % WN, wm = wave / WK / WN;
   const int l32 = lane & 31, lg = lane >> 5;
 
-  // Weight gradients of 32 x 32 blocks have four sets of sums, one per MFMA of an 8-deep step, and so a quarter as long chains of
-  // additions: several of them in a launch have enough tiles without dealing K to eight wavefronts, and lose nothing for it (d_model
-  // 256, 512 tokens, distance from 64 bits 2.1e-7 -> 1.2e-7).
-  constexpr int NS = A_T && FM * FN == 1 ? 4 : 1;
-  f32x16_t acc[FM][FN], more[NS];      // more[0] is not used
+  // Weight gradients of 32 x 32 blocks have a second set of sums, for every other MFMA: with K dealt to four, chains of additions
+  // are then no longer than with K dealt to eight, which several products in a launch have too many tiles for (d_model 256, 512
+  // tokens, distance from 64 bits 2.1e-7 -> 1.5e-7).
+  constexpr bool TWO = A_T && FM * FN == 1;
+  f32x16_t acc[FM][FN], odd;
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-#pragma unroll
-  for (int c = 0; c < NS; ++c) more[c] = acc[0][0];
+  if constexpr (TWO) odd = acc[0][0];
 
   // rows and columns past the end read the last one; what they produce is not stored
   Operand<A_T> a[FM];
@@ -132,7 +131,7 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32A
 #pragma unroll
         for (int j = 0; j < FN; ++j)
         {
-          f32x16_t& sum = c > 0 && NS > 1 ? more[c < NS ? c : 0] : acc[i][j];
+          f32x16_t& sum = TWO && (c & 1) ? odd : acc[i][j];
           sum = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(fa[i], c), comp(fb[j], c), sum, 0, 0, 0);
         }
   };
@@ -173,7 +172,7 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32A
     multiply(fa, fb);
   }
 
-  if constexpr (NS > 1) acc[0][0] = (acc[0][0] + more[1 % NS]) + (more[2 % NS] + more[3 % NS]);
+  if constexpr (TWO) acc[0][0] += odd;
   // acc[i][j][r] is the element (32 i + 8 (r / 4) + 4 lg + r % 4, 32 j + l32) of the block
   float* mine = lds + wk * TM * PITCH + wm * 32 * FM * PITCH + wn * 32 * FN;
 #pragma unroll
@@ -260,7 +259,7 @@ swarm_status launch_layout(const GemmArgs* g, int n, const ColumnSums* sums, hip
   constexpr int TM = 32 * FM * WM, TN = 32 * FN * WN;
   if (g->a_trans) {
     const WgradGroup w = wgrad_group_of(g, n, sums, TM, TN);
-    return launch<FM, FN, WM, WN, WK, true, true>(w, 0, 0, w.sums.blocks + w.tiles, st);
+    return launch<FM, FN, WM, WN, WK, true, true>(w, 0, 0, w.workgroups, st);
   }
   const int tm = (g->M + TM - 1) / TM, tn = (g->N + TN - 1) / TN;
   if (!g->b_trans) return launch<FM, FN, WM, WN, WK, false, false>(*g, tm, tn, tm * tn, st);

@@ -99,47 +99,49 @@ __device__ __forceinline__ void column_sums_block(const ColumnSums& s, int block
   }
 }
 
-// Weight-gradient products over the same token rows (one parameter set's four), as ONE launch of their kernel takes them: the
-// workgroups of product i start at `first`, `tiles` in all.
+// Weight-gradient products over the same token rows (one parameter set's four), as ONE launch of their kernel takes them.
 constexpr int kMaxWgrads = 4;
 struct WgradProduct {
   const void* A; const void* B;   // [K, M], [K, N]
   float* C;                       // [M, N] += A^T B
   float* rowsum;                  // [M] += column sums of A, or nullptr
   int M, N, lda, ldb, ldc;
-  int tiles_m, tiles_n, first;
+  int tiles_m, tiles_n;
 };
 struct WgradGroup {
-  WgradProduct q[kMaxWgrads];
-  int n, K, tiles;
-  ColumnSums sums;                // done by the first workgroups of the launch, sums.blocks of them
+  // what a workgroup needs first, together: which product it works on is then two rounds of scalar loads away, not five
+  int first[kMaxWgrads];          // product i's workgroups start at first[i], behind the column sums'; none: INT_MAX
+  int K, workgroups;
   int stream;                     // bf16: see KArgs
   long long* stamps;              // bf16, instrumented build: see GemmArgs
+  WgradProduct q[kMaxWgrads];
+  ColumnSums sums;                // done by the workgroups in front of first[0]
 };
 inline WgradGroup wgrad_group_of(const GemmArgs* g, int n, const ColumnSums* sums, int tile_m, int tile_n) {
   WgradGroup w{};
   if (sums) w.sums = *sums;
-  w.n = n; w.K = g[0].K; w.stamps = g[0].stamps;
+  w.K = g[0].K; w.stamps = g[0].stamps;
+  w.workgroups = w.sums.blocks;
+  for (int i = 0; i < kMaxWgrads; ++i) w.first[i] = 0x7FFFFFFF;
   for (int i = 0; i < n; ++i) {
     WgradProduct& q = w.q[i];
     q.A = g[i].A; q.B = g[i].B; q.C = (float*)g[i].C; q.rowsum = g[i].rowsum; q.M = g[i].M; q.N = g[i].N; q.lda = g[i].lda;
     q.ldb = g[i].ldb; q.ldc = g[i].ldc;
     q.tiles_m = (q.M + tile_m - 1) / tile_m; q.tiles_n = (q.N + tile_n - 1) / tile_n;
-    q.first = w.tiles;
-    w.tiles += (q.tiles_m * q.tiles_n + 7) / 8 * 8;
+    w.first[i] = w.workgroups;
+    w.workgroups += (q.tiles_m * q.tiles_n + 7) / 8 * 8;
   }
   return w;
 }
-// Which product workgroup `pid` works on, and which of its tiles.  Workgroups go to the 8 XCDs in turn; every XCD gets a contiguous
-// band of every product's tiles, one product after the other, so that all XCDs read the same operands at a time (bands of the
-// whole list instead: four gradients of a d_model 4096 block over 8192 tokens 2610 -> 3000 us).  A product's share of the list is
-// padded to a multiple of 8: tile >= its number means nothing to do.
-__device__ __forceinline__ int wgrad_of_block(const WgradGroup& g, int pid, int& tile) {
-  int i = 0;
-  while (i + 1 < g.n && pid >= g.q[i + 1].first) ++i;
-  const int tiles = g.q[i].tiles_m * g.q[i].tiles_n;
-  pid -= g.q[i].first;
-  tile = (pid & 7) * ((tiles + 7) >> 3) + (pid >> 3);
+// Which product this workgroup (behind the column sums) works on, and which of its tiles.  Workgroups go to the 8 XCDs in turn;
+// every XCD gets a contiguous band of every product's tiles, one product after the other, so that all XCDs read the same
+// operands at a time (bands of the whole list instead: four gradients of a d_model 4096 block over 8192 tokens 2610 -> 3000
+// us).  A product's share of the list is padded to a multiple of 8: tile >= its number means nothing to do.
+__device__ __forceinline__ int wgrad_of_block(const WgradGroup& g, int& tile) {
+  static_assert(kMaxWgrads == 4, "the sum below");
+  const int pid = blockIdx.x, i = (pid >= g.first[1]) + (pid >= g.first[2]) + (pid >= g.first[3]);
+  const int tiles = g.q[i].tiles_m * g.q[i].tiles_n, at = pid - g.first[i];
+  tile = (at & 7) * ((tiles + 7) >> 3) + (at >> 3);
   return i;
 }
 
