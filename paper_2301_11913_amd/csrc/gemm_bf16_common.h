@@ -76,6 +76,11 @@ __device__ __forceinline__ bool tile_of_block(const WgradGroup& g, KArgs& p, int
   tile_n = tile % per_group / gsz;
   return tile_n < q.tiles_n;
 }
+// First row (column) of a tile of `size` out of `all` >= size.  The last tile of a ragged size ends with it instead of reaching
+// over: what it shares with its neighbour both compute, in the same order, and write with the same bits.  Nothing is read or written
+// out of range, and nothing has to be guarded, where a kernel only stores (no output is also an input of its launch).
+__device__ __forceinline__ int tile_origin(int tile, int size, int all) { return min(tile * size, all - size); }
+
 // What a kernel for this layout is launched with.
 template <bool A_T> struct LaunchArgs { typedef KArgs type; };
 template <> struct LaunchArgs<true> { typedef WgradGroup type; };

@@ -1,4 +1,4 @@
-// bf16 MFMA GEMM on 128 x 128 tiles, two workgroups per compute unit:  C[M,N] (+)= sum_k A(m,k) B(n,k), whole tiles only.
+// bf16 MFMA GEMM on 128 x 128 tiles, two workgroups per compute unit:  C[M,N] (+)= sum_k A(m,k) B(n,k).
 //
 // For products with more 128 x 128 tiles than compute units and too few 256 x 256 ones.  Four wavefronts of 64 x 64 and two
 // LDS stages of 64 k (64 KB) leave room for a second workgroup on the unit: what bounds a tile here is the fill of its first
@@ -76,7 +76,9 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_bf16_pair_kernel(KArgs p) {
   int tile_m, tile_n;
   tile_of_block(p, tile_m, tile_n);
   const int glu = (!B_T && p.epilogue == EPI_BIAS_GEGLU) ? p.split : 0;
-  const int m0 = tile_m * kTile, n0 = glu ? tile_n * (kTile / 2) : tile_n * kTile;
+  // (weight gradients, which add to their output, come in whole tiles only)
+  const int m0 = tile_origin(tile_m, kTile, p.M);
+  const int n0 = glu ? tile_origin(tile_n, kTile / 2, glu) : tile_origin(tile_n, kTile, p.N);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
@@ -161,12 +163,12 @@ swarm_status launch(const KArgs& k, hipStream_t st) {
 
 }  // namespace
 
-// M, N multiples of 128, K of 64; the caller has checked alignment and the layout.
+// M and N at least 128 (weight gradients: multiples of it), K a multiple of 64; the caller has checked alignment and the layout.
 swarm_status gemm_bf16_pair(const GemmArgs& g, int stream, hipStream_t st) {
   KArgs k = kargs_of(g);
   k.stamps = nullptr;
   k.stream = stream;
-  k.tiles_m = g.M / kTile; k.tiles_n = g.N / kTile;
+  k.tiles_m = (g.M + kTile - 1) / kTile; k.tiles_n = (g.N + kTile - 1) / kTile;
   if (!g.a_trans && !g.b_trans) return launch<false, false>(k, st);
   if (!g.a_trans) return launch<false, true>(k, st);
   if (g.b_trans) return launch<true, true>(k, st);

@@ -86,10 +86,11 @@ def test_coded_equals_unfused(shape, scale_bits):
 
 
 @pytest.mark.parametrize("scale_bits", [32, 16])
-@pytest.mark.parametrize("shape", [(1024, 8, 256, 528, 8), (1024, 8, 192, 768, 8), (2304, 18, 256, 1024, 8)])
+@pytest.mark.parametrize("shape", [(1024, 8, 256, 528, 8), (1024, 8, 192, 768, 8), (2304, 18, 256, 1024, 8),
+                                   (1024, 8, 256, 525, 8), (1024, 8, 2112, 700, 8), (1024, 8, 1024, 1025, 8)])
 def test_coded_equals_unfused_on_every_route(shape, scale_bits):
     """Token counts at which the last product runs on 264 tiles of 128 x 128, on 192 of 256 x 128, and on 288 of 256 x 256
-    of which the last columns are a product of their own."""
+    of which the last columns are a product of their own; ragged ones on 128 x 128, 256 x 128 and 256 x 256 tiles."""
     d, H, f, S, B = shape
     wl = synth.Workload(name="coded", dtype="bf16", d_model=d, n_heads=H, d_ffn=f, seq=S, batch=B, n_layers=1, n_repeat=1,
                         grad_sigma=1e-2, seed=77 + d + S)

@@ -626,6 +626,19 @@ def test_gemm_ragged_routes(M, N, K, a_t, b_t, epi):
     test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
 
 
+# Ragged products on the kernels of whole tiles, whose last tile ends with the operand: either side of each of their rules (256 and
+# 512 tiles of 128 x 128, 320 for a long K, full and not so full rounds), one row or eight columns past a tile, the fewest rows.
+@pytest.mark.parametrize("M,N,K,a_t,b_t,epi", [
+    (257, 11016, 192, False, False, 1), (2085, 2056, 64, False, False, 2), (2500, 2312, 2112, False, False, 2),
+    (2500, 2312, 2048, False, False, 0), (300, 22024, 768, False, False, 3), (2309, 4104, 768, False, False, 0),
+    (2309, 4104, 704, False, False, 2), (4100, 2568, 64, False, False, 3), (4097, 5128, 832, False, False, 1),
+    (5001, 8200, 768, False, False, 2), (2085, 2056, 64, False, True, 4), (2500, 2312, 1600, False, True, 0),
+    (2500, 2312, 1536, False, True, 4), (2309, 4104, 2048, False, True, 0), (3333, 4104, 64, False, True, 4),
+    (4100, 2568, 128, False, True, 0), (5001, 8200, 128, False, True, 4), (2176, 2184, 64, False, False, 1)])
+def test_gemm_overlapping_tiles(M, N, K, a_t, b_t, epi):
+    test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
+
+
 # Row sums of the left operand beside a weight gradient (the bias gradient), where the product's kernel takes them along:
 # one tile, fewer and more columns of tiles than fragment rows, ragged rows and token counts, both dtypes.
 @pytest.mark.parametrize("bf16,M,N,K", [(1, 64, 64, 33), (1, 200, 128, 333), (1, 768, 192, 1665), (1, 768, 3072, 130),

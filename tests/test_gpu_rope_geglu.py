@@ -63,6 +63,9 @@ def test_mfma_shapes_bf16(shape):
     # with two workgroups per unit (132 .. 272 of them)
     (512, 4, 1024, 704, 2, 1, 1),
     (256, 2, 2048, 1088, 2, 1, 1),
+    # ragged ones, the last tile of every product overlapping its neighbour: on 128 x 128 tiles, and all three on 256 x 256
+    (512, 4, 2048, 1501, 2, 1, 1),
+    (768, 6, 3584, 1850, 2, 1, 1),
 ])
 def test_odd_multiples_of_128_tokens_bf16(shape):
     _check(_wl("bf16", shape), dt=np.float32)
