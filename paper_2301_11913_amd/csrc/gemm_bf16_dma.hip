@@ -1,4 +1,5 @@
-// bf16 MFMA GEMM, pipelined variant for tile-aligned shapes:  C[M,N] (+)= sum_k A(m,k) B(n,k).
+// bf16 MFMA GEMM, pipelined, on whole tiles (the last of a ragged product overlaps its neighbour):  C[M,N] (+)= sum_k A(m,k)
+// B(n,k).
 //
 // Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4, 16 bytes per lane,
 // no staging registers) through a ring of NS stages of K-depth DBK, so NS-1 slices are in flight while
@@ -17,10 +18,10 @@
 // One workgroup owns one output tile and walks K in order: deterministic.
 //
 // Two kernels share this file, both on v_mfma_f32_16x16x32_bf16: gemm_bf16_k32_kernel (256 x 256 and 256 x 128 tiles on
-// eight wavefronts: the dgrad layout, weight gradients of any size and several in a launch, the rotary and GeGLU epilogues) and gemm_bf16_w4_kernel (256 x 256 tiles
-// on four wavefronts: the forward layout with the store / bias / residual / int8-encoding / GeLU epilogues).  They
-// accumulate a tile in the same order and give the same bits.  gemm_bf16_dma at the end decides which kernel a product
-// runs on: these, 128 x 128 tiles with two workgroups per unit (gemm_bf16_pair.hip), K over the wavefronts
+// eight wavefronts: the dgrad layout, weight gradients of any size and several in a launch, the rotary and GeGLU epilogues) and
+// gemm_bf16_w4_kernel (256 x 256 tiles on four wavefronts: the forward layout with the store / bias / residual /
+// int8-encoding / GeLU epilogues).  They accumulate a tile in the same order and give the same bits.  gemm_bf16_dma at the end
+// decides which kernel a product runs on: these, 128 x 128 tiles with two workgroups per unit (gemm_bf16_pair.hip), K over the wavefronts
 // (gemm_bf16_kw.hip) or, by refusing, the register-staged kernel (gemm_bf16.hip).
 #include <algorithm>
 #include <type_traits>
@@ -1015,6 +1016,7 @@ static bool two_tiles_per_unit(const GemmArgs& g) {
 enum class Ragged { none, t256, t256x128, pair };
 static Ragged ragged_on_whole_tiles(const GemmArgs& g) {
   if (g.K % DBK || g.M < 256 || g.N < 256 || (g.M % 128 == 0 && g.N % 128 == 0)) return Ragged::none;
+  if (g.aux && g.aux == g.C) return Ragged::none;       // in place: the rows of both tiles would be added to twice
   const bool geglu = g.epilogue == EPI_BIAS_GEGLU;      // its gathered tile: 64 columns at least per wavefront
   const long t128 = tiles_of(g, 128), t256 = tiles_of(g, 256);
   const long rounds = (t256 + 255) / 256, pairs = (t128 + 511) / 512;

@@ -639,6 +639,22 @@ def test_gemm_overlapping_tiles(M, N, K, a_t, b_t, epi):
     test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
 
 
+# In place (the second operand of the epilogue is the output): every row is added to once, whatever the tiles.
+@pytest.mark.parametrize("M,N,K,b_t,epi", [(2309, 4104, 768, False, 2), (2500, 2312, 2112, False, 2), (2085, 2056, 64, True, 4)])
+def test_gemm_ragged_in_place(M, N, K, b_t, epi):
+    lib = _lib()
+    A, B, aux = (_bf(synth.normal(7, n, s)).cuda() for n, s in (("A", (M, K)), ("B", (K, N) if b_t else (N, K)), ("x", (M, N))))
+    bias, got = _bf(synth.normal(7, "b", (N,))).cuda(), aux.clone()
+    apart = torch.empty_like(aux)
+    for x, c in ((aux, apart), (got, got)):
+        assert lib.swarm_kernel_gemm(1, M, N, K, A.data_ptr(), K, 0, B.data_ptr(), B.shape[1], b_t, c.data_ptr(), N, epi,
+                                     bias.data_ptr(), x.data_ptr(), N, None, N, None) == 0
+    torch.cuda.synchronize()
+    a, b = apart.double(), got.double()
+    # two kernels, two orders of the same sums: one bf16 unit of the largest result
+    assert (a - b).abs().max() <= 2.0 ** -7 * a.abs().max()
+
+
 # Row sums of the left operand beside a weight gradient (the bias gradient), where the product's kernel takes them along:
 # one tile, fewer and more columns of tiles than fragment rows, ragged rows and token counts, both dtypes.
 @pytest.mark.parametrize("bf16,M,N,K", [(1, 64, 64, 33), (1, 200, 128, 333), (1, 768, 192, 1665), (1, 768, 3072, 130),
