@@ -117,13 +117,15 @@ def gemm_roofline(step, steps, ms_per_step, workload):
     if att:
         out["attainable_peak"] = att
         out["frac_of_attainable"] = round(achieved / att, 4)
-    if table:
-        out["operand_data"] = gemm_on_constant_operands(table[0]["M"], table[0]["N"], table[0]["K"])
+    # a weight-gradient row is a parameter set's products in one launch (M = their widths in units of N), no product of its own
+    single = next((r for r in table if r["layout"] != "wgrad"), None)
+    if single:
+        out["operand_data"] = gemm_on_constant_operands(single["M"], single["N"], single["K"])
     return out
 
 
 def gemm_on_constant_operands(M, N, K):
-    """The step's most expensive product (forward layout, plain store) on random and on all-zero operands: the same
+    """The step's most expensive single product (forward layout, plain store) on random and on all-zero operands: the same
     instructions over the same addresses; what differs is the switching activity, hence the clock the chip holds
     under its power limit.  Context for `frac`, not part of it."""
     import torch

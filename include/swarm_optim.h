@@ -42,7 +42,7 @@ swarm_status swarm_lamb_step(const swarm_lamb_config *cfg, size_t n_elems, float
                              size_t workspace_bytes, void *hip_stream);
 
 /* swarm_lamb_step for callers that cannot allocate device memory or carry a workspace (code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc): the same three kernels with their scratch (update
+ * capture, tight serving loops, harnesses that forbid hipMalloc): the same kernels with their scratch (update
  * direction, partial sums of the norms, ratio) in a static device array inside the library, 64 MiB + 33 KiB per GPU,
  * held from the library's load until the process ends.  n_elems <= SWARM_LAMB_STATIC_MAX_ELEMS (one 4096 x 4096
  * matrix), SWARM_ERR_WORKSPACE beyond; everything else as swarm_lamb_step, and the results are bit-identical to it.

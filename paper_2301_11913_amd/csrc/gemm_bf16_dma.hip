@@ -21,8 +21,8 @@
 // eight wavefronts: the dgrad layout, weight gradients of any size and several in a launch, the rotary and GeGLU epilogues) and
 // gemm_bf16_w4_kernel (256 x 256 tiles on four wavefronts: the forward layout with the store / bias / residual /
 // int8-encoding / GeLU epilogues).  They accumulate a tile in the same order and give the same bits.  gemm_bf16_dma at the end
-// decides which kernel a product runs on: these, 128 x 128 tiles with two workgroups per unit (gemm_bf16_pair.hip), K over the wavefronts
-// (gemm_bf16_kw.hip) or, by refusing, the register-staged kernel (gemm_bf16.hip).
+// decides which kernel a product runs on: these, 128 x 128 tiles with two workgroups per unit (gemm_bf16_pair.hip), K over the
+// wavefronts (gemm_bf16_kw.hip) or, by refusing, the register-staged kernel (gemm_bf16.hip).
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -323,8 +323,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(typename Lau
   // every wavefront sums one of its eight fragment rows, the columns of wavefronts one apart: per slice two more fragment
   // reads and two more MFMAs, against a column of ones, instead of a second read of A (a column sum of its own takes 13..23 us
   // for 4096 tokens x 2048..8192).  They sit between the sub-steps, behind one branch: a test in every row of multiplies
-  // instead costs 9 % of the product, a second copy of the loop its registers.  Every 32 slices the sums move on to doubles, kept in LDS behind the stages: over shared
-  // layers K is up to 2^22, where one running fp32 sum loses.
+  // instead costs 9 % of the product, a second copy of the loop its registers.  Every 32 slices the sums move on to doubles, kept
+  // in LDS behind the stages: over shared layers K is up to 2^22, where one running fp32 sum loses.
   f32x4 rsum = {0.f, 0.f, 0.f, 0.f};
   const int sum_row = A_T && p.rowsum && tile_n < 2 ? 4 * tile_n + wn : -1;
   double* total = reinterpret_cast<double*>(lds + NS * STAGE) + wm * WTM + 16 * max(sum_row, 0) + 4 * q;

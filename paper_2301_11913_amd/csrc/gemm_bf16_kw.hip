@@ -6,8 +6,8 @@
 // one.  So a workgroup keeps NS slices in LDS, NS - 1 of them in flight, and divides K as well as the tile: WM x WN x WK
 // wavefronts, each multiplying a 64 x 64 block (or, for the fewest tiles, 16 or 32 rows of one) over its own 32 of the 32 * WK
 // values of k in a slice.  That keeps the LDS bytes per flop of a 64 x 64 block (16 fragment reads for 32 MFMAs) on a tile as small
-// as 64 x 64, and gives a 128 x 128 tile eight wavefronts, two per SIMD.  The WK partial blocks meet once, in LDS, and are added in index order;
-// the epilogue then runs on rows of eight columns.
+// as 64 x 64, and gives a 128 x 128 tile eight wavefronts, two per SIMD.  The WK partial blocks meet once, in LDS, and are added
+// in index order; the epilogue then runs on rows of eight columns.
 //
 // Loads are buffer loads into LDS with the operand's exact size in the descriptor: what lies behind its last row reads
 // as zero, so a ragged M or N costs nothing in the loop and only the stores are guarded.  The descriptor moves along K

@@ -143,11 +143,8 @@ def streaming(path: str, tokens: str, d_model: str, d_ffn: str) -> None:
              ("ln_bwd_kernel<unsigned short, 2, false", "LayerNorm backward", 8.0 * T * d, "dy, x, residual gradient in, dx out"),
              ("ln_bwd_kernel<unsigned short, 2, true", "LayerNorm backward, int8 output encoded", (6.0 + 1.0625) * T * d,
               "dy, x, residual gradient in, codes + scales out"),
-             ("colsum_partial_kernel", "bias-gradient column sums (four widths, average)", 2.0 * T * (5 * d + f) / 4,
-              "gradient tensor in"),
              ("swarm::codec_encode_kernel", "codec encode", 3.0625 * T * d, "x in, codes + scales out"),
-             ("swarm::codec_decode_kernel", "codec decode", 3.0625 * T * d, "codes + scales in, x out"),
-             ("attn_delta_kernel", "attention backward row sums", 4.0 * T * d, "o, do in")]
+             ("swarm::codec_decode_kernel", "codec decode", 3.0625 * T * d, "codes + scales in, x out")]
     print("| kernel | what | launches | median us | algorithmic bytes per launch | GB/s | of 8 TB/s |")
     print("|---|---|---|---|---|---|---|")
     for prefix, what, nbytes, note in table:

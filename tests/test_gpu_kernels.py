@@ -618,7 +618,7 @@ def test_gemm_two_workgroups_per_unit(M, N, K, a_t, b_t, epi):
     (4001, 4096, 96, False, True, 0), (1536, 4608, 65, True, True, 5), (1536, 4608, 641, True, True, 5),
     (3072, 3072, 321, True, True, 5), (4096, 4096, 130, True, True, 5), (4104, 4000, 1, True, True, 5),
     (3072, 4096, 700, True, True, 5), (4104, 4104, 65, True, True, 5), (16392, 1544, 200, True, True, 5), (8200, 4096, 64, False, False, 2), (8200, 4096, 96, False, False, 3),
-    (8200, 4104, 64, False, True, 4),
+    (8200, 4104, 64, False, True, 4), (8200, 4104, 96, False, True, 0), (8200, 3904, 64, True, True, 5),
     # K no multiple of 32: the register-staged kernel only, on both of its tiles
     (4096, 2560, 72, False, True, 0), (4104, 2560, 40, False, False, 1), (300, 256, 136, False, True, 4),
     (130, 264, 24, False, False, 3), (64, 19200, 65, True, True, 5)])

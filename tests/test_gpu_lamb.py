@@ -42,10 +42,11 @@ def test_lamb_steps(n):
     _run(n, 3, seed=n % 97)
 
 
-def test_lamb_hyperparameters_and_fp32_copy():
-    _run(50000, 2, seed=5, param_dtype=torch.float32, lr=2e-3, beta1=0.8, beta2=0.99, eps=1e-8, weight_decay=0.0,
+@pytest.mark.parametrize("n", [4097, 12288, 50000])
+def test_lamb_hyperparameters_and_fp32_copy(n):
+    _run(n, 2, seed=5, param_dtype=torch.float32, lr=2e-3, beta1=0.8, beta2=0.99, eps=1e-8, weight_decay=0.0,
          grad_scale=0.25)
-    _run(50000, 2, seed=6, param_dtype=None, weight_decay=0.1)
+    _run(n, 2, seed=6, param_dtype=None, weight_decay=0.1)
 
 
 def test_lamb_zero_gradient_and_zero_weights():
