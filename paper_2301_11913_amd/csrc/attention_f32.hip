@@ -243,14 +243,28 @@ __global__ __launch_bounds__(kNT, DH == 64 ? 2 : 1) void attn_f32_dq_kernel(cons
   load_row<DH>(q, base + (size_t)qrow * ld, lg);
   load_row<DH>(g, dout + ((size_t)b * S + qrow) * d + h * DH, lg);
   const float L = lse[((size_t)b * H + h) * S + qrow];
-  float D = 0.f;
+  float D;
   {
+    // halves are added to halves all the way, seven or eight roundings deep: a running sum of DH / 2 products would be 18
     float4 out[DH / 8];
+    float t[8][4];
     load_row<DH>(out, o + ((size_t)b * S + qrow) * d + h * DH, lg);
 #pragma unroll
-    for (int c = 0; c < DH / 8; ++c)
-      D += (out[c].x * g[c].x + out[c].y * g[c].y) + (out[c].z * g[c].z + out[c].w * g[c].w);
-    D += __shfl_xor(D, 32, 64);
+    for (int c = 0; c < 8; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        t[c][e] = fmaf(comp(out[c], e), comp(g[c], e), 0.f);
+        if constexpr (DH == 128) t[c][e] = fmaf(comp(out[c + 8], e), comp(g[c + 8], e), t[c][e]);
+      }
+#pragma unroll
+    for (int half = 4; half >= 1; half /= 2)
+#pragma unroll
+      for (int c = 0; c < half; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[c][e] += t[c + half][e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[0][e] += __shfl_xor(t[0][e], 32, 64);
+    D = (t[0][0] + t[0][2]) + (t[0][1] + t[0][3]);
   }
   if (wave == 0 && lg == 0 && query < S) delta[((size_t)b * H + h) * S + query] = D;
   f32x16_t out[DH / 32];

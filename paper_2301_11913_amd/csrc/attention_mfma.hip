@@ -578,7 +578,8 @@ __global__ __launch_bounds__(kDkDvThreads) void attn_bwd_dkdv_kernel(const bf16_
 }
 
 // products of eight values each, summed in order
-__device__ __forceinline__ float dot8(const bf16x8& x, const bf16x8& y, float acc) {
+__device__ __forceinline__ float dot8(const bf16x8& x, const bf16x8& y) {
+  float acc = 0.f;
   const uint4 a = __builtin_bit_cast(uint4, x), g = __builtin_bit_cast(uint4, y);
   const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, gw[4] = {g.x, g.y, g.z, g.w};
 #pragma unroll
@@ -629,11 +630,16 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_bwd_dq_kernel(const bf16
     qf[ks] = global_frag(Q, ld, qrow, S, 16 * ks + 8 * lg);
     dof[ks] = global_frag(dO, d, qrow, S, 16 * ks + 8 * lg);
   }
-  float L2 = 0.f, dl = 0.f;
+  // eights are summed in order, then halves added to halves: 11 or 12 roundings deep, where one running sum is DH / 2
+  float L2 = 0.f, part_dl[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
-    dl = dot8(global_frag(o + (size_t)b * S * d + h * DH, d, qrow, S, 16 * ks + 8 * lg), dof[ks], dl);
-  dl += __shfl_xor(dl, 32, 64);
+    part_dl[ks] = dot8(global_frag(o + (size_t)b * S * d + h * DH, d, qrow, S, 16 * ks + 8 * lg), dof[ks]);
+#pragma unroll
+  for (int half = KS / 2; half >= 1; half /= 2)
+#pragma unroll
+    for (int ks = 0; ks < half; ++ks) part_dl[ks] += part_dl[ks + half];
+  const float dl = part_dl[0] + __shfl_xor(part_dl[0], 32, 64);
   if (qrow < S) {
     L2 = lse[((size_t)b * H + h) * S + qrow] * kLog2e;
     if (grp == 0 && lg == 0) delta[((size_t)b * H + h) * S + qrow] = dl;

@@ -407,6 +407,32 @@ def test_attention_f32(shape, std):
 def test_attention_f32_few_short_rows(shape):
     test_attention_f32(shape, 1.5)
 
+
+# The row sums of dO O that the backward leaves for dK / dV: one product of 1 and dh - 1 of less than half a unit of it.  Halves
+# added to halves lose at most half a unit (2^-24) per addition on the way of the 1: bf16 seven in its eight columns and
+# log2(dh / 8) behind, fp32 log2(dh).  One running sum of the dh / 2 products of a lane loses dh / 2 - 1 of them whole (fp32: 2^-26
+# each, in fours).
+@pytest.mark.parametrize("bf16,dh", [(1, 64), (1, 128), (0, 64), (0, 128)])
+@pytest.mark.parametrize("at", [0, 1])
+def test_attention_row_sums(bf16, dh, at):
+    B, S, H = 1, 300, 2
+    lib, dt = _attn_lib(), torch.bfloat16 if bf16 else torch.float32
+    o, dout = (torch.full((B, S, H, dh), 2.0 ** -e, dtype=dt) for e in ((12, 13) if bf16 else (13, 13)))
+    col = at * (8 if bf16 else 4)
+    o[..., col] = 1
+    dout[..., col] = 1
+    qkv = torch.zeros((B, S, 3 * H * dh), dtype=dt, device="cuda")
+    od, dod, dqkv = o.cuda(), dout.cuda(), torch.empty_like(qkv)
+    lse = torch.arange(1, S + 1, dtype=torch.float32).log().expand(B, H, S).contiguous().cuda()
+    delta = torch.full((B, H, S), 9.0, device="cuda")
+    assert lib.swarm_kernel_attention_bwd(bf16, qkv.data_ptr(), od.data_ptr(), dod.data_ptr(), lse.data_ptr(), delta.data_ptr(),
+                                          dqkv.data_ptr(), B, S, H, dh, None) == 0
+    torch.cuda.synchronize()
+    want = (o.double() * dout.double()).sum(-1).transpose(1, 2)
+    additions = 7 + int(math.log2(dh // 8)) if bf16 else int(math.log2(dh))
+    assert ((delta.double().cpu() - want).abs() <= additions * 2.0 ** -24).all()
+
+
 def _attention_f32_run(qkv, dout, B, S, H, dh):
     lib = _attn_lib()
     qd, dod = qkv.cuda(), dout.cuda()
