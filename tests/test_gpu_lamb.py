@@ -64,6 +64,26 @@ def test_lamb_zero_gradient_and_zero_weights():
     assert ratio.item() == 1.0 and torch.allclose(w0, torch.full_like(w0, -1e-3), rtol=1e-5)
 
 
+# Rounded once in each moment, behind what the small second term brings along: half a unit of the moment and two of the term.
+# (With the large term rounded by itself first: up to a whole unit.)
+@pytest.mark.parametrize("n", [3000, 4101, 8195, 12288, 12289, 70001])
+def test_lamb_moments_round_once(n):
+    import paper_2301_11913_amd as sw
+    g = torch.Generator().manual_seed(n)
+    w, m, v = torch.randn(n, generator=g) * 0.02, torch.randn(n, generator=g) * 1e-3, torch.rand(n, generator=g) * 1e-6 + 1e-7
+    grad = torch.randn(n, generator=g) * 1e-5
+    b1, b2 = torch.tensor([0.9, 0.95])
+    term1, term2 = (1 - b1).double() * grad.double(), (1 - b2).double() * grad.double() ** 2
+    want_m, want_v = b1.double() * m.double() + term1, b2.double() * v.double() + term2
+    d = [t.cuda() for t in (w, grad, m, v)]
+    ws = torch.empty(sw.swarm_lamb_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    sw.swarm_lamb_step(d[0], None, d[1], d[2], d[3], 100, ws, beta1=0.9, beta2=0.95)
+    torch.cuda.synchronize()
+    for got, want, term in ((d[2], want_m, term1), (d[3], want_v, term2)):
+        unit = 2.0 ** (torch.floor(torch.log2(want.abs())) - 23)
+        assert ((got.double().cpu() - want).abs() <= 0.5 * unit + 2.0 ** -23 * term.abs()).all()
+
+
 def test_lamb_is_reproducible():
     a = _run(300001, 2, seed=9)
     b = _run(300001, 2, seed=9)
