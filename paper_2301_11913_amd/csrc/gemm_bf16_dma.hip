@@ -323,8 +323,9 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(typename Lau
   // every wavefront sums one of its eight fragment rows, the columns of wavefronts one apart: per slice two more fragment
   // reads and two more MFMAs, against a column of ones, instead of a second read of A (a column sum of its own takes 13..23 us
   // for 4096 tokens x 2048..8192).  They sit between the sub-steps, behind one branch: a test in every row of multiplies
-  // instead costs 9 % of the product, a second copy of the loop its registers.  Every 32 slices the sums move on to doubles, kept
-  // in LDS behind the stages: over shared layers K is up to 2^22, where one running fp32 sum loses.
+  // instead costs 9 % of the product, a second copy of the loop its registers.  Every 16 slices the sums move on to doubles, kept in
+  // LDS behind the stages: over shared layers K is up to 2^22, where one running fp32 sum loses.  (Distance from 64 bits over 1554 rows
+  // 2.75e-8, that of a column sum of its own 2.72e-8; with 32 slices 3.2e-8, with eight 2.5e-8 and the launch 1 % slower.)
   f32x4 rsum = {0.f, 0.f, 0.f, 0.f};
   const int sum_row = A_T && p.rowsum && tile_n < 2 ? 4 * tile_n + wn : -1;
   double* total = reinterpret_cast<double*>(lds + NS * STAGE) + wm * WTM + 16 * max(sum_row, 0) + 4 * q;
@@ -444,7 +445,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(typename Lau
         const uint4 ones = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
         rsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0, __builtin_bit_cast(bf16x8, ones), rsum, 0, 0, 0);
         rsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1, __builtin_bit_cast(bf16x8, ones), rsum, 0, 0, 0);
-        if ((kt & 31) == 31) {
+        if ((kt & 15) == 15) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             if (holds_sum) total[r] += (double)rsum[r];
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_k32_kernel(typename Lau
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int row = m0 + wm * WTM + 16 * sum_row + 4 * q + r;
-      if (row < p.M) p.rowsum[row] += (float)(total[r] + (double)rsum[r]);
+      if (row < p.M) p.rowsum[row] = (float)((double)p.rowsum[row] + total[r] + (double)rsum[r]);
     }
   }
 #ifdef SWARM_KERNEL_HOOKS

@@ -182,19 +182,20 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32A
 #pragma unroll
       for (int r = 0; r < 16; ++r) mine[(32 * i + 8 * (r >> 2) + 4 * lg + (r & 3)) * PITCH + 32 * j + l32] = acc[i][j][r];
   const bool sum_rows = A_T && g.rowsum && n0 == 0;
-  if (sum_rows && wn == 0) {                               // into the column behind the tile's
+  // into the columns behind the tile's, still in doubles: K parts rounded one by one leave the sums 6.2e-8 from 64 bits, so 4.6e-8
+  if (sum_rows && wn == 0) {
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
       const double s = rsum[i] + __shfl_xor(rsum[i], 32, 64);
-      if (lg == 0) mine[(32 * i + l32) * PITCH + TN] = (float)s;
+      if (lg == 0) *reinterpret_cast<double*>(&mine[(32 * i + l32) * PITCH + TN]) = s;
     }
   }
   __syncthreads();
   if (sum_rows && threadIdx.x < TM && m0 + (int)threadIdx.x < g.M) {
-    float s = 0.f;
+    double s = g.rowsum[m0 + threadIdx.x];
 #pragma unroll
-    for (int w = 0; w < WK; ++w) s += lds[(w * TM + threadIdx.x) * PITCH + TN];
-    g.rowsum[m0 + threadIdx.x] += s;
+    for (int w = 0; w < WK; ++w) s += *reinterpret_cast<const double*>(&lds[(w * TM + threadIdx.x) * PITCH + TN]);
+    g.rowsum[m0 + threadIdx.x] = (float)s;
   }
   for (int e = threadIdx.x; e < TM * TN / 4; e += NT) {
     const int rl = e / (TN / 4), cl = e % (TN / 4) * 4;

@@ -702,6 +702,31 @@ def test_weight_gradient_row_sums(bf16, M, N, K):
     assert ((dW.cpu() - (dW0 + A.T @ B)).abs() <= (2 * K + 1) * 2.0 ** -24 * (A.abs().T @ B.abs() + dW0.abs())).all()
 
 
+# How often the bias gradient is rounded: positive values are added up, so every rounding is one of a growing running sum.  In units of
+# the result, root mean square: fp32, values of 1..2, sums of four, doubles over the rest and one rounding at the end, 0.29 (with a
+# quarter of K rounded by each wavefront and added up in fp32 0.5).  bf16 on 256 x 256 tiles, values that differ by up to 2^16: the sum of
+# 2048 rows in two runs of 32 multiplies, each ending at half of it and so with half the roundings: 1.55 (in one run of 64 3.05).
+@pytest.mark.parametrize("bf16,K,shapes,units", [
+    (0, 512, [(256, 1024), (1024, 256), (256, 256), (768, 256)], 0.4), (0, 1000, [(1024, 1024), (1024, 2048)], 0.4),
+    (1, 2048, [(1024, 4096), (4096, 1024), (1024, 1024), (3072, 1024)], 2.2)])
+def test_bias_gradient_rounding(bf16, K, shapes, units):
+    lib = _lib()
+    g = torch.Generator().manual_seed(K)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    A, B = ([((1 + torch.rand((K, s[i]), generator=g)) * 2.0 ** -torch.randint(0, 16 if bf16 else 1, (K, s[i]), generator=g)).to(dt)
+             for s in shapes] for i in (0, 1))
+    dev = [[a.cuda(), b.cuda(), torch.zeros(s, device="cuda"), torch.zeros(s[0], device="cuda")] for a, b, s in zip(A, B, shapes)]
+    mn = (C.c_int * (2 * len(shapes)))(*[x for s in shapes for x in s])
+    ptrs = (C.c_void_p * (4 * len(shapes)))(*[t.data_ptr() for p in dev for t in p])
+    lib.swarm_kernel_wgrads.argtypes = [C.c_int, C.c_int, C.c_void_p, C.c_int, C.c_void_p, C.c_void_p]
+    assert lib.swarm_kernel_wgrads(bf16, len(shapes), mn, K, ptrs, None) == 0
+    torch.cuda.synchronize()
+    for a, d in zip(A, dev):
+        want = a.double().sum(0)
+        off = (d[3].double().cpu() - want) / 2.0 ** (torch.floor(torch.log2(want)) - 23)
+        assert off.square().mean().sqrt() <= units
+
+
 # Several weight gradients over the same rows in one launch, bias gradients with them: every tile shape (64 x 64 with four and two
 # stages, 128 x 64, 128 x 128, 256 x 256; fp32 32, 64 and 128), each with one k value, a whole slice and parts of one, ragged M
 # and N, products smaller than a tile beside larger ones, and shares of the launch that are no multiple of 8 tiles.
