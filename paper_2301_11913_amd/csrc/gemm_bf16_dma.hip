@@ -1015,9 +1015,20 @@ static bool two_tiles_per_unit(const GemmArgs& g) {
 //                  in its loop, where 256 x 128 tiles with half of the operand bytes are ahead from 320 of them (0.90..0.96 /
 //                  0.93..1.01); beyond, where its rounds are full and K is not long.
 enum class Ragged { none, t256, t256x128, pair };
+// An output that is also an input, whole or in part: gradients that are added to, a second operand of the epilogue in place.
+static bool output_is_input(const GemmArgs& g) {
+  if (g.epilogue == EPI_ACCUM_F32) return true;
+  if (!g.aux) return false;
+  const size_t cols = (size_t)g.N + (g.epilogue == EPI_DGEGLU ? g.split : 0);
+  auto meets = [&](const void* out, int ld, size_t bytes) {
+    const uintptr_t a = (uintptr_t)g.aux, c = (uintptr_t)out;
+    return out && a < c + ((size_t)(g.M - 1) * ld + cols) * bytes && c < a + ((size_t)(g.M - 1) * g.ldaux + cols) * 2;
+  };
+  return meets(g.C, g.ldc, g.epilogue == EPI_BIAS_RESID_ENCODE ? 1 : 2) || meets(g.C2, g.ldc2, 2);
+}
 static Ragged ragged_on_whole_tiles(const GemmArgs& g) {
   if (g.K % DBK || g.M < 256 || g.N < 256 || (g.M % 128 == 0 && g.N % 128 == 0)) return Ragged::none;
-  if (g.aux && g.aux == g.C) return Ragged::none;       // in place: the rows of both tiles would be added to twice
+  if (output_is_input(g)) return Ragged::none;          // rows of both tiles would be added to twice, or once by each at a time
   const bool geglu = g.epilogue == EPI_BIAS_GEGLU;      // its gathered tile: 64 columns at least per wavefront
   const long t128 = tiles_of(g, 128), t256 = tiles_of(g, 256);
   const long rounds = (t256 + 255) / 256, pairs = (t128 + 511) / 512;

@@ -660,7 +660,10 @@ def test_gemm_ragged_routes(M, N, K, a_t, b_t, epi):
     (2309, 4104, 704, False, False, 2), (4100, 2568, 64, False, False, 3), (4097, 5128, 832, False, False, 1),
     (5001, 8200, 768, False, False, 2), (2085, 2056, 64, False, True, 4), (2500, 2312, 1600, False, True, 0),
     (2500, 2312, 1536, False, True, 4), (2309, 4104, 2048, False, True, 0), (3333, 4104, 64, False, True, 4),
-    (4100, 2568, 128, False, True, 0), (5001, 8200, 128, False, True, 4), (2176, 2184, 64, False, False, 1)])
+    (4100, 2568, 128, False, True, 0), (5001, 8200, 128, False, True, 4), (2176, 2184, 64, False, False, 1),
+    # an output that is added to: on tiles that do not overlap
+    (2085, 2056, 64, False, False, 5), (2309, 4104, 768, False, False, 5), (2500, 2312, 2112, False, False, 5),
+    (2085, 2056, 64, False, True, 5), (2309, 4104, 2048, False, True, 5)])
 def test_gemm_overlapping_tiles(M, N, K, a_t, b_t, epi):
     test_gemm_ragged_and_small(M, N, K, a_t, b_t, epi)
 
