@@ -521,7 +521,18 @@ swarm_status ln_bwd_dispatch(const T* dy, const T* x, const float* mean, const f
 
 }  // namespace
 
+// Vectors that share memory (tied parameters, or one buffer for all that a caller does not want) are added to one after the other:
+// workgroups of one launch would add to the same value at the same time.
 swarm_status column_sums(const ColumnSums& s, hipStream_t st) {
+  bool apart = true;
+  for (int i = 0; i < s.n_out; ++i)
+    for (int j = 0; j < i; ++j) apart = apart && (s.out[i] + s.cols <= s.out[j] || s.out[j] + s.cols <= s.out[i]);
+  for (int o = 0; !apart && o < s.n_out; ++o) {
+    const swarm_status one = column_sums(column_sums_of(s.partial + (o >> 1) * s.set + (size_t)(o & 1) * s.cols, s.rows, s.cols,
+                                                        s.stride, 0, s.out[o], nullptr, nullptr, nullptr), st);
+    if (one != SWARM_OK) return one;
+  }
+  if (!apart) return SWARM_OK;
   if (s.rows > 32) hipLaunchKernelGGL(column_sums_kernel<1024>, dim3(s.blocks), dim3(1024), 0, st, s);
   else hipLaunchKernelGGL(column_sums_kernel<256>, dim3(s.blocks), dim3(256), 0, st, s);
   return launch_status();

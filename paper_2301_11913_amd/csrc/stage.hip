@@ -264,16 +264,6 @@ ColumnSums ln_column_sums(const Dims& D, const swarm_block_grads& gp, const LnPa
   return column_sums_of(L.base, n * layernorm_bwd_partial_rows(D.T), D.d, (size_t)2 * D.d, L.slots * L.floats, gp.ln1_g,
                         gp.ln1_b, gp.ln2_g, gp.ln2_b);
 }
-swarm_status add_ln_grads(const ColumnSums& c, hipStream_t st) {
-  bool apart = true;      // the two norms' gradients, that is: tied ones are added one after the other
-  for (int i = 0; i < 2; ++i)
-    for (int j = 2; j < 4; ++j) apart = apart && (c.out[i] + c.cols <= c.out[j] || c.out[j] + c.cols <= c.out[i]);
-  if (apart) return column_sums(c, st);
-  for (int i = 0; i < 2; ++i)
-    SWARM_TRY(column_sums(column_sums_of(c.partial + i * c.set, c.rows, c.cols, c.stride, 0, c.out[2 * i], c.out[2 * i + 1], nullptr,
-                                         nullptr), st));
-  return SWARM_OK;
-}
 
 // Weight and bias gradients of one parameter set over `n` consecutive applications whose tensors start at the
 // given pointers (slot pitch = one application's tensor): with layer sharing (Sections 2.3 and 4.3) the sum over
@@ -287,7 +277,7 @@ swarm_status set_weight_grads(const Dims& D, const swarm_block_grads& gp, int n,
                    weight_grad(rows, ag.dqkv, 3 * d, s.a, d, gp.w_qkv, gp.b_qkv)};
   const swarm_status together = gemm_wgrads(w, 4, ln, D.bf16, st);
   if (together != SWARM_ERR_SHAPE) return together;
-  if (ln) SWARM_TRY(add_ln_grads(*ln, st));
+  if (ln) SWARM_TRY(column_sums(*ln, st));
   for (GemmArgs& g : w) {
     if (!gemm_sums_rows(g, D.bf16)) {
       SWARM_TRY(colsum_accum(g.A, rows, g.M, g.rowsum, partial, D.bf16, st));
@@ -429,7 +419,7 @@ swarm_status run_backward(const Dims& D, const swarm_stage_config* cfg, const sw
     for (int r = R - 1; r >= 0; --r) {
       app = l * R + r;
       if (kept == P.ln.slots) {
-        SWARM_TRY(add_ln_grads(ln_column_sums(D, grad_params[l], P.ln, kept), st));
+        SWARM_TRY(column_sums(ln_column_sums(D, grad_params[l], P.ln, kept), st));
         kept = 0;
       }
       BwdTemps t = P.t;
