@@ -279,7 +279,10 @@ swarm_status set_weight_grads(const Dims& D, const swarm_block_grads& gp, int n,
   if (together != SWARM_ERR_SHAPE) return together;
   if (ln) SWARM_TRY(column_sums(*ln, st));
   for (GemmArgs& g : w) {
-    if (!gemm_sums_rows(g, D.bf16)) {
+    // the product's own launch may not add to one value twice either
+    const float* c = (const float*)g.C;
+    const bool apart = g.rowsum + g.M <= c || c + (size_t)g.M * g.N <= g.rowsum;
+    if (!apart || !gemm_sums_rows(g, D.bf16)) {
       SWARM_TRY(colsum_accum(g.A, rows, g.M, g.rowsum, partial, D.bf16, st));
       g.rowsum = nullptr;
     }

@@ -187,7 +187,7 @@ def test_shared_equals_unrolled_on_gpu(dtype, R, d, seq):
 @pytest.mark.parametrize("dtype,tied", [
     ("bf16", [("ln1_g", "ln2_g")]), ("bf16", [("b_o", "b_2")]), ("f32", [("ln1_b", "ln2_g"), ("b_o", "ln1_g")]),
     ("f32", [("w_qkv", "w_1")]), ("bf16", [("w_1", "w_2"), ("b_2", "ln2_b")]), ("bf16", [("ln1_g", "ln1_b")]),
-    ("f32", [("ln2_g", "ln2_b"), ("ln1_g", "ln1_b")])])
+    ("f32", [("ln2_g", "ln2_b"), ("ln1_g", "ln1_b")]), ("bf16", [("w_2", "b_2"), ("w_o", "b_o")]), ("f32", [("w_1", "b_1")])])
 def test_tied_gradients(dtype, tied):
     """Two parameters whose gradients are one buffer: what a launch adds up for both may not be added at the same time."""
     import paper_2301_11913_amd as sw
