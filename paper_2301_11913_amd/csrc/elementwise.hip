@@ -528,12 +528,14 @@ swarm_status column_sums(const ColumnSums& s, hipStream_t st) {
   for (int i = 0; i < s.n_out; ++i)
     for (int j = 0; j < i; ++j) apart = apart && (s.out[i] + s.cols <= s.out[j] || s.out[j] + s.cols <= s.out[i]);
   for (int o = 0; !apart && o < s.n_out; ++o) {
-    const swarm_status one = column_sums(column_sums_of(s.partial + (o >> 1) * s.set + (size_t)(o & 1) * s.cols, s.rows, s.cols,
-                                                        s.stride, 0, s.out[o], nullptr, nullptr, nullptr), st);
-    if (one != SWARM_OK) return one;
+    ColumnSums one = column_sums_of(s.partial + (o >> 1) * s.set + (ptrdiff_t)(o & 1) * s.cols, s.rows, s.cols, s.stride, s.out[o],
+                                    nullptr);
+    one.parts = s.parts; one.part = s.part;
+    const swarm_status done = column_sums(one, st);
+    if (done != SWARM_OK) return done;
   }
   if (!apart) return SWARM_OK;
-  if (s.rows > 32) hipLaunchKernelGGL(column_sums_kernel<1024>, dim3(s.blocks), dim3(1024), 0, st, s);
+  if (s.rows * s.parts > 32) hipLaunchKernelGGL(column_sums_kernel<1024>, dim3(s.blocks), dim3(1024), 0, st, s);
   else hipLaunchKernelGGL(column_sums_kernel<256>, dim3(s.blocks), dim3(256), 0, st, s);
   return launch_status();
 }
@@ -580,7 +582,7 @@ swarm_status layernorm_bwd(const void* dy, const void* x, const float* mean, con
   }
   if (s != SWARM_OK) return s;
   if (!dgamma) return SWARM_OK;
-  return column_sums(column_sums_of(partial, layernorm_bwd_partial_rows(T), d, (size_t)2 * d, 0, dgamma, dbeta, nullptr, nullptr), st);
+  return column_sums(column_sums_of(partial, layernorm_bwd_partial_rows(T), d, 2 * (ptrdiff_t)d, dgamma, dbeta), st);
 }
 
 // Fused LayerNorm + maxout_k (k in {2, 4, 8}, d % 8 == 0; anything else: SWARM_ERR_SHAPE, nothing launched).
@@ -626,7 +628,7 @@ swarm_status layernorm_bwd_maxout(const void* dz, const void* x, const float* me
 #undef LN_MOB
   if (s != SWARM_OK) return s;
   if (!dgamma) return SWARM_OK;
-  return column_sums(column_sums_of(partial, layernorm_bwd_partial_rows(T), d, (size_t)2 * d, 0, dgamma, dbeta, nullptr, nullptr), st);
+  return column_sums(column_sums_of(partial, layernorm_bwd_partial_rows(T), d, 2 * (ptrdiff_t)d, dgamma, dbeta), st);
 }
 
 size_t colsum_scratch_floats(int T, int N) { return (size_t)((T + kCsRows - 1) / kCsRows) * N; }
@@ -638,7 +640,7 @@ swarm_status colsum_accum(const void* X, int T, int N, float* out, float* partia
     hipLaunchKernelGGL(colsum_partial_kernel<bf16_raw>, grid, dim3(256), 0, st, (const bf16_raw*)X, T, N, partial);
   else
     hipLaunchKernelGGL(colsum_partial_kernel<float>, grid, dim3(256), 0, st, (const float*)X, T, N, partial);
-  return column_sums(column_sums_of(partial, P, N, (size_t)N, 0, out, nullptr, nullptr, nullptr), st);
+  return column_sums(column_sums_of(partial, P, N, N, out, nullptr), st);
 }
 
 }  // namespace swarm

@@ -50,42 +50,47 @@ struct GemmArgs {
   long long* stamps;       // instrumented build only: 16 int64 per workgroup of the 256 x 256 kernel (phase stamps)
 };
 
-// Sums over the rows of a [rows, stride] matrix of partial sums, added to up to four vectors: out[2 i + j][c] += sum_p
-// partial[i * set + p * stride + j * cols + c] (LayerNorm backward: dgamma, dbeta, of one or two norms).
+// Sums over the rows of `parts` matrices [rows, stride] of partial sums, added to up to four vectors: out[2 i + j][c] += sum_q sum_p
+// partial[i * set + q * part + p * stride + j * cols + c] (LayerNorm backward: dgamma, dbeta, of one or two norms, of one or
+// more applications).
 struct ColumnSums {
   const float* partial;
   int rows, cols, n_out;
-  size_t stride, set;
+  int parts;
+  ptrdiff_t stride, set, part;
   float* out[4];
   int blocks;         // workgroups that do it: 64 columns of one vector each
 };
-inline ColumnSums column_sums_of(const float* partial, int rows, int cols, size_t stride, size_t set, float* o0, float* o1,
-                                 float* o2, float* o3) {
-  ColumnSums c{partial, rows, cols, o2 ? 4 : o1 ? 2 : 1, stride, set, {o0, o1, o2, o3}, 0};
+inline ColumnSums column_sums_of(const float* partial, int rows, int cols, ptrdiff_t stride, float* o0, float* o1) {
+  ColumnSums c{partial, rows, cols, o1 ? 2 : 1, 1, stride, 0, 0, {o0, o1, nullptr, nullptr}, 0};
   c.blocks = (cols + 63) / 64 * c.n_out;
   return c;
 }
-// One of those workgroups, of THREADS: 64 columns x THREADS / 64 row groups, each with eight running sums (fixed assignment p mod
-// 8, fixed combine order) that keep as many loads in flight.  Latency bound: with four row groups the 512 partial rows of a
+// One of those workgroups, of THREADS: 64 columns x THREADS / 64 row groups, each with eight running sums (rows in a fixed
+// assignment, a fixed combine order) that keep as many loads in flight.  Latency bound: with four row groups the 512 partial rows of a
 // LayerNorm backward are sixteen dependent rounds of loads, with sixteen groups four.
 template <int THREADS>
 __device__ __forceinline__ void column_sums_block(const ColumnSums& s, int block, float (*red)[64]) {
   constexpr int RG = THREADS / 64;
   const int per_out = (s.cols + 63) / 64, o = block / per_out, l = threadIdx.x & 63, rg = threadIdx.x >> 6;
   const int c = block % per_out * 64 + l;
-  const float* partial = s.partial + (o >> 1) * s.set + (size_t)(o & 1) * s.cols;
-  const int per = (s.rows + RG - 1) / RG, p0 = rg * per, p1 = min(s.rows, p0 + per);
+  const float* partial = s.partial + (o >> 1) * s.set + (ptrdiff_t)(o & 1) * s.cols;
+  const int all = s.rows * s.parts, per = (all + RG - 1) / RG, p0 = rg * per, p1 = min(all, p0 + per);
   float sum = 0.f;
   if (c < s.cols) {
     float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int p = p0;
-    for (; p + 8 <= p1; p += 8) {
+    for (int p = p0; p < p1;) {                    // the rows of this group, part by part
+      const int q = p / s.rows, end = min(p1, (q + 1) * s.rows);
+      const float* at = partial + q * s.part + (ptrdiff_t)(p - q * s.rows) * s.stride + c;
+      for (; p + 8 <= end; p += 8, at += 8 * s.stride) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) a[u] += partial[(size_t)(p + u) * s.stride + c];
+        for (int u = 0; u < 8; ++u) a[u] += at[u * s.stride];
+      }
+#pragma unroll
+      for (int u = 0; u < 7; ++u)
+        if (p + u < end) a[u] += at[u * s.stride];
+      p = end;
     }
-#pragma unroll
-    for (int u = 0; u < 7; ++u)
-      if (p + u < p1) a[u] += partial[(size_t)(p + u) * s.stride + c];
     sum = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
   }
   red[rg][l] = sum;

@@ -253,18 +253,6 @@ swarm_status block_backward(const Dims& D, const swarm_block_params& p, const Sa
   return SWARM_OK;
 }
 
-// The LayerNorm parameter gradients of a set from the partial sums of `n` applications: with the weight gradients (`sums`), or
-// in a launch of their own where a set has more applications than there is room for.
-struct LnPartials {
-  float* base;        // [2 norms][slots][floats]
-  size_t floats;      // of one norm of one application: [layernorm_bwd_partial_rows][2 d]
-  int slots;
-};
-ColumnSums ln_column_sums(const Dims& D, const swarm_block_grads& gp, const LnPartials& L, int n) {
-  return column_sums_of(L.base, n * layernorm_bwd_partial_rows(D.T), D.d, (size_t)2 * D.d, L.slots * L.floats, gp.ln1_g,
-                        gp.ln1_b, gp.ln2_g, gp.ln2_b);
-}
-
 // Weight and bias gradients of one parameter set over `n` consecutive applications whose tensors start at the
 // given pointers (slot pitch = one application's tensor): with layer sharing (Sections 2.3 and 4.3) the sum over
 // the applications is the K dimension of a single product, dW += [dY_0; ...; dY_{n-1}]^T [X_0; ...; X_{n-1}],
@@ -314,9 +302,10 @@ size_t plan_forward(const Dims& D, void* ws, FwdPlan& P) {
 // Token rows per weight-gradient product (a longer run of shared applications is cut into several products).
 constexpr long long kMaxWgradRows = 1ll << 22;
 
-// Applications of a set whose LayerNorm partial sums are kept (a launch for every norm of every application instead: four
-// applications of a d_model 256 block on 171 tokens, training, eight launches of 4..5 us).
-constexpr int kLnSlots = 8;
+// Applications of a set whose LayerNorm partial sums are kept and added up at once.  A launch for each application instead: four
+// applications of a d_model 256 block on 171 tokens, training, 475 -> 487 us; of 4096 on 2048 tokens, whose sums (134 MB) then come
+// from the memory-side cache, 12.48 -> 12.50 ms.  Sixteen instead of eight: within 0.5 % either way.
+constexpr int kLnKept = 8;
 
 int wgrad_chunk(const Dims& D, int R) {
   return (int)std::max<long long>(1, std::min<long long>(R, kMaxWgradRows / D.T));
@@ -329,7 +318,7 @@ struct BwdPlan {
   char* app_slots;                        // [apps] slots of app_pitch bytes: qkv, h, u, row statistics, lse, input
   size_t app_pitch, off_h, off_u, off_stats, off_lse, off_x;
   BwdTemps t;
-  LnPartials ln;
+  int ln_kept;               // applications whose LayerNorm partial sums can wait (see ln_partials_at)
   char *du_slots, *dh_slots, *dqkv_slots;   // [R] slots of [T,f1], [T,d], [T,3d]: one per application of a set
   char* dys[2];              // [R] slots of [T,d] (gradient of each application's output), by parameter-set parity
   float* rope;
@@ -363,10 +352,10 @@ size_t plan_backward(const Dims& D, int L, int R, void* ws, BwdPlan& P) {
   P.t.dg = D.rope_geglu ? cv.take(Tf) : nullptr;
   P.t.dc = cv.take(Td); P.t.dout = cv.take(Td); P.t.da = cv.take(Td);
   P.t.delta = (float*)cv.take((size_t)D.B * D.H * D.S * 4);
-  P.t.partial = (float*)cv.take(colsum_scratch_floats(wgrad_chunk(D, R) * D.T, std::max(3 * D.d, D.f1)) * 4);
-  P.ln.floats = layernorm_bwd_scratch_floats(D.T, D.d);
-  P.ln.slots = std::min(R, kLnSlots);
-  P.ln.base = (float*)cv.take(2 * P.ln.slots * P.ln.floats * 4);
+  const size_t ln_floats = layernorm_bwd_scratch_floats(D.T, D.d);
+  P.t.partial = (float*)cv.take(
+      std::max(ln_floats, colsum_scratch_floats(wgrad_chunk(D, R) * D.T, std::max(3 * D.d, D.f1))) * 4);
+  P.ln_kept = ln_floats * 4 <= P.off_stats - P.off_u ? std::min(R, kLnKept) : 1;
   P.splitk = splitk_floats_of(D) ? (float*)cv.take(splitk_floats_of(D) * 4) : nullptr;
   return cv.total();
 }
@@ -388,6 +377,25 @@ Saved saved_at(const BwdPlan& P, const Dims& D, int i, const void* x) {
   s.lse = (float*)(slot + P.off_lse);
   s.rope = P.rope;
   return s;
+}
+
+// Where the LayerNorm partial sums of application i wait for the weight gradients of its set: in the saved tensors that its own
+// backward has read for the last time, which are not written again in the call.  q|k|v and h are free when LN1 is reached, 4 T d elements
+// against 8 d bytes for every four or more rows; u when LN2 is, where f is wide enough: otherwise LN2's are in the scratch of
+// the column sums, of one application at a time.
+void ln_partials_at(const BwdPlan& P, int i, float*& ln1, float*& ln2) {
+  char* slot = P.app_slots + (size_t)i * P.app_pitch;
+  ln1 = (float*)slot;
+  ln2 = P.ln_kept > 1 ? (float*)(slot + P.off_u) : P.t.partial;
+}
+// The LayerNorm parameter gradients from the partial sums of `n` applications, i being the first of them and the last of the set.
+ColumnSums ln_column_sums(const Dims& D, const BwdPlan& P, const swarm_block_grads& gp, int i, int n) {
+  float *ln1, *ln2;
+  ln_partials_at(P, i, ln1, ln2);
+  ColumnSums c = column_sums_of(ln1, layernorm_bwd_partial_rows(D.T), D.d, 2 * (ptrdiff_t)D.d, gp.ln1_g, gp.ln1_b);
+  c.set = ln2 - ln1; c.out[2] = gp.ln2_g; c.out[3] = gp.ln2_b; c.n_out = 4; c.blocks *= 2;
+  c.parts = n; c.part = -(ptrdiff_t)(P.app_pitch / 4);
+  return c;
 }
 
 // Recompute the forward from the stage input (keeping every application's intermediates), then the reverse
@@ -421,13 +429,12 @@ swarm_status run_backward(const Dims& D, const swarm_stage_config* cfg, const sw
     int kept = 0;                // applications whose LayerNorm partial sums wait
     for (int r = R - 1; r >= 0; --r) {
       app = l * R + r;
-      if (kept == P.ln.slots) {
-        SWARM_TRY(column_sums(ln_column_sums(D, grad_params[l], P.ln, kept), st));
+      if (kept == P.ln_kept) {
+        SWARM_TRY(column_sums(ln_column_sums(D, P, grad_params[l], app + kept, kept), st));
         kept = 0;
       }
       BwdTemps t = P.t;
-      t.ln1 = P.ln.base + kept * P.ln.floats;
-      t.ln2 = t.ln1 + P.ln.slots * P.ln.floats;
+      ln_partials_at(P, app, t.ln1, t.ln2);
       ++kept;
       const void* dy = from_caller ? grad_out : base + (size_t)r * Td;
       const AppGrads ag{P.du_slots + (size_t)r * Tf1, P.dh_slots + (size_t)r * Td, P.dqkv_slots + (size_t)r * 3 * Td};
@@ -440,7 +447,7 @@ swarm_status run_backward(const Dims& D, const swarm_stage_config* cfg, const sw
         SWARM_TRY(block_backward(D, params[l], sv, t, ag, dy, dx, st));
       }
     }
-    const ColumnSums ln = ln_column_sums(D, grad_params[l], P.ln, kept);
+    const ColumnSums ln = ln_column_sums(D, P, grad_params[l], l * R + kept - 1, kept);
     for (int r0 = 0; r0 < R; r0 += chunk) {
       const int n = std::min(chunk, R - r0);
       const void* dy = from_caller ? grad_out : base + (size_t)r0 * Td;

@@ -74,6 +74,23 @@ def test_workspace_bytes_and_config_validation(lib):
         assert sw.swarm_stage_workspace_bytes(bad, True) == 0
 
 
+# What a program has set aside for a configuration stays enough: forward, backward, and the same with coded boundaries.
+@pytest.mark.parametrize("cfg,sizes", [
+    ((4096, 32, 16384, 1, 16, 1, 2048, "bf16", 1e-5, "rotary_geglu"), (420773888, 9082503168, 454328576, 9116057856)),
+    ((4096, 32, 16384, 2, 1, 4, 2048, "bf16"), (873594880, 3040083968, 1007812864, 3174301952)),
+    ((1024, 16, 4096, 2, 2, 8, 512, "bf16"), (176488448, 802684928, 193265920, 819462400)),
+    ((768, 12, 3072, 1, 1, 5, 333, "bf16"), (28239616, 71800832, 33354752, 76915968)),
+    ((256, 4, 1024, 1, 4, 1, 171, "bf16"), (1144064, 9132288, 1319424, 9307648)),
+    ((256, 4, 1024, 1, 1, 4, 128, "f32"), (5783552, 14442496, 6832384, 15491328)),
+    ((256, 2, 64, 1, 3, 2, 96, "bf16"), (913920, 4463616, 1110784, 4660480)),
+    ((128, 2, 64, 2, 9, 1, 1, "f32"), (6144, 139264, 7424, 140544)),
+    ((64, 1, 64, 1, 8, 16, 1024, "bf16", 1e-5, "rotary_geglu"), (25755648, 314114048, 29950208, 318308608))])
+def test_workspace_sizes_hold(lib, cfg, sizes):
+    c = sw.StageConfig(*cfg)
+    now = [f(c, back) for f in (sw.swarm_stage_workspace_bytes, sw.swarm_stage_coded_workspace_bytes) for back in (False, True)]
+    assert all(0 < n <= size for n, size in zip(now, sizes)), now
+
+
 def test_null_and_shape_errors_without_gpu(lib):
     cfg = sw.StageConfig(256, 4, 1024, 1, 1, 4, 128, "f32")
     blocks = (binding._BlockPtrs * 1)()

@@ -168,10 +168,11 @@ def test_forward_and_backward_replay_from_a_hip_graph():
                 assert torch.allclose(g[k].double(), n * one, rtol=1e-6, atol=1e-6 * float(one.abs().max())), (n, k)
 
 
-# (8 applications' LayerNorm partial sums are kept before they are added up)
-@pytest.mark.parametrize("dtype,R,d,seq", [("bf16", 3, 256, 96), ("bf16", 8, 128, 40), ("bf16", 9, 128, 40), ("f32", 17, 128, 37)])
-def test_shared_equals_unrolled_on_gpu(dtype, R, d, seq):
-    wl = synth.Workload(name="shared", dtype=dtype, d_model=d, n_heads=2, d_ffn=512, seq=seq, batch=2,
+# (8 applications' LayerNorm partial sums are kept, where the FFN is wide enough to hold them, before they are added up)
+@pytest.mark.parametrize("dtype,R,d,seq,f", [("bf16", 3, 256, 96, 512), ("bf16", 8, 128, 40, 512), ("bf16", 9, 128, 40, 512),
+                                             ("f32", 17, 128, 37, 512), ("bf16", 3, 256, 96, 64), ("f32", 3, 256, 1, 64)])
+def test_shared_equals_unrolled_on_gpu(dtype, R, d, seq, f):
+    wl = synth.Workload(name="shared", dtype=dtype, d_model=d, n_heads=2, d_ffn=f, seq=seq, batch=2,
                         n_layers=1, n_repeat=R, grad_sigma=1e-2, seed=77)
     params, x, G = synth.make_params(wl), synth.make_x_in(wl), synth.make_grad_out(wl)
     shared = run_gpu(wl, params, x, G)
