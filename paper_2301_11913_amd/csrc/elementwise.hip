@@ -478,10 +478,10 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict
 
 // Stage 2, where it does not ride in the launch of the weight gradients (training passes at d_model 768 on 5 x 333 tokens with
 // sixteen row groups instead of four 364 -> 356 us, two blocks of 1024 on 4096 tokens 1400 -> 1385, 2048 1793 -> 1778).
-template <int THREADS>
+template <int THREADS, bool PARTS>
 __global__ __launch_bounds__(THREADS) void column_sums_kernel(ColumnSums s) {
   __shared__ float red[THREADS / 64][64];
-  column_sums_block<THREADS>(s, blockIdx.x, red);
+  column_sums_of_vector<THREADS, PARTS>(s, blockIdx.y, blockIdx.x * 64, red);
 }
 
 template <typename T, bool DEC, int MAXK = 0>
@@ -535,8 +535,12 @@ swarm_status column_sums(const ColumnSums& s, hipStream_t st) {
     if (done != SWARM_OK) return done;
   }
   if (!apart) return SWARM_OK;
-  if (s.rows * s.parts > 32) hipLaunchKernelGGL(column_sums_kernel<1024>, dim3(s.blocks), dim3(1024), 0, st, s);
-  else hipLaunchKernelGGL(column_sums_kernel<256>, dim3(s.blocks), dim3(256), 0, st, s);
+  const dim3 grid((s.cols + 63) / 64, s.n_out);
+  const bool many = s.rows * s.parts > 32;
+  if (s.parts > 1 && many) hipLaunchKernelGGL((column_sums_kernel<1024, true>), grid, dim3(1024), 0, st, s);
+  else if (s.parts > 1) hipLaunchKernelGGL((column_sums_kernel<256, true>), grid, dim3(256), 0, st, s);
+  else if (many) hipLaunchKernelGGL((column_sums_kernel<1024, false>), grid, dim3(1024), 0, st, s);
+  else hipLaunchKernelGGL((column_sums_kernel<256, false>), grid, dim3(256), 0, st, s);
   return launch_status();
 }
 

@@ -51,14 +51,16 @@ struct Operand {
 
 __device__ __forceinline__ float comp(const float4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
-// What a kernel for this layout is launched with: weight gradients come several in a launch.
-template <bool A_T> struct F32Args { typedef GemmArgs type; };
+// What a kernel is launched with.  GROUP: several weight gradients in a launch; one alone has a kernel of its own, since finding its
+// place in a group's arguments takes 0.2 us (1024 x 512 over 128 tokens 4.60 -> 4.83).
+template <bool GROUP> struct F32Args { typedef GemmArgs type; };
 template <> struct F32Args<true> { typedef WgradGroup type; };
 
 // A workgroup: WM x WN x WK wavefronts; wavefront (wm, wn, wk) multiplies block (wm, wn) of 32 FM x 32 FN over the
 // wk-th part of K.
-template <int FM, int FN, int WM, int WN, int WK, bool A_T, bool B_T>
-__global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32Args<A_T>::type args, int tiles_m, int tiles_n) {
+template <int FM, int FN, int WM, int WN, int WK, bool A_T, bool B_T, bool GROUP>
+__global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32Args<GROUP>::type args, int tiles_m, int tiles_n) {
+  static_assert(!GROUP || (A_T && B_T), "groups are of weight gradients");
   constexpr int TM = 32 * FM * WM, TN = 32 * FN * WN, NT = WM * WN * WK * 64;
   constexpr int U = FM * FN == 1 ? 4 : 2;      // 8-deep steps per slice: 32 registers of fragments in flight
   constexpr int PITCH = TN + 4;
@@ -67,7 +69,7 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32A
   // contiguous bands of tiles per XCD, walked in groups of 8 tile rows
   int pid;
   GemmArgs g;
-  if constexpr (A_T) {
+  if constexpr (GROUP) {
     if ((int)blockIdx.x < args.first[0]) {
       column_sums_block<NT>(args.sums, blockIdx.x, reinterpret_cast<float (*)[64]>(lds));
       return;
@@ -241,11 +243,11 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(typename F32A
   }
 }
 
-template <int FM, int FN, int WM, int WN, int WK, bool A_T, bool B_T>
-swarm_status launch(const typename F32Args<A_T>::type& g, int tm, int tn, int tiles, hipStream_t st) {
+template <int FM, int FN, int WM, int WN, int WK, bool A_T, bool B_T, bool GROUP = false>
+swarm_status launch(const typename F32Args<GROUP>::type& g, int tm, int tn, int tiles, hipStream_t st) {
   constexpr int TM = 32 * FM * WM, TN = 32 * FN * WN;
   constexpr size_t lds_bytes = (size_t)WK * TM * (TN + 4) * sizeof(float);
-  auto kern = gemm_f32_kernel<FM, FN, WM, WN, WK, A_T, B_T>;
+  auto kern = gemm_f32_kernel<FM, FN, WM, WN, WK, A_T, B_T, GROUP>;
   if constexpr (lds_bytes > 64 * 1024) {
     static LdsOptIn opted;   // per instantiation
     if (lds_opt_in((const void*)kern, lds_bytes, opted) != SWARM_OK) return SWARM_ERR_LAUNCH;
@@ -258,11 +260,12 @@ swarm_status launch(const typename F32Args<A_T>::type& g, int tm, int tn, int ti
 template <int FM, int FN, int WM, int WN, int WK>
 swarm_status launch_layout(const GemmArgs* g, int n, const ColumnSums* sums, hipStream_t st) {
   constexpr int TM = 32 * FM * WM, TN = 32 * FN * WN;
-  if (g->a_trans) {
+  if (n > 1 || sums) {
     const WgradGroup w = wgrad_group_of(g, n, sums, TM, TN);
-    return launch<FM, FN, WM, WN, WK, true, true>(w, 0, 0, w.workgroups, st);
+    return launch<FM, FN, WM, WN, WK, true, true, true>(w, 0, 0, w.workgroups, st);
   }
   const int tm = (g->M + TM - 1) / TM, tn = (g->N + TN - 1) / TN;
+  if (g->a_trans) return launch<FM, FN, WM, WN, WK, true, true>(*g, tm, tn, tm * tn, st);
   if (!g->b_trans) return launch<FM, FN, WM, WN, WK, false, false>(*g, tm, tn, tm * tn, st);
   return launch<FM, FN, WM, WN, WK, false, true>(*g, tm, tn, tm * tn, st);
 }

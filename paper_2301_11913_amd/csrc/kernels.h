@@ -66,21 +66,21 @@ inline ColumnSums column_sums_of(const float* partial, int rows, int cols, ptrdi
   c.blocks = (cols + 63) / 64 * c.n_out;
   return c;
 }
-// One of those workgroups, of THREADS: 64 columns x THREADS / 64 row groups, each with eight running sums (rows in a fixed
+// One of those workgroups, of THREADS: vector o, 64 columns from c0 on x THREADS / 64 row groups, each with eight running sums (rows in a fixed
 // assignment, a fixed combine order) that keep as many loads in flight.  Latency bound: with four row groups the 512 partial rows of a
 // LayerNorm backward are sixteen dependent rounds of loads, with sixteen groups four.
-template <int THREADS>
-__device__ __forceinline__ void column_sums_block(const ColumnSums& s, int block, float (*red)[64]) {
+// (PARTS: of any number of them; else of one.)
+template <int THREADS, bool PARTS>
+__device__ __forceinline__ void column_sums_of_vector(const ColumnSums& s, int o, int c0, float (*red)[64]) {
   constexpr int RG = THREADS / 64;
-  const int per_out = (s.cols + 63) / 64, o = block / per_out, l = threadIdx.x & 63, rg = threadIdx.x >> 6;
-  const int c = block % per_out * 64 + l;
+  const int l = threadIdx.x & 63, rg = threadIdx.x >> 6, c = c0 + l;
   const float* partial = s.partial + (o >> 1) * s.set + (ptrdiff_t)(o & 1) * s.cols;
-  const int all = s.rows * s.parts, per = (all + RG - 1) / RG, p0 = rg * per, p1 = min(all, p0 + per);
+  const int all = PARTS ? s.rows * s.parts : s.rows, per = (all + RG - 1) / RG, p0 = rg * per, p1 = min(all, p0 + per);
   float sum = 0.f;
   if (c < s.cols) {
     float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int p = p0; p < p1;) {                    // the rows of this group, part by part
-      const int q = p / s.rows, end = min(p1, (q + 1) * s.rows);
+      const int q = PARTS ? p / s.rows : 0, end = min(p1, (q + 1) * s.rows);
       const float* at = partial + q * s.part + (ptrdiff_t)(p - q * s.rows) * s.stride + c;
       for (; p + 8 <= end; p += 8, at += 8 * s.stride) {
 #pragma unroll
@@ -102,6 +102,12 @@ __device__ __forceinline__ void column_sums_block(const ColumnSums& s, int block
     float* out = o == 0 ? s.out[0] : o == 1 ? s.out[1] : o == 2 ? s.out[2] : s.out[3];
     out[c] += sum;
   }
+}
+// The block-th of s.blocks, in the launch of something else.
+template <int THREADS>
+__device__ __forceinline__ void column_sums_block(const ColumnSums& s, int block, float (*red)[64]) {
+  const int per_out = (s.cols + 63) / 64;
+  column_sums_of_vector<THREADS, true>(s, block / per_out, block % per_out * 64, red);
 }
 
 // Weight-gradient products over the same token rows (one parameter set's four), as ONE launch of their kernel takes them.

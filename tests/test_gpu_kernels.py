@@ -740,7 +740,8 @@ def test_bias_gradient_rounding(bf16, K, shapes, units):
     (1, 63, [(1032, 4104), (4104, 1032), (264, 1032), (3096, 1032)]), (1, 64, [(1024, 4096), (4096, 1024), (1024, 1024), (3072, 1024)]),
     (1, 2113, [(1032, 4104), (4104, 1032), (1032, 1032), (3096, 1032)]), (1, 129, [(3080, 4104), (8, 264)]),
     (0, 1, [(64, 64), (33, 36)]), (0, 77, [(256, 1024), (1024, 256), (256, 256), (768, 256)]),
-    (0, 130, [(1000, 1028), (777, 516), (64, 64)]), (0, 203, [(1024, 4096), (2052, 1024), (300, 68)])])
+    (0, 130, [(1000, 1028), (777, 516), (64, 64)]), (0, 203, [(1024, 4096), (2052, 1024), (300, 68)]),
+    (0, 33, [(4096, 4092), (132, 260)])])
 def test_weight_gradients_in_one_launch(bf16, K, shapes):
     lib = _lib()
     g = torch.Generator(device="cuda").manual_seed(K + sum(map(sum, shapes)))

@@ -170,7 +170,8 @@ def test_forward_and_backward_replay_from_a_hip_graph():
 
 # (8 applications' LayerNorm partial sums are kept, where the FFN is wide enough to hold them, before they are added up)
 @pytest.mark.parametrize("dtype,R,d,seq,f", [("bf16", 3, 256, 96, 512), ("bf16", 8, 128, 40, 512), ("bf16", 9, 128, 40, 512),
-                                             ("f32", 17, 128, 37, 512), ("bf16", 3, 256, 96, 64), ("f32", 3, 256, 1, 64)])
+                                             ("f32", 17, 128, 37, 512), ("bf16", 3, 256, 96, 64), ("f32", 3, 256, 1, 64),
+                                             ("f32", 9, 128, 1, 512)])
 def test_shared_equals_unrolled_on_gpu(dtype, R, d, seq, f):
     wl = synth.Workload(name="shared", dtype=dtype, d_model=d, n_heads=2, d_ffn=f, seq=seq, batch=2,
                         n_layers=1, n_repeat=R, grad_sigma=1e-2, seed=77)
