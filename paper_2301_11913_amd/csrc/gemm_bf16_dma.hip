@@ -849,13 +849,16 @@ int g_gemm_four_waves = 1;   // measurement switch of the instrumented build (sw
 
 // An output of at least twice the 32 MB of L2 cannot wait there for its consumer; written (and its residual /
 // pre-activation rows read) non-temporally it leaves the operand panels in the L2 instead.  A gradient that is added to is read
-// again by the next microbatch: it stays in the 256 MB memory-side cache, unless together with the operands it does not fit (8192
-// x 4096 over 1024 tokens 115 us streamed, 100 cached; 20480 x 4096 222, 237; four gradients of one set count together).
+// again by the next microbatch: it stays in the 256 MB memory-side cache, as long as it leaves room there for what the pass reads in
+// between, above all the weights that the data gradient reads next.  Measured in whole passes at 41 sizes of head and stage, streamed
+// against cached, by the bytes of the gradients of a launch and their operands: 86..140 MiB 1.02..1.06, 144..155 0.98..1.03, 156..170
+// 0.97..1.04, from 171 on 0.88..1.00 (one 1.03).  (A head of 50432 x 1024 over 256 tokens 457 us cached, 408 streamed: its data gradient
+// 270 and 225.)  Alone, again and again on the same memory, a product is faster cached up to 272 MiB.
 bool streams_output(const GemmArgs& g) { return (size_t)g.M * g.N * 2 >= ((size_t)64 << 20); }
 bool streams_gradients(const GemmArgs* g, int n) {
   size_t bytes = 0;
   for (int i = 0; i < n; ++i) bytes += (size_t)g[i].M * g[i].N * 4 + ((size_t)g[i].M + g[i].N) * g[i].K * 2;
-  return bytes >= ((size_t)272 << 20);
+  return bytes >= ((size_t)156 << 20);
 }
 
 swarm_status launch_w4(const KArgs& k, hipStream_t st) {
