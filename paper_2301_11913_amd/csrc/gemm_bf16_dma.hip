@@ -1008,7 +1008,8 @@ static bool two_tiles_per_unit(const GemmArgs& g) {
 
 // Ragged forward and data-gradient products on the kernels of whole tiles, whose last tile ends with the operand (tile_origin).
 // Measured at 963 shapes, d_model 256..4096, 256..8192 rows, against what they ran on before (gemm_bf16_kw or the register-staged
-// kernel): forward 6.5 % faster on average, data gradient 2.7 %, none more than 2 % slower.
+// kernel): forward 6.5 % faster on average, data gradient 2.7 %, none more than 2 % slower.  Fewer rows or columns than 256 were not among
+// them; there 128 x 128 tiles take 0.77..0.93 of the time up to 320 of them (200 x 20224, K = 1024 22.5 -> 19.0) and 0.82..1.37 beyond.
 //   256 x 256      where they replace more than two rounds of 128 x 128 and their own rounds are full: forward one round of more
 //                  than half 0.67..0.93 of the time (1821 x 4608, K = 1536 49.2 -> 33.4 us), two from 0.7 full 0.69..0.91, more
 //                  from 0.75; not below K = 768 (7868 x 2048, K = 512 30.7 / 31.4).  The transposed operand's reads and the GeLU'
@@ -1051,14 +1052,16 @@ static Ragged ragged_on_whole_tiles(const GemmArgs& g) {
   return (long)((g.M + 255) / 256) * ((g.N + 127) / 128) <= 256 ? Ragged::t256x128 : Ragged::none;
 }
 
-// Ragged products that the register-staged kernel of gemm_bf16.hip takes faster than gemm_bf16_kw.  Its 256 x 256 tiles (128
+// Ragged products that the register-staged kernel of gemm_bf16.hip takes faster than gemm_bf16_kw: of those that
+// ragged_on_whole_tiles leaves, so with a K that is no multiple of 64, 128..255 rows or columns, or in place.  Its 256 x 256 tiles (128
 // x 128 below 160 of those) move half the operand bytes and pay prologue and epilogue less often, but waste more of a last
 // round that is not full.  So the measure is how many rounds of 256 small tiles replace one of large ones (4 at most), and
-// the line moves with K, measured in turn at 700..16000 tokens and d_model 256..8192:
-//   forward           2500 x 6144, K = 1536 (4 rounds for 1) 67 against 75 us; 7000 x 4608 (8 for 2) 112 / 151; K = 2048..4096
-//                     2..9 %, from 8192 on gemm_bf16_kw is ahead again unless the operands exceed the 256 MB memory-side
-//                     cache (10000 x 3072, K = 12288: 793 / 957); at 3 for 1 (6000 x 3072, K = 768 with GeLU) 75 / 62;
-//   data gradient     gemm_bf16_kw always, but for two rounds of it at K = 256 (5000 x 1024: 16.2 / 17.3);
+// for how long a K that holds; us here / on gemm_bf16_kw:
+//   forward           4 for 1 (4000 x 4096) K = 544 30 / 39, 1056 48 / 55, 3104 113 / 119; 200 x 50432, K = 4096 132 / 158; from K = 4096 on
+//                     gemm_bf16_kw unless the operands exceed the 256 MB memory-side cache; two rounds of 128 x 128 (200 x 32000) K =
+//                     256 11.1 / 14.8, 1024 25 / 29, 4096 89 / 84; at 5 for 2 (6000 x 3072) K = 544 53 / 47;
+//   data gradient     gemm_bf16_kw (4096 tall and wide K = 1056 54 / 55, 4128 169 / 151), but for two rounds at K <= 256 (5000 x
+//                     1024, K = 160 9.9 / 12.9; 200 x 20224, K = 256 10.9 / 12.9);
 //   weight gradients  those that wgrad_alone leaves, two rounds for one and few tokens.
 static bool register_staged_is_faster(const GemmArgs& g) {
   if (g.M % 128 == 0 && g.N % 128 == 0 && g.K % DBK == 0) return false;

@@ -1,10 +1,10 @@
 // LAMB step for one parameter tensor (appendix "Additional Details for Section 4.3").  Streaming kernels: moments + update
 // direction + per-workgroup partial sums of |w|^2 and |u|^2; the trust ratio, their sum in a fixed order; the weight update (and
-// the copy in the stage's dtype).  What bounds a short tensor is launches, 4 us each and more: one of at most kSmall elements,
-// as eight of a block's twelve are, is done by one workgroup in one launch (4096: 8.8 -> 4.1 us, 12288: 8.9 -> 6.6, 16384: 9.1 / 8.0
-// where two launches take 7.8), and up to kMaxFolded workgroups every one of the update adds up the partial sums itself (65536:
-// 9.5 -> 8.1).  Beyond that a single workgroup does; with fewer, looping workgroups and no third launch 2^26 elements take 490
-// us instead of 470.
+// the copy in the stage's dtype).  What bounds a short tensor is launches, 4 us each and more: one of at most kSmall elements (of a
+// block's twelve seven at d_model 4096, eight where b_1 has no more) is done by one workgroup in one launch (4096: 8.8 -> 4.1 us,
+// 12288: 8.9 -> 6.6, 16384: 9.1 / 8.0 where two launches take 7.8), and up to kMaxFolded workgroups every one of the update adds up
+// the partial sums itself (65536: 9.5 -> 8.1).  Beyond that a single workgroup does; with fewer, looping workgroups and no third
+// launch 2^26 elements take 490 us instead of 470.
 #include <atomic>
 #include <cmath>
 
