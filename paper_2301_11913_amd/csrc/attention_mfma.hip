@@ -214,10 +214,15 @@ __device__ __forceinline__ void tile_head_batch(int nt, int H, int& tile, int& h
 // requested two or three ahead instead of one change nothing.  So where the launch leaves units idle the chain is cut
 // (layout_of): d_head 64, one sequence of 512 with 16 heads 16.4 -> 10.6 us, 5 sequences of 333 with 12 heads
 // 14.3 -> 9.2 us, the whole training pass of the latter with dQ (15.3 -> 9.7) and dK / dV (24.6 -> 19) 396 -> 374 us.
-template <int DH, int KG>
+//
+// PAIRS: `passes` tiles, else one, behind whose merge the second group ends: with the loop over tiles around it a launch of single
+// tiles takes 0.15..0.5 us longer (one sequence of 512, 16 heads of 64 9.83 -> 9.58; 8 heads of 128 14.22 -> 13.71; its dQ, at 128,
+// half a microsecond).
+template <int DH, int KG, bool PAIRS>
 __global__ __launch_bounds__(kThreads* KG, 2) void attn_fwd_kernel(const bf16_raw* __restrict__ qkv,
                                                                    bf16_raw* __restrict__ o, float* __restrict__ lse,
                                                                    int S, int H, int passes) {
+  if constexpr (!PAIRS) passes = 1;
   using T = Tile64<DH>;
   constexpr int KS = DH / 16, DB = DH / 32;
   constexpr int STAGE = 2 * T::ELEMS;
@@ -378,6 +383,7 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_fwd_kernel(const bf16_ra
       part[(16 * DB + 1) * 64] = l;
     }
     __syncthreads();
+    if (!PAIRS && grp) return;
     if (!grp) {
       const float m1 = part[16 * DB * 64], l1 = part[(16 * DB + 1) * 64], top = fmaxf(m, m1);
       const float f0 = __builtin_amdgcn_exp2f((m - top) * c), f1 = __builtin_amdgcn_exp2f((m1 - top) * c);
@@ -388,7 +394,7 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_fwd_kernel(const bf16_ra
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[i][r] = oacc[i][r] * f0 + part[(16 * i + r) * 64] * f1;
     }
-    __syncthreads();                 // the next pass loads into the stages again
+    if constexpr (PAIRS) __syncthreads();   // the next pass loads into the stages again
   }
   if (grp == 0 && qrow < S) {
     store_rowT<DB>(o + ((size_t)b * S + qrow) * d + h * DH, oacc, 1.0f / l, lg);
@@ -593,13 +599,14 @@ __device__ __forceinline__ float dot8(const bf16x8& x, const bf16x8& y) {
 // dQ: tiles, wavefronts and groups as in the forward.  It runs before dK / dV and leaves delta[b,h,s] = sum_c dO[s,h,c] O[s,h,c]
 // for it: a row of dO is in its registers anyway, and a kernel of its own for this is another 1.5..3 us of a backward pass (one
 // sequence of 64, 4 heads 12.2 -> 10.6 us; 8 of 512, 16 heads 53.4 -> 50.1).
-template <int DH, int KG>
+template <int DH, int KG, bool PAIRS>
 __global__ __launch_bounds__(kThreads* KG, 2) void attn_bwd_dq_kernel(const bf16_raw* __restrict__ qkv,
                                                                   const bf16_raw* __restrict__ dout,
                                                                   const bf16_raw* __restrict__ o,
                                                                   const float* __restrict__ lse,
                                                                   float* __restrict__ delta,
                                                                   bf16_raw* __restrict__ dqkv, int S, int H, int passes) {
+  if constexpr (!PAIRS) passes = 1;
   using T = Tile64<DH>;
   constexpr int KS = DH / 16, DB = DH / 32;
   constexpr int STAGE = 2 * T::ELEMS;           // K, V
@@ -734,13 +741,14 @@ __global__ __launch_bounds__(kThreads* KG, 2) void attn_bwd_dq_kernel(const bf16
         for (int r = 0; r < 16; ++r) part[(16 * i + r) * 64] = dqacc[i][r];
     }
     __syncthreads();
+    if (!PAIRS && grp) return;
     if (!grp) {
 #pragma unroll
       for (int i = 0; i < DB; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) dqacc[i][r] += part[(16 * i + r) * 64];
     }
-    __syncthreads();                 // the next pass loads into the stages again
+    if constexpr (PAIRS) __syncthreads();   // the next pass loads into the stages again
   }
   if (grp == 0 && qrow < S) store_rowT<DB>(dqkv + ((size_t)b * S + qrow) * ld + h * DH, dqacc, scale, lg);
   }   // pass
@@ -766,23 +774,23 @@ Layout layout_of(int B, int S, int H, int dh) {
   return {passes, grid <= 256 && keys >= enough ? 2 : 1, grid};
 }
 
-template <int DH, int KG>
+template <int DH, int KG, bool PAIRS = true>
 swarm_status launch_fwd(const bf16_raw* qkv, bf16_raw* o, float* lse, int S, int H, Layout L, hipStream_t st) {
   constexpr size_t lds_bytes = (size_t)KG * 2 * 2 * 64 * DH * sizeof(bf16_raw);
   static LdsOptIn a0;
-  if (lds_opt_in((const void*)attn_fwd_kernel<DH, KG>, lds_bytes, a0) != SWARM_OK) return SWARM_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_fwd_kernel<DH, KG>), dim3(L.grid), dim3(kThreads * KG), lds_bytes, st, qkv, o, lse, S, H,
+  if (lds_opt_in((const void*)attn_fwd_kernel<DH, KG, PAIRS>, lds_bytes, a0) != SWARM_OK) return SWARM_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_fwd_kernel<DH, KG, PAIRS>), dim3(L.grid), dim3(kThreads * KG), lds_bytes, st, qkv, o, lse, S, H,
                      L.passes);
   return launch_status();
 }
 
-template <int DH, int KG>
+template <int DH, int KG, bool PAIRS = true>
 swarm_status launch_dq(const bf16_raw* qkv, const bf16_raw* dout, const bf16_raw* o, const float* lse, float* delta,
                        bf16_raw* dqkv, int S, int H, Layout L, hipStream_t st) {
   constexpr size_t lds_bytes = (size_t)KG * 2 * 2 * 64 * DH * sizeof(bf16_raw);
   static LdsOptIn a0;
-  if (lds_opt_in((const void*)attn_bwd_dq_kernel<DH, KG>, lds_bytes, a0) != SWARM_OK) return SWARM_ERR_LAUNCH;
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, KG>), dim3(L.grid), dim3(kThreads * KG), lds_bytes, st, qkv, dout, o, lse,
+  if (lds_opt_in((const void*)attn_bwd_dq_kernel<DH, KG, PAIRS>, lds_bytes, a0) != SWARM_OK) return SWARM_ERR_LAUNCH;
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, KG, PAIRS>), dim3(L.grid), dim3(kThreads * KG), lds_bytes, st, qkv, dout, o, lse,
                      delta, dqkv, S, H, L.passes);
   return launch_status();
 }
@@ -794,8 +802,11 @@ swarm_status launch_bwd(const bf16_raw* qkv, const bf16_raw* o, const bf16_raw* 
   static LdsOptIn a1;
   if (lds_opt_in((const void*)attn_bwd_dkdv_kernel<DH>, lds_dkdv, a1) != SWARM_OK) return SWARM_ERR_LAUNCH;
   const Layout L = layout_of(B, S, H, DH);
-  const swarm_status dq = L.groups == 2 ? launch_dq<DH, 2>(qkv, dout, o, lse, delta, dqkv, S, H, L, st)
-                                        : launch_dq<DH, 1>(qkv, dout, o, lse, delta, dqkv, S, H, L, st);
+  // (single tiles: see PAIRS; at d_head 64 the kernel of pairs takes them 0.15 us faster all the same)
+  const swarm_status dq = L.groups == 1 ? launch_dq<DH, 1>(qkv, dout, o, lse, delta, dqkv, S, H, L, st)
+                          : DH == 128 && L.passes == 1
+                              ? launch_dq<DH, 2, DH == 64>(qkv, dout, o, lse, delta, dqkv, S, H, L, st)
+                              : launch_dq<DH, 2>(qkv, dout, o, lse, delta, dqkv, S, H, L, st);
   if (dq != SWARM_OK) return dq;
   hipLaunchKernelGGL(attn_bwd_dkdv_kernel<DH>, dim3(L.grid), dim3(kDkDvThreads), lds_dkdv, st, qkv, dout, lse, delta, dqkv,
                      S, H, L.passes);
@@ -805,8 +816,9 @@ swarm_status launch_bwd(const bf16_raw* qkv, const bf16_raw* o, const bf16_raw* 
 template <int DH>
 swarm_status launch_fwd_of(const bf16_raw* qkv, bf16_raw* o, float* lse, int B, int S, int H, hipStream_t st) {
   const Layout L = layout_of(B, S, H, DH);
-  if (L.groups == 2) return launch_fwd<DH, 2>(qkv, o, lse, S, H, L, st);
-  return launch_fwd<DH, 1>(qkv, o, lse, S, H, L, st);
+  if (L.groups == 1) return launch_fwd<DH, 1>(qkv, o, lse, S, H, L, st);
+  if (L.passes == 1) return launch_fwd<DH, 2, false>(qkv, o, lse, S, H, L, st);
+  return launch_fwd<DH, 2>(qkv, o, lse, S, H, L, st);
 }
 
 }  // namespace
