@@ -80,7 +80,7 @@ __device__ __forceinline__ void column_sums_of_vector(const ColumnSums& s, int o
   if (c < s.cols) {
     float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int p = p0; p < p1;) {                    // the rows of this group, part by part
-      const int q = PARTS ? p / s.rows : 0, end = min(p1, (q + 1) * s.rows);
+      const int q = PARTS && s.parts > 1 ? p / s.rows : 0, end = min(p1, (q + 1) * s.rows);
       const float* at = partial + q * s.part + (ptrdiff_t)(p - q * s.rows) * s.stride + c;
       for (; p + 8 <= end; p += 8, at += 8 * s.stride) {
 #pragma unroll
